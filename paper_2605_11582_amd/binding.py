@@ -1,8 +1,13 @@
-"""Thin ctypes binding of libegt.so: argument marshalling only.
+"""Thin binding of libegt.so: argument marshalling only.
 
 Host functions take and return numpy arrays; device functions take torch tensors
 (used for device memory and the current stream, nothing else).  There is no CPU
 fallback: if the built library is missing, loading raises.
+
+Everything is declared for ctypes; what a serving loop calls per token - the single
+products and the prepared calls - goes through the extension module egt_call
+(csrc/egt_call.cpp) to the same entry points, because marshalling a call in Python took
+twice as long as the GPU takes for the product.
 """
 from __future__ import annotations
 
@@ -99,6 +104,8 @@ class StackPlan(C.Structure):
 STACK_ENTRY_BYTES = 160
 
 _lib = None
+_call = None              # the extension module egt_call, bound to the loaded library
+_plain = ("egt_sparse_gemv", "egt_sparse_gemm_smallm", "egt_sparse_gemm_smallm_ws", "egt_sparse_gemm_smallm_static", "egt_int4_gemv")
 
 
 def _declare(L: C.CDLL, names=None) -> C.CDLL:
@@ -161,6 +168,35 @@ def lib() -> C.CDLL:
         import torch  # noqa: F401
         _lib = _declare(C.CDLL(LIB_PATH))
     return _lib
+
+
+def _address(fn) -> int:
+    return C.cast(fn, C.c_void_p).value
+
+
+def _native():
+    """The extension module through which device calls go."""
+    global _call
+    if _call is None:
+        L = lib()
+        import torch
+        try:
+            from . import egt_call
+        except ImportError as e:
+            raise RuntimeError("egt_call.so is not built or does not load: run `python -m paper_2605_11582_amd.build` "
+                               "(there is no fallback path)") from e
+        egt_call.bind(*[_address(getattr(L, name)) for name in _plain], _check,
+                      torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+        _call = egt_call
+    return _call
+
+
+def _prepared(kind: str, fn, args, keep, stream=None):
+    """A call of the library entry point `fn` with marshalled arguments: called with nothing it
+    launches on the stream current now (or `stream`), called with an integer on that stream.
+    `args`: one tuple, or a list of tuples for several launches.  `keep` is kept alive."""
+    native = _native()
+    return native.Call(getattr(native, kind), _address(fn), args if isinstance(args, list) else [args], _stream_ptr(stream), keep)
 
 
 def status_str(status: int) -> str:
@@ -432,12 +468,17 @@ def _check_int4_dev(q, qparams, rows: int, cols: int, group: int) -> None:
 
 def int4_gemv(q, qparams, rows: int, cols: int, group: int, x, y, stream=None) -> None:
     """q, qparams, x, y: device tensors (uint8 / int16-viewable / float16 / float16)."""
+    if (_call or _native()).int4_gemv(q, qparams, rows, cols, group, x, y, stream):
+        return
+    # something is not as it should be (or there is nothing to compute): the checks that say what
     _check_int4_dev(q, qparams, rows, cols, group)
     _check(lib().egt_int4_gemv(_dev(q), _dev(qparams), rows, cols, group, _need(x, 2 * cols, "x", True),
                                _need(y, 2 * rows, "y", True), _stream_ptr(stream)))
 
 
 def sparse_gemv(p: Packed, x, y, stream=None) -> None:
+    if (_call or _native()).sparse_gemv(p, x, y, stream):
+        return
     v = p.view()
     _check_packed_dev(p)
     _check(lib().egt_sparse_gemv(C.byref(v), _need(x, 2 * p.cols, "x", True), _need(y, 2 * p.rows, "y", True),
@@ -457,6 +498,8 @@ def _check_xy(p: "Packed", X, Y) -> None:
 
 def sparse_gemm_smallm(p: Packed, X, Y, stream=None) -> None:
     """X: (M, K) float16 device tensor, Y: (M, R) float16 device tensor; rows may be strided."""
+    if (_call or _native()).sparse_gemm_smallm(0, p, X, Y, None, stream):
+        return
     _check_xy(p, X, Y)
     v = p.view()
     _check(lib().egt_sparse_gemm_smallm(C.byref(v), X.data_ptr(), X.stride(0), Y.data_ptr(),
@@ -468,28 +511,17 @@ def sparse_gemm_smallm(p: Packed, X, Y, stream=None) -> None:
 # The stream defaults to the one current at preparation; pass `stream_ptr` (an int)
 # to launch elsewhere, e.g. on a capturing stream.
 def prepared_sparse_gemv(p: Packed, x, y, stream=None):
-    fn, v = lib().egt_sparse_gemv, p.view()
+    v = p.view()
     _check_packed_dev(p)
-    ref, xp, yp, sp = C.byref(v), _need(x, 2 * p.cols, "x", True), _need(y, 2 * p.rows, "y", True), _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(v, p, x, y)):
-        st = fn(ref, xp, yp, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    args = (C.addressof(v), _need(x, 2 * p.cols, "x", True), _need(y, 2 * p.rows, "y", True))
+    return _prepared("GEMV", lib().egt_sparse_gemv, args, (v, p, x, y), stream)
 
 
 def prepared_sparse_gemm_smallm(p: Packed, X, Y, stream=None):
-    fn, v = lib().egt_sparse_gemm_smallm, p.view()
+    v = p.view()
     _check_xy(p, X, Y)
-    args = (C.byref(v), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), X.shape[0])
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(v, p, X, Y)):
-        st = fn(*args, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    args = (C.addressof(v), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), X.shape[0])
+    return _prepared("GEMM", lib().egt_sparse_gemm_smallm, args, (v, p, X, Y), stream)
 
 
 def smallm_ws_bytes(p: Packed, M: int, ldx=None) -> int:
@@ -503,25 +535,21 @@ def smallm_ws_bytes(p: Packed, M: int, ldx=None) -> int:
 def prepared_sparse_gemm_smallm_ws(p: Packed, X, Y, workspace, stream=None):
     """The K-split form; `workspace`: a device tensor of at least smallm_ws_bytes bytes (or None
     when that is 0)."""
-    fn, v = lib().egt_sparse_gemm_smallm_ws, p.view()
+    v = p.view()
     _check_xy(p, X, Y)
     need = smallm_ws_bytes(p, X.shape[0], X.stride(0))
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         raise ValueError(f"workspace of {need} bytes required")
     wp = 0 if workspace is None else _dev(workspace)
     wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    args = (C.byref(v), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), X.shape[0], wp, wb)
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(v, p, X, Y, workspace)):
-        st = fn(*args, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    args = (C.addressof(v), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), X.shape[0], wp, wb)
+    return _prepared("GEMM_WS", lib().egt_sparse_gemm_smallm_ws, args, (v, p, X, Y, workspace), stream)
 
 
 def sparse_gemm_smallm_static(p: Packed, X, Y, stream=None) -> None:
     """The K-split form on the library's built-in scratch buffer (allocates nothing)."""
+    if (_call or _native()).sparse_gemm_smallm(2, p, X, Y, None, stream):
+        return
     _check_xy(p, X, Y)
     v = p.view()
     _check(lib().egt_sparse_gemm_smallm_static(C.byref(v), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0),
@@ -529,20 +557,15 @@ def sparse_gemm_smallm_static(p: Packed, X, Y, stream=None) -> None:
 
 
 def sparse_gemm_smallm_ws(p: Packed, X, Y, workspace, stream=None) -> None:
+    if (_call or _native()).sparse_gemm_smallm(1, p, X, Y, workspace, stream):
+        return
     prepared_sparse_gemm_smallm_ws(p, X, Y, workspace, stream)()
 
 
 def prepared_int4_gemv(q, qparams, rows: int, cols: int, group: int, x, y, stream=None):
-    fn = lib().egt_int4_gemv
     _check_int4_dev(q, qparams, rows, cols, group)
     args = (_dev(q), _dev(qparams), rows, cols, group, _need(x, 2 * cols, "x", True), _need(y, 2 * rows, "y", True))
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(q, qparams, x, y)):
-        st = fn(*args, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    return _prepared("INT4", lib().egt_int4_gemv, args, (q, qparams, x, y), stream)
 
 
 def _ptr_array(tensors):
@@ -551,26 +574,20 @@ def _ptr_array(tensors):
 
 def prepared_sparse_gemv_batch(ps, xs, ys, stream=None):
     """One launch for len(ps) identically shaped matrices: ys[k] = W[k].xs[k]."""
-    fn = lib().egt_sparse_gemv_batch
     for p, x, y in zip(ps, xs, ys):
         _check_packed_dev(p)
         _need(x, 2 * p.cols, "x", True)
         _need(y, 2 * p.rows, "y", True)
     views = (View * len(ps))(*[p.view() for p in ps])
-    xa, ya, n, sp = _ptr_array(xs), _ptr_array(ys), len(ps), _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(views, ps, xs, ys, xa, ya)):
-        st = fn(views, xa, ya, n, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    xa, ya = _ptr_array(xs), _ptr_array(ys)
+    args = (C.addressof(views), C.addressof(xa), C.addressof(ya), len(ps))
+    return _prepared("GEMV_BATCH", lib().egt_sparse_gemv_batch, args, (views, ps, xs, ys, xa, ya), stream)
 
 
 def prepared_sparse_gemm_smallm_batch(ps, Xs, Ys, stream=None):
     """One launch for len(ps) identically shaped matrices and M tokens each: Ys[k] = Xs[k] . W[k]^T.
     Xs[k]: (M, K), Ys[k]: (M, R) float16 device tensors, all Xs with one row stride, all Ys with one
     (the members may share one X)."""
-    fn = lib().egt_sparse_gemm_smallm_batch
     for p, X, Y in zip(ps, Xs, Ys):
         _check_xy(p, X, Y)
         if X.shape[0] != Xs[0].shape[0] or X.stride(0) != Xs[0].stride(0) or Y.stride(0) != Ys[0].stride(0):
@@ -578,14 +595,8 @@ def prepared_sparse_gemm_smallm_batch(ps, Xs, Ys, stream=None):
     views = (View * len(ps))(*[p.view() for p in ps])
     xa = (C.c_void_p * len(ps))(*[X.data_ptr() for X in Xs])
     ya = (C.c_void_p * len(ps))(*[Y.data_ptr() for Y in Ys])
-    args = (views, xa, Xs[0].stride(0), ya, Ys[0].stride(0), Xs[0].shape[0], len(ps))
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(views, ps, Xs, Ys, xa, ya)):
-        st = fn(*args, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    args = (C.addressof(views), C.addressof(xa), Xs[0].stride(0), C.addressof(ya), Ys[0].stride(0), Xs[0].shape[0], len(ps))
+    return _prepared("GEMM_BATCH", lib().egt_sparse_gemm_smallm_batch, args, (views, ps, Xs, Ys, xa, ya), stream)
 
 
 def sparse_gemm_smallm_batch(ps, Xs, Ys, stream=None) -> None:
@@ -593,19 +604,13 @@ def sparse_gemm_smallm_batch(ps, Xs, Ys, stream=None) -> None:
 
 
 def prepared_int4_gemv_batch(qs, qparams, rows: int, cols: int, group: int, xs, ys, stream=None):
-    fn = lib().egt_int4_gemv_batch
     for q, qp, x, y in zip(qs, qparams, xs, ys):
         _check_int4_dev(q, qp, rows, cols, group)
         _need(x, 2 * cols, "x", True)
         _need(y, 2 * rows, "y", True)
     qa, pa, xa, ya = _ptr_array(qs), _ptr_array(qparams), _ptr_array(xs), _ptr_array(ys)
-    n, sp = len(qs), _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(qs, qparams, xs, ys, qa, pa, xa, ya)):
-        st = fn(qa, pa, rows, cols, group, xa, ya, n, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    args = (C.addressof(qa), C.addressof(pa), rows, cols, group, C.addressof(xa), C.addressof(ya), len(qs))
+    return _prepared("INT4_BATCH", lib().egt_int4_gemv_batch, args, (qs, qparams, xs, ys, qa, pa, xa, ya), stream)
 
 
 def sparse_gemv_batch(ps, xs, ys, stream=None) -> None:
@@ -651,17 +656,13 @@ def prepared_gemv_stack(items, stream=None, form=STACK_AUTO):
     _check(lib().egt_gemv_stack_plan(arr, n, form, _np_ptr(table), table.nbytes, C.byref(plan)))
     dev = keep[0][-1].device
     table_dev = torch.from_numpy(table).to(dev)
-    fn, tp, ref, sp = lib().egt_gemv_stack_run, table_dev.data_ptr(), C.byref(plan), _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(table_dev, plan, keep, views, arr)):
-        st = fn(tp, ref, stream_ptr)
-        if st:
-            _check(st)
+    call = _prepared("TABLE", lib().egt_gemv_stack_run, (table_dev.data_ptr(), C.addressof(plan)),
+                     (table_dev, plan, keep, views, arr), stream)
     call.plan = plan
     return call
 
 
-def _prepared_gemm_table(items, M, stream):
+def _prepared_gemm_table(items, M):
     import torch
     n = len(items)
     arr = (GemmItem * n)()
@@ -676,7 +677,7 @@ def _prepared_gemm_table(items, M, stream):
     table = np.zeros(int(plan.table_bytes), dtype=np.uint8)
     _check(lib().egt_gemm_stack_plan(arr, n, M, _np_ptr(table), table.nbytes, C.byref(plan)))
     table_dev = torch.from_numpy(table).to(items[0][2].device)
-    return lib().egt_gemm_stack_run, table_dev.data_ptr(), C.byref(plan), plan, (table_dev, views, arr, items)
+    return (table_dev.data_ptr(), C.addressof(plan)), plan, (table_dev, views, arr, items)
 
 
 def prepared_gemm_stack(items, stream=None):
@@ -696,31 +697,17 @@ def prepared_gemm_stack(items, stream=None):
         if X.shape[0] != M or not X.is_contiguous() or not Y.is_contiguous():
             raise ValueError("every X and Y of the table must be contiguous and hold the same number of tokens")
         by_form.setdefault(p.n_keep, []).append((p, X, Y))
-    tables = [_prepared_gemm_table(group, M, stream) for group in by_form.values()]
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _tables=tables):
-        for fn, tp, ref, _, _ in _tables:
-            st = fn(tp, ref, stream_ptr)
-            if st:
-                _check(st)
-    call.plans = [t[3] for t in tables]
+    tables = [_prepared_gemm_table(group, M) for group in by_form.values()]
+    call = _prepared("TABLE", lib().egt_gemm_stack_run, [t[0] for t in tables], tables, stream)
+    call.plans = [t[1] for t in tables]
     call.plan = call.plans[0]
     return call
 
 
 def prepared_stream_read(src, nbytes: int, sink, stream=None):
-    fn = lib().egt_stream_read
     if src.numel() * src.element_size() < nbytes or sink.numel() * sink.element_size() < 4 * 4096:
         raise ValueError("stream_read: src shorter than nbytes, or sink shorter than 4096 words")
-    args = (_dev(src), nbytes, _dev(sink))
-    sp = _stream_ptr(stream)
-
-    def call(stream_ptr=sp, _keep=(src, sink)):
-        st = fn(*args, stream_ptr)
-        if st:
-            _check(st)
-    return call
+    return _prepared("READ", lib().egt_stream_read, (_dev(src), nbytes, _dev(sink)), (src, sink), stream)
 
 
 def stream_read(src, nbytes: int, sink, stream=None) -> None:
