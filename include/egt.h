@@ -10,11 +10,14 @@
  * through the same linear layers at once.
  *
  * General rules
- *  - Plain C linkage, no exceptions cross the boundary, no global state; every
- *    call is thread-safe with respect to the library (buffers are the caller's).
+ *  - Plain C linkage, no exceptions cross the boundary, no global state but the
+ *    worker threads below; every call is thread-safe with respect to the library
+ *    (buffers are the caller's).
  *  - The library never allocates or frees device memory and keeps no handles.
  *    Every buffer is owned by the caller.
- *  - "HOST" functions take host pointers and run on the CPU.  "DEVICE" functions
+ *  - "HOST" functions take host pointers and run on the CPU, the large ones on up
+ *    to 15 worker threads beside the caller's, which end by themselves when no
+ *    call has come for a fifth of a second.  "DEVICE" functions
  *    take device pointers (16-byte aligned), enqueue kernels on `stream`
  *    (a hipStream_t passed as void*, NULL = the default stream) and return
  *    without synchronising.

@@ -3,13 +3,25 @@
 // Sec. 3.3 "Sparse Index Structure" of the paper).  Plain C++, no GPU calls.
 #include "egt.h"
 
+#include "egt_host_simd.h"
+
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
+#include <system_error>
 #include <thread>
+#include <type_traits>
 #include <vector>
+
+#if defined(__unix__)
+#include <pthread.h>
+#define EGT_HOST_ATFORK 1
+#endif
 
 namespace {
 
@@ -17,9 +29,12 @@ namespace {
 inline double half_to_double(uint16_t h) {
   const int sign = h >> 15, e = (h >> 10) & 31, m = h & 1023;
   double v;
-  if (e == 0) v = std::ldexp((double)m, -24);
+  if (e == 0) v = (double)m * 0x1p-24;
   else if (e == 31) v = m ? NAN : INFINITY;
-  else v = std::ldexp((double)(m + 1024), e - 25);
+  else {
+    const uint64_t u = ((uint64_t)(e + 1008) << 52) | ((uint64_t)m << 42);
+    std::memcpy(&v, &u, 8);
+  }
   return sign ? -v : v;
 }
 
@@ -29,35 +44,131 @@ inline uint16_t double_to_half(double v) {
   if (std::isnan(v)) return sign | 0x7E00u;
   double a = std::fabs(v);
   if (a >= 65520.0) return sign | 0x7C00u;          // rounds to infinity
-  if (a < std::ldexp(1.0, -14)) {                    // subnormal range: units of 2^-24
-    const double q = std::nearbyint(std::ldexp(a, 24));
+  if (a < 0x1p-14) {                                 // subnormal range: units of 2^-24
+    const double q = std::nearbyint(a * 0x1p24);
     return sign | (uint16_t)q;                       // q == 1024 is the smallest normal
   }
-  int e;
-  std::frexp(a, &e);                                 // a = f * 2^e, f in [0.5, 1)
-  e -= 1;                                            // a in [2^e, 2^(e+1))
-  double q = std::nearbyint(std::ldexp(a, 10 - e));  // in [1024, 2048]
-  if (q >= 2048.0) { q = 1024.0; e += 1; }
-  return sign | (uint16_t)(((e + 15) << 10) + ((int)q - 1024));
+  uint64_t u;                                        // 42 of the 52 mantissa bits go, to nearest even
+  std::memcpy(&u, &a, 8);
+  u = (u + 0x1FFFFFFFFFFull + ((u >> 42) & 1)) >> 42;    // (a carry moves on into the exponent)
+  return sign | (uint16_t)(u - (1008u << 10));
 }
 
 inline bool half_is_finite(uint16_t h) { return ((h >> 10) & 31) != 31; }
 
 // ---------------------------------------------------------------- threading
-template <class F>
-void parallel_rows(int rows, F &&body) {
-  unsigned hw = std::thread::hardware_concurrency();
-  int nt = (int)std::min<unsigned>(hw ? hw : 1u, 16u);
-  nt = std::max(1, std::min(nt, rows / 64));
-  if (nt <= 1) { body(0, rows); return; }
-  std::vector<std::thread> th;
-  const int chunk = (rows + nt - 1) / nt;
-  for (int t = 0; t < nt; ++t) {
-    const int r0 = t * chunk, r1 = std::min(rows, r0 + chunk);
-    if (r0 >= r1) break;
-    th.emplace_back([&body, r0, r1] { body(r0, r1); });
+// Worker threads of the host functions.  Starting 15 threads takes 300 us, longer than they
+// then need for a matrix of four million weights, so they stay for the next call - and leave
+// by themselves when none has come for a fifth of a second.  At most MAX of them live at a
+// time, whatever calls there are; a call that finds them at work for another thread's call
+// does its work alone.  The calling thread takes part itself: a job is finished even if no
+// worker could be started.
+class Workers {
+ public:
+  static constexpr int MAX = 15;
+
+  // job(0), ..., job(parts - 1), each once, in any order and on any of up to `helpers` + 1 threads
+  template <class F>
+  static void run(int parts, int helpers, F &&job) {
+    Workers *w = helpers > 0 ? instance() : nullptr;
+    if (!w || !w->begin(parts, helpers, [](void *f, int k) { (*(std::remove_reference_t<F> *)f)(k); }, (void *)&job)) {
+      for (int k = 0; k < parts; ++k) job(k);
+      return;
+    }
+    w->work();
+    w->finish();
   }
-  for (auto &x : th) x.join();
+
+ private:
+  typedef void (*Part)(void *, int);
+  std::mutex mu_;
+  std::condition_variable wake_, done_;
+  std::atomic<uint32_t> epoch_{0};                   // counts jobs: idle workers watch it before they go to sleep
+  int alive_ = 0, inside_ = 0, seats_ = 0;           // workers; workers in the current job; how many more may join it
+  bool busy_ = false;
+  Part part_ = nullptr;
+  void *arg_ = nullptr;
+  int parts_ = 0;
+  std::atomic<int> next_{0};
+
+  // One object for the process.  It is never destroyed (workers may still be waiting when the
+  // process ends), and a child process starts with one of its own: threads do not survive fork.
+  static std::atomic<Workers *> &slot() {
+    static std::atomic<Workers *> s{[] {
+#ifdef EGT_HOST_ATFORK
+      pthread_atfork(nullptr, nullptr, [] { slot().store(new Workers); });
+#endif
+      return new Workers;
+    }()};
+    return s;
+  }
+  static Workers *instance() { return slot().load(); }
+
+  bool begin(int parts, int helpers, Part part, void *arg) {
+    std::lock_guard<std::mutex> lock(mu_);
+    if (busy_) return false;
+    busy_ = true;
+    part_ = part; arg_ = arg; parts_ = parts;
+    next_.store(0);
+    seats_ = std::min(helpers, MAX);
+    for (; alive_ < seats_; ++alive_) {
+      try {
+        std::thread([this] { serve(); }).detach();
+      } catch (const std::system_error &) {
+        break;
+      }
+    }
+    epoch_.fetch_add(1);
+    wake_.notify_all();
+    return true;
+  }
+  void work() {
+    for (int k; (k = next_.fetch_add(1)) < parts_;) part_(arg_, k);
+  }
+  void finish() {
+    std::unique_lock<std::mutex> lock(mu_);
+    seats_ = 0;                                       // who has not come by now is not needed
+    done_.wait(lock, [&] { return inside_ == 0; });
+    busy_ = false;
+  }
+  void serve() {
+    std::unique_lock<std::mutex> lock(mu_);
+    for (;;) {
+      if (!wake_.wait_for(lock, std::chrono::milliseconds(200), [&] { return seats_ > 0; })) {
+        --alive_;
+        return;
+      }
+      --seats_;
+      ++inside_;
+      const uint32_t seen = epoch_.load();
+      lock.unlock();
+      work();
+      lock.lock();
+      if (--inside_ == 0) done_.notify_one();
+      lock.unlock();
+      // the next pass over the same matrix usually follows at once: worth 20 us of looking
+      const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(20);
+      while (epoch_.load(std::memory_order_relaxed) == seen && std::chrono::steady_clock::now() < until) {}
+      lock.lock();
+    }
+  }
+};
+
+// body(r0, r1) over all rows in blocks; a thread pays from about 64 Ki columns' work on
+template <class F>
+void parallel_rows(int rows, int cols, F &&body) {
+  const unsigned hw = std::thread::hardware_concurrency();
+  const int64_t by_work = ((int64_t)rows * (int64_t)std::max(cols, 1)) >> 16;
+  const int nt = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1u), (int64_t)Workers::MAX + 1, (int64_t)rows / 8, by_work}));
+  if (nt <= 1) { body(0, rows); return; }
+  const int parts = std::min(rows, 4 * nt);           // (a thread that is held up leaves its share to the others)
+  Workers::run(parts, nt - 1, [&](int k) { body((int)((int64_t)rows * k / parts), (int)((int64_t)rows * (k + 1) / parts)); });
+}
+// check over all rows, then, if go() says so, body over all rows
+template <class C, class G, class F>
+void parallel_rows(int rows, int cols, C &&check, G &&go, F &&body) {
+  parallel_rows(rows, cols, check);
+  if (go()) parallel_rows(rows, cols, body);
 }
 
 // INT4 values in either nibble order
@@ -125,6 +236,21 @@ inline QParam make_qparam(double vmin, double vmax) {
   z = std::min(15.0, std::max(0.0, z));
   return {sb, s, (int)z};
 }
+#ifdef EGT_HOST_SIMD
+// the same from extrema that hold 0
+inline QParam make_qparam_simd(float lo, float hi) {
+  uint16_t sb = double_to_half(((double)hi - (double)lo) / 15.0);
+  if ((sb & 0x7FFF) == 0) sb = 0x3C00;
+  const float s = egt_simd::half_to_float(sb);
+  return {sb, s, egt_simd::zero_point(lo, s)};
+}
+#endif
+// FP16 bits of a zero point
+inline uint16_t zero_bits(int z) {
+  static const uint16_t bits[16] = {0x0000, 0x3C00, 0x4000, 0x4200, 0x4400, 0x4500, 0x4600, 0x4700,
+                                    0x4800, 0x4880, 0x4900, 0x4980, 0x4A00, 0x4A80, 0x4B00, 0x4B80};
+  return bits[z];
+}
 inline int make_code(double v, const QParam &p) {
   double q = std::nearbyint(v / p.s) + (double)p.z;
   q = std::min(15.0, std::max(0.0, q));
@@ -177,10 +303,13 @@ egt_status egt_prune_n4(const uint16_t *w, int64_t ldw, int rows, int cols, int 
   if (!w || !mask) return EGT_ERR_NULL;
   if (rows < 0 || cols < 0 || cols % 4 != 0 || n_keep < 1 || n_keep > 4 || ldw < cols || ldm < cols)
     return EGT_ERR_SHAPE;
-  parallel_rows(rows, [=](int r0, int r1) {
+  parallel_rows(rows, cols, [=](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       uint8_t *mr = mask + (int64_t)r * ldm;
+#ifdef EGT_HOST_SIMD
+      if (egt_simd::available()) { egt_simd::prune_row(wr, cols, n_keep, mr); continue; }
+#endif
       for (int c = 0; c < cols; c += 4) {
         // |w| ordering of finite binary16 numbers = ordering of the low 15 bits
         int mag[4];
@@ -209,7 +338,7 @@ egt_status egt_prune_n4_importance(const uint16_t *w, int64_t ldw, const float *
   for (int c = 0; c < cols; ++c)
     if (!(act_norm[c] >= 0.0f) || std::isinf(act_norm[c])) return EGT_ERR_NONFINITE;
   std::atomic<int> err(EGT_OK);
-  parallel_rows(rows, [&](int r0, int r1) {
+  parallel_rows(rows, cols, [&](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       for (int c = 0; c < cols; ++c) {
         if ((w[(int64_t)r * ldw + c] & 0x7C00) == 0x7C00) err.store(EGT_ERR_NONFINITE);
@@ -221,7 +350,7 @@ egt_status egt_prune_n4_importance(const uint16_t *w, int64_t ldw, const float *
     }
   });
   if (err.load() != EGT_OK) return (egt_status)err.load();
-  parallel_rows(rows, [=](int r0, int r1) {
+  parallel_rows(rows, cols, [=](int r0, int r1) {
 #pragma clang fp contract(off)
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
@@ -307,12 +436,15 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
   // group that is both over-full and holds a non-finite kept weight reports the mask.
   std::atomic<int64_t> first(INT64_MAX);             // (index of the 4-group in the matrix) * 8 + code
   const int64_t gpr = cols / 4;
-  parallel_rows(rows, [&](int r0, int r1) {
+  auto validate = [&](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       if ((int64_t)r * gpr * 8 > first.load(std::memory_order_relaxed)) break;
       const uint16_t *wr = w + (int64_t)r * ldw;
       const uint8_t *mr = mask + (int64_t)r * ldm;
       const int n_row = n_of(r);
+#ifdef EGT_HOST_SIMD
+      if (egt_simd::available() && egt_simd::row_valid(wr, mr, cols, n_row)) continue;
+#endif
       for (int c = 0; c < cols; c += 4) {
         int cnt = 0;
         bool nonfinite = false;
@@ -329,22 +461,29 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
         break;
       }
     }
-  });
-  if (first.load() != INT64_MAX) return (egt_status)(first.load() & 7);
+  };
 
   const int G = is_int4(val_kind) ? cols / group : 0;
   // first slot of every row (uniform rows: r * S)
+  std::vector<uint32_t> start((size_t)rows + 1);
   for (int64_t r = 0, t = 0; r <= rows; ++r) {
-    out->row_ptr[r] = (uint32_t)t;
+    start[(size_t)r] = (uint32_t)t;
     if (r < rows) t += (int64_t)n_of((int)r) * (cols / 4);
   }
   uint8_t *vals8 = (uint8_t *)out->values;
   uint16_t *vals16 = (uint16_t *)out->values;
-  uint32_t *row_ptr = out->row_ptr;
+  const uint32_t *row_ptr = start.data();
   uint16_t *idx = out->idx, *qparams = out->qparams;
+#ifdef EGT_HOST_SIMD
+  const bool simd = egt_simd::available() && (!is_int4(val_kind) || group % 8 == 0);
+#else
+  const bool simd = false;
+#endif
 
-  parallel_rows(rows, [=](int r0, int r1) {
+  auto encode = [=](int r0, int r1) {
     std::vector<QParam> qp((size_t)std::max(G, 1));
+    std::vector<float> qs((size_t)std::max(G, 1));
+    std::vector<int> qz((size_t)std::max(G, 1));
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       const uint8_t *mr = mask + (int64_t)r * ldm;
@@ -353,24 +492,47 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
         // the row's own group size; its parameters are stored once per `group` columns
         const int gr = row_group ? row_group[r] : group, rep = gr / group;
         for (int g0 = 0; g0 < G; g0 += rep) {
-          double vmin = INFINITY, vmax = -INFINITY;
-          for (int c = g0 * group; c < g0 * group + gr; ++c) {
-            if (!mr[c]) continue;
-            const double v = half_to_double(wr[c]);
-            vmin = std::min(vmin, v);
-            vmax = std::max(vmax, v);
+          QParam p;
+#ifdef EGT_HOST_SIMD
+          if (simd) {
+            float lo, hi;
+            egt_simd::extrema(wr + g0 * group, mr + g0 * group, gr, lo, hi);
+            p = make_qparam_simd(lo, hi);
+          } else
+#endif
+          {
+            double vmin = INFINITY, vmax = -INFINITY;
+            for (int c = g0 * group; c < g0 * group + gr; ++c) {
+              if (!mr[c]) continue;
+              const double v = half_to_double(wr[c]);
+              vmin = std::min(vmin, v);
+              vmax = std::max(vmax, v);
+            }
+            if (vmin > vmax) { vmin = 0.0; vmax = 0.0; }        // nothing kept
+            p = make_qparam(vmin, vmax);
           }
-          if (vmin > vmax) { vmin = 0.0; vmax = 0.0; }          // nothing kept
-          const QParam p = make_qparam(vmin, vmax);
           for (int g = g0; g < g0 + rep; ++g) {
             qp[g] = p;
+            qs[g] = (float)p.s; qz[g] = p.z;
             uint16_t *o = qparams + ((int64_t)r * G + g) * 2;
             o[0] = p.s_bits;
-            o[1] = double_to_half((double)p.z);
+            o[1] = zero_bits(p.z);
           }
         }
       }
       int64_t t = (int64_t)row_ptr[r];                            // global slot id
+#ifdef EGT_HOST_SIMD
+      if (simd) {
+        // (a row starts on a whole index word and a whole byte of values)
+        egt_simd::with_n(n_row, [&](auto c) {
+          constexpr int n = decltype(c)::n;
+          if (val_kind == EGT_VAL_FP16) egt_simd::pack_row_fp16<n>(wr, mr, cols, (uint8_t *)(vals16 + t), (uint8_t *)(idx + (t >> 3)));
+          else egt_simd::pack_row_int4<n>(wr, mr, cols, group, qs.data(), qz.data(), val_kind == EGT_VAL_INT4_PAIRED, vals8 + (t >> 1),
+                                          (uint8_t *)(idx + (t >> 3)));
+        });
+        continue;
+      }
+#endif
       uint32_t word = 0;
       for (int c = 0; c < cols; c += 4) {
         const int set = choose4(mr + c, n_row);
@@ -394,7 +556,10 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
         }
       }
     }
-  });
+  };
+  parallel_rows(rows, cols, validate, [&] { return first.load() == INT64_MAX; }, encode);
+  if (first.load() != INT64_MAX) return (egt_status)(first.load() & 7);
+  std::memcpy(out->row_ptr, start.data(), sizeof(uint32_t) * start.size());
   out->rows = rows; out->cols = cols; out->n_keep = row_n_keep ? 0 : n_keep;
   out->group_size = group; out->val_kind = val_kind;
   out->total_slots = row_ptr[rows];
@@ -434,9 +599,16 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
   std::atomic<int> err(EGT_OK);
   const uint16_t *idx = in->idx;
   const uint32_t *row_ptr = in->row_ptr;
-  parallel_rows(rows, [&](int r0, int r1) {
+  auto ascending = [&](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       int64_t t = (int64_t)row_ptr[r];
+#ifdef EGT_HOST_SIMD
+      if (egt_simd::available()) {
+        const uint8_t *ix = (const uint8_t *)(idx + (t >> 3));
+        if (!egt_simd::with_n(n_row[r], [&](auto c) { return egt_simd::offsets_ascend<decltype(c)::n>(ix, cols); })) err.store(EGT_ERR_BUFFER);
+        continue;
+      }
+#endif
       for (int c = 0; c < cols; c += 4) {
         int prev = -1;
         for (int k = 0; k < n_row[r]; ++k, ++t) {
@@ -446,8 +618,7 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
         }
       }
     }
-  });
-  if (err.load() != EGT_OK) return (egt_status)err.load();
+  };
 
   const uint8_t *vals8 = (const uint8_t *)in->values;
   const uint16_t *vals16 = (const uint16_t *)in->values;
@@ -455,8 +626,32 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
   const int val_kind = in->val_kind;
   const int G = is_int4(val_kind) ? cols / group : 0;
   const int *nr = n_row.data();
-  parallel_rows(rows, [=](int r0, int r1) {
+  auto decode = [=](int r0, int r1) {
+#ifdef EGT_HOST_SIMD
+    const bool simd = egt_simd::available() && (!is_int4(val_kind) || group % 8 == 0);
+    std::vector<float> qs((size_t)std::max(G, 1));
+    std::vector<int> qz((size_t)std::max(G, 1));
+#endif
     for (int r = r0; r < r1; ++r) {
+#ifdef EGT_HOST_SIMD
+      bool plain = simd;                               // zero points are integers in 0..15 and scales finite (of any encoder)
+      for (int g = 0; g < G && plain; ++g) {
+        const uint16_t *p = qparams + ((int64_t)r * G + g) * 2;
+        const float z = egt_simd::half_to_float(p[1]);
+        plain = half_is_finite(p[0]) && z >= 0.0f && z <= 15.0f && z == (float)(int)z;
+        qs[g] = egt_simd::half_to_float(p[0]); qz[g] = plain ? (int)z : 0;
+      }
+      if (plain) {
+        const int64_t t = (int64_t)row_ptr[r];
+        egt_simd::with_n(nr[r], [&](auto c) {
+          egt_simd::unpack_row<decltype(c)::n>(val_kind == EGT_VAL_FP16 ? (const uint8_t *)(vals16 + t) : vals8 + (t >> 1),
+                                               (const uint8_t *)(idx + (t >> 3)), cols, group, is_int4(val_kind) ? qs.data() : nullptr, qz.data(),
+                                               val_kind == EGT_VAL_INT4_PAIRED, w_dense ? w_dense + (int64_t)r * ldw : nullptr,
+                                               mask ? mask + (int64_t)r * ldm : nullptr);
+        });
+        continue;
+      }
+#endif
       if (w_dense) std::memset(w_dense + (int64_t)r * ldw, 0, sizeof(uint16_t) * (size_t)cols);
       if (mask) std::memset(mask + (int64_t)r * ldm, 0, (size_t)cols);
       int64_t t = (int64_t)row_ptr[r];
@@ -479,8 +674,9 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
         }
       }
     }
-  });
-  return EGT_OK;
+  };
+  parallel_rows(rows, cols, ascending, [&] { return err.load() == EGT_OK; }, decode);
+  return (egt_status)err.load();
 }
 
 egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, int group,
@@ -489,17 +685,35 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
   if (rows < 0 || cols < 0 || group <= 0 || group % 4 != 0 || cols % group != 0 || ldw < cols)
     return EGT_ERR_SHAPE;
   std::atomic<int> err(EGT_OK);
-  parallel_rows(rows, [&](int r0, int r1) {
-    for (int r = r0; r < r1; ++r)
+  auto finite = [&](int r0, int r1) {
+    for (int r = r0; r < r1; ++r) {
+#ifdef EGT_HOST_SIMD
+      if (egt_simd::available() && egt_simd::all_finite(w + (int64_t)r * ldw, cols)) continue;
+#endif
       for (int c = 0; c < cols; ++c)
         if (!half_is_finite(w[(int64_t)r * ldw + c])) err.store(EGT_ERR_NONFINITE);
-  });
-  if (err.load() != EGT_OK) return (egt_status)err.load();
+    }
+  };
   const int G = cols / group;
-  parallel_rows(rows, [=](int r0, int r1) {
+  auto quantise = [=](int r0, int r1) {
+#ifdef EGT_HOST_SIMD
+    const bool simd = egt_simd::available() && group % 8 == 0;
+#endif
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       for (int g = 0; g < G; ++g) {
+#ifdef EGT_HOST_SIMD
+        if (simd) {
+          float lo, hi;
+          egt_simd::extrema(wr + g * group, nullptr, group, lo, hi);
+          const QParam p = make_qparam_simd(lo, hi);
+          uint16_t *o = qparams + ((int64_t)r * G + g) * 2;
+          o[0] = p.s_bits;
+          o[1] = zero_bits(p.z);
+          egt_simd::quant_group(wr + g * group, group, (float)p.s, p.z, q + (int64_t)r * (cols / 2) + g * group / 2);
+          continue;
+        }
+#endif
         double vmin = INFINITY, vmax = -INFINITY;
         for (int c = g * group; c < (g + 1) * group; ++c) {
           const double v = half_to_double(wr[c]);
@@ -509,7 +723,7 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
         const QParam p = make_qparam(vmin, vmax);
         uint16_t *o = qparams + ((int64_t)r * G + g) * 2;
         o[0] = p.s_bits;
-        o[1] = double_to_half((double)p.z);
+        o[1] = zero_bits(p.z);
         for (int c = g * group; c < (g + 1) * group; c += 2) {
           const int q0 = make_code(half_to_double(wr[c]), p);
           const int q1 = make_code(half_to_double(wr[c + 1]), p);
@@ -517,8 +731,9 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
         }
       }
     }
-  });
-  return EGT_OK;
+  };
+  parallel_rows(rows, cols, finite, [&] { return err.load() == EGT_OK; }, quantise);
+  return (egt_status)err.load();
 }
 
 egt_status egt_fit_verify_cost(const int *m, const double *t, int n, double *a, double *b) {

@@ -448,6 +448,40 @@ def test_quant_int4_dense_bit_exact(g, cols):
     assert np.array_equal(q, oq) and np.array_equal(qp, oqp)
 
 
+@pytest.mark.parametrize("group", [8, 12, 64])                       # vector loops, plain loops, vector loops
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("spread", [0, 1, 2])
+def test_encoder_loops_bit_exact_on_ties_and_extreme_weights(group, n, spread):
+    # weights on a grid of half code steps (quotients that are exact ties), every finite FP16 pattern, powers of two
+    # from the subnormals up; masks that leave groups short; a row length that ends inside a block of 32 for the mask
+    rng = np.random.default_rng(100 * group + 10 * n + spread)
+    rows, cols = 70, 192
+    if spread == 0:
+        w = (rng.integers(-15, 16, (rows, cols)) * 0.5 * 2.0 ** rng.integers(-10, 3, (rows, 1))).astype(np.float16)
+    elif spread == 1:
+        bits = rng.integers(0, 65536, (rows, cols)).astype(np.uint16)
+        w = np.where((bits & 0x7C00) == 0x7C00, bits & 0x83FF, bits).astype(np.uint16).view(np.float16)
+    else:
+        w = (rng.choice([-1.0, 0.0, 1.0], (rows, cols)) * 2.0 ** rng.integers(-24, 15, (rows, cols))).astype(np.float16)
+    for width in (cols, cols - 4, 4):
+        assert np.array_equal(B.prune_n4(w[:, :width], n), O.prune_n4_magnitude(w[:, :width], n))
+    mask = (B.prune_n4(w, n) & (rng.random(w.shape) >= 0.2)).astype(np.uint8)
+    for kind in (B.VAL_INT4, B.VAL_INT4_PAIRED, B.VAL_FP16):
+        g = 0 if kind == B.VAL_FP16 else group
+        p, o = B.pack_2bitcsr(w, mask, n, g, kind), O.pack_2bitcsr(w, mask, n, g, kind)
+        _same_packed(p, o)
+        back, slots = B.unpack_2bitcsr(p)
+        col, value, _ = O.decode_2bitcsr(o)
+        ref = np.zeros(w.shape)
+        np.put_along_axis(ref, col, value, axis=1)
+        with np.errstate(over="ignore"):              # (a decoded value beyond 65504 is infinite)
+            ref = ref.astype(np.float16)
+        assert np.array_equal(back, ref) and np.array_equal(slots.sum(axis=1), np.full(rows, n * cols // 4))
+    q, qp = B.quant_int4(w, group)
+    oq, oqp = O.quant_int4_dense(w, group)
+    assert np.array_equal(q, oq) and np.array_equal(qp, oqp)
+
+
 def test_device_entry_points_reject_bad_arguments_without_a_gpu():
     L = B.lib()
     v = B.View(8, 64, 2, 32, 0, 16, 16, 16, 16)          # fake non-null aligned pointers, never used
