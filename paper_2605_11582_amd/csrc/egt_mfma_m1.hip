@@ -85,12 +85,12 @@ __global__ __launch_bounds__(1024) void k_sparse_m1_batch(const GemvBatch b, con
                                   pick4(b.x, blockIdx.y), pick4(b.y, blockIdx.y), g);
 }
 
-// Shapes the diagonal kernel covers: 2:4; K = 1024 or 2048 (several rows per tile)
+// Shapes the diagonal kernel covers: 2:4; K = 1024 or 2048 (INT4, several rows per tile)
 // or a multiple of 64 from 4096 up to 8 tiles per row (more would not leave two waves per
 // phase in a 16-wave workgroup to stage x in four pieces per thread); INT4 groups of 32 << j.
 bool sparse_m1_supported(const egt_2bitcsr &w) {
   if (w.n_keep != 2) return false;
-  const bool multirow = w.cols == 1024 || w.cols == 2048;
+  const bool multirow = w.val_kind != EGT_VAL_FP16 && (w.cols == 1024 || w.cols == 2048);
   if (!multirow && (w.cols < 4096 || w.cols % 64 != 0 || w.cols > 8 * 4096)) return false;
   if (w.val_kind == EGT_VAL_INT4) {
     const int gm = w.group_size / 32;
@@ -111,7 +111,6 @@ hipError_t launch_sparse_m1_batch(const egt_2bitcsr *ws, const uint16_t *const *
   }
   M1Geom g;
   m1_geometry(w, g);
-  const bool multirow = g.mr_shift >= 0;
   const bool g32 = w.val_kind == EGT_VAL_INT4 && w.group_size == 32;
   // tuning knobs: tiles per wave, waves per phase per block
   // measured optima: 4 tiles per wave and 4 waves per phase for one phase, 2 waves per phase
@@ -121,9 +120,9 @@ hipError_t launch_sparse_m1_batch(const egt_2bitcsr *ws, const uint16_t *const *
   if (wpp < 1) wpp = 1;
   if (wpp * g.phases > 16) wpp = 16 / g.phases;
   if (tpi != 1 && tpi != 2 && tpi != 4 && tpi != 8) tpi = 4;
-  if (w.val_kind == EGT_VAL_FP16 && tpi == 8) tpi = 4;
+  const bool lin = w.val_kind == EGT_VAL_FP16;
+  if (lin && tpi == 8) tpi = 4;
   if (g32) tpi = 4;
-  const bool lin = w.val_kind == EGT_VAL_FP16 && !multirow && !tune_flag("EGT_M1_NOLIN");
   LaunchShape ls;
   if (!m1_block_shape(g, lin, wpp, tpi, 1, 4, ls)) {
     // (a developer build's knobs may ask for a workgroup too small to stage x: the shipped shape then)
@@ -182,17 +181,10 @@ hipError_t launch_sparse_m1_batch(const egt_2bitcsr *ws, const uint16_t *const *
       default: return EGT_GO(EGT_VAL_INT4, 4);
     }
   }
-  if (lin) {
-    switch (tpi) {
-      case 1: return EGT_GOL(1);
-      case 2: return EGT_GOL(2);
-      default: return EGT_GOL(4);
-    }
-  }
   switch (tpi) {
-    case 1: return EGT_GO(EGT_VAL_FP16, 1);
-    case 2: return EGT_GO(EGT_VAL_FP16, 2);
-    default: return EGT_GO(EGT_VAL_FP16, 4);
+    case 1: return EGT_GOL(1);
+    case 2: return EGT_GOL(2);
+    default: return EGT_GOL(4);
   }
 #undef EGT_GO
 #undef EGT_GO3

@@ -52,6 +52,37 @@ def test_sparse_gemv_small(rows, cols, n, g, kind):
     G.assert_close(y, y_ref, a_ref, "sparse_gemv")
 
 
+# rows that fill no tile of the row-per-wave kernels: the smallest rows, several rows per tile (a ragged last tile), one
+# tile with empty quads, a half chunk at the end of a row and as the first of its tile, several tiles per row, more rows
+# than a wave owns, the longest rows
+@pytest.mark.parametrize("rows,cols,g", [(5, 64, 32), (37, 96, 32), (2000, 256, 64), (131, 320, 64), (67, 736, 32), (300, 1344, 64), (33, 2880, 64),
+                                         (45, 4064, 32), (19, 4128, 32), (21, 5152, 32), (9, 11008, 256), (7, 24576, 128), (60001, 128, 128)])
+def test_rows_of_any_length_in_every_storage_form(rows, cols, g):
+    rng = np.random.default_rng(rows + cols)
+    x = synth.activations(cols, rows + cols)
+    w = synth.weights(rows, cols, rows + cols)
+    q, qp = B.quant_int4(w, g)
+    y_ref, a_ref = O.int4_gemv(q, qp, g, x)
+    G.assert_close(G.run_int4_gemv(q, qp, g, x), y_ref, a_ref, "dense")
+    masks = {n: B.prune_n4(w, n) for n in (1, 2, 3, 4)}
+    for n, kind in ((2, 0), (1, 0), (2, 2), (2, 1), (1, 1)):
+        p = B.pack_2bitcsr(w, masks[n], n, 0 if kind == 1 else g, kind)
+        y_ref, a_ref = O.gemv(G.oracle_view(p), x)
+        G.assert_close(G.run_sparse_gemv(p, x), y_ref, a_ref, f"n={n} kind={kind}")
+        if rows > 1:                                     # a broken row pointer: NaN in that row, the others as before
+            good = G.run_sparse_gemv(p, x)
+            p.row_ptr[rows // 2] += 8
+            bad = G.run_sparse_gemv(p, x)
+            keep = np.arange(rows) != rows // 2
+            assert np.isnan(bad[rows // 2]) and np.array_equal(bad[keep].view(np.uint16), good[keep].view(np.uint16))
+    for choices in ((1, 2), (1, 2, 3, 4)):
+        nk = rng.choice(choices, size=rows).astype(np.int32)
+        mask = np.choose((nk - 1)[:, None], [masks[n] for n in (1, 2, 3, 4)]).astype(np.uint8)
+        p = B.pack_2bitcsr_rows(w, mask, nk, g, 0)
+        y_ref, a_ref = O.gemv_rows(G.oracle_view(p), x)
+        G.assert_close(G.run_sparse_gemv(p, x), y_ref, a_ref, f"rows keep {choices}")
+
+
 @pytest.mark.parametrize("rows,cols,n,g,M", [(70, 4096, 2, 64, 1), (70, 4096, 1, 32, 1), (300, 1024, 2, 128, 6)])
 def test_row_group_sizes_run_on_the_ordinary_kernels(rows, cols, n, g, M):
     # rows quantised with group sizes of their own are stored at the finest granularity
