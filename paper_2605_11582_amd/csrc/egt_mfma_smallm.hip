@@ -61,12 +61,21 @@ struct SmallMKsGeom {
   int64_t ldx, ldy;
   uint32_t nib_mask, nib_magic;                        // 0x00F0000F, FP16 {1024.0, 64.0}
   uint32_t m8, m4, m2;                                 // masks of spread_idx
-  // K split over workgroups (blockIdx.y = slice s of nslices: the K-steps
-  // [s * nsteps / nslices, (s + 1) * nsteps / nslices)), and where the FP32 partial sums of
+  // K split over workgroups (blockIdx.y = slice s of nslices: nsteps = slice_q * nslices + slice_r, the first
+  // slice_r slices have slice_q + 1 K-steps, the others slice_q), and where the FP32 partial sums of
   // slice s, token m, row r go: ws[(s * M + m) * ws_ld + r]
   int nslices;
   int64_t ws_ld;
   float *ws;
+};
+// ... and the launch, from the host: divisions in the prologue would delay the first request by some 500 cycles.
+struct SmallMKsLaunch : SmallMKsGeom {
+  int nw;              // waves per workgroup
+  int blocks;          // workgroups along x
+  int tiles_q, tiles_r;     // ntiles = tiles_q * blocks + tiles_r: workgroup b owns tiles_q + (b < tiles_r)
+  int mtiles;               // row tiles of one member where several matrices run as one, else 0
+  int slice_q, slice_r;     // nsteps = slice_q * nslices + slice_r
+  int phases, phases_q;     // ceil(K-steps / nw) of a slice of slice_q + 1 steps and of one of slice_q
 };
 
 template <int KIND, int QW>
@@ -86,6 +95,13 @@ struct ATile {                        // A operand of one row tile, one K-step
 template <int ORD, int LOADS>
 struct TileRequest {
   static_assert(ORD >= 0 && ORD < LOADS, "a tile request beyond the count the vmcnt waits are built on");
+};
+
+struct SmallMBatch {
+  const uint32_t *row_ptr[EGT_MAX_BATCH];
+  const uint8_t *values[EGT_MAX_BATCH], *idx[EGT_MAX_BATCH], *qparams[EGT_MAX_BATCH];
+  const __half *X[EGT_MAX_BATCH];
+  __half *Y[EGT_MAX_BATCH];
 };
 
 constexpr int KS_PAIR = 1024 + 32;                 // 2:4: LDS bytes of a pair of tokens (512 B each)
@@ -109,10 +125,14 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {     // value of lan
 // RND: a workgroup may own more than NIT row tiles and takes them in rounds.
 // KS: the grid's y dimension splits K; a workgroup walks only the K-steps of its slice and
 // leaves FP32 partial sums in the caller's workspace (k_smallm_sum_slices finishes them).
-template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND, bool KS = false>
+// JOINT: several identically shaped matrices under one X as one: row tile v of the launch is tile
+// v - k * mtiles of member k = v / mtiles, so that X is staged once for all of them and a workgroup's
+// tiles, whoever they belong to, are requested together (g.ntiles counts the tiles of all members).
+template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND, bool KS = false, bool JOINT = false>
 __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_ptr, const uint8_t *__restrict__ values,
                                                const uint8_t *__restrict__ idx, const uint8_t *__restrict__ qparams,
-                                               const __half *__restrict__ X, __half *__restrict__ Y, const SmallMKsGeom g) {
+                                               const __half *__restrict__ X, __half *__restrict__ Y, const SmallMKsLaunch g,
+                                               const SmallMBatch *batch = nullptr) {
   extern __shared__ __align__(16) uint8_t xs[];       // X regions, later the partial sums
   static_assert(!(N1 && NT > 1), "1:4 runs one token group per pass");
   constexpr bool INT4 = KIND == EGT_VAL_INT4;
@@ -136,20 +156,20 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
   constexpr bool SEP = HOLD;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = blockDim.x >> 6;
+  const int nw = g.nw, nblocks = g.blocks;
   const int i = lane & 15, kb = lane >> 4;
   // row, chunk this lane fetches (LINA: of the index words only)
   const int li = (INT4 || LINA) ? (lane >> 2) : i, lc = (INT4 || LINA) ? (lane & 3) : kb;
   const int from = 4 * (4 * i + kb);                  // lane that fetched the chunk of lane (i, kb), as a byte address
   // Row tiles of this workgroup: blockIdx.x + k * gridDim.x, k < mytiles, taken NIT at a time
   // (rounds); round rr holds tiles_of(rr) of them.
-  const int mytiles = (g.ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int mytiles = g.tiles_q + ((int)blockIdx.x < g.tiles_r ? 1 : 0);
   const int rounds = RND ? (mytiles + NIT - 1) / NIT : 1;
   auto tiles_of = [&](int rr) { return RND ? min(NIT, mytiles - rr * NIT) : mytiles; };
   // the K-steps of this workgroup: [step0, nsteps)
-  const int step0 = KS ? (int)blockIdx.y * g.nsteps / g.nslices : 0;
-  const int nsteps = KS ? ((int)blockIdx.y + 1) * g.nsteps / g.nslices : g.nsteps;
-  const int phases = (nsteps - step0 + nw - 1) / nw;
+  const int step0 = KS ? (int)blockIdx.y * g.slice_q + min((int)blockIdx.y, g.slice_r) : 0;
+  const int nsteps = KS ? step0 + g.slice_q + ((int)blockIdx.y < g.slice_r ? 1 : 0) : g.nsteps;
+  const int phases = KS ? (nsteps - step0 == g.slice_q ? g.phases_q : g.phases) : g.phases;
   const uint32_t magic = in_vgpr(g.nib_magic);
   const uint32_t S_row = (uint32_t)g.nchunks * 32u;
   uint8_t *region = xs + wave * REGION;
@@ -162,24 +182,46 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
   constexpr int PSTRIDE = SEP ? PART : REGION;        // bytes from one wave's partial sums to the next
   uint8_t *parts = SEP ? xs + nw * REGION : xs;
   uint32_t *flags = (uint32_t *)(xs + nw * (SEP ? REGION + PART : REGION));
-  const int frow0 = 16 * ((int)blockIdx.x + (int)(threadIdx.x >> 4) * (int)gridDim.x) + (int)(threadIdx.x & 15);
-  auto flag_row = [&](int rr) {                       // the row whose pointer this thread checks in round rr
-    return RND ? frow0 + 16 * rr * NIT * (int)gridDim.x : frow0;
+  // member of row tile v of the launch, and the tile inside it
+  auto member = [&](int &v) {
+    if constexpr (!JOINT) return 0;
+    const int k = (v >= g.mtiles) + (v >= 2 * g.mtiles) + (v >= 3 * g.mtiles);
+    v -= k * g.mtiles;
+    return k;
   };
-  auto flag_checked = [&](int rr) { return (int)threadIdx.x < 16 * tiles_of(rr) && flag_row(rr) < g.rows; };
-  auto load_rp = [&](int rr) { return flag_checked(rr) ? row_ptr[flag_row(rr)] : 0u; };
+  // the row (of its member) whose pointer this thread checks in round rr
+  auto flag_row = [&](int rr, int &k) {
+    int v = (int)blockIdx.x + ((RND ? rr * NIT : 0) + (int)(threadIdx.x >> 4)) * nblocks;
+    k = member(v);
+    return 16 * v + (int)(threadIdx.x & 15);
+  };
+  auto flag_checked = [&](int rr) { int k; return (int)threadIdx.x < 16 * tiles_of(rr) && flag_row(rr, k) < g.rows; };
+  auto load_rp = [&](int rr) {
+    int k;
+    const int r = flag_row(rr, k);
+    if (!flag_checked(rr)) return 0u;
+    if constexpr (JOINT) return pick4(batch->row_ptr, (unsigned)k)[r];
+    return row_ptr[r];
+  };
   const bool fcheck0 = flag_checked(0);
-  uint32_t frp = fcheck0 ? row_ptr[frow0] : 0u, frp_next = 0;
+  uint32_t frp = load_rp(0), frp_next = 0;
 
-  const __amdgpu_buffer_rsrc_t r_val = make_rsrc(values, g.val_bytes), r_idx = make_rsrc(idx, g.idx_bytes);
-  const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(qparams, g.qp_bytes), r_x = make_rsrc(X, g.x_bytes);
+  const __amdgpu_buffer_rsrc_t r_val0 = make_rsrc(values, g.val_bytes), r_idx0 = make_rsrc(idx, g.idx_bytes);
+  const __amdgpu_buffer_rsrc_t r_qp0 = make_rsrc(qparams, g.qp_bytes), r_x = make_rsrc(X, g.x_bytes);
   auto load_a = [&](ATile<KIND, QW> &a, int it, int step, int rr) {
     // A tile past the last one of the round is requested out of range of the buffers: such a
     // request returns zeros and moves no data (the count of requests per phase stays fixed).
     const int nit_r = RND ? tiles_of(rr) : mytiles;
     const bool on = it < nit_r;                                               // uniform
     const uint32_t off_range = 0xFFFFFFF0u;
-    const int rt = (int)blockIdx.x + ((RND ? rr * NIT : 0) + min(it, nit_r - 1)) * (int)gridDim.x;
+    int rt = (int)blockIdx.x + ((RND ? rr * NIT : 0) + min(it, nit_r - 1)) * nblocks;
+    // (pinned, so that the member and its buffer resources are worked out at every request: kept for all of a
+    //  workgroup's tiles they would fill the scalar registers and spill)
+    if constexpr (JOINT) asm volatile("" : "+s"(rt));
+    const unsigned mk = (unsigned)member(rt);                                 // uniform
+    const __amdgpu_buffer_rsrc_t r_val = JOINT ? make_rsrc(pick4(batch->values, mk), g.val_bytes) : r_val0;
+    const __amdgpu_buffer_rsrc_t r_idx = JOINT ? make_rsrc(pick4(batch->idx, mk), g.idx_bytes) : r_idx0;
+    const __amdgpu_buffer_rsrc_t r_qp = JOINT ? make_rsrc(pick4(batch->qparams, mk), g.qp_bytes) : r_qp0;
     const int s = min(step, nsteps - 1);
     // (the lane offsets are recomputed at every request: kept across the loops they would
     //  occupy a dozen registers)
@@ -550,15 +592,17 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
 
     // ---- partial sums to LDS: tile (it, jj) of wave w at w * PSTRIDE + (it * NT + jj) * 1024,
     //      float 4 * lane + v = D[row 4 (lane >> 4) + v][token lane & 15]
-    if (threadIdx.x < 16 * NIT)
-      flags[threadIdx.x] = ((RND ? flag_checked(r) : fcheck0) && frp == (uint32_t)flag_row(r) * S_row) ? 1u : 0u;
+    if (threadIdx.x < 16 * NIT) {
+      int k;
+      flags[threadIdx.x] = ((RND ? flag_checked(r) : fcheck0) && frp == (uint32_t)flag_row(r, k) * S_row) ? 1u : 0u;
+    }
 #pragma unroll
     for (int it = 0; it < NIT; ++it)
 #pragma unroll
       for (int jj = 0; jj < NT; ++jj)
         if (it < nit) *(f4 *)(parts + wave * PSTRIDE + (it * NT + jj) * 1024 + 16 * lane) = acc[it][jj];
     lds_barrier();
-    for (int unit = threadIdx.x; unit < NIT * NT * 256; unit += (int)blockDim.x) {
+    for (int unit = threadIdx.x; unit < NIT * NT * 256; unit += 64 * nw) {
       const int tj = unit >> 8, it = tj / NT, jj = tj % NT;
       if (it >= nit || j0 + jj >= ngroups) continue;  // uniform over a wave
       const int v = unit & 3, sl = (unit >> 2) & 63;  // register v of lane sl of the tile
@@ -569,7 +613,9 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
       float sum = 0.f;
 #pragma unroll
       for (int w = 0; w < NWMAX; ++w) sum += w < nw ? part[w] : 0.f;
-      const int row0 = 16 * ((int)blockIdx.x + (r * NIT + it) * (int)gridDim.x) + 4 * (sl >> 4);
+      int rt = (int)blockIdx.x + (r * NIT + it) * nblocks;
+      const int mk = member(rt);
+      const int row0 = 16 * rt + 4 * (sl >> 4);
       const int row = row0 + v;
       const int tok = 16 * (j0 + jj) + (sl & 15);
       if constexpr (KS) {
@@ -582,7 +628,7 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
       if (flags[16 * it + 4 * (sl >> 4) + v]) hv = __half_as_ushort(__float2half(sum));
       const uint32_t h1 = quad_bcast<1>(hv), h2 = quad_bcast<2>(hv), h3 = quad_bcast<3>(hv);
       if (tok < g.M) {
-        __half *dst = Y + (int64_t)tok * g.ldy + row;
+        __half *dst = (JOINT ? pick4(batch->Y, (unsigned)__builtin_amdgcn_readfirstlane(mk)) : Y) + (int64_t)tok * g.ldy + row;
         if (g.vec_store && row0 + 3 < g.rows) {
           if (v == 0) *(u2 *)dst = u2{hv | (h1 << 16), h2 | (h3 << 16)};
         } else if (row < g.rows) {
@@ -609,24 +655,24 @@ __global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks(const uint32_t 
                                                                   const uint8_t *__restrict__ qparams,
                                                                   const __half *__restrict__ X,
                                                                   __half *__restrict__ Y,
-                                                                  const SmallMKsGeom g) {
+                                                                  const SmallMKsLaunch g) {
   smallm_ks_body<KIND, NT, NIT, NWMAX, QW, N1, RND, KS>(row_ptr, values, idx, qparams, X, Y, g);
 }
 
-// Up to four identically shaped products (the q/k/v or gate/up projections under the same
-// tokens or under tokens of their own) in one launch: blockIdx.y names the member, whose
-// workgroups run the very body of the single-matrix kernel.
-struct SmallMBatch {
-  const uint32_t *row_ptr[EGT_MAX_BATCH];
-  const uint8_t *values[EGT_MAX_BATCH], *idx[EGT_MAX_BATCH], *qparams[EGT_MAX_BATCH];
-  const __half *X[EGT_MAX_BATCH];
-  __half *Y[EGT_MAX_BATCH];
-};
+// Up to four identically shaped products (the q/k/v or gate/up projections) in one launch.  Under
+// tokens of their own, blockIdx.y names the member, whose workgroups run the very body of the
+// single-matrix kernel; under the same tokens the members run as one matrix (JOINT).  Three times
+// 4096 x 4096 at 16 tokens: 14.5 us member by member, 8.0 as one.
 template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND>
-__global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks_batch(const SmallMBatch b, const SmallMKsGeom g) {
+__global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks_batch(const SmallMBatch b, const SmallMKsLaunch g) {
   const unsigned k = blockIdx.y;
   smallm_ks_body<KIND, NT, NIT, NWMAX, QW, N1, RND, false>(pick4(b.row_ptr, k), pick4(b.values, k), pick4(b.idx, k), pick4(b.qparams, k),
                                                            pick4(b.X, k), pick4(b.Y, k), g);
+}
+
+template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND>
+__global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks_joint(const SmallMBatch b, const SmallMKsLaunch g) {
+  smallm_ks_body<KIND, NT, NIT, NWMAX, QW, N1, RND, false, true>(nullptr, nullptr, nullptr, nullptr, b.X[0], nullptr, g, &b);
 }
 
 // Shapes covered: 2:4 with K a multiple of 64, 1:4 with K a multiple of 128; INT4 groups
@@ -668,7 +714,7 @@ __global__ __launch_bounds__(256) void k_smallm_sum_slices(const float *__restri
 }
 
 template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND, bool KS = false>
-static hipError_t go_ks(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, const SmallMKsGeom &g, int nw,
+static hipError_t go_ks(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, const SmallMKsLaunch &g, int nw,
                         int nblocks, hipStream_t stream, const SmallMBatch *batch = nullptr, int count = 1) {
   const size_t region = N1 ? 16 * KS_TOKEN_N1 : 8 * KS_PAIR;
   const size_t x_bytes = (size_t)nw * region, p_bytes = (size_t)nw * NIT * NT * 1024;
@@ -676,6 +722,9 @@ static hipError_t go_ks(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, co
   // the start of each wave's own region; + row-pointer flags
   const size_t lds = (NT > 1 ? x_bytes + p_bytes : x_bytes) + 64 * NIT;
   if constexpr (!KS) {
+    if constexpr (KIND == EGT_VAL_INT4)
+      if (batch && g.mtiles)
+        return launch(k_sparse_smallm_ks_joint<KIND, NT, NIT, NWMAX, QW, N1, (NIT > 1)>, dim3(nblocks), dim3(64 * nw), lds, stream, *batch, g);
     if (batch)
       return launch(k_sparse_smallm_ks_batch<KIND, NT, NIT, NWMAX, QW, N1, RND>, dim3(nblocks, count), dim3(64 * nw), lds, stream, *batch, g);
   }
@@ -708,6 +757,16 @@ static void smallm_geometry(const egt_2bitcsr &w, int64_t ldx, uint16_t *Y, int6
   g.nib_mask = 0x00F0000Fu; g.nib_magic = 0x54006400u;
   g.m8 = 0x00FF00FFu; g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
   g.nslices = 1; g.ws_ld = 0; g.ws = nullptr;
+}
+// Fills in the launch: workgroups, waves, and what the kernel would have to divide for.
+static void smallm_launch_geometry(SmallMKsLaunch &g, int nblocks, int nw, int nslices = 1) {
+  g.nw = nw; g.blocks = nblocks;
+  g.tiles_q = g.ntiles / nblocks; g.tiles_r = g.ntiles % nblocks;
+  g.mtiles = 0;
+  g.nslices = nslices;
+  g.slice_q = g.nsteps / nslices; g.slice_r = g.nsteps % nslices;
+  g.phases_q = (g.slice_q + nw - 1) / nw;
+  g.phases = nslices == 1 ? g.phases_q : (g.slice_q + nw) / nw;
 }
 
 // K split over workgroups: at larger M every compute unit pulls the whole of X (M * K * 2
@@ -767,7 +826,7 @@ hipError_t launch_sparse_smallm_split(const egt_2bitcsr &w, const uint16_t *X, i
     bool force;
     if (use_xs(w, ldx, M, xs_bytes, force)) return launch_sparse_smallm_xs(w, X, ldx, Y, ldy, M, ws, force, stream);
   }
-  SmallMKsGeom g;
+  SmallMKsLaunch g;
   int qw, row_blocks;
   smallm_geometry(w, ldx, Y, ldy, M, g, qw);
   g.nslices = smallm_slices(w, M, row_blocks);
@@ -777,6 +836,7 @@ hipError_t launch_sparse_smallm_split(const egt_2bitcsr &w, const uint16_t *X, i
   const int min_steps = g.nsteps / g.nslices;          // the shortest slice
   const int nw = min_steps < nwmax ? min_steps : nwmax;
   const int nblocks = row_blocks;
+  smallm_launch_geometry(g, nblocks, nw, g.nslices);
   const bool one = nblocks == g.ntiles;
   hipError_t e;
 #define EGT_KSS(NT, NIT, NWMAX)                                                                              \
@@ -794,7 +854,7 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
                                     int64_t ldy, int M, hipStream_t stream, const SmallMBatch *batch, int count) {
   if (w.rows == 0) return hipSuccess;
   const bool int4 = w.val_kind == EGT_VAL_INT4, n1 = w.n_keep == 1;
-  SmallMKsGeom g;
+  SmallMKsLaunch g;
   int qw;
   {
     const uint64_t chunks = (uint64_t)w.rows * (uint64_t)(w.cols / (n1 ? 128 : 64));
@@ -802,6 +862,11 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
     if (vb >= (1ull << 32) || xb >= (1ull << 32)) return hipErrorInvalidValue;   // 32-bit offsets
   }
   smallm_geometry(w, ldx, Y, ldy, M, g, qw);
+  bool joint = batch != nullptr;                      // members under one X: their row tiles as those of one matrix
+  const int mtiles = g.ntiles;
+  for (int k = 1; batch && k < count; ++k) joint = joint && batch->X[k] == batch->X[0];
+  joint = joint && int4;                              // (FP16 values: a product of more than 256 tiles has fewer waves, another order of additions)
+  if (joint) g.ntiles *= count;
   if (batch)                                          // 8-byte stores only where every member's Y allows them
     for (int k = 0; k < count; ++k)
       if ((uintptr_t)batch->Y[k] % 8 != 0) g.vec_store = 0;
@@ -823,6 +888,8 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
   const bool one = nblocks == g.ntiles;               // one row tile per workgroup
   if (f16x && !one && nwmax > 8) nwmax = 8;           // several tiles with FP16 values: 8 waves of 256 registers
   const int nw = g.nsteps < nwmax ? g.nsteps : nwmax;
+  smallm_launch_geometry(g, nblocks, nw);
+  if (joint) g.mtiles = mtiles;
   // (NIT > 1: the form with rounds only where a workgroup owns more than NIT row tiles)
 #define EGT_KS(KIND, NT, NIT, NWMAX, QW, N1)                                                     \
   ((NIT > 1 && (int64_t)nblocks * NIT < g.ntiles) ? go_ks<KIND, NT, NIT, NWMAX, QW, N1, (NIT > 1)>(w, X, Y, g, nw, nblocks, stream, batch, count) \

@@ -733,6 +733,32 @@ def test_sparse_gemm_batch_equals_separate_calls(rows, cols, n, g, kind, M, coun
             ybufs[k][1:M + 1, :rows].fill_(0)
 
 
+@pytest.mark.parametrize("rows,cols,n,g,kind,M,count", [
+    (16, 1024, 2, 128, 0, 5, 4),        # a tile a member
+    (1303, 512, 2, 64, 0, 9, 4),        # 328 tiles: two of a workgroup's tiles in different members, ragged last tiles
+    (5000, 256, 2, 128, 0, 16, 3),      # more tiles than a round holds
+    (4100, 640, 2, 128, 0, 40, 3),      # two token groups a pass, rounds
+    (4100, 512, 1, 128, 0, 20, 2),      # 1:4, two passes
+    (3000, 512, 2, 0, 1, 7, 2),         # FP16 values: 16 waves alone, 8 as one: stays member by member
+    (4200, 512, 2, 0, 1, 20, 2),
+])
+def test_products_under_one_x_run_as_one_matrix(rows, cols, n, g, kind, M, count):
+    # every member has the bits of its own call, rows with a broken pointer are NaN in their member only
+    torch = G.torch_mod()
+    ps = [_small_case(rows, cols, n, g, kind, seed=7700 + 13 * k + rows)[0] for k in range(count)]
+    X = synth.activation_rows(M, cols, 7700)
+    ps[count - 1].row_ptr[rows - 1] += 8
+    ps[0].row_ptr[0] += 8
+    Xd = G.to_dev(X.view(np.uint16)).view(torch.float16)
+    Ys = [torch.full((M, rows), 9.0, dtype=torch.float16, device="cuda") for _ in range(count)]
+    B.sparse_gemm_smallm_batch([p.to("cuda") for p in ps], [Xd] * count, Ys)
+    torch.cuda.synchronize()
+    for k in range(count):
+        Y = Ys[k].cpu().numpy()
+        assert np.array_equal(Y.view(np.uint16), G.run_sparse_gemm(ps[k], X).view(np.uint16)), k
+        assert np.isnan(Y).sum() == M * ((k == 0) + (k == count - 1))
+
+
 @pytest.mark.parametrize("M", [1, 3, 16, 40])
 def test_fused_projections_equal_the_separate_products(M):
     # q/k/v packed as one matrix (concat_rows): every output has the bits of the separate product
