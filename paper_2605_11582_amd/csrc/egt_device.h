@@ -55,6 +55,10 @@ hipError_t launch_sparse_smallm(const egt_2bitcsr &w, const uint16_t *X, int64_t
                                 int64_t ldy, int M, hipStream_t stream);
 hipError_t launch_sparse_smallm_batch(const egt_2bitcsr *ws, const uint16_t *const *Xs, int64_t ldx, uint16_t *const *Ys,
                                       int64_t ldy, int M, int count, hipStream_t stream);
+// 2 <= M <= 32, INT4, short rows: X held in registers; `count` matrices under one X (egt_mfma_smallm_hold.hip)
+bool sparse_smallm_hold_supported(const egt_2bitcsr &w, int64_t ldx, int M, int count);
+hipError_t launch_sparse_smallm_hold(const egt_2bitcsr *ws, const uint16_t *X, int64_t ldx, uint16_t *const *Ys, int64_t ldy, int M, int count,
+                                     hipStream_t stream);
 // any number of 2:4 (or of 1:4) INT4 small-M products in one launch (egt_gemm_stack_plan / egt_gemm_stack_run)
 bool smallm_stack_item_ok(const egt_2bitcsr &w, int M);
 int smallm_stack_blocks(int M, int n_keep, int rows);

@@ -19,6 +19,7 @@ hipError_t launch_sparse(const egt_2bitcsr &w, const uint16_t *X, int64_t ldx, u
   // 16-byte loads of X: token rows must start on a 16-byte boundary there
   if (M >= 2 && ldx % 8 == 0 && sparse_m1_tokens_supported(w, M) && !tune_flag("EGT_NO_M1T"))
     return launch_sparse_m1_tokens(w, X, ldx, Y, ldy, M, stream);
+  if (M >= 2 && sparse_smallm_hold_supported(w, ldx, M, 1)) return launch_sparse_smallm_hold(&w, X, ldx, &Y, ldy, M, 1, stream);
   if (M >= 2 && sparse_smallm_supported(w, ldx, M)) return launch_sparse_smallm(w, X, ldx, Y, ldy, M, stream);
   return launch_sparse_generic(w, X, ldx, Y, ldy, M, stream);
 }
@@ -56,7 +57,14 @@ hipError_t launch_sparse_gemm_batch(const egt_2bitcsr *ws, const uint16_t *const
   // the small-M kernel where a single call would take it (M = 1 and the few-token form of the M = 1 kernel have
   // batched forms of their own or none: one launch per member there)
   const bool tokens_form = M >= 2 && ldx % 8 == 0 && sparse_m1_tokens_supported(w, M) && !tune_flag("EGT_NO_M1T");
-  if (count >= 2 && M >= 2 && w.val_kind != EGT_VAL_INT4_PAIRED && !tokens_form && sparse_smallm_supported(w, ldx, M))
+  bool shared = true;
+  for (int k = 1; k < count; ++k) shared = shared && Xs[k] == Xs[0];
+  // up to 16 tokens the kernels of a small-M product add in the same order, so a member has the bits of its own
+  // call in either; with more it has to run in the one that its own call takes
+  const bool hold = M >= 2 && !tokens_form && sparse_smallm_hold_supported(w, ldx, M, 1);
+  if (M >= 2 && !tokens_form && shared && (hold || M <= 16) && sparse_smallm_hold_supported(w, ldx, M, count))
+    return launch_sparse_smallm_hold(ws, Xs[0], ldx, Ys, ldy, M, count, stream);
+  if (count >= 2 && M >= 2 && w.val_kind != EGT_VAL_INT4_PAIRED && !tokens_form && !(hold && M > 16) && sparse_smallm_supported(w, ldx, M))
     return launch_sparse_smallm_batch(ws, Xs, ldx, Ys, ldy, M, count, stream);
   for (int k = 0; k < count; ++k) {
     const hipError_t e = launch_sparse(ws[k], Xs[k], ldx, Ys[k], ldy, M, stream);

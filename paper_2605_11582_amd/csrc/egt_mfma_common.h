@@ -188,6 +188,28 @@ __device__ __forceinline__ T pick4(T const (&a)[EGT_MAX_BATCH], unsigned i) {
   return (i & 2) ? hi : lo;
 }
 
+// The same for products of several tokens.
+struct SmallMBatch {
+  const uint32_t *row_ptr[EGT_MAX_BATCH];
+  const uint8_t *values[EGT_MAX_BATCH], *idx[EGT_MAX_BATCH], *qparams[EGT_MAX_BATCH];
+  const __half *X[EGT_MAX_BATCH];
+  __half *Y[EGT_MAX_BATCH];
+};
+
+// Value of lane byte_addr / 4.
+__device__ __forceinline__ uint32_t lane_perm(int byte_addr, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(byte_addr, (int)v);
+}
+// Buffer resource over `bytes` bytes at p: loads through it take a 32-bit lane offset
+// plus a 32-bit wave-uniform offset (scalar registers, scalar arithmetic).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+template <int N>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {     // value of lane N of the 4-lane group
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, N * 0x55, 0xf, 0xf, true);
+}
+
 // Index of the four-lane group, (lane >> 2) & 3, selects among four values.
 __device__ __forceinline__ float select4(int k, float a0, float a1, float a2, float a3) {
   return (k & 2) ? ((k & 1) ? a3 : a2) : ((k & 1) ? a1 : a0);

@@ -97,28 +97,8 @@ struct TileRequest {
   static_assert(ORD >= 0 && ORD < LOADS, "a tile request beyond the count the vmcnt waits are built on");
 };
 
-struct SmallMBatch {
-  const uint32_t *row_ptr[EGT_MAX_BATCH];
-  const uint8_t *values[EGT_MAX_BATCH], *idx[EGT_MAX_BATCH], *qparams[EGT_MAX_BATCH];
-  const __half *X[EGT_MAX_BATCH];
-  __half *Y[EGT_MAX_BATCH];
-};
-
 constexpr int KS_PAIR = 1024 + 32;                 // 2:4: LDS bytes of a pair of tokens (512 B each)
 constexpr int KS_TOKEN_N1 = 1024 + 16;             // 1:4: LDS bytes of a token (1 KiB)
-
-__device__ __forceinline__ uint32_t lane_perm(int byte_addr, uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_ds_bpermute(byte_addr, (int)v);
-}
-// Buffer resource over `bytes` bytes at p: loads through it take a 32-bit lane offset
-// plus a 32-bit wave-uniform offset (scalar registers, scalar arithmetic).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-template <int N>
-__device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {     // value of lane N of the 4-lane group
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, N * 0x55, 0xf, 0xf, true);
-}
 
 // KIND: INT4 or FP16 values.  NT: token groups per pass.  NIT: row tiles per workgroup.
 // NWMAX: waves per workgroup at most.  QW: {scale, zero} pairs per chunk.  N1: 1:4.
@@ -661,8 +641,8 @@ __global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks(const uint32_t 
 
 // Up to four identically shaped products (the q/k/v or gate/up projections) in one launch.  Under
 // tokens of their own, blockIdx.y names the member, whose workgroups run the very body of the
-// single-matrix kernel; under the same tokens the members run as one matrix (JOINT).  Three times
-// 4096 x 4096 at 16 tokens: 14.5 us member by member, 8.0 as one.
+// single-matrix kernel; under the same tokens the members run as one matrix (JOINT; rows of up to
+// 4096 columns mostly in egt_mfma_smallm_hold.hip).
 template <int KIND, int NT, int NIT, int NWMAX, int QW, bool N1, bool RND>
 __global__ __launch_bounds__(64 * NWMAX) void k_sparse_smallm_ks_batch(const SmallMBatch b, const SmallMKsLaunch g) {
   const unsigned k = blockIdx.y;

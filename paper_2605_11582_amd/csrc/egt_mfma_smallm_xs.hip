@@ -47,13 +47,6 @@ constexpr int XS_REGION = 8 * XS_PAIR;               // one step, one token grou
 constexpr int XS_MAX_REGIONS = 16;                   // 135 168 B
 constexpr int XS_T = 2;                              // row tiles a wave works on at a time
 
-__device__ __forceinline__ uint32_t xs_lane_perm(int byte_addr, uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_ds_bpermute(byte_addr, (int)v);
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t xs_rsrc(const void *p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
 // What a lane fetched of one row tile over the steps of a slice (lane 4 r + c: chunk c of
 // row r of every step), and the row pointer lane r < 16 checks.
 template <int SPS>
@@ -80,9 +73,9 @@ __global__ __launch_bounds__(512) void k_smallm_xs(const uint32_t *__restrict__ 
   const int sps = g.slice_q + (slice < g.slice_r ? 1 : 0);              // <= SPS (host)
   const int tile0 = rb * g.tiles_q + min(rb, g.tiles_r), tile1 = tile0 + g.tiles_q + (rb < g.tiles_r ? 1 : 0);
 
-  const __amdgpu_buffer_rsrc_t r_val = xs_rsrc(values, g.val_bytes), r_idx = xs_rsrc(idx, g.idx_bytes);
-  const __amdgpu_buffer_rsrc_t r_qp = xs_rsrc(qparams, g.qp_bytes), r_x = xs_rsrc(X, g.x_bytes);
-  const __amdgpu_buffer_rsrc_t r_rp = xs_rsrc(row_ptr, g.rp_bytes);
+  const __amdgpu_buffer_rsrc_t r_val = make_rsrc(values, g.val_bytes), r_idx = make_rsrc(idx, g.idx_bytes);
+  const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(qparams, g.qp_bytes), r_x = make_rsrc(X, g.x_bytes);
+  const __amdgpu_buffer_rsrc_t r_rp = make_rsrc(row_ptr, g.rp_bytes);
   const uint32_t off_range = 0xFFFFFFF0u;             // past every buffer: zeros, no traffic
 
   // ---- X of the slice: region (step ls, group grp) at (ls * NG + grp) * XS_REGION; request u
@@ -183,10 +176,10 @@ __global__ __launch_bounds__(512) void k_smallm_xs(const uint32_t *__restrict__ 
           // fetched form -> operand form: lane (i, kb) takes what lane 4 i + kb fetched
           u4 nib;
 #pragma unroll
-          for (int d = 0; d < 4; ++d) nib[d] = xs_lane_perm(from, a[k].nib[ls][d]);
-          iw0[k] = xs_lane_perm(from, a[k].iw[ls][0]);
-          iw1[k] = xs_lane_perm(from, a[k].iw[ls][1]);
-          const uint32_t qp = xs_lane_perm(from, a[k].qp[ls]);
+          for (int d = 0; d < 4; ++d) nib[d] = lane_perm(from, a[k].nib[ls][d]);
+          iw0[k] = lane_perm(from, a[k].iw[ls][0]);
+          iw1[k] = lane_perm(from, a[k].iw[ls][1]);
+          const uint32_t qp = lane_perm(from, a[k].qp[ls]);
           const uint32_t s2 = __builtin_amdgcn_perm(qp, qp, 0x01000100u);
           const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(qp, qp, 0x03020302u), g.nib_magic);
 #pragma unroll

@@ -759,6 +759,54 @@ def test_products_under_one_x_run_as_one_matrix(rows, cols, n, g, kind, M, count
         assert np.isnan(Y).sum() == M * ((k == 0) + (k == count - 1))
 
 
+@pytest.mark.parametrize("rows,cols,n,g,M,count", [
+    (40, 4096, 2, 128, 2, 1),           # a tile a workgroup, sixteen K-steps, a ragged last tile
+    (4128, 4096, 2, 64, 5, 1),          # 258 tiles: two for two of the workgroups
+    (20500, 4032, 2, 32, 16, 1),        # six and five tiles in sets of two, a last K-step of three chunks
+    (12200, 4096, 2, 128, 7, 1),        # three tiles, a set of three
+    (37000, 2048, 2, 128, 9, 1),        # two streams, ten tiles
+    (9000, 1024, 2, 128, 3, 1),         # four streams, three tiles
+    (17000, 64, 2, 32, 16, 1),          # one chunk, eight streams
+    (9000, 2304, 2, 128, 32, 1),        # two token groups
+    (30000, 512, 2, 64, 17, 1),         # two token groups, streams
+    (3000, 4608, 1, 128, 11, 1),        # 1:4
+    (14000, 1920, 1, 32, 16, 1),        # 1:4, streams, four scales a chunk
+    (21000, 4096, 1, 64, 4, 1),         # 1:4, more than four tiles
+    (4100, 4096, 2, 128, 5, 4),         # 1028 tiles of four members under one X
+    (1303, 1024, 2, 64, 32, 3),         # ragged members, two token groups, streams
+    (7000, 512, 1, 128, 16, 4),
+])
+def test_activations_held_in_registers(rows, cols, n, g, M, count):
+    # rows over a workgroup's tiles, streams and sets; Y with a stride and an offset of its own
+    torch = G.torch_mod()
+    cases = [_small_case(rows, cols, n, g, 0, seed=8100 + 7 * k + rows) for k in range(count)]
+    X = synth.activation_rows(M, cols, 8100 + rows)
+    refs = [O.gemm_smallm(o, X) for _, o in cases]
+    ps = [p for p, _ in cases]
+    ps[count - 1].row_ptr[rows - 1] += 8
+    Xd = G.to_dev(X.view(np.uint16)).view(torch.float16)
+    pds = [p.to("cuda") for p in ps]
+    ld = rows + (5 if rows % 2 else 12)
+    ybufs = [torch.full((M + 2, ld), G.CANARY, dtype=torch.int16, device="cuda") for _ in range(count)]
+    Ys = [yb[1:M + 1, :rows].view(torch.float16) for yb in ybufs]
+    for rep in range(2):
+        if count == 1:
+            B.sparse_gemm_smallm(pds[0], Xd, Ys[0])
+        else:
+            B.sparse_gemm_smallm_batch(pds, [Xd] * count, Ys)
+        torch.cuda.synchronize()
+        for k in range(count):
+            host = ybufs[k].cpu().numpy().view(np.uint16)
+            assert np.all(host[0] == G.CANARY) and np.all(host[M + 1] == G.CANARY) and np.all(host[:, rows:] == G.CANARY), ("write outside Y", k)
+            Y = np.ascontiguousarray(host[1:M + 1, :rows]).view(np.float16)
+            good = slice(0, rows - 1 if k == count - 1 else rows)
+            G.assert_close(Y[:, good], refs[k][0][:, good], refs[k][1][:, good], f"member {k}")
+            assert np.isnan(Y).sum() == (M if k == count - 1 else 0)
+            if count > 1:
+                assert np.array_equal(Y.view(np.uint16), G.run_sparse_gemm(ps[k], X).view(np.uint16)), k
+            ybufs[k][1:M + 1, :rows].fill_(0)
+
+
 @pytest.mark.parametrize("M", [1, 3, 16, 40])
 def test_fused_projections_equal_the_separate_products(M):
     # q/k/v packed as one matrix (concat_rows): every output has the bits of the separate product
