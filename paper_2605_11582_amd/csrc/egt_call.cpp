@@ -13,8 +13,10 @@
 // The module is not linked against libegt.so: binding.py hands over the addresses of the
 // entry points of the library it has loaded (bind), whichever build that is.
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <cstdint>
+#include <exception>
 #include <vector>
 
 #include "egt.h"
@@ -65,7 +67,7 @@ struct {
   PyObject *raw_stream = nullptr, *get_device = nullptr;
 } B;
 struct {
-  PyObject *rows, *cols, *n_keep, *group, *val_kind, *row_ptr, *values, *idx, *qparams, *total_slots, *cuda_stream, *stream_ptr;
+  PyObject *rows, *cols, *n_keep, *group, *val_kind, *row_ptr, *values, *idx, *qparams, *total_slots, *cuda_stream, *stream_ptr, *value;
 } S;
 
 // ---------------------------------------------------------------- prepared calls
@@ -77,6 +79,26 @@ struct Call {
   PyObject *keep, *dict;
 };
 
+// What ctypes takes for a pointer: an integer, None, or an object that carries one (c_void_p)
+bool pointer_of(PyObject *o, void *&p) {
+  p = nullptr;
+  if (o == Py_None) return true;
+  if (PyLong_Check(o)) {
+    // (handles are read as the bits they are: negative ones too)
+    p = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
+    return p || !PyErr_Occurred();
+  }
+  PyObject *v = PyObject_GetAttr(o, S.value);
+  if (!v || !(v == Py_None || PyLong_Check(v))) {
+    Py_XDECREF(v);
+    PyErr_SetString(PyExc_TypeError, "stream_ptr: expected an integer, None or a c_void_p");
+    return false;
+  }
+  const bool ok = pointer_of(v, p);
+  Py_DECREF(v);
+  return ok;
+}
+
 PyObject *call_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
   Call *c = (Call *)self;
   const Py_ssize_t n = PyVectorcall_NARGS(nargsf), nk = kwnames ? PyTuple_GET_SIZE(kwnames) : 0;
@@ -86,8 +108,7 @@ PyObject *call_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObje
       PyErr_SetString(PyExc_TypeError, "a prepared call takes one argument, stream_ptr");
       return nullptr;
     }
-    stream = PyLong_AsVoidPtr(args[0]);
-    if (!stream && PyErr_Occurred()) return nullptr;
+    if (!pointer_of(args[0], stream)) return nullptr;
   }
   int st = 0;
   // (a launch waits when the queue is full: other threads of the program go on meanwhile)
@@ -172,12 +193,10 @@ bool plain_tensor(PyObject *o, int64_t bytes, bool f16, void *&ptr) {
   return true;
 }
 bool get_tensor(PyObject *o, PyObject *name, int64_t bytes, bool may_be_none, void *&ptr) {
-  PyObject *a = PyObject_GetAttr(o, name);
+  THPObjectPtr a(PyObject_GetAttr(o, name));     // (the packed matrix keeps it)
   if (!a) return false;
   ptr = nullptr;
-  const bool ok = a == Py_None ? may_be_none : plain_tensor(a, bytes, false, ptr);
-  Py_DECREF(a);                                       // (the packed matrix keeps it)
-  return ok;
+  return a.get() == Py_None ? may_be_none : plain_tensor(a.get(), bytes, false, ptr);
 }
 bool get_view(PyObject *p, egt_2bitcsr &w) {
   int64_t rows, cols, n, group, kind, total;
@@ -215,6 +234,16 @@ bool get_stream(PyObject *stream, void *&s) {
 PyObject *answer(bool ok) {
   if (!ok) PyErr_Clear();
   return PyBool_FromLong(ok);
+}
+// A tensor without memory of its own (under a transform, a fake mode, of a sparse layout) throws
+// where its address or its strides are asked for: no exception may cross into the interpreter.
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (const std::exception &) {
+    return answer(false);
+  }
 }
 
 // sparse_gemv(p, x, y, stream)
@@ -299,9 +328,9 @@ PyObject *bind(PyObject *, PyObject *args) {
 
 PyMethodDef methods[] = {
     {"bind", bind, METH_VARARGS, nullptr},
-    {"sparse_gemv", (PyCFunction)(void (*)(void))sparse_gemv, METH_FASTCALL, nullptr},
-    {"sparse_gemm_smallm", (PyCFunction)(void (*)(void))sparse_gemm_smallm, METH_FASTCALL, nullptr},
-    {"int4_gemv", (PyCFunction)(void (*)(void))int4_gemv, METH_FASTCALL, nullptr},
+    {"sparse_gemv", (PyCFunction)(void (*)(void))guarded<sparse_gemv>, METH_FASTCALL, nullptr},
+    {"sparse_gemm_smallm", (PyCFunction)(void (*)(void))guarded<sparse_gemm_smallm>, METH_FASTCALL, nullptr},
+    {"int4_gemv", (PyCFunction)(void (*)(void))guarded<int4_gemv>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "egt_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr, nullptr}};
@@ -328,7 +357,7 @@ PyMODINIT_FUNC PyInit_egt_call(void) {
   struct { PyObject **at; const char *name; } const names[] = {
       {&S.rows, "rows"}, {&S.cols, "cols"}, {&S.n_keep, "n_keep"}, {&S.group, "group"}, {&S.val_kind, "val_kind"}, {&S.row_ptr, "row_ptr"},
       {&S.values, "values"}, {&S.idx, "idx"}, {&S.qparams, "qparams"}, {&S.total_slots, "total_slots"}, {&S.cuda_stream, "cuda_stream"},
-      {&S.stream_ptr, "stream_ptr"}};
+      {&S.stream_ptr, "stream_ptr"}, {&S.value, "value"}};
   for (const auto &n : names)
     if (!(*n.at = PyUnicode_InternFromString(n.name))) return nullptr;
   const char *kinds[KINDS] = {"GEMV", "READ", "GEMM", "GEMM_WS", "INT4", "GEMV_BATCH", "GEMM_BATCH", "INT4_BATCH", "TABLE"};
