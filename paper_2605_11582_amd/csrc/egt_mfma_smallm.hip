@@ -235,10 +235,12 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
     } else if (LINA) {
       const uint32_t vrow = (uint32_t)min((int)in_vgpr((uint32_t)i), g.rows - 1 - 16 * rt);
       const uint32_t vl = on ? 64u * vrow * (uint32_t)g.nchunks + 16u * (uint32_t)kb : off_range;
+      // (a mask and not a selection: of that the compiler makes a branch with the request in both of its arms)
+      const uint32_t keep = (uint32_t)__builtin_amdgcn_readfirstlane((it - nit_r) >> 31);
       (void)TileRequest<VW, LPT>{};                   // requests 1 .. VW
 #pragma unroll
       for (int k = 0; k < VW; ++k)                    // chunk k of the step (clamped: uniform)
-        a.nib[k] = __builtin_amdgcn_raw_buffer_load_b128(r_val, vl, on ? 64u * (cu + (uint32_t)min(k, g.nchunks - 1 - 4 * s)) : 0u, 0);
+        a.nib[k] = __builtin_amdgcn_raw_buffer_load_b128(r_val, vl, keep & (64u * (cu + (uint32_t)min(k, g.nchunks - 1 - 4 * s))), 0);
     } else {
       (void)TileRequest<VW, LPT>{};                   // requests 1 .. VW
 #pragma unroll
