@@ -32,9 +32,8 @@ struct SmallMXsGeom {
   int ntiles;          // ceil(rows / 16)
   int gshift;          // group = 64 << gshift columns
   int groups_per_row;
-  int nslices;         // K slices (blockIdx.x): slice s owns slice_q + (s < slice_r) steps
-  int row_blocks;      // row blocks (blockIdx.y): block b owns tiles_q + (b < tiles_r) tiles
-  int nw, slice_q, slice_r, tiles_q, tiles_r;         // (from the host: divisions in the prologue would delay the first request)
+  int nslices;         // K slices; slice s owns the steps [s * nsteps / nslices, (s + 1) * nsteps / nslices)
+  int row_blocks;      // row block b owns the tiles [b * ntiles / row_blocks, (b + 1) * ntiles / row_blocks)
   uint32_t val_bytes, idx_bytes, qp_bytes, x_bytes, rp_bytes;   // extents of the arrays
   int64_t ldx;
   float *ws;           // 16 x 16 sums as the matrix instruction leaves them: ws[((s * ntiles + tile) * NG + grp) * 256 + 4 * lane + j]
@@ -67,11 +66,11 @@ __global__ __launch_bounds__(512) void k_smallm_xs(const uint32_t *__restrict__ 
   extern __shared__ __align__(16) uint8_t xs[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = g.nw;
-  const int slice = (int)blockIdx.x, rb = (int)blockIdx.y;
-  const int step0 = slice * g.slice_q + min(slice, g.slice_r);
-  const int sps = g.slice_q + (slice < g.slice_r ? 1 : 0);              // <= SPS (host)
-  const int tile0 = rb * g.tiles_q + min(rb, g.tiles_r), tile1 = tile0 + g.tiles_q + (rb < g.tiles_r ? 1 : 0);
+  const int nw = blockDim.x >> 6;
+  const int slice = (int)blockIdx.x % g.nslices, rb = (int)blockIdx.x / g.nslices;
+  const int step0 = slice * g.nsteps / g.nslices;
+  const int sps = (slice + 1) * g.nsteps / g.nslices - step0;           // <= SPS (host)
+  const int tile0 = rb * g.ntiles / g.row_blocks, tile1 = (rb + 1) * g.ntiles / g.row_blocks;
 
   const __amdgpu_buffer_rsrc_t r_val = make_rsrc(values, g.val_bytes), r_idx = make_rsrc(idx, g.idx_bytes);
   const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(qparams, g.qp_bytes), r_x = make_rsrc(X, g.x_bytes);
@@ -273,9 +272,6 @@ bool sparse_smallm_xs_plan(const egt_2bitcsr &w, int64_t ldx, int M, bool force,
   const int per_wave = (units + 7) / 8;
   nw = (units + per_wave - 1) / per_wave;
   if (nw < 4) nw = 4;                                 // X of the slice is fetched by all waves
-  g.nw = nw;
-  g.slice_q = g.nsteps / g.nslices; g.slice_r = g.nsteps % g.nslices;
-  g.tiles_q = g.ntiles / g.row_blocks; g.tiles_r = g.ntiles % g.row_blocks;
   const int sps_max = (g.nsteps + g.nslices - 1) / g.nslices;
   lds = (size_t)sps_max * (size_t)ng * XS_REGION;
   return true;
@@ -327,7 +323,7 @@ static hipError_t go_xs(const egt_2bitcsr &w, const uint16_t *X, const SmallMXsG
     if (e != hipSuccess) return e;
     asked_dev = dev;
   }
-  return launch(k_smallm_xs<NG, SPS, XS_T>, dim3(g.nslices, g.row_blocks), dim3(64 * nw), lds, stream, w.row_ptr,
+  return launch(k_smallm_xs<NG, SPS, XS_T>, dim3(g.row_blocks * g.nslices), dim3(64 * nw), lds, stream, w.row_ptr,
                 (const uint8_t *)w.values, (const uint8_t *)w.idx, (const uint8_t *)w.qparams, (const __half *)X, g);
 }
 
