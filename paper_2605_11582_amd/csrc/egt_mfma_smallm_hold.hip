@@ -402,11 +402,11 @@ hipError_t launch_sparse_smallm_hold(const egt_2bitcsr *ws, const uint16_t *X, i
     if ((uintptr_t)Ys[j] % 8 != 0) g.vec_store = 0;
   }
   const bool n1 = ws[0].n_keep == 1;
-#define EGT_H(QW, N1, NG) (count > 1 ? go_hold<QW, N1, NG, true>(b, g, ring, lds, stream) : go_hold<QW, N1, NG, false>(b, g, ring, lds, stream))
-  if (n1) return qw == 4 ? EGT_H(4, true, 1) : qw == 2 ? EGT_H(2, true, 1) : EGT_H(1, true, 1);
-  if (ng == 2) return qw == 2 ? EGT_H(2, false, 2) : EGT_H(1, false, 2);
-  return qw == 2 ? EGT_H(2, false, 1) : EGT_H(1, false, 1);
-#undef EGT_H
+#define EGT_HOLD(QW, N1, NG) (count > 1 ? go_hold<QW, N1, NG, true>(b, g, ring, lds, stream) : go_hold<QW, N1, NG, false>(b, g, ring, lds, stream))
+  if (n1) return qw == 4 ? EGT_HOLD(4, true, 1) : qw == 2 ? EGT_HOLD(2, true, 1) : EGT_HOLD(1, true, 1);
+  if (ng == 2) return qw == 2 ? EGT_HOLD(2, false, 2) : EGT_HOLD(1, false, 2);
+  return qw == 2 ? EGT_HOLD(2, false, 1) : EGT_HOLD(1, false, 1);
+#undef EGT_HOLD
 }
 
 }  // namespace egt
