@@ -41,13 +41,9 @@ hipError_t launch_sparse_m1_paired(const egt_2bitcsr &w, const uint16_t *x, uint
 bool sparse_m1_n1_supported(const egt_2bitcsr &w);
 hipError_t launch_sparse_m1_n1(const egt_2bitcsr &w, const uint16_t *x, uint16_t *y, hipStream_t stream);
 
-// M = 1, any row length (see sparse_rows_supported): 2:4, 1:4, rows of different lengths, dense INT4; `count`
-// identically shaped members
+// M = 1, 2:4 with FP16 values, rows that do not fill the tiles of the kernels above (see sparse_rows_supported)
 bool sparse_rows_supported(const egt_2bitcsr &w);
-hipError_t launch_sparse_rows(const egt_2bitcsr *ws, const uint16_t *const *xs, uint16_t *const *ys, int count, hipStream_t stream);
-bool int4_rows_supported(int rows, int cols, int group);
-hipError_t launch_int4_rows(const uint8_t *const *qs, const uint16_t *const *qps, int rows, int cols, int group, const uint16_t *const *xs,
-                            uint16_t *const *ys, int count, hipStream_t stream);
+hipError_t launch_sparse_rows(const egt_2bitcsr &w, const uint16_t *x, uint16_t *y, hipStream_t stream);
 
 // 2 <= M <= 64 on the sparse matrix cores (2:4 and 1:4; see sparse_smallm_supported)
 bool sparse_smallm_supported(const egt_2bitcsr &w, int64_t ldx, int M);

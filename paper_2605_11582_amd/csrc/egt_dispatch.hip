@@ -8,14 +8,12 @@ namespace egt {
 hipError_t launch_sparse(const egt_2bitcsr &w, const uint16_t *X, int64_t ldx, uint16_t *Y,
                          int64_t ldy, int M, hipStream_t stream) {
   if (w.val_kind == EGT_VAL_INT4_PAIRED) {            // tuned for M = 1 at 2:4; everything else slot by slot
-    if (M == 1 && sparse_m1_paired_supported(w) && !tune_flag("EGT_ROWS_ALL")) return launch_sparse_m1_paired(w, X, Y, stream);
-    if (M == 1 && sparse_rows_supported(w)) return launch_sparse_rows(&w, &X, &Y, 1, stream);
+    if (M == 1 && sparse_m1_paired_supported(w)) return launch_sparse_m1_paired(w, X, Y, stream);
     return launch_sparse_generic(w, X, ldx, Y, ldy, M, stream);
   }
-  if (M == 1 && tune_flag("EGT_ROWS_ALL") && sparse_rows_supported(w)) return launch_sparse_rows(&w, &X, &Y, 1, stream);
   if (M == 1 && sparse_m1_supported(w)) return launch_sparse_m1(w, X, Y, stream);
   if (M == 1 && sparse_m1_n1_supported(w)) return launch_sparse_m1_n1(w, X, Y, stream);
-  if (M == 1 && sparse_rows_supported(w)) return launch_sparse_rows(&w, &X, &Y, 1, stream);
+  if (M == 1 && sparse_rows_supported(w)) return launch_sparse_rows(w, X, Y, stream);
   // 16-byte loads of X: token rows must start on a 16-byte boundary there
   if (M >= 2 && ldx % 8 == 0 && sparse_m1_tokens_supported(w, M) && !tune_flag("EGT_NO_M1T"))
     return launch_sparse_m1_tokens(w, X, ldx, Y, ldy, M, stream);
@@ -26,8 +24,7 @@ hipError_t launch_sparse(const egt_2bitcsr &w, const uint16_t *X, int64_t ldx, u
 
 hipError_t launch_int4(const uint8_t *q, const uint16_t *qparams, int rows, int cols, int group,
                        const uint16_t *x, uint16_t *y, hipStream_t stream) {
-  if (int4_m1_supported(cols, group) && !tune_flag("EGT_ROWS_ALL")) return launch_int4_m1(q, qparams, rows, cols, group, x, y, stream);
-  if (int4_rows_supported(rows, cols, group)) return launch_int4_rows(&q, &qparams, rows, cols, group, &x, &y, 1, stream);
+  if (int4_m1_supported(cols, group)) return launch_int4_m1(q, qparams, rows, cols, group, x, y, stream);
   return launch_int4_generic(q, qparams, rows, cols, group, x, y, stream);
 }
 
@@ -40,12 +37,10 @@ hipError_t launch_sparse_batch(const egt_2bitcsr *ws, const uint16_t *const *xs,
     }
     return hipSuccess;
   }
-  if (tune_flag("EGT_ROWS_ALL") && sparse_rows_supported(ws[0])) return launch_sparse_rows(ws, xs, ys, count, stream);
   if (sparse_m1_supported(ws[0])) return launch_sparse_m1_batch(ws, xs, ys, count, stream);
   if (sparse_m1_n1_supported(ws[0])) return launch_sparse_m1_n1_batch(ws, xs, ys, count, stream);
-  if (ws[0].n_keep != 0 && sparse_rows_supported(ws[0])) return launch_sparse_rows(ws, xs, ys, count, stream);
-  for (int k = 0; k < count; ++k) {                   // shapes without a tuned kernel: one launch each
-    const hipError_t e = launch_sparse_generic(ws[k], xs[k], ws[k].cols, ys[k], ws[k].rows, 1, stream);
+  for (int k = 0; k < count; ++k) {                   // shapes without a batched kernel: one launch each, as a call of its own
+    const hipError_t e = launch_sparse(ws[k], xs[k], ws[k].cols, ys[k], ws[k].rows, 1, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -76,8 +71,7 @@ hipError_t launch_sparse_gemm_batch(const egt_2bitcsr *ws, const uint16_t *const
 hipError_t launch_int4_batch(const uint8_t *const *qs, const uint16_t *const *qps, int rows, int cols,
                              int group, const uint16_t *const *xs, uint16_t *const *ys, int count,
                              hipStream_t stream) {
-  if (int4_m1_supported(cols, group) && !tune_flag("EGT_ROWS_ALL")) return launch_int4_m1_batch(qs, qps, rows, cols, group, xs, ys, count, stream);
-  if (int4_rows_supported(rows, cols, group)) return launch_int4_rows(qs, qps, rows, cols, group, xs, ys, count, stream);
+  if (int4_m1_supported(cols, group)) return launch_int4_m1_batch(qs, qps, rows, cols, group, xs, ys, count, stream);
   for (int k = 0; k < count; ++k) {
     const hipError_t e = launch_int4_generic(qs[k], qps[k], rows, cols, group, xs[k], ys[k], stream);
     if (e != hipSuccess) return e;

@@ -35,9 +35,6 @@ __global__ __launch_bounds__(1024) void k_sparse_m1_n1_batch(const GemvBatch b, 
 
 // Shapes covered: 1:4; K = 2048 or 4096 (several rows per tile) or a multiple of 128
 // from 8192 up to 4 tiles per row (four waves per phase stage x); INT4 groups of 32 << j.
-// (Rows that leave a third of their tiles' lanes empty, 4096 x 11008, are 10 % faster on the
-// row-walking kernel, whose tiles are half as wide; they stay here because a product has the bits
-// of the same product in a table, and tables run this body.)
 bool sparse_m1_n1_supported(const egt_2bitcsr &w) {
   if (w.n_keep != 1) return false;
   const bool multirow = w.cols == 2048 || w.cols == 4096;

@@ -83,6 +83,94 @@ def test_rows_of_any_length_in_every_storage_form(rows, cols, g):
         G.assert_close(G.run_sparse_gemv(p, x), y_ref, a_ref, f"rows keep {choices}")
 
 
+# Row lengths and forms that the row-per-wave kernels do not take.  Their products hold a weight s (q - z) in FP32: not
+# rounded to FP16, in its range up to 15 times the largest scale, and multiplied with kept columns only.
+SLOT_BY_SLOT = [(70, 2880, 64, "dense"), (33, 736, 32, "dense"), (21, 4160, 32, "dense"), (70, 1536, 128, "dense"), (70, 2880, 64, 2), (67, 736, 32, 2), (21, 5152, 32, 2),
+                (70, 2880, 64, 1), (45, 1344, 32, 1), (19, 7040, 128, 1), (70, 2880, 64, "paired"), (130, 4096, 128, "12"), (45, 2112, 64, "1234")]
+
+
+def _slot_by_slot_case(rows, cols, g, form, w):
+    """(run(x), float64 product(x), whether column c is kept in each row (c)) of w in the storage form."""
+    if form == "dense":
+        q, qp = B.quant_int4(w, g)
+        return (lambda x: G.run_int4_gemv(q, qp, g, x)), (lambda x: O.int4_gemv(q, qp, g, x)), lambda c: np.ones(rows, bool)
+    if isinstance(form, str) and form.isdigit():
+        nk = np.random.default_rng(rows).choice([int(k) for k in form], size=rows).astype(np.int32)
+        mask = np.choose((nk - 1)[:, None], [B.prune_n4(w, n) for n in (1, 2, 3, 4)]).astype(np.uint8)
+        p = B.pack_2bitcsr_rows(w, mask, nk, g, 0)
+        return (lambda x: G.run_sparse_gemv(p, x)), (lambda x: O.gemv_rows(G.oracle_view(p), x)), lambda c: mask[:, c] != 0
+    n, kind = (2, 2) if form == "paired" else (form, 0)
+    mask = B.prune_n4(w, n)
+    p = B.pack_2bitcsr(w, mask, n, g, kind)
+    return (lambda x: G.run_sparse_gemv(p, x)), (lambda x: O.gemv(G.oracle_view(p), x)), lambda c: mask[:, c] != 0
+
+
+@pytest.mark.parametrize("rows,cols,g,form", SLOT_BY_SLOT)
+def test_weights_of_the_slot_by_slot_products_are_held_in_32_bits(rows, cols, g, form):
+    # two columns of different groups against each other: what is left of the two weights is exact in FP32 and rounds once
+    w = synth.weights(rows, cols, 9100 + rows)
+    a, b = 1, cols // 2 + 2
+    for c in (a, b):                                     # (kept in every row)
+        w[:, c & ~3:(c & ~3) + 4] *= np.where(np.arange(c & ~3, (c & ~3) + 4) == c, 1.0, 0.001).astype(np.float16)
+    run, ref, kept = _slot_by_slot_case(rows, cols, g, form, w)
+    assert kept(a).all() and kept(b).all()
+    x = np.zeros(cols, dtype=np.float16)
+    x[a], x[b] = 1.0, -1.0
+    y_ref, a_ref = ref(x)
+    y = run(x).astype(np.float64)
+    # y: half a unit in the last place of FP16 (2^-11, 2^-25 below the normals); the sum: one rounding to FP32
+    assert np.all(np.abs(y - y_ref) <= 2.0**-11 * np.abs(y_ref) + 2.0**-24 * a_ref + 2.0**-25)
+
+
+@pytest.mark.parametrize("rows,cols,g,form", SLOT_BY_SLOT)
+def test_weights_beyond_fp16_of_the_slot_by_slot_products(rows, cols, g, form):
+    # a group of extrema 0 and 65504 has s = 4368, and 15 s = 65520 is no FP16 number
+    rng = np.random.default_rng(9200 + rows)
+    w = rng.choice(np.array([0.0, 4368.0, 65504.0], dtype=np.float16), size=(rows, cols))
+    run, ref, _ = _slot_by_slot_case(rows, cols, g, form, w)
+    x = (rng.standard_normal(cols) * 2.0**-9).astype(np.float16)
+    x[::7] = 0
+    y_ref, a_ref = ref(x)
+    G.assert_close(run(x), y_ref, a_ref, f"{form}")
+
+
+@pytest.mark.parametrize("rows,cols,g,form", [c for c in SLOT_BY_SLOT if c[3] != "dense"] + [(70, 2880, 0, "fp16"), (70, 2880, 0, "fp16_14")])
+def test_infinite_activations_of_columns_that_a_row_does_not_keep(rows, cols, g, form):
+    w = synth.weights(rows, cols, 9300 + rows)
+    if str(form).startswith("fp16"):
+        n = 1 if form == "fp16_14" else 2
+        mask = B.prune_n4(w, n)
+        p = B.pack_2bitcsr(w, mask, n, 0, 1)
+        run, kept = (lambda x: G.run_sparse_gemv(p, x)), (lambda c: mask[:, c] != 0)
+    else:
+        run, _, kept = _slot_by_slot_case(rows, cols, g, form, w)
+    x = synth.activations(cols, 9300)
+    seen = 0
+    for c in (0, 4 * (cols // 8) + 1, cols - 1):
+        for v in (np.inf, np.nan):
+            xs = [x.copy(), x.copy()]
+            xs[0][c], xs[1][c] = 0.0, v
+            y = [run(k) for k in xs]
+            rest = ~kept(c)
+            seen += int(rest.sum())
+            assert np.array_equal(y[0][rest].view(np.uint16), y[1][rest].view(np.uint16)), (c, v)
+    assert seen > 0
+
+
+def test_infinite_activations_of_dense_rows_off_the_tiles():
+    # (q - z) x, and not q x - z sum(x): an infinity stays one where its code is not the zero point
+    rows, cols, g = 130, 1536, 128
+    w = synth.weights(rows, cols, 9400)
+    q, qp = B.quant_int4(w, g)
+    W = O.dequant_int4_dense(q, qp, g)
+    x = synth.activations(cols, 9400)
+    x[77] = np.inf
+    y = G.run_int4_gemv(q, qp, g, x)
+    with np.errstate(invalid="ignore"):
+        want = W[:, 77] * np.inf
+    assert np.array_equal(y, want.astype(np.float16), equal_nan=True)
+
+
 @pytest.mark.parametrize("rows,cols,n,g,M", [(70, 4096, 2, 64, 1), (70, 4096, 1, 32, 1), (300, 1024, 2, 128, 6)])
 def test_row_group_sizes_run_on_the_ordinary_kernels(rows, cols, n, g, M):
     # rows quantised with group sizes of their own are stored at the finest granularity
@@ -699,6 +787,25 @@ def test_sparse_gemv_batch_equals_separate_calls(rows, cols, n, g, kind, count):
         y = ys[k].cpu().numpy()
         G.assert_close(y, refs[k][0], refs[k][1], f"batch member {k}")
         assert np.array_equal(y.view(np.uint16), G.run_sparse_gemv(ps[k], xs[k]).view(np.uint16))
+
+
+@pytest.mark.parametrize("rows,cols,g,kind", [(64, 4096, 128, 0), (45, 2112, 64, 0), (33, 2048, 0, 1), (33, 2048, 64, 2)])
+def test_sparse_gemv_batch_of_ragged_matrices_equals_separate_calls(rows, cols, g, kind):
+    # members of one shape whose rows keep different counts: other row pointers, other extents
+    torch = G.torch_mod()
+    ps = []
+    for k, choices in enumerate(((1, 2), (1, 2, 3, 4), (1,))):
+        w, mask, nk = _ragged_case(rows, cols, g, kind, 7300 + k + rows, choices, drop=0.1)
+        ps.append(B.pack_2bitcsr_rows(w, mask, nk, g, kind))
+    assert len({p.total_slots for p in ps}) == 3
+    xs = [synth.activations(cols, 7300 + k) for k in range(3)]
+    ys = [torch.full((rows,), 9.0, dtype=torch.float16, device="cuda") for _ in ps]
+    B.sparse_gemv_batch([p.to("cuda") for p in ps], [G.to_dev(x.view(np.uint16)).view(torch.float16) for x in xs], ys)
+    torch.cuda.synchronize()
+    for p, x, y in zip(ps, xs, ys):
+        y_ref, a_ref = O.gemv_rows(G.oracle_view(p), x)
+        G.assert_close(y.cpu().numpy(), y_ref, a_ref, "ragged batch")
+        assert np.array_equal(y.cpu().numpy().view(np.uint16), G.run_sparse_gemv(p, x).view(np.uint16))
 
 
 @pytest.mark.parametrize("rows,cols,n,g,kind,M,count,shared", [
