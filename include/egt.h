@@ -17,7 +17,9 @@
  *    Every buffer is owned by the caller.
  *  - "HOST" functions take host pointers and run on the CPU, the large ones on up
  *    to 15 worker threads beside the caller's, which end by themselves when no
- *    call has come for a fifth of a second.  "DEVICE" functions
+ *    call has come for a fifth of a second and are stopped and joined when the
+ *    library is unloaded or the process ends (no call may be on its way when it is
+ *    unloaded); a forked child starts with none.  "DEVICE" functions
  *    take device pointers (16-byte aligned), enqueue kernels on `stream`
  *    (a hipStream_t passed as void*, NULL = the default stream) and return
  *    without synchronising.

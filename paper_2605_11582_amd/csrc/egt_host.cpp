@@ -13,7 +13,7 @@
 #include <cstdint>
 #include <cstring>
 #include <mutex>
-#include <system_error>
+#include <new>
 #include <thread>
 #include <type_traits>
 #include <vector>
@@ -62,7 +62,8 @@ inline bool half_is_finite(uint16_t h) { return ((h >> 10) & 31) != 31; }
 // by themselves when none has come for a fifth of a second.  At most MAX of them live at a
 // time, whatever calls there are; a call that finds them at work for another thread's call
 // does its work alone.  The calling thread takes part itself: a job is finished even if no
-// worker could be started.
+// worker could be started.  A library that is unloaded (or a process that ends) first stops
+// and joins them: no thread may be left in code that is no longer mapped.
 class Workers {
  public:
   static constexpr int MAX = 15;
@@ -70,7 +71,7 @@ class Workers {
   // job(0), ..., job(parts - 1), each once, in any order and on any of up to `helpers` + 1 threads
   template <class F>
   static void run(int parts, int helpers, F &&job) {
-    Workers *w = helpers > 0 ? instance() : nullptr;
+    Workers *w = helpers > 0 ? &instance() : nullptr;
     if (!w || !w->begin(parts, helpers, [](void *f, int k) { (*(std::remove_reference_t<F> *)f)(k); }, (void *)&job)) {
       for (int k = 0; k < parts; ++k) job(k);
       return;
@@ -79,44 +80,56 @@ class Workers {
     w->finish();
   }
 
+  // No worker is started from here on, and none is left when this returns.
+  void stop() {
+    std::thread last;
+    {
+      std::unique_lock<std::mutex> lock(mu_);
+      stopping_ = true;
+      epoch_.fetch_add(1);
+      wake_.notify_all();
+      done_.wait(lock, [&] { return alive_ == 0; });
+      last = std::move(left_);
+    }
+    if (last.joinable()) last.join();
+  }
+
+  // One object for the process, in memory of the library's own: it is stopped, but never destroyed (at the end of
+  // a process other threads may still be in a call).  A child process starts with a fresh one: threads do not
+  // survive fork, and a lock of another thread would stay locked.
+  static Workers &instance() { return *reinterpret_cast<Workers *>(memory_); }
+  static void start_afresh() { new (memory_) Workers; }
+
  private:
   typedef void (*Part)(void *, int);
+  static unsigned char memory_[];
   std::mutex mu_;
   std::condition_variable wake_, done_;
   std::atomic<uint32_t> epoch_{0};                   // counts jobs: idle workers watch it before they go to sleep
+  std::thread thread_[MAX];                          // joinable: a worker that has not left
+  std::thread left_;                                 // the worker that left last; it has joined the one before it
   int alive_ = 0, inside_ = 0, seats_ = 0;           // workers; workers in the current job; how many more may join it
-  bool busy_ = false;
+  bool busy_ = false, stopping_ = false;
   Part part_ = nullptr;
   void *arg_ = nullptr;
   int parts_ = 0;
   std::atomic<int> next_{0};
 
-  // One object for the process.  It is never destroyed (workers may still be waiting when the
-  // process ends), and a child process starts with one of its own: threads do not survive fork.
-  static std::atomic<Workers *> &slot() {
-    static std::atomic<Workers *> s{[] {
-#ifdef EGT_HOST_ATFORK
-      pthread_atfork(nullptr, nullptr, [] { slot().store(new Workers); });
-#endif
-      return new Workers;
-    }()};
-    return s;
-  }
-  static Workers *instance() { return slot().load(); }
-
   bool begin(int parts, int helpers, Part part, void *arg) {
     std::lock_guard<std::mutex> lock(mu_);
-    if (busy_) return false;
+    if (busy_ || stopping_) return false;
     busy_ = true;
     part_ = part; arg_ = arg; parts_ = parts;
     next_.store(0);
     seats_ = std::min(helpers, MAX);
-    for (; alive_ < seats_; ++alive_) {
+    for (int k = 0; k < MAX && alive_ < seats_; ++k) {
+      if (thread_[k].joinable()) continue;
       try {
-        std::thread([this] { serve(); }).detach();
-      } catch (const std::system_error &) {
+        thread_[k] = std::thread([this, k] { serve(k); });
+      } catch (const std::exception &) {              // (no thread or no memory for one)
         break;
       }
+      ++alive_;
     }
     epoch_.fetch_add(1);
     wake_.notify_all();
@@ -131,28 +144,44 @@ class Workers {
     done_.wait(lock, [&] { return inside_ == 0; });
     busy_ = false;
   }
-  void serve() {
+  void serve(int k) {
     std::unique_lock<std::mutex> lock(mu_);
     for (;;) {
-      if (!wake_.wait_for(lock, std::chrono::milliseconds(200), [&] { return seats_ > 0; })) {
-        --alive_;
-        return;
-      }
+      const bool called = wake_.wait_for(lock, std::chrono::milliseconds(200), [&] { return seats_ > 0 || stopping_; });
+      if (!called || seats_ == 0) break;              // (a job that has begun is finished first)
       --seats_;
       ++inside_;
       const uint32_t seen = epoch_.load();
       lock.unlock();
       work();
       lock.lock();
-      if (--inside_ == 0) done_.notify_one();
+      if (--inside_ == 0) done_.notify_all();
       lock.unlock();
       // the next pass over the same matrix usually follows at once: worth 20 us of looking
       const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(20);
       while (epoch_.load(std::memory_order_relaxed) == seen && std::chrono::steady_clock::now() < until) {}
       lock.lock();
     }
+    // a thread cannot join itself: it leaves its handle to the next one that leaves, or to stop()
+    std::thread before = std::move(left_);
+    left_ = std::move(thread_[k]);
+    if (--alive_ == 0) done_.notify_all();
+    lock.unlock();
+    if (before.joinable()) before.join();
   }
 };
+alignas(Workers) unsigned char Workers::memory_[sizeof(Workers)];
+
+// Runs when the library is loaded, and when it is unloaded or the process ends.
+struct WorkersOfTheLibrary {
+  WorkersOfTheLibrary() {
+    Workers::start_afresh();
+#ifdef EGT_HOST_ATFORK
+    pthread_atfork(nullptr, nullptr, [] { Workers::start_afresh(); });     // (given back when the library is unloaded)
+#endif
+  }
+  ~WorkersOfTheLibrary() { Workers::instance().stop(); }
+} workers_of_the_library;
 
 // body(r0, r1) over all rows in blocks; a thread pays from about 64 Ki columns' work on
 template <class F>
