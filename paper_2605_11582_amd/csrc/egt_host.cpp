@@ -16,7 +16,6 @@
 #include <new>
 #include <thread>
 #include <type_traits>
-#include <vector>
 
 #if defined(__unix__)
 #include <pthread.h>
@@ -68,11 +67,13 @@ class Workers {
  public:
   static constexpr int MAX = 15;
 
-  // job(0), ..., job(parts - 1), each once, in any order and on any of up to `helpers` + 1 threads
+  // job(0), ..., job(parts - 1), each once, in any order and on any of up to `helpers` + 1 threads.  A part does not
+  // throw - on a worker it would have nowhere to throw to - and so allocates nothing.
   template <class F>
   static void run(int parts, int helpers, F &&job) {
+    static_assert(noexcept(job(0)), "a part does not throw");
     Workers *w = helpers > 0 ? &instance() : nullptr;
-    if (!w || !w->begin(parts, helpers, [](void *f, int k) { (*(std::remove_reference_t<F> *)f)(k); }, (void *)&job)) {
+    if (!w || !w->begin(parts, helpers, [](void *f, int k) noexcept { (*(std::remove_reference_t<F> *)f)(k); }, (void *)&job)) {
       for (int k = 0; k < parts; ++k) job(k);
       return;
     }
@@ -101,7 +102,7 @@ class Workers {
   static void start_afresh() { new (memory_) Workers; }
 
  private:
-  typedef void (*Part)(void *, int);
+  typedef void (*Part)(void *, int) noexcept;
   static unsigned char memory_[];
   std::mutex mu_;
   std::condition_variable wake_, done_;
@@ -191,13 +192,7 @@ void parallel_rows(int rows, int cols, F &&body) {
   const int nt = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)(hw ? hw : 1u), (int64_t)Workers::MAX + 1, (int64_t)rows / 8, by_work}));
   if (nt <= 1) { body(0, rows); return; }
   const int parts = std::min(rows, 4 * nt);           // (a thread that is held up leaves its share to the others)
-  Workers::run(parts, nt - 1, [&](int k) { body((int)((int64_t)rows * k / parts), (int)((int64_t)rows * (k + 1) / parts)); });
-}
-// check over all rows, then, if go() says so, body over all rows
-template <class C, class G, class F>
-void parallel_rows(int rows, int cols, C &&check, G &&go, F &&body) {
-  parallel_rows(rows, cols, check);
-  if (go()) parallel_rows(rows, cols, body);
+  Workers::run(parts, nt - 1, [&](int k) noexcept { body((int)((int64_t)rows * k / parts), (int)((int64_t)rows * (k + 1) / parts)); });
 }
 
 // INT4 values in either nibble order
@@ -280,6 +275,8 @@ inline uint16_t zero_bits(int z) {
                                     0x4800, 0x4880, 0x4900, 0x4980, 0x4A00, 0x4A80, 0x4B00, 0x4B80};
   return bits[z];
 }
+// ... and back from the two halves a group is stored as
+inline QParam stored_qparam(const uint16_t *p) { return {p[0], half_to_double(p[0]), (int)half_to_double(p[1])}; }
 inline int make_code(double v, const QParam &p) {
   double q = std::nearbyint(v / p.s) + (double)p.z;
   q = std::min(15.0, std::max(0.0, q));
@@ -492,16 +489,18 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
     }
   };
 
+  parallel_rows(rows, cols, validate);
+  if (first.load() != INT64_MAX) return (egt_status)(first.load() & 7);
+
   const int G = is_int4(val_kind) ? cols / group : 0;
   // first slot of every row (uniform rows: r * S)
-  std::vector<uint32_t> start((size_t)rows + 1);
   for (int64_t r = 0, t = 0; r <= rows; ++r) {
-    start[(size_t)r] = (uint32_t)t;
+    out->row_ptr[r] = (uint32_t)t;
     if (r < rows) t += (int64_t)n_of((int)r) * (cols / 4);
   }
   uint8_t *vals8 = (uint8_t *)out->values;
   uint16_t *vals16 = (uint16_t *)out->values;
-  const uint32_t *row_ptr = start.data();
+  const uint32_t *row_ptr = out->row_ptr;
   uint16_t *idx = out->idx, *qparams = out->qparams;
 #ifdef EGT_HOST_SIMD
   const bool simd = egt_simd::available() && (!is_int4(val_kind) || group % 8 == 0);
@@ -510,13 +509,11 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
 #endif
 
   auto encode = [=](int r0, int r1) {
-    std::vector<QParam> qp((size_t)std::max(G, 1));
-    std::vector<float> qs((size_t)std::max(G, 1));
-    std::vector<int> qz((size_t)std::max(G, 1));
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       const uint8_t *mr = mask + (int64_t)r * ldm;
       const int n_row = n_of(r);
+      uint16_t *qr = is_int4(val_kind) ? qparams + (int64_t)r * G * 2 : nullptr;     // the row's {scale, zero} pairs
       if (is_int4(val_kind)) {
         // the row's own group size; its parameters are stored once per `group` columns
         const int gr = row_group ? row_group[r] : group, rep = gr / group;
@@ -541,11 +538,8 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
             p = make_qparam(vmin, vmax);
           }
           for (int g = g0; g < g0 + rep; ++g) {
-            qp[g] = p;
-            qs[g] = (float)p.s; qz[g] = p.z;
-            uint16_t *o = qparams + ((int64_t)r * G + g) * 2;
-            o[0] = p.s_bits;
-            o[1] = zero_bits(p.z);
+            qr[2 * g] = p.s_bits;
+            qr[2 * g + 1] = zero_bits(p.z);
           }
         }
       }
@@ -556,7 +550,7 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
         egt_simd::with_n(n_row, [&](auto c) {
           constexpr int n = decltype(c)::n;
           if (val_kind == EGT_VAL_FP16) egt_simd::pack_row_fp16<n>(wr, mr, cols, (uint8_t *)(vals16 + t), (uint8_t *)(idx + (t >> 3)));
-          else egt_simd::pack_row_int4<n>(wr, mr, cols, group, qs.data(), qz.data(), val_kind == EGT_VAL_INT4_PAIRED, vals8 + (t >> 1),
+          else egt_simd::pack_row_int4<n>(wr, mr, cols, group, qr, val_kind == EGT_VAL_INT4_PAIRED, vals8 + (t >> 1),
                                           (uint8_t *)(idx + (t >> 3)));
         });
         continue;
@@ -565,6 +559,7 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
       uint32_t word = 0;
       for (int c = 0; c < cols; c += 4) {
         const int set = choose4(mr + c, n_row);
+        const QParam p = qr ? stored_qparam(qr + 2 * (c / group)) : QParam{};       // (group % 4 == 0)
         for (int j = 0; j < 4; ++j) {
           if (!(set >> j & 1)) continue;
           word |= (uint32_t)j << (2 * (t & 7));
@@ -572,7 +567,6 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
           if (val_kind == EGT_VAL_FP16) {
             vals16[t] = kept ? wr[c + j] : (uint16_t)0;
           } else {
-            const QParam &p = qp[(c + j) / group];
             const int q = kept ? make_code(half_to_double(wr[c + j]), p) : p.z;
             // (a row is a whole number of 4-byte words and no other row shares them: the
             //  first nibble of a byte sets it, the second is or-ed in)
@@ -586,9 +580,7 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
       }
     }
   };
-  parallel_rows(rows, cols, validate, [&] { return first.load() == INT64_MAX; }, encode);
-  if (first.load() != INT64_MAX) return (egt_status)(first.load() & 7);
-  std::memcpy(out->row_ptr, start.data(), sizeof(uint32_t) * start.size());
+  parallel_rows(rows, cols, encode);
   out->rows = rows; out->cols = cols; out->n_keep = row_n_keep ? 0 : n_keep;
   out->group_size = group; out->val_kind = val_kind;
   out->total_slots = row_ptr[rows];
@@ -611,17 +603,15 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
   if ((w_dense && ldw < cols) || (mask && ldm < cols)) return EGT_ERR_SHAPE;
   // row_ptr: the uniform progression, or a running sum of whole rows that ends at total_slots
   const int64_t quarter = cols / 4;
-  std::vector<int> n_row((size_t)rows);
   for (int r = 0; r < rows; ++r) {
     const int64_t len = (int64_t)in->row_ptr[r + 1] - (int64_t)in->row_ptr[r];
     if (mixed) {
       if (quarter == 0 || len % quarter != 0 || len / quarter < 1 || len / quarter > 4) return EGT_ERR_BUFFER;
-      n_row[r] = (int)(len / quarter);
-    } else {
-      if (in->row_ptr[r] != (uint32_t)((int64_t)r * in->n_keep * quarter) || len != in->n_keep * quarter) return EGT_ERR_BUFFER;
-      n_row[r] = in->n_keep;
+    } else if (in->row_ptr[r] != (uint32_t)((int64_t)r * in->n_keep * quarter) || len != in->n_keep * quarter) {
+      return EGT_ERR_BUFFER;
     }
   }
+  auto n_of = [=](int r) { return mixed ? (int)((int64_t)(in->row_ptr[r + 1] - in->row_ptr[r]) / quarter) : in->n_keep; };
   if (rows > 0 && in->row_ptr[0] != 0) return EGT_ERR_BUFFER;
   if (mixed && in->row_ptr[rows] != in->total_slots) return EGT_ERR_BUFFER;
   // offsets of a 4-group must ascend strictly
@@ -631,16 +621,17 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
   auto ascending = [&](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       int64_t t = (int64_t)row_ptr[r];
+      const int n_row = n_of(r);
 #ifdef EGT_HOST_SIMD
       if (egt_simd::available()) {
         const uint8_t *ix = (const uint8_t *)(idx + (t >> 3));
-        if (!egt_simd::with_n(n_row[r], [&](auto c) { return egt_simd::offsets_ascend<decltype(c)::n>(ix, cols); })) err.store(EGT_ERR_BUFFER);
+        if (!egt_simd::with_n(n_row, [&](auto c) { return egt_simd::offsets_ascend<decltype(c)::n>(ix, cols); })) err.store(EGT_ERR_BUFFER);
         continue;
       }
 #endif
       for (int c = 0; c < cols; c += 4) {
         int prev = -1;
-        for (int k = 0; k < n_row[r]; ++k, ++t) {
+        for (int k = 0; k < n_row; ++k, ++t) {
           const int off = (idx[t >> 3] >> (2 * (t & 7))) & 3;
           if (off <= prev) err.store(EGT_ERR_BUFFER);
           prev = off;
@@ -648,33 +639,32 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
       }
     }
   };
+  parallel_rows(rows, cols, ascending);
+  if (err.load() != EGT_OK) return (egt_status)err.load();
 
   const uint8_t *vals8 = (const uint8_t *)in->values;
   const uint16_t *vals16 = (const uint16_t *)in->values;
   const uint16_t *qparams = in->qparams;
   const int val_kind = in->val_kind;
   const int G = is_int4(val_kind) ? cols / group : 0;
-  const int *nr = n_row.data();
   auto decode = [=](int r0, int r1) {
 #ifdef EGT_HOST_SIMD
     const bool simd = egt_simd::available() && (!is_int4(val_kind) || group % 8 == 0);
-    std::vector<float> qs((size_t)std::max(G, 1));
-    std::vector<int> qz((size_t)std::max(G, 1));
 #endif
     for (int r = r0; r < r1; ++r) {
+      const int n_row = n_of(r);
 #ifdef EGT_HOST_SIMD
       bool plain = simd;                               // zero points are integers in 0..15 and scales finite (of any encoder)
       for (int g = 0; g < G && plain; ++g) {
         const uint16_t *p = qparams + ((int64_t)r * G + g) * 2;
         const float z = egt_simd::half_to_float(p[1]);
         plain = half_is_finite(p[0]) && z >= 0.0f && z <= 15.0f && z == (float)(int)z;
-        qs[g] = egt_simd::half_to_float(p[0]); qz[g] = plain ? (int)z : 0;
       }
       if (plain) {
         const int64_t t = (int64_t)row_ptr[r];
-        egt_simd::with_n(nr[r], [&](auto c) {
+        egt_simd::with_n(n_row, [&](auto c) {
           egt_simd::unpack_row<decltype(c)::n>(val_kind == EGT_VAL_FP16 ? (const uint8_t *)(vals16 + t) : vals8 + (t >> 1),
-                                               (const uint8_t *)(idx + (t >> 3)), cols, group, is_int4(val_kind) ? qs.data() : nullptr, qz.data(),
+                                               (const uint8_t *)(idx + (t >> 3)), cols, group, is_int4(val_kind) ? qparams + (int64_t)r * G * 2 : nullptr,
                                                val_kind == EGT_VAL_INT4_PAIRED, w_dense ? w_dense + (int64_t)r * ldw : nullptr,
                                                mask ? mask + (int64_t)r * ldm : nullptr);
         });
@@ -685,7 +675,7 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
       if (mask) std::memset(mask + (int64_t)r * ldm, 0, (size_t)cols);
       int64_t t = (int64_t)row_ptr[r];
       for (int c = 0; c < cols; c += 4) {
-        for (int k = 0; k < nr[r]; ++k, ++t) {
+        for (int k = 0; k < n_row; ++k, ++t) {
           const int col = c + ((idx[t >> 3] >> (2 * (t & 7))) & 3);
           if (mask) mask[(int64_t)r * ldm + col] = 1;
           if (!w_dense) continue;
@@ -704,8 +694,8 @@ egt_status egt_unpack_2bitcsr(const egt_2bitcsr *in, uint16_t *w_dense, int64_t 
       }
     }
   };
-  parallel_rows(rows, cols, ascending, [&] { return err.load() == EGT_OK; }, decode);
-  return (egt_status)err.load();
+  parallel_rows(rows, cols, decode);
+  return EGT_OK;
 }
 
 egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, int group,
@@ -723,6 +713,8 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
         if (!half_is_finite(w[(int64_t)r * ldw + c])) err.store(EGT_ERR_NONFINITE);
     }
   };
+  parallel_rows(rows, cols, finite);
+  if (err.load() != EGT_OK) return (egt_status)err.load();
   const int G = cols / group;
   auto quantise = [=](int r0, int r1) {
 #ifdef EGT_HOST_SIMD
@@ -761,8 +753,8 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
       }
     }
   };
-  parallel_rows(rows, cols, finite, [&] { return err.load() == EGT_OK; }, quantise);
-  return (egt_status)err.load();
+  parallel_rows(rows, cols, quantise);
+  return EGT_OK;
 }
 
 egt_status egt_fit_verify_cost(const int *m, const double *t, int n, double *a, double *b) {

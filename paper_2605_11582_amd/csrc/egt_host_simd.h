@@ -137,6 +137,10 @@ EGT_V inline void extrema(const uint16_t *w, const uint8_t *mask, int n, float &
 
 EGT_V inline float half_to_float(uint16_t h) { return _mm_cvtss_f32(_mm_cvtph_ps(_mm_cvtsi32_si128(h))); }
 
+// A stored {scale, zero} pair: the zero point is an integer in 0..15.
+struct Pair { float s; int z; };
+EGT_V inline Pair pair_of(const uint16_t *qp, int g) { return {half_to_float(qp[2 * g]), (int)half_to_float(qp[2 * g + 1])}; }
+
 // Zero point of a group whose extrema (0 among them) start at `lo`, for the scale s.
 EGT_V inline int zero_point(float lo, float s) {
   const __m128 q = _mm_div_ss(_mm_set_ss(-lo), _mm_set_ss(s));
@@ -170,12 +174,13 @@ EGT_V inline uint64_t kept8(const uint8_t *mask) {
   return ~(uint64_t)_mm_cvtsi128_si64(_mm_cmpeq_epi8(v, _mm_setzero_si128()));
 }
 
-// One row of INT4 values at N:4, 32 columns = n index words at a time.  s, z: per group.
-// values and idx: the row's first byte and word (whole words: 4 n bytes of values per step).
+// One row of INT4 values at N:4, 32 columns = n index words at a time.  qp: the row's
+// {scale, zero} pairs.  values and idx: the row's first byte and word (whole words: 4 n bytes of values per step).
 template <int n>
-EGT_V inline void pack_row_int4(const uint16_t *w, const uint8_t *mask, int cols, int group, const float *s, const int *z, bool paired,
+EGT_V inline void pack_row_int4(const uint16_t *w, const uint8_t *mask, int cols, int group, const uint16_t *qp, bool paired,
                                 uint8_t *values, uint8_t *idx) {
   int g = 0, left = group;                            // group of the next eight columns, columns left in it
+  Pair p = cols > 0 ? pair_of(qp, 0) : Pair{};
   for (int c = 0; c < cols; c += 32) {
     u128 val = 0;
     uint64_t off = 0;
@@ -183,10 +188,10 @@ EGT_V inline void pack_row_int4(const uint16_t *w, const uint8_t *mask, int cols
     for (int k = 0; k < 4; ++k) {
       const int cc = c + 8 * k;
       const uint64_t kept = kept8(mask + cc), chosen = chosen8<n>(kept);
-      const uint64_t q = (codes8(w + cc, s[g], z[g]) & kept) | ((0x0101010101010101ull * (uint64_t)z[g]) & ~kept);
+      const uint64_t q = (codes8(w + cc, p.s, p.z) & kept) | ((0x0101010101010101ull * (uint64_t)p.z) & ~kept);
       val |= (u128)_pext_u64(q, chosen & 0x0F0F0F0F0F0F0F0Full) << (8 * n * k);
       off |= _pext_u64(0x0302010003020100ull, chosen & 0x0303030303030303ull) << (4 * n * k);
-      if ((left -= 8) == 0) { ++g; left = group; }
+      if ((left -= 8) == 0 && cc + 8 < cols) { p = pair_of(qp, ++g); left = group; }
     }
     if (paired) {
       u128 v = 0;
@@ -278,19 +283,20 @@ inline bool offsets_ascend(const uint8_t *idx, int cols) {
   }
   return ok;
 }
-// Decodes one row: w (may be null) and mask (may be null) of `cols` columns.  s, z: per group
-// (INT4; group a multiple of eight), FP16 values otherwise (s == nullptr).
+// Decodes one row: w (may be null) and mask (may be null) of `cols` columns.  qp: the row's
+// {scale, zero} pairs (INT4; group a multiple of eight), FP16 values otherwise (nullptr).
 template <int n>
-EGT_V inline void unpack_row(const uint8_t *values, const uint8_t *idx, int cols, int group, const float *s, const int *z, bool paired,
+EGT_V inline void unpack_row(const uint8_t *values, const uint8_t *idx, int cols, int group, const uint16_t *qp, bool paired,
                              uint16_t *w, uint8_t *mask) {
   const uint32_t *tab = group_masks().m[n];
   int g = 0, left = group;
+  Pair p = qp && cols > 0 ? pair_of(qp, 0) : Pair{};
   for (int c = 0; c < cols; c += 32) {
     uint64_t off = 0;
     std::memcpy(&off, idx, 2 * (size_t)n);
     idx += 2 * n;
     u128 val = 0;
-    if (s && w) {
+    if (qp && w) {
       std::memcpy(&val, values, 4 * (size_t)n);
       values += 4 * n;
       if (paired) {
@@ -313,12 +319,12 @@ EGT_V inline void unpack_row(const uint8_t *values, const uint8_t *idx, int cols
       if (!w) continue;
       const __m128i in = _mm_cvtsi64_si128((long long)cols8);
       const __m128i lanes = _mm_cvtepi8_epi16(in);
-      if (s) {
+      if (qp) {
         const uint64_t q = _pdep_u64((uint64_t)(val >> (8 * n * k)), cols8 & 0x0F0F0F0F0F0F0F0Full);
-        const __m256 f = _mm256_cvtepi32_ps(_mm256_sub_epi32(_mm256_cvtepu8_epi32(_mm_cvtsi64_si128((long long)q)), _mm256_set1_epi32(z[g])));
-        const __m128i h = _mm256_cvtps_ph(_mm256_mul_ps(f, _mm256_set1_ps(s[g])), _MM_FROUND_TO_NEAREST_INT | _MM_FROUND_NO_EXC);
+        const __m256 f = _mm256_cvtepi32_ps(_mm256_sub_epi32(_mm256_cvtepu8_epi32(_mm_cvtsi64_si128((long long)q)), _mm256_set1_epi32(p.z)));
+        const __m128i h = _mm256_cvtps_ph(_mm256_mul_ps(f, _mm256_set1_ps(p.s)), _MM_FROUND_TO_NEAREST_INT | _MM_FROUND_NO_EXC);
         _mm_storeu_si128((__m128i *)(w + cc), _mm_and_si128(h, lanes));
-        if ((left -= 8) == 0) { ++g; left = group; }
+        if ((left -= 8) == 0 && cc + 8 < cols) { p = pair_of(qp, ++g); left = group; }
       } else {
         for (int h = 0; h < 2; ++h) {
           uint64_t v = 0;

@@ -2,6 +2,7 @@
 or a process that ends while they are still there.  Each in a child process of its own (a fault there ends the child,
 not the test run)."""
 import os
+import shutil
 import subprocess
 import sys
 
@@ -112,3 +113,59 @@ def test_worker_threads(what):
     assert run.returncode == 0, (run.returncode, run.stdout[-1500:], run.stderr[-1500:])
     if what == "UNLOAD":
         assert run.stdout.split() == ["mapped", "0"], run.stdout
+
+
+NO_MEMORY = r"""
+#include "egt.h"
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <new>
+#include <vector>
+static bool armed = false;
+void *operator new(size_t n) { void *p = armed ? nullptr : std::malloc(n); if (!p) throw std::bad_alloc(); return p; }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+int main() {
+  const int R = 1024, K = 1024;
+  for (int kind = 0; kind < 3; ++kind) for (int group : {128, 12, 4}) {
+    const int cols = group == 12 ? 960 : K, gr = kind == EGT_VAL_FP16 ? 0 : group;
+    std::vector<uint16_t> w(R * K);
+    for (size_t i = 0; i < w.size(); ++i) w[i] = (uint16_t)((i * 2654435761u >> 13) & 0xBBFF);
+    struct Out { std::vector<uint8_t> mask, v, q, m2; std::vector<uint16_t> ix, qp, d, dqp; std::vector<uint32_t> rp; };
+    Out o[2];
+    for (Out &x : o) { x.mask.resize(R * K); x.v.resize(R * K); x.q.resize(R * K); x.m2.resize(R * K); x.ix.resize(R * K); x.qp.resize(R * K); x.d.resize(R * K); x.dqp.resize(R * K); x.rp.resize(R + 1); }
+    for (int k = 0; k < 2; ++k) {
+      Out &x = o[k];
+      egt_2bitcsr p{};
+      p.row_ptr = x.rp.data(); p.values = x.v.data(); p.idx = x.ix.data(); p.qparams = x.qp.data();
+      armed = k == 1;                                    // no memory, and no thread, to be had
+      int st = egt_prune_n4(w.data(), K, R, cols, 2, x.mask.data(), K);
+      st |= egt_pack_2bitcsr(w.data(), K, x.mask.data(), K, R, cols, 2, gr, kind, &p);
+      st |= egt_unpack_2bitcsr(&p, x.d.data(), K, x.m2.data(), K);
+      if (kind != EGT_VAL_FP16) st |= egt_quant_int4(w.data(), K, R, cols, group, x.q.data(), x.dqp.data());
+      armed = false;
+      if (st) { std::printf("status %d\n", st); return 1; }
+    }
+    if (o[0].mask != o[1].mask || o[0].v != o[1].v || o[0].q != o[1].q || o[0].m2 != o[1].m2 || o[0].ix != o[1].ix || o[0].qp != o[1].qp ||
+        o[0].d != o[1].d || o[0].dqp != o[1].dqp || o[0].rp != o[1].rp) { std::puts("other bytes"); return 1; }
+  }
+  std::puts("ok");
+}
+"""
+
+
+@pytest.mark.parametrize("first", [False, True])
+def test_host_functions_without_memory(first, tmp_path):
+    """No C++ exception leaves a host function, and none ends a worker: the parts of a job allocate nothing."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "nomem.cpp", str(tmp_path / "nomem")
+    # `first`: not even the first call has memory, so no worker is ever started
+    src.write_text(NO_MEMORY.replace("k == 1", "true") if first else NO_MEMORY)
+    build = subprocess.run([gxx, "-std=c++17", "-O1", "-pthread", "-ffp-contract=off", "-I" + os.path.join(ROOT, "include"), str(src),
+                            os.path.join(ROOT, "paper_2605_11582_amd", "csrc", "egt_host.cpp"), "-o", exe], capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-2000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout.split() == ["ok"], (run.returncode, run.stdout[-500:], run.stderr[-500:])
