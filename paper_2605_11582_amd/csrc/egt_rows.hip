@@ -1,10 +1,11 @@
-// M = 1 products of 2:4 matrices with FP16 values, of any row length, on the sparse matrix cores.
+// M = 1 products of 2:4 matrices with FP16 values and short rows on the sparse matrix cores.
 //
 // The row-per-wave kernel (egt_mfma_m1.hip) wants FP16 rows of 4096 columns and more in whole 64s.
-// Any other row used to be followed slot by slot, or, at 1024 and 2048 columns, by a form of that
-// kernel with several rows to a tile.  Here a tile is 16 quads of four chunks (a chunk: 16 bytes of values, 16 columns), and a row takes ceil(chunks / 4) quads:
-// `rpt` whole rows lie in a tile, or a row lies in `phases` tiles.  Between a half and all of the
-// lanes carry weights then; the rest ask out of range of the buffers (zeros, no traffic).
+// Shorter ones used to be followed slot by slot, or, at 1024 and 2048 columns, by a form of that
+// kernel with several rows to a tile.  Here a tile is 16 quads of four chunks (a chunk: 16 bytes of
+// values, 16 columns), and a row takes ceil(chunks / 4) quads: `rpt` whole rows lie in a tile, or a
+// row lies in `phases` tiles.  Between a half and all of the lanes carry weights then; the rest ask
+// out of range of the buffers (zeros, no traffic).
 //
 // The mapping is the diagonal one: lane (i, kb) = i + 16 kb takes chunk kb of quad i, column n
 // of B carries the activations of quad n, and D[i][i] is quad i's share of its row.  The 16
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(512, 4) void k_rows(const uint32_t *__restrict__ ro
 
 // Everything but the pointers.
 static bool rows_geometry(const egt_2bitcsr &w, RowsGeom &g) {
-  if (w.n_keep != 2 || w.val_kind != EGT_VAL_FP16 || w.rows < 1 || w.cols < 32 || w.cols % 32 != 0 || w.cols > 24576) return false;
+  if (w.n_keep != 2 || w.val_kind != EGT_VAL_FP16 || w.rows < 1 || w.cols < 32 || w.cols % 32 != 0 || w.cols >= 4096) return false;
   g.rows = w.rows;
   g.nchunks = w.cols / ROWS_CHUNK;
   const int quads = (g.nchunks + 3) / 4;
@@ -231,24 +232,23 @@ static bool rows_geometry(const egt_2bitcsr &w, RowsGeom &g) {
 static void rows_shape(RowsGeom &g, dim3 &grid, dim3 &block, size_t &lds) {
   const int nb = (g.nrg + ROWS_TPI - 1) / ROWS_TPI;   // batches of the matrix
   const size_t x_bytes = ((size_t)g.quads * ROWS_QUAD + 1023) & ~(size_t)1023;
-  int waves = x_bytes <= 8192 ? 4 : 8, per_cu = 24;   // (a larger x is shared by more waves)
+  int waves = 4, per_cu = 24;
   tune_pair("EGT_ROWS_TUNE", waves, per_cu);
   waves = waves < 1 ? 1 : waves > 8 ? 8 : waves;
   per_cu = per_cu < 1 ? 1 : per_cu > 64 ? 64 : per_cu;
   g.batches = (nb + 256 * per_cu - 1) / (256 * per_cu);
   g.batches = std::max(1, std::min(g.batches, ROWS_PER_WAVE / (ROWS_TPI * g.rpt)));
-  auto red_bytes = [&] {
-    g.red_stride = (g.batches * ROWS_TPI * g.rpt) | 1;
-    return (size_t)waves * (size_t)g.qpr * (size_t)g.red_stride * sizeof(float);
-  };
-  while (x_bytes + red_bytes() > 64 * 1024 && g.batches > 1) --g.batches;
+  g.red_stride = (g.batches * ROWS_TPI * g.rpt) | 1;
   const int nwaves = (nb + g.batches - 1) / g.batches;
   grid = dim3((unsigned)((nwaves + waves - 1) / waves));
   block = dim3(64u * (unsigned)waves);
-  lds = x_bytes + red_bytes();
+  lds = x_bytes + (size_t)waves * (size_t)g.qpr * (size_t)g.red_stride * sizeof(float);   // (8 KB and at most 33 KB)
 }
 
-// 2:4, FP16 values, rows of up to 24576 columns (x fits LDS) in whole index words.
+// 2:4, FP16 values, rows of fewer than 4096 columns in whole index words.  Longer ones are a chain of
+// five and more tiles a row in one wave: below the line 0.76 to 0.95 times the time of the slot-by-slot kernel
+// (64 ... 32000 rows x 3104 ... 4064), above it few rows lose 1.15 to 1.4 times (256 x 4128 4.6 -> 5.5 us, 256 x 16416
+// 9.8 -> 13.4) and many gain a tenth at most.
 bool sparse_rows_supported(const egt_2bitcsr &w) {
   RowsGeom g;
   return rows_geometry(w, g);

@@ -1,0 +1,99 @@
+"""Which kernels a device call launches, without a GPU: the library runs in a child process with a stand-in for the
+HIP runtime's launch that writes down the kernel's name and launch shape instead of launching.  Pointers are made up;
+nothing follows them on the host."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+STAND_IN = r"""
+#include <stddef.h>
+#include <stdio.h>
+typedef struct { unsigned x, y, z; } dim3_t;
+static struct { const void *f; const char *name; } seen[8192];
+static int n;
+void __hipRegisterFunction(void **m, const void *f, char *dev, const char *name, unsigned t, void *a, void *b, void *c, void *d, int *w) {
+  if (n < 8192) { seen[n].f = f; seen[n++].name = name; }
+}
+int hipLaunchKernel(const void *f, dim3_t grid, dim3_t block, void **args, size_t lds, void *stream) {
+  const char *name = "?";
+  for (int k = 0; k < n; ++k) if (seen[k].f == f) name = seen[k].name;
+  printf("launch %s %u %u %u %zu\n", name, grid.x, grid.y, block.x, lds);
+  fflush(stdout);
+  return 0;
+}
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipFuncSetAttribute(const void *f, int a, int v) { return 0; }
+"""
+
+CHILD = r"""
+import ctypes as C, json, sys
+sys.path.insert(0, {root!r})
+from paper_2605_11582_amd import binding as B
+L = B._declare(C.CDLL(B.LIB_PATH))                          # (without PyTorch)
+P = 1 << 20
+def view(rows, cols, n, g, kind, total=0):
+    return B.View(rows, cols, n, g, kind, P, P, P, P if kind != 1 else None, total)
+for c in json.loads({calls!r}):
+    print("call", flush=True)
+    k, st = c["call"], 0
+    if k == "gemv": st = L.egt_sparse_gemv(C.byref(view(*c["w"])), P, P, None)
+    elif k == "int4": st = L.egt_int4_gemv(P, P, *c["w"], P, P, None)
+    else:
+        count = c["count"]
+        views = (B.View * count)(*[view(*c["w"]) for _ in range(count)])
+        xs = (C.c_void_p * count)(*[P + (0 if c.get("shared") else 4096 * j) for j in range(count)])
+        ys = (C.c_void_p * count)(*[P + (j << 24) for j in range(count)])
+        if k == "gemv_batch": st = L.egt_sparse_gemv_batch(views, xs, ys, count, None)
+        elif k == "int4_batch": st = L.egt_int4_gemv_batch(xs, xs, *c["w"], xs, ys, count, None)
+        elif k == "gemm": st = L.egt_sparse_gemm_smallm(C.byref(views[0]), P, c["w"][1], P, c["w"][0], c["M"], None)
+        else: st = L.egt_sparse_gemm_smallm_batch(views, xs, c["w"][1], ys, c["w"][0], c["M"], count, None)
+    assert st == 0, (c, st)
+"""
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """launches(calls): per call the list of (kernel, grid x, grid y, threads) it launches."""
+    cc = shutil.which("gcc")
+    if not cc:
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("route")
+    lib = str(d / "launch.so")
+    (d / "launch.c").write_text(STAND_IN)
+    subprocess.run([cc, "-shared", "-fPIC", "-O1", str(d / "launch.c"), "-o", lib], check=True)
+
+    def run(calls):
+        env = dict(os.environ)
+        env["LD_PRELOAD"] = " ".join(v for v in (lib, env.get("LD_PRELOAD", "")) if v)
+        out = subprocess.run([sys.executable, "-c", CHILD.replace("{root!r}", repr(ROOT)).replace("{calls!r}", repr(json.dumps(calls)))],
+                             capture_output=True, text=True, env=env, timeout=120)
+        assert out.returncode == 0, out.stderr[-2000:]
+        res = []
+        for line in out.stdout.splitlines():
+            if line == "call":
+                res.append([])
+            elif line.startswith("launch "):
+                name, gx, gy, threads, _ = line.split()[1:]
+                res[-1].append((name, int(gx), int(gy), int(threads)))
+        assert len(res) == len(calls)
+        return res
+    return run
+
+
+def _names(res):
+    return [[name for name, *_ in call] for call in res]
+
+
+def test_fp16_rows_of_one_token(launches):
+    # (rows, cols, n_keep, group, value kind)
+    short = [(5, 64), (300, 1024), (300, 2048), (4096, 2816), (7, 4064)]
+    long = [(256, 4128), (11008, 4128), (256, 16416)]
+    res = _names(launches([{"call": "gemv", "w": (*s, 2, 0, 1)} for s in short + long]))
+    assert all(len(c) == 1 and "k_rows" in c[0] for c in res[:len(short)]), res
+    assert all(len(c) == 1 and "k_sparse_generic_m1" in c[0] for c in res[len(short):]), res
