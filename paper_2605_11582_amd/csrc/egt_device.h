@@ -44,6 +44,7 @@ hipError_t launch_sparse_m1_n1(const egt_2bitcsr &w, const uint16_t *x, uint16_t
 // M = 1, 2:4 with FP16 values, rows that do not fill the tiles of the kernels above (see sparse_rows_supported)
 bool sparse_rows_supported(const egt_2bitcsr &w);
 hipError_t launch_sparse_rows(const egt_2bitcsr &w, const uint16_t *x, uint16_t *y, hipStream_t stream);
+hipError_t launch_sparse_rows_batch(const egt_2bitcsr *ws, const uint16_t *const *xs, uint16_t *const *ys, int count, hipStream_t stream);
 
 // 2 <= M <= 64 on the sparse matrix cores (2:4 and 1:4; see sparse_smallm_supported)
 bool sparse_smallm_supported(const egt_2bitcsr &w, int64_t ldx, int M);

@@ -39,6 +39,7 @@ hipError_t launch_sparse_batch(const egt_2bitcsr *ws, const uint16_t *const *xs,
   }
   if (sparse_m1_supported(ws[0])) return launch_sparse_m1_batch(ws, xs, ys, count, stream);
   if (sparse_m1_n1_supported(ws[0])) return launch_sparse_m1_n1_batch(ws, xs, ys, count, stream);
+  if (sparse_rows_supported(ws[0])) return launch_sparse_rows_batch(ws, xs, ys, count, stream);
   for (int k = 0; k < count; ++k) {                   // shapes without a batched kernel: one launch each, as a call of its own
     const hipError_t e = launch_sparse(ws[k], xs[k], ws[k].cols, ys[k], ws[k].rows, 1, stream);
     if (e != hipSuccess) return e;

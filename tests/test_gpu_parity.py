@@ -770,6 +770,8 @@ def test_stream_read_folds_every_word_once():
 # ---------------------------------------------------------------- batched launches
 @pytest.mark.parametrize("rows,cols,n,g,kind,count", [(70, 4096, 2, 128, 0, 3), (33, 11008, 2, 128, 0, 2),
                                                       (40, 4096, 1, 128, 0, 4), (21, 4096, 2, 0, 1, 2),
+                                                      # FP16 rows of fewer than 4096 columns: several a tile, a tile, several tiles
+                                                      (131, 96, 2, 0, 1, 4), (1003, 1024, 2, 0, 1, 4), (70, 2048, 2, 0, 1, 3), (45, 4064, 2, 0, 1, 2),
                                                       (19, 96, 3, 32, 0, 3)])
 def test_sparse_gemv_batch_equals_separate_calls(rows, cols, n, g, kind, count):
     torch = G.torch_mod()

@@ -97,3 +97,9 @@ def test_fp16_rows_of_one_token(launches):
     res = _names(launches([{"call": "gemv", "w": (*s, 2, 0, 1)} for s in short + long]))
     assert all(len(c) == 1 and "k_rows" in c[0] for c in res[:len(short)]), res
     assert all(len(c) == 1 and "k_sparse_generic_m1" in c[0] for c in res[len(short):]), res
+
+
+@pytest.mark.parametrize("cols", [64, 1024, 2048, 2816, 4064])
+def test_a_batch_of_short_fp16_rows_is_one_launch(launches, cols):
+    (call,) = launches([{"call": "gemv_batch", "w": (300, cols, 2, 0, 1), "count": 4}])
+    assert len(call) == 1 and "k_rows" in call[0][0] and call[0][2] == 4, call
