@@ -1,6 +1,6 @@
 // Small-M products with the activations held in registers: INT4, 2 to 32 tokens, rows of at
-// most as many K-steps as a workgroup has waves and as X has room for in LDS (2:4: 4096 columns,
-// above 16 tokens 2304; 1:4: 4608).
+// most as many K-steps as a workgroup of the kernel in egt_mfma_smallm.hip has waves (2:4: 4096
+// columns, above 16 tokens 2048; 1:4: 4096, up to 16 tokens).
 //
 // In the kernel of egt_mfma_smallm.hip a wave owns a K-step of up to three or four row tiles;
 // where a workgroup has more of them it starts anew - X from the L2 into LDS, B operands out of
@@ -22,7 +22,8 @@
 // K-steps and take the tiles in turn.
 //
 // The sum of a row: each K-step's products by the matrix instructions, then the K-steps in
-// ascending order, as in the other kernel, bit for bit.
+// ascending order.  The other kernel adds the K-steps of a wave first; with a wave for every
+// K-step the two give the same bits, so that a product may take either, alone or in a batch.
 #include "egt_mfma_common.h"
 
 #include "egt_tune.h"
@@ -304,7 +305,7 @@ static bool hold_plan(const egt_2bitcsr &w, int64_t ldx, int64_t ldy, int M, int
   g.rows = w.rows; g.M = M;
   g.nchunks = w.cols / chunk;
   g.nsteps = (g.nchunks + 3) / 4;
-  if (g.nsteps > 16) return false;
+  if (g.nsteps > (n1 || M > 16 ? 8 : 16)) return false;     // (see the sum of a row)
   g.kpieces = w.cols / 8;
   qw = w.group_size < chunk ? chunk / w.group_size : 1;
   g.gshift = 0;

@@ -884,6 +884,8 @@ def test_products_under_one_x_run_as_one_matrix(rows, cols, n, g, kind, M, count
     (4100, 4096, 2, 128, 5, 4),         # 1028 tiles of four members under one X
     (1303, 1024, 2, 64, 32, 3),         # ragged members, two token groups, streams
     (7000, 512, 1, 128, 16, 4),
+    # more K-steps than the other kernel has waves: the sums of a batch and of a single call have to run in one order
+    (3000, 4608, 1, 128, 11, 2), (5000, 4352, 1, 64, 7, 4), (3000, 2304, 2, 128, 24, 3),
 ])
 def test_activations_held_in_registers(rows, cols, n, g, M, count):
     # rows over a workgroup's tiles, streams and sets; Y with a stride and an offset of its own

@@ -90,6 +90,14 @@ def _names(res):
     return [[name for name, *_ in call] for call in res]
 
 
+@pytest.mark.parametrize("cols,n,M,hold", [(4096, 2, 16, True), (4160, 2, 16, False), (2048, 2, 32, True), (2112, 2, 17, False),
+                                           (4096, 1, 16, True), (4224, 1, 5, False), (4096, 1, 17, False)])
+def test_products_held_in_registers_have_a_wave_for_every_k_step(launches, cols, n, M, hold):
+    # (the order of the sums of a row is then that of the other kernel, whichever a call or a batch takes)
+    res = _names(launches([{"call": "gemm", "w": (1000, cols, n, 128 if cols % 128 == 0 else 64, 0), "M": M, "count": 1}]))
+    assert len(res[0]) == 1 and ("k_smallm_hold" in res[0][0]) == hold, res
+
+
 def test_fp16_rows_of_one_token(launches):
     # (rows, cols, n_keep, group, value kind)
     short = [(5, 64), (300, 1024), (300, 2048), (4096, 2816), (7, 4064)]
