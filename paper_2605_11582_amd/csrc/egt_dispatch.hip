@@ -56,10 +56,9 @@ hipError_t launch_sparse_gemm_batch(const egt_2bitcsr *ws, const uint16_t *const
   bool shared = true;
   for (int k = 1; k < count; ++k) shared = shared && Xs[k] == Xs[0];
   // (the two kernels of a small-M product add in the same order: a member has the bits of its own call in either)
-  const bool hold = M >= 2 && !tokens_form && sparse_smallm_hold_supported(w, ldx, M, 1);
   if (M >= 2 && !tokens_form && shared && sparse_smallm_hold_supported(w, ldx, M, count))
     return launch_sparse_smallm_hold(ws, Xs[0], ldx, Ys, ldy, M, count, stream);
-  if (count >= 2 && M >= 2 && w.val_kind != EGT_VAL_INT4_PAIRED && !tokens_form && !(hold && M > 16) && sparse_smallm_supported(w, ldx, M))
+  if (count >= 2 && M >= 2 && w.val_kind != EGT_VAL_INT4_PAIRED && !tokens_form && sparse_smallm_supported(w, ldx, M))
     return launch_sparse_smallm_batch(ws, Xs, ldx, Ys, ldy, M, count, stream);
   for (int k = 0; k < count; ++k) {
     const hipError_t e = launch_sparse(ws[k], Xs[k], ldx, Ys[k], ldy, M, stream);

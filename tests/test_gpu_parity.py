@@ -812,6 +812,7 @@ def test_sparse_gemv_batch_of_ragged_matrices_equals_separate_calls(rows, cols, 
 
 @pytest.mark.parametrize("rows,cols,n,g,kind,M,count,shared", [
     (70, 4096, 2, 128, 0, 16, 3, True), (33, 11008, 2, 128, 0, 7, 2, False), (300, 4096, 2, 128, 0, 33, 3, True),
+    (108, 128, 2, 128, 0, 29, 4, False), (1487, 1536, 2, 32, 0, 24, 4, False), (70, 2048, 2, 64, 0, 17, 2, False),
     (4100, 1024, 2, 64, 0, 5, 4, False), (40, 4096, 1, 128, 0, 16, 2, True), (21, 4096, 2, 0, 1, 8, 2, False),
     (50, 4096, 2, 32, 0, 64, 2, True),
     # no batched kernel: two tokens on the M = 1 kernel's mapping, the paired nibble order, a slot-by-slot shape, one token

@@ -98,6 +98,14 @@ def test_products_held_in_registers_have_a_wave_for_every_k_step(launches, cols,
     assert len(res[0]) == 1 and ("k_smallm_hold" in res[0][0]) == hold, res
 
 
+def test_a_batch_of_several_tokens_is_one_launch(launches):
+    # (members under one X or each under its own)
+    calls = [{"call": "gemm_batch", "w": (*s, 128, 0), "M": M, "count": 4, "shared": shared}
+             for s in ((108, 128, 2), (18, 2048, 2), (1487, 1536, 2), (300, 4096, 1)) for M in (5, 16, 17, 24, 32, 64) for shared in (False, True)]
+    for call, res in zip(calls, launches(calls)):
+        assert len(res) == 1, (call, res)
+
+
 def test_fp16_rows_of_one_token(launches):
     # (rows, cols, n_keep, group, value kind)
     short = [(5, 64), (300, 1024), (300, 2048), (4096, 2816), (7, 4064)]
