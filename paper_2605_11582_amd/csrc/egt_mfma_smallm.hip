@@ -44,6 +44,7 @@
 
 #include "egt_tune.h"
 
+#include <algorithm>
 #include <cstring>
 
 namespace egt {
@@ -704,9 +705,9 @@ static hipError_t go_ks(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, co
   // the start of each wave's own region; + row-pointer flags
   const size_t lds = (NT > 1 ? x_bytes + p_bytes : x_bytes) + 64 * NIT;
   if constexpr (!KS) {
-    if constexpr (KIND == EGT_VAL_INT4)
+    if constexpr (KIND == EGT_VAL_INT4 && NIT > 1)    // (members as one matrix: more tiles than workgroups)
       if (batch && g.mtiles)
-        return launch(k_sparse_smallm_ks_joint<KIND, NT, NIT, NWMAX, QW, N1, (NIT > 1)>, dim3(nblocks), dim3(64 * nw), lds, stream, *batch, g);
+        return launch(k_sparse_smallm_ks_joint<KIND, NT, NIT, NWMAX, QW, N1, true>, dim3(nblocks), dim3(64 * nw), lds, stream, *batch, g);
     if (batch)
       return launch(k_sparse_smallm_ks_batch<KIND, NT, NIT, NWMAX, QW, N1, RND>, dim3(nblocks, count), dim3(64 * nw), lds, stream, *batch, g);
   }
@@ -844,11 +845,7 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
     if (vb >= (1ull << 32) || xb >= (1ull << 32)) return hipErrorInvalidValue;   // 32-bit offsets
   }
   smallm_geometry(w, ldx, Y, ldy, M, g, qw);
-  bool joint = batch != nullptr;                      // members under one X: their row tiles as those of one matrix
   const int mtiles = g.ntiles;
-  for (int k = 1; batch && k < count; ++k) joint = joint && batch->X[k] == batch->X[0];
-  joint = joint && int4;                              // (FP16 values: a product of more than 256 tiles has fewer waves, another order of additions)
-  if (joint) g.ntiles *= count;
   if (batch)                                          // 8-byte stores only where every member's Y allows them
     for (int k = 0; k < count; ++k)
       if ((uintptr_t)batch->Y[k] % 8 != 0) g.vec_store = 0;
@@ -865,6 +862,26 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
     nwmax = nwmax < 1 ? 1 : nwmax > nwcap ? nwcap : nwmax;
     blocks_per_cu = blocks_per_cu < 1 ? 1 : blocks_per_cu > 4 ? 4 : blocks_per_cu;
   }
+  // Members under one X: their row tiles as those of one matrix (X is staged once for a workgroup's tiles of all
+  // members), or each member as its own workgroups.  As one
+  //  - where the compute units then see two thirds of the rounds of row tiles or fewer (4440 x 4352 at 1:4, 3 tokens, three
+  //    members, one round for three: 16.4 -> 10.3 us; 13824 x 5120, 8 tokens, two members, three for four: 1.18 times the time);
+  //  - where no second workgroup fits beside one (1:4: from five K-steps on; 13211 x 256 at 1:4, 56 tokens, four members
+  //    of one K-step: 36 -> 136 us);
+  //  - with two token groups a pass from the third tile of a workgroup on (1102 x 6336, 25 tokens, four members, two
+  //    tiles: 15.8 -> 18.1 us; 2948 x 7104, 31 tokens, three members, three tiles: 25.5 -> 18.7).
+  // (FP16 values: a product of more than 256 tiles has fewer waves, another order of additions.)
+  bool joint = batch != nullptr && int4;
+  for (int k = 1; batch && k < count; ++k) joint = joint && batch->X[k] == batch->X[0];
+  {
+    const int cus = 256 * blocks_per_cu, nit = wide ? 4 : 3;
+    const int64_t all = (int64_t)mtiles * count;
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t rounds = up(up(all, cus), nit);
+    const int64_t rounds_apart = up((int64_t)std::min(mtiles, cus) * count, cus) * up(up(mtiles, cus), nit);
+    joint = joint && g.nsteps >= (n1 ? 5 : nwmax) && all > (n1 || !wide ? cus : 2 * cus) && 3 * rounds <= 2 * rounds_apart;
+  }
+  if (joint) g.ntiles *= count;
   int nblocks = 256 * blocks_per_cu;                  // more row tiles than nblocks * NIT: rounds in the kernel
   if (nblocks > g.ntiles) nblocks = g.ntiles;
   const bool one = nblocks == g.ntiles;               // one row tile per workgroup
