@@ -870,8 +870,9 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
   // members), or each member as its own workgroups.  As one
   //  - where the compute units then see two thirds of the rounds of row tiles or fewer (4440 x 4352 at 1:4, 3 tokens, three
   //    members, one round for three: 16.4 -> 10.3 us; 13824 x 5120, 8 tokens, two members, three for four: 1.18 times the time);
-  //  - where no second workgroup fits beside one (1:4: from five K-steps on; 13211 x 256 at 1:4, 56 tokens, four members
-  //    of one K-step: 36 -> 136 us);
+  //  - where no second workgroup fits beside one: from five K-steps on at 1:4 and with two token groups a pass in a member of
+  //    several tiles a workgroup, else with all waves (13211 x 256 at 1:4, 56 tokens, four members of one K-step:
+  //    36 -> 136 us; 4234 x 1792, 50 tokens, three members: 31.3 -> 17.6);
   //  - with two token groups a pass from the third tile of a workgroup on (1102 x 6336, 25 tokens, four members, two
   //    tiles: 15.8 -> 18.1 us; 2948 x 7104, 31 tokens, three members, three tiles: 25.5 -> 18.7).
   // (FP16 values: a product of more than 256 tiles has fewer waves, another order of additions.)
@@ -883,7 +884,7 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
     auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     const int64_t rounds = up(up(all, cus), nit);
     const int64_t rounds_apart = up((int64_t)std::min(mtiles, cus) * count, cus) * up(up(mtiles, cus), nit);
-    joint = joint && g.nsteps >= (n1 ? 5 : nwmax) && all > (n1 || !wide ? cus : 2 * cus) && 3 * rounds <= 2 * rounds_apart;
+    joint = joint && g.nsteps >= ((n1 || (wide && mtiles > cus)) ? 5 : nwmax) && all > (n1 || !wide ? cus : 2 * cus) && 3 * rounds <= 2 * rounds_apart;
   }
   if (joint) g.ntiles *= count;
   int nblocks = 256 * blocks_per_cu;                  // more row tiles than nblocks * NIT: rounds in the kernel

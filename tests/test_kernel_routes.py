@@ -100,10 +100,10 @@ def test_products_held_in_registers_have_a_wave_for_every_k_step(launches, cols,
 
 # (rows, cols, n_keep), tokens, members; whether the members' row tiles run as those of one matrix
 @pytest.mark.parametrize("w,M,count,joint", [
-    ((4096, 11008, 2), 5, 3, True), ((3254, 7936, 1), 22, 4, True), ((5437, 2688, 2), 20, 2, True), ((3843, 3328, 1), 33, 4, True), ((4338, 2624, 2), 26, 4, True),
+    ((4096, 11008, 2), 5, 3, True), ((3254, 7936, 1), 22, 4, True), ((5437, 2688, 2), 20, 2, True), ((3843, 3328, 1), 33, 4, True), ((4234, 1792, 2), 50, 3, True), ((4338, 2624, 2), 26, 4, True),
     ((1024, 11008, 2), 5, 3, False),    # a tile a workgroup
     ((6293, 4160, 2), 5, 2, False), ((13824, 5120, 2), 8, 2, False),      # two rounds for two, three for four
-    ((13211, 256, 1), 56, 4, False), ((1150, 768, 2), 38, 4, False),      # fewer K-steps than waves
+    ((13211, 256, 1), 56, 4, False), ((1150, 768, 2), 38, 4, False), ((2831, 1216, 2), 53, 4, False),     # fewer K-steps than waves
     ((1102, 6336, 2), 25, 4, False),    # two token groups, two tiles a workgroup
 ])
 def test_members_under_one_x_run_as_one_matrix_where_that_pays(launches, w, M, count, joint):
