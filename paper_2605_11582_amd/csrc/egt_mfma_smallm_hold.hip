@@ -350,6 +350,11 @@ static bool hold_plan(const egt_2bitcsr &w, int64_t ldx, int64_t ldy, int M, int
   // 1:4 rows of more than 2048 columns, where a workgroup has two to four tiles: two streams of at most two
   // tiles each do not pay for the longer start (8192 x 4096, 5 tokens: 5.2 us in the other kernel, 5.6 here; 16384 x 4096: 7.7, 8.7)
   if (n1 && g.nsteps > 4 && max_tiles >= 2 && max_tiles <= 4) return false;
+  // Several members whose workgroups in the other kernel do one full round, three row tiles each, where the waves here are all
+  // in use (11008 x 2048, 2 tokens, two members: 7.8 us there, 9.3 here; 11008 x 1024, three: 7.4, 9.0; with 500 or
+  // 780 tiles a member 0.9 and 0.8 times the time here); and 1:4 members of two tiles a workgroup in all (3259 x 512: 4.1, 4.6)
+  if (count > 1 && !n1 && M <= 16 && g.mtiles > 512 && g.mtiles <= 768 && g.nsteps >= 4 && g.nsteps <= 8 && g.nw >= 14) return false;
+  if (count > 1 && n1 && max_tiles == 2) return false;
   if (16 * per_set > 64 * g.nw) return false;         // (a thread per row of a set)
   lds = (size_t)g.flags_at + sizeof(uint32_t) * 2 * 16 * (size_t)per_set;
   return lds <= 160 * 1024 - 1024;

@@ -98,6 +98,15 @@ def test_products_held_in_registers_have_a_wave_for_every_k_step(launches, cols,
     assert len(res[0]) == 1 and ("k_smallm_hold" in res[0][0]) == hold, res
 
 
+@pytest.mark.parametrize("w,M,count,hold", [
+    ((11008, 2048, 2), 2, 2, False), ((11008, 1024, 2), 12, 3, False), ((11008, 1792, 2), 2, 2, False),
+    ((12500, 2048, 2), 2, 2, True), ((7900, 2048, 2), 2, 2, True), ((11008, 2048, 2), 2, 1, True), ((11008, 1280, 2), 2, 4, True), ((11008, 2304, 2), 2, 2, True),
+    ((3259, 512, 1), 2, 2, False), ((5000, 512, 1), 2, 2, True), ((3259, 512, 1), 2, 1, True)])
+def test_batches_held_in_registers_where_that_pays(launches, w, M, count, hold):
+    (call,) = launches([{"call": "gemm_batch", "w": (*w, 64, 0), "M": M, "count": count, "shared": True}])
+    assert len(call) == 1 and ("k_smallm_hold" in call[0][0]) == hold, call
+
+
 # (rows, cols, n_keep), tokens, members; whether the members' row tiles run as those of one matrix
 @pytest.mark.parametrize("w,M,count,joint", [
     ((4096, 11008, 2), 5, 3, True), ((3254, 7936, 1), 22, 4, True), ((5437, 2688, 2), 20, 2, True), ((3843, 3328, 1), 33, 4, True), ((4234, 1792, 2), 50, 3, True), ((4338, 2624, 2), 26, 4, True),
