@@ -6,8 +6,9 @@
 //
 //  - sparse_gemv, sparse_gemm_smallm, int4_gemv: one product with plain arguments.  They
 //    check what the ctypes path of binding.py checks; where anything is not as it should be
-//    (a wrong type, a short buffer, an error status) they launch nothing and return False, and
-//    binding.py goes through its own checks, which say what is wrong.
+//    (a wrong type, a short buffer, a refused argument) they launch nothing and return False, and
+//    binding.py goes through its own checks, which say what is wrong.  An error of the HIP runtime is
+//    raised from here: the call is not made a second time.
 //  - Call: a prepared call, arguments marshalled once; calling it crosses the C ABI.
 //
 // The module is not linked against libegt.so: binding.py hands over the addresses of the
@@ -235,6 +236,12 @@ PyObject *answer(bool ok) {
   if (!ok) PyErr_Clear();
   return PyBool_FromLong(ok);
 }
+// ... of a call that has reached the library
+PyObject *outcome(int st) {
+  if (st != EGT_ERR_HIP) return answer(st == EGT_OK);
+  PyErr_Clear();
+  return PyObject_CallFunction(B.check, "i", st);      // (raises)
+}
 // A tensor without memory of its own (under a transform, a fake mode, of a sparse layout) throws
 // where its address or its strides are asked for: no exception may cross into the interpreter.
 template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
@@ -257,7 +264,7 @@ PyObject *sparse_gemv(PyObject *, PyObject *const *a, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   st = B.sparse_gemv(&w, x, y, s);
   Py_END_ALLOW_THREADS
-  return answer(st == 0);
+  return outcome(st);
 }
 
 // X (M, cols) or Y (M, rows): FP16, rows of contiguous elements
@@ -290,7 +297,7 @@ PyObject *sparse_gemm_smallm(PyObject *, PyObject *const *a, Py_ssize_t n) {
      : form == 1 ? B.gemm_ws(&w, x, ldx, y, ldy, (int)M, ws, (size_t)wb, s)
                  : B.gemm_static(&w, x, ldx, y, ldy, (int)M, s);
   Py_END_ALLOW_THREADS
-  return answer(st == 0);
+  return outcome(st);
 }
 
 // int4_gemv(q, qparams, rows, cols, group, x, y, stream)
@@ -306,7 +313,7 @@ PyObject *int4_gemv(PyObject *, PyObject *const *a, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   st = B.int4(q, qp, (int)rows, (int)cols, (int)group, x, y, s);
   Py_END_ALLOW_THREADS
-  return answer(st == 0);
+  return outcome(st);
 }
 
 // bind(sparse_gemv, gemm, gemm_ws, gemm_static, int4, check, raw_stream, get_device): addresses of the entry

@@ -47,3 +47,36 @@ def test_tensors_without_memory_are_left_to_the_checks():
     with FakeTensorMode():                                # (device tensors without a device)
         torch.vmap(body)(torch.empty((3, 4096), dtype=torch.float16, device="cuda"),
                          torch.empty((3, 4, 64), dtype=torch.float16, device="cuda"))
+
+
+@pytest.mark.gpu
+def test_an_error_of_the_hip_runtime_is_raised_by_the_call_that_meets_it():
+    """Entry points that fail once with a HIP error: one call, one exception; nothing is tried again in silence."""
+    calls = []
+    types = {"egt_sparse_gemv": C.CFUNCTYPE(C.c_int, *[C.c_void_p] * 4),
+             "egt_sparse_gemm_smallm": C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int, C.c_void_p),
+             "egt_sparse_gemm_smallm_ws": C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p),
+             "egt_int4_gemv": C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p)}
+    types["egt_sparse_gemm_smallm_static"] = types["egt_sparse_gemm_smallm"]
+
+    def failing(name):
+        def entry(*a):
+            calls.append(name)
+            return 7
+        return types[name](entry)
+    fns = [failing(name) for name in egt._plain]
+    native = egt._native()
+    t = torch.zeros(1 << 16, dtype=torch.float16, device="cuda")
+    p = egt.Packed(64, 64, 2, 64, egt.VAL_INT4, t, t, t, t)
+    X, Y = t[:256].view(4, 64), t[:256].view(4, 64)
+    native.bind(*[C.cast(f, C.c_void_p).value for f in fns], egt._check, torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    try:
+        for call in (lambda: egt.sparse_gemv(p, t, t), lambda: egt.int4_gemv(t, t, 64, 64, 64, t, t), lambda: egt.sparse_gemm_smallm(p, X, Y),
+                     lambda: egt.sparse_gemm_smallm_ws(p, X, Y, None), lambda: egt.sparse_gemm_smallm_static(p, X, Y)):
+            with pytest.raises(egt.EgtError) as e:
+                call()
+            assert e.value.status == 7 and len(calls) == 1, calls
+            calls.clear()
+    finally:
+        egt._call = None
+        egt._native()
