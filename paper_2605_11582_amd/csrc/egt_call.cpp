@@ -77,7 +77,7 @@ struct Call {
   vectorcallfunc vectorcall;
   std::vector<Thunk> *thunks;
   void *stream;
-  PyObject *keep, *dict;
+  PyObject *keep, *dict, *weak;
 };
 
 // What ctypes takes for a pointer: an integer, None, or an object that carries one (c_void_p)
@@ -153,7 +153,7 @@ PyObject *call_new(PyTypeObject *type, PyObject *args, PyObject *) {
   c->stream = (void *)(uintptr_t)stream;
   Py_INCREF(keep);
   c->keep = keep;
-  c->dict = nullptr;
+  c->dict = c->weak = nullptr;
   return (PyObject *)c;
 }
 int call_traverse(PyObject *self, visitproc visit, void *arg) {
@@ -168,6 +168,7 @@ int call_clear(PyObject *self) {
 }
 void call_dealloc(PyObject *self) {
   PyObject_GC_UnTrack(self);
+  if (((Call *)self)->weak) PyObject_ClearWeakRefs(self);
   call_clear(self);
   delete ((Call *)self)->thunks;
   Py_TYPE(self)->tp_free(self);
@@ -340,6 +341,12 @@ PyMethodDef methods[] = {
     {"int4_gemv", (PyCFunction)(void (*)(void))guarded<int4_gemv>, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "egt_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+// A copy of a call, shallow or deep, is the call itself, as for a function: its pointers are those of its buffers.
+PyObject *call_copy(PyObject *self, PyObject *) {
+  Py_INCREF(self);
+  return self;
+}
+PyMethodDef call_methods[] = {{"__copy__", call_copy, METH_NOARGS, nullptr}, {"__deepcopy__", call_copy, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyGetSetDef call_getset[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr, nullptr}};
 
 }  // namespace
@@ -352,6 +359,8 @@ PyMODINIT_FUNC PyInit_egt_call(void) {
   CallType.tp_call = PyVectorcall_Call;
   CallType.tp_vectorcall_offset = offsetof(Call, vectorcall);
   CallType.tp_dictoffset = offsetof(Call, dict);
+  CallType.tp_weaklistoffset = offsetof(Call, weak);
+  CallType.tp_methods = call_methods;
   CallType.tp_traverse = call_traverse;
   CallType.tp_clear = call_clear;
   CallType.tp_dealloc = call_dealloc;

@@ -33,6 +33,27 @@ def test_stream_argument_of_the_wrong_type():
             call(bad)
 
 
+def test_prepared_calls_are_referred_to_and_copied_like_functions():
+    import copy
+    import gc
+    import weakref
+
+    class Kept:
+        pass
+    kept = Kept()
+    fn = READ(lambda *a: 0)
+    call = egt._native().Call(egt._native().READ, C.cast(fn, C.c_void_p).value, [(1, 2, 3)], 7, [kept])
+    call.plan = {"count": 1}
+    assert copy.copy(call) is call and copy.deepcopy({"step": [call]})["step"][0] is call
+    ref, kept_ref = weakref.ref(call), weakref.ref(kept)
+    table = weakref.WeakKeyDictionary({call: 1})
+    assert ref() is call and table[call] == 1
+    call.itself = call                                    # (a cycle)
+    del call, kept
+    gc.collect()
+    assert ref() is None and kept_ref() is None and not table
+
+
 def test_tensors_without_memory_are_left_to_the_checks():
     """The elements of a batch under vmap have no memory of their own: asking for their address throws in C++."""
     from torch._subclasses.fake_tensor import FakeTensorMode
