@@ -1,5 +1,5 @@
-"""The small-M kernels wait on vector-memory requests with hand-counted `s_waitcnt vmcnt(n)`;
-every n is built from ATile::LOADS, the number of requests that fetch one row tile.  This
+"""The small-M kernels and the row-walking kernel wait on vector-memory requests with hand-counted
+`s_waitcnt vmcnt(n)`; n is built from the number of requests that fetch one row tile.  This
 test compiles the kernels to gfx950 assembly (no GPU needed) and checks that the requests
 the compiler emitted are whole multiples of that number, so a request added to or dropped
 from the tile fetch without the count following fails here, on the CPU, and not as a wrong
@@ -22,20 +22,39 @@ def _hipcc():
     return None
 
 
-@pytest.fixture(scope="module")
-def smallm_asm(tmp_path_factory):
-    """The small-M source compiled to gfx950 assembly, split into (kernel name, body) pairs."""
+def _assembly(source, directory):
+    """A source compiled to gfx950 assembly, split into (kernel name, body) pairs."""
     hipcc = _hipcc()
     if hipcc is None:
         pytest.skip("hipcc not found")
-    asm = str(tmp_path_factory.mktemp("asm") / "smallm.s")
+    asm = str(directory / (source + ".s"))
     res = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off",
                           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
                           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "--cuda-device-only", "-S",
-                          os.path.join(CSRC, "egt_mfma_smallm.hip"), "-o", asm], capture_output=True, text=True)
+                          os.path.join(CSRC, source), "-o", asm], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     parts = re.split(r"\n(_Z\w+):[^\n]*\n", open(asm).read())
     return [(name, body.split(".Lfunc_end")[0]) for name, body in zip(parts[1::2], parts[2::2])]
+
+
+@pytest.fixture(scope="module")
+def smallm_asm(tmp_path_factory):
+    return _assembly("egt_mfma_smallm.hip", tmp_path_factory.mktemp("asm"))
+
+
+def _lane_loops(body):
+    """Loops over the lanes of a wave around a request (what the compiler makes of a resource or a uniform offset that it
+    does not know to be uniform: one request per distinct value)."""
+    lines, labels, found = body.split("\n"), {}, 0
+    for k, ln in enumerate(lines):
+        m = re.match(r"(\.LBB\w+):", ln)
+        if m:
+            labels[m.group(1)] = k
+        m = re.search(r"s_cbranch_execnz (\.LBB\w+)", ln)
+        if m and m.group(1) in labels:
+            loop = "\n".join(lines[labels[m.group(1)]:k])
+            found += bool(k - labels[m.group(1)] < 60 and re.search(r"\bbuffer_load", loop) and re.search(r"v_readfirstlane", loop) and "saveexec" in loop)
+    return found
 
 
 def test_tile_requests_of_the_small_m_kernels_match_the_wait_counts(smallm_asm):
@@ -48,7 +67,7 @@ def test_tile_requests_of_the_small_m_kernels_match_the_wait_counts(smallm_asm):
     assert not re.search(r"wait_vmem<[^>]*\b[2-9]\b[^>]*>", text), "a literal request count in a wait"
     seen = 0
     for name, body in smallm_asm:
-        m = re.search(r"k_sparse_smallm_ksILi(\d)ELi(\d+)ELi(\d+)E", name)   # KIND, NT, NIT
+        m = re.search(r"k_sparse_smallm_ks(?:_batch|_joint)?ILi(\d)ELi(\d+)ELi(\d+)E", name)   # KIND, NT, NIT
         if not m:
             continue
         kind, nit = int(m.group(1)), int(m.group(3))
@@ -58,8 +77,9 @@ def test_tile_requests_of_the_small_m_kernels_match_the_wait_counts(smallm_asm):
         assert len(tile_requests) % (nit * per_tile[kind]) == 0, (name, len(tile_requests), nit, per_tile[kind])
         waits = {int(v) for v in re.findall(r"vmcnt\((\d+)\)", body)}
         assert max(waits) <= 2 * nit * per_tile[kind], (name, sorted(waits))   # at most two phases of tiles pending
+        assert _lane_loops(body) == 0, name
         seen += 1
-    assert seen >= 20
+    assert seen >= 60
 
 
 def test_requests_of_the_row_split_stack_kernel_match_its_wait_counts(smallm_asm):
@@ -84,3 +104,46 @@ def test_requests_of_the_row_split_stack_kernel_match_its_wait_counts(smallm_asm
         assert not re.search(r"\bscratch_|\bflat_", body), name
         seen += 1
     assert seen == 5
+
+
+def _prologue(body, wait):
+    """(requests of tiles, requests of x to LDS) in the straight line before the first `vmcnt(wait)`, up to the first
+    barrier; a request that stands in both arms of a branch (lanes on, lanes off) writes one register and counts once."""
+    lines = body.split("\n")
+    end = next(k for k, ln in enumerate(lines) if re.search(r"vmcnt\(%d\)" % wait, ln))
+    requests = [ln for ln in lines[:end] if re.search(r"\bbuffer_load", ln)]
+    tiles = [ln for ln in requests if " lds" not in ln]
+    first = next(k for k, ln in enumerate(lines) if ln in tiles)
+    assert not any(" lds" in ln for ln in lines[first:end]), "x requested between the tiles"
+    return {re.search(r"buffer_load_\w+ (\S+),", ln).group(1) for ln in tiles}, len(requests) - len(tiles)
+
+
+def test_requests_of_the_products_held_in_registers_match_the_wait_count(tmp_path):
+    # k_smallm_hold<QW, N1, NG, RING, ...>: x and then RING tiles of three requests each are asked for; the wait for x allows
+    # exactly the tiles to stay pending
+    seen = 0
+    for name, body in _assembly("egt_mfma_smallm_hold.hip", tmp_path):
+        m = re.search(r"k_smallm_holdILi(\d+)ELb(\d)ELi(\d+)ELi(\d+)E", name)
+        if not m:
+            continue
+        ring = int(m.group(4))
+        registers, to_lds = _prologue(body, 3 * ring)
+        assert len(registers) == 3 * ring and to_lds >= 1, (name, registers, to_lds)
+        assert _lane_loops(body) == 0 and not re.search(r"\bscratch_|\bflat_", body), name
+        seen += 1
+    assert seen >= 40
+
+
+def test_requests_of_the_row_walking_kernel_match_the_wait_count(tmp_path):
+    # k_rows<MP>: x, then two items of four tiles of two requests each
+    text = open(os.path.join(CSRC, "egt_rows.hip")).read()
+    tpi, loads = int(re.search(r"ROWS_TPI = (\d+);", text).group(1)), int(re.search(r"LOADS = (\d+);", text).group(1))
+    seen = 0
+    for name, body in _assembly("egt_rows.hip", tmp_path):
+        if "k_rows" not in name:
+            continue
+        registers, to_lds = _prologue(body, 2 * tpi * loads)
+        assert len(registers) == 2 * tpi * loads and to_lds == 1, (name, registers, to_lds)
+        assert _lane_loops(body) == 0 and not re.search(r"\bscratch_|\bflat_", body), name
+        seen += 1
+    assert seen == 4
