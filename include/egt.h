@@ -253,7 +253,9 @@ egt_status egt_sparse_gemm_smallm_static(const egt_2bitcsr *w, const uint16_t *X
  * launch: the q/k/v or gate/up projections of a decoder layer.  Sec. 3.3 starts from
  * one kernel per linear layer; fusing the launches removes the fixed cost a short
  * kernel cannot amortise.  w: array of `count` views; x, y: arrays of `count` device
- * pointers (host arrays of device pointers).  Results equal those of `count` separate
+ * pointers (host arrays of device pointers).  Where no batched kernel takes the shape (the
+ * paired nibble order, shapes of the slot-by-slot kernels) the members run as one launch
+ * each.  Results equal those of `count` separate
  * egt_sparse_gemv / egt_int4_gemv calls bit for bit. */
 egt_status egt_sparse_gemv_batch(const egt_2bitcsr *w, const uint16_t *const *x, uint16_t *const *y,
                                  int count, void *stream);

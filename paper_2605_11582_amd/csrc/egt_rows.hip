@@ -28,6 +28,8 @@
 //
 // Measured, us per launch before and now (weights in the last-level cache): 20000 x 2816 13.5,
 // 11.6; 5003 x 2880 5.6, 4.3; 2000 x 2048 5.0, 3.1; 4096 x 1024 5.8, 2.9; 60000 x 512 13.3, 5.9.
+// What bounds it: the launch for a few megabytes, the memory beyond (20000 x 2816: 64 MB at 5.5 TB/s, the
+// vector units 8 % busy).
 #include "egt_mfma_common.h"
 
 #include "egt_tune.h"
@@ -250,10 +252,10 @@ static void rows_shape(RowsGeom &g, dim3 &grid, dim3 &block, size_t &lds) {
   const int nwaves = (nb + g.batches - 1) / g.batches;
   grid = dim3((unsigned)((nwaves + waves - 1) / waves));
   block = dim3(64u * (unsigned)waves);
-  lds = x_bytes + (size_t)waves * (size_t)g.qpr * (size_t)g.red_stride * sizeof(float);   // (8 KB and at most 33 KB)
+  lds = x_bytes + (size_t)waves * (size_t)g.qpr * (size_t)g.red_stride * sizeof(float);   // (at most 8 KB and 17 KB)
 }
 
-// 2:4, FP16 values, rows of fewer than 4096 columns in whole index words.  Longer ones are a chain of
+// 2:4, FP16 values, rows of fewer than 4096 columns in whole index words (and values below 2 GiB: 32-bit offsets).  Longer ones are a chain of
 // five and more tiles a row in one wave: below the line 0.76 to 0.95 times the time of the slot-by-slot kernel
 // (64 ... 32000 rows x 3104 ... 4064), above it few rows lose 1.15 to 1.4 times (256 x 4128 4.6 -> 5.5 us, 256 x 16416
 // 9.8 -> 13.4) and many gain a tenth at most.
