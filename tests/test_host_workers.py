@@ -91,6 +91,15 @@ assert ok
 assert os.waitpid(pid, 0)[1] == 0
 """
 
+FORK_AFTER_UNLOAD = r"""
+prune(weights(0))
+_ctypes.dlclose(L._handle)
+pid = os.fork()                                           # (nothing of the library is called in the child any more)
+if pid == 0:
+    os._exit(0)
+assert os.waitpid(pid, 0)[1] == 0
+"""
+
 LAST = r"""
 w = weights(0)
 prune(w)                                                  # the process ends with the workers waiting
@@ -106,7 +115,7 @@ time.sleep(0.1)                                           # the process ends wit
 """
 
 
-@pytest.mark.parametrize("what", ["UNLOAD", "UNLOAD_AND_LOAD", "LEAVE", "TWO", "FORK", "LAST", "DAEMON"])
+@pytest.mark.parametrize("what", ["UNLOAD", "UNLOAD_AND_LOAD", "LEAVE", "TWO", "FORK", "FORK_AFTER_UNLOAD", "LAST", "DAEMON"])
 def test_worker_threads(what):
     code = (COMMON + globals()[what]).replace("{lib!r}", repr(LIB))
     run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
