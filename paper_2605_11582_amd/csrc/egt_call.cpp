@@ -18,6 +18,7 @@
 
 #include <cstdint>
 #include <exception>
+#include <memory>
 #include <vector>
 
 #include "egt.h"
@@ -122,7 +123,7 @@ PyObject *call_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObje
 }
 
 // Call(kind, address, [arguments of each launch, ...], stream, keep)
-PyObject *call_new(PyTypeObject *type, PyObject *args, PyObject *) {
+PyObject *call_new(PyTypeObject *type, PyObject *args, PyObject *) try {
   int kind;
   unsigned long long fn, stream;
   PyObject *launches, *keep;
@@ -131,7 +132,7 @@ PyObject *call_new(PyTypeObject *type, PyObject *args, PyObject *) {
     PyErr_SetString(PyExc_ValueError, "unknown kind of call");
     return nullptr;
   }
-  std::vector<Thunk> thunks;
+  auto thunks = std::make_unique<std::vector<Thunk>>();
   for (Py_ssize_t k = 0; k < PyList_GET_SIZE(launches); ++k) {
     PyObject *a = PyList_GET_ITEM(launches, k);
     if (!PyTuple_Check(a) || PyTuple_GET_SIZE(a) != N_ARGS[kind]) {
@@ -144,17 +145,19 @@ PyObject *call_new(PyTypeObject *type, PyObject *args, PyObject *) {
       t.a[j] = (int64_t)PyLong_AsUnsignedLongLongMask(PyTuple_GET_ITEM(a, j));
       if (t.a[j] == -1 && PyErr_Occurred()) return nullptr;
     }
-    thunks.push_back(t);
+    thunks->push_back(t);
   }
   Call *c = (Call *)type->tp_alloc(type, 0);
   if (!c) return nullptr;
   c->vectorcall = call_call;
-  c->thunks = new std::vector<Thunk>(std::move(thunks));
+  c->thunks = thunks.release();
   c->stream = (void *)(uintptr_t)stream;
   Py_INCREF(keep);
   c->keep = keep;
   c->dict = c->weak = nullptr;
   return (PyObject *)c;
+} catch (const std::exception &) {                     // (no memory)
+  return PyErr_NoMemory();
 }
 int call_traverse(PyObject *self, visitproc visit, void *arg) {
   Py_VISIT(((Call *)self)->keep);

@@ -1,5 +1,9 @@
 """The extension module between Python and the C ABI, without a GPU: what it hands on and what it refuses."""
 import ctypes as C
+import os
+import shutil
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -52,6 +56,47 @@ def test_prepared_calls_are_referred_to_and_copied_like_functions():
     del call, kept
     gc.collect()
     assert ref() is None and kept_ref() is None and not table
+
+
+NO_MEMORY = r"""
+#include <cstdlib>
+#include <new>
+static bool armed = false;
+extern "C" void arm(int on) { armed = on != 0; }
+void *operator new(size_t n) { void *p = armed ? nullptr : std::malloc(n ? n : 1); if (!p) throw std::bad_alloc(); return p; }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+"""
+CHILD = r"""
+import ctypes, sys
+sys.path.insert(0, {root!r})
+from paper_2605_11582_amd import binding as egt
+native, arm = egt._native(), ctypes.CDLL({lib!r}).arm
+args = (native.READ, 1 << 20, [(1, 2, 3)], 7, None)
+native.Call(*args)
+arm(1)
+try:
+    native.Call(*args)
+    print("made")
+except MemoryError:
+    print("no memory")
+arm(0)
+native.Call(*args)
+"""
+
+
+def test_a_prepared_call_without_memory_is_a_memory_error(tmp_path):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no host compiler")
+    lib, root = str(tmp_path / "nomem.so"), os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    (tmp_path / "nomem.cpp").write_text(NO_MEMORY)
+    subprocess.run([gxx, "-shared", "-fPIC", "-O1", str(tmp_path / "nomem.cpp"), "-o", lib], check=True)
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = " ".join(v for v in (lib, env.get("LD_PRELOAD", "")) if v)
+    run = subprocess.run([sys.executable, "-c", CHILD.replace("{root!r}", repr(root)).replace("{lib!r}", repr(lib))],
+                         capture_output=True, text=True, env=env, timeout=120)
+    assert run.returncode == 0 and run.stdout.split("\n")[0] == "no memory", (run.returncode, run.stdout[-300:], run.stderr[-800:])
 
 
 def test_tensors_without_memory_are_left_to_the_checks():
