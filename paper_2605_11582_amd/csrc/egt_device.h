@@ -46,6 +46,13 @@ bool sparse_rows_supported(const egt_2bitcsr &w);
 hipError_t launch_sparse_rows(const egt_2bitcsr &w, const uint16_t *x, uint16_t *y, hipStream_t stream);
 hipError_t launch_sparse_rows_batch(const egt_2bitcsr *ws, const uint16_t *const *xs, uint16_t *const *ys, int count, hipStream_t stream);
 
+// M = 1, INT4 rows that do not fill the tiles of the kernels above (see sparse_codes_supported, int4_codes_supported)
+bool sparse_codes_supported(const egt_2bitcsr &w);
+hipError_t launch_sparse_codes(const egt_2bitcsr *ws, const uint16_t *const *xs, uint16_t *const *ys, int count, hipStream_t stream);
+bool int4_codes_supported(int rows, int cols, int group);
+hipError_t launch_int4_codes(const uint8_t *const *qs, const uint16_t *const *qps, int rows, int cols, int group, const uint16_t *const *xs,
+                             uint16_t *const *ys, int count, hipStream_t stream);
+
 // 2 <= M <= 64 on the sparse matrix cores (2:4 and 1:4; see sparse_smallm_supported)
 bool sparse_smallm_supported(const egt_2bitcsr &w, int64_t ldx, int M);
 hipError_t launch_sparse_smallm(const egt_2bitcsr &w, const uint16_t *X, int64_t ldx, uint16_t *Y,

@@ -15,10 +15,8 @@
 // differ in the order of the additions (20000 x 2816: error against 64 bits 2.0777e-4 either way,
 // all of it the rounding of y).
 //
-// Only FP16 values: INT4 weights would have to be rounded to FP16 before the instruction (the
-// slot-by-slot kernels hold them in FP32, and in range up to 15 times the largest scale), and a
-// row that keeps one of four would multiply a second column of its 4-groups by zero, which an
-// infinity there turns into NaN.
+// Only FP16 values at 2:4 (INT4 rows: egt_mfma_codes.hip): a row of FP16 values that keeps one of four would
+// multiply a second column of its 4-groups by zero, which an infinity there turns into NaN.
 //
 //  - A wave owns up to 64 consecutive rows and walks them TPI tiles at a time with two sets of
 //    registers.

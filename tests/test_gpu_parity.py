@@ -171,6 +171,37 @@ def test_infinite_activations_of_dense_rows_off_the_tiles():
     assert np.array_equal(y, want.astype(np.float16), equal_nan=True)
 
 
+# The kernel of exact codes at the edges of its tiles: a unit a row (a tile holds sixteen rows), rows that fill half a tile and
+# just more, a tile less one unit, a tile, one unit more (two tiles), the most tiles; for each group size (128 and more, 64,
+# 32: other units), with rows that end inside a wave and inside a workgroup.
+CODES_EDGES = [(r, c, g, f) for g, cols in ((128, (128, 1920, 2048, 2176, 3968)), (64, (64, 1984, 2112)), (32, (32, 992, 1056, 4064))) for c in cols
+               for r, f in ((67, "dense"), (1, 2), (67, 2), (5, "paired"), (18, 1), (63, "12"))]
+CODES_EDGES += [(5, 4224, 128, 1), (18, 7936, 256, "12"), (63, 4096, 128, "12"), (3, 24576, 128, "1234"), (3, 24576, 64, "dense"), (5, 16384, 32, "12"), (7, 16352, 32, "paired"),
+                (5, 16320, 32, 1), (3300, 1056, 32, "dense"), (70, 5184, 64, "1234"), (19, 2592, 32, "1234")]
+
+
+@pytest.mark.parametrize("rows,cols,g,form", CODES_EDGES)
+def test_exact_codes_at_the_edges_of_their_tiles(rows, cols, g, form):
+    w = synth.weights(rows, cols, 9500 + rows + cols)
+    run, ref, _ = _slot_by_slot_case(rows, cols, g, form, w)
+    x = synth.activations(cols, 9500 + cols)
+    y_ref, a_ref = ref(x)
+    # half a unit in the last place of the result, and a rounding to FP32 for every addition of the row
+    assert np.all(np.abs(run(x).astype(np.float64) - y_ref) <= 2.0**-11 * np.abs(y_ref) + cols * 2.0**-24 * a_ref + 2.0**-25)
+
+
+@pytest.mark.parametrize("rows,cols,g,n,kind,count", [(70, 1920, 128, 2, 0, 3), (19, 2112, 64, 1, 0, 4), (33, 4128, 32, 2, 2, 2), (131, 96, 32, 2, 0, 4)])
+def test_batches_of_exact_codes_equal_separate_calls(rows, cols, g, n, kind, count):
+    torch = G.torch_mod()
+    ps = [_small_case(rows, cols, n, g, kind, seed=9600 + 13 * k + rows)[0] for k in range(count)]
+    xs = [synth.activations(cols, 9600 + k) for k in range(count)]
+    ys = [torch.full((rows,), 9.0, dtype=torch.float16, device="cuda") for _ in range(count)]
+    B.sparse_gemv_batch([p.to("cuda") for p in ps], [G.to_dev(x.view(np.uint16)).view(torch.float16) for x in xs], ys)
+    torch.cuda.synchronize()
+    for p, x, y in zip(ps, xs, ys):
+        assert np.array_equal(y.cpu().numpy().view(np.uint16), G.run_sparse_gemv(p, x).view(np.uint16))
+
+
 @pytest.mark.parametrize("rows,cols,n,g,M", [(70, 4096, 2, 64, 1), (70, 4096, 1, 32, 1), (300, 1024, 2, 128, 6)])
 def test_row_group_sizes_run_on_the_ordinary_kernels(rows, cols, n, g, M):
     # rows quantised with group sizes of their own are stored at the finest granularity

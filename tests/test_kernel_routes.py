@@ -141,3 +141,32 @@ def test_fp16_rows_of_one_token(launches):
 def test_a_batch_of_short_fp16_rows_is_one_launch(launches, cols):
     (call,) = launches([{"call": "gemv_batch", "w": (300, cols, 2, 0, 1), "count": 4}])
     assert len(call) == 1 and "k_rows" in call[0][0] and call[0][2] == 4, call
+
+
+# (rows, cols, n_keep, group, value kind); which rows run with exact codes on the matrix cores, on both sides of each line
+@pytest.mark.parametrize("w,codes", [
+    ((11008, 4096, 0, 128, 0), True), ((300, 40960, 0, 128, 0), False),                                   # rows differ; wider than x in LDS
+    ((5, 64, 2, 64, 0), True), ((20000, 2816, 2, 128, 0), True), ((20000, 2816, 2, 256, 2), True), ((300, 4096, 2, 128, 0), False), ((300, 1024, 2, 128, 0), False),
+    ((300, 1056, 2, 96, 0), False), ((300, 2880, 2, 12, 0), False), ((300, 2880, 3, 64, 0), False),          # groups that are no 32 << j, rows that keep three
+    ((300, 4224, 1, 128, 0), True), ((300, 4096, 1, 128, 0), False),
+    ((30000, 4096, 0, 64, 0), True), ((5460, 4160, 1, 64, 0), True), ((5461, 4160, 1, 64, 0), False), ((5461, 4160, 1, 32, 0), False),    # waves of a row, waves of a launch
+    ((5460, 4160, 0, 64, 0), True), ((5461, 4160, 0, 64, 0), False), ((30000, 4096, 2, 32, 2), True), ((6552, 4128, 2, 32, 2), True), ((6553, 4128, 2, 32, 2), False),
+    ((300, 16384, 0, 32, 0), True), ((300, 16416, 0, 32, 0), False),
+    ((300, 2816, 0, 0, 1), False),                                                                          # FP16 values
+])
+def test_rows_of_exact_codes(launches, w, codes):
+    (call,) = launches([{"call": "gemv", "w": (*w, w[0] * w[1] // 2 // 8 * 8 if w[2] == 0 else 0)}])
+    assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
+
+
+@pytest.mark.parametrize("w,codes", [((5003, 2880, 64), True), ((70, 1536, 128), True), ((2278, 1504, 32), False), ((2400, 1504, 32), True), ((300, 384, 128), False), ((300, 2944, 128), False),
+                                     ((300, 24512, 64), True), ((300, 24640, 64), False), ((24000, 4064, 32), True), ((6552, 4128, 32), True), ((6553, 4128, 32), False), ((300, 2880, 36), False)])
+def test_dense_rows_of_exact_codes(launches, w, codes):
+    (call,) = launches([{"call": "int4", "w": w}])
+    assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
+
+
+@pytest.mark.parametrize("w", [(300, 1920, 2, 128, 0), (300, 2112, 1, 64, 0), (300, 4128, 2, 32, 2)])
+def test_a_batch_of_exact_codes_is_one_launch(launches, w):
+    (call,) = launches([{"call": "gemv_batch", "w": w, "count": 4}])
+    assert len(call) == 1 and "k_codes_batch" in call[0][0] and call[0][2] == 4, call
