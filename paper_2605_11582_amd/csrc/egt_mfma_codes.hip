@@ -41,7 +41,7 @@
 namespace egt {
 
 enum { CODES_24 = 0, CODES_14 = 1, CODES_MIXED = 2, CODES_DENSE = 3, CODES_24P = 4 };    // 24P: paired nibble order
-constexpr int CODES_TPI = 4;                          // tiles of a wave (a tile has up to 16 rows, so a wave 64 at most)
+constexpr int CODES_TPI = 4;                          // tiles of a wave at most (a tile has up to 16 rows, so a wave 64 at most)
 constexpr int CODES_WAVES = 16;                       // waves of a workgroup at most
 
 struct CodesGeom {
@@ -109,11 +109,11 @@ __device__ __forceinline__ uint32_t codes_pair(uint32_t d, int p, uint32_t off, 
 }
 
 // FORM: CODES_*.  CPL: columns of a chunk.  UNITS: of a tile.  MP: a row takes several tiles.
-template <int FORM, int CPL, int UNITS, bool MP>
+template <int FORM, int CPL, int UNITS, int TPI, bool MP>
 __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &g) {
   extern __shared__ __align__(16) uint8_t xs[];       // x, then the quads' sums of the workgroup's rows
   constexpr bool DENSE = FORM == CODES_DENSE, MIXED = FORM == CODES_MIXED, PAIRED = FORM == CODES_24P;
-  constexpr int TPI = CODES_TPI, LOADS = DENSE ? 2 : MIXED ? 5 : 3;        // (requests of a tile)
+  constexpr int LOADS = DENSE ? 2 : MIXED ? 5 : 3;        // (requests of a tile)
   constexpr int VB = codes_vb(FORM, CPL), IB = codes_ib(FORM, CPL);
   constexpr uint32_t OUT = 0x7FFFFFF0u;               // past every buffer (they are below 2 GiB): zeros, no traffic
   constexpr int L = 64 / UNITS, QB = 2 * L * CPL, QP = QB / 16, QM = QP > 16 ? 15 : QP - 1;   // chunks of a unit; a unit of x: bytes, pieces, and the bits of its number that move them
@@ -383,19 +383,19 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   }
 }
 
-template <int FORM, int CPL, int UNITS, bool MP>
+template <int FORM, int CPL, int UNITS, int TPI, bool MP>
 __global__ __launch_bounds__(1024) void k_codes(const uint32_t *__restrict__ row_ptr, const uint8_t *__restrict__ values,
                                                   const uint8_t *__restrict__ idx, const uint8_t *__restrict__ qparams,
                                                   const __half *__restrict__ x, __half *__restrict__ y, const CodesGeom g) {
   const CodesPtrs P{row_ptr, values, idx, qparams, x, y};
-  codes_body<FORM, CPL, UNITS, MP>(P, g);
+  codes_body<FORM, CPL, UNITS, TPI, MP>(P, g);
 }
 // Up to four identically shaped matrices, blockIdx.y names the member.
-template <int FORM, int CPL, int UNITS, bool MP>
+template <int FORM, int CPL, int UNITS, int TPI, bool MP>
 __global__ __launch_bounds__(1024) void k_codes_batch(const GemvBatch b, const CodesGeom g) {
   const unsigned k = blockIdx.y;
   const CodesPtrs P{pick4(b.row_ptr, k), pick4(b.values, k), pick4(b.idx, k), pick4(b.qparams, k), pick4(b.x, k), pick4(b.y, k)};
-  codes_body<FORM, CPL, UNITS, MP>(P, g);
+  codes_body<FORM, CPL, UNITS, TPI, MP>(P, g);
 }
 
 namespace {
@@ -441,14 +441,22 @@ bool codes_geometry(int form, int rows, int cols, int n_keep, int group, uint32_
 }
 
 // The waves of a workgroup are the phases of `wpp` row sets.
-void codes_shape(CodesGeom &g, int unit, dim3 &grid, dim3 &block, size_t &lds) {
+void codes_shape(CodesGeom &g, int unit, bool dense, int count, int &tpi, dim3 &grid, dim3 &block, size_t &lds) {
   const size_t x_bytes = ((size_t)g.units * (size_t)(2 * unit) + 1023) & ~(size_t)1023;
-  int waves = 4, unused = 0;                          // (2, 6 and 8 waves: 1.1 to 1.5 times the time on 20000 x 2816 and 11008 x 4096)
-  tune_pair("EGT_CODES_TUNE", waves, unused);
+  const int nrg = (g.rows + g.rpt - 1) / g.rpt;       // row groups
+  // Few tiles: one or two to a wave, since the launch then lasts as long as a wave's instructions (us with 1, 2, 4 tiles a wave:
+  // 300 x 768 2.6, 2.8, 3.3; 4000 x 1920 3.1, 3.2, 3.7; 5000 x 3072 4.1, 4.0, 4.4; 11008 x 3072 6.1, 5.6, 5.4; dense 5003 x 2880,
+  // 10006 tiles, 5.3, 4.7, 4.9).
+  const int64_t tiles = (int64_t)nrg * g.phases * count;
+  tpi = tiles <= 2048 ? 1 : tiles <= (dense ? 10240 : 5120) ? 2 : 4;
+  int waves = 4;                                      // (2, 6 and 8 waves: 1.1 to 1.5 times the time on 20000 x 2816 and 11008 x 4096)
+  tune_pair("EGT_CODES_TUNE", waves, tpi);
+  if (tpi != 1 && tpi != 2) tpi = 4;
+
   waves = waves < 1 ? 1 : waves > CODES_WAVES ? CODES_WAVES : waves;
   g.wpp = std::max(1, waves / g.phases);
   g.wpp_inv = (65536 + g.wpp - 1) / g.wpp;
-  const int rows_wg = g.wpp * CODES_TPI * g.rpt, nrg = (g.rows + g.rpt - 1) / g.rpt, sets = (nrg + CODES_TPI - 1) / CODES_TPI;
+  const int rows_wg = g.wpp * tpi * g.rpt, sets = (nrg + tpi - 1) / tpi;
   g.red_stride = rows_wg | 1;
   g.split = 0;
   while (g.split < 4 && (rows_wg << (g.split + 1)) <= 64 * g.wpp * g.phases) ++g.split;
@@ -474,6 +482,7 @@ int codes_form(const egt_2bitcsr &w) {
 static bool codes_pay(int form, const CodesGeom &g, int unit) {
   const bool dense = form == CODES_DENSE;
   const int64_t cols = 8 * (int64_t)g.npieces;
+  if (tune_flag("EGT_CODES_ALL")) return true;
   if (dense && cols < 1536 && g.rows * cols < 3500000) return false;
   if (unit == 128 || (dense && unit == 64)) return true;
   const bool one = form == CODES_14 || form == CODES_MIXED;
@@ -498,14 +507,17 @@ template <int FORM, int CPL, int UNITS>
 static hipError_t go(const GemvBatch &b, CodesGeom &g, int count, hipStream_t stream) {
   dim3 grid, block;
   size_t lds;
-  codes_shape(g, CPL * (64 / UNITS), grid, block, lds);
+  int tpi;
+  codes_shape(g, CPL * (64 / UNITS), FORM == CODES_DENSE, count, tpi, grid, block, lds);
   grid.y = (unsigned)count;
-#define EGT_C(MP)                                                                                                            \
-  (FORM != CODES_MIXED && count > 1 ? launch(k_codes_batch<FORM == CODES_MIXED ? CODES_14 : FORM, CPL, UNITS, MP>, grid, block, lds, stream, b, g) \
-             : launch(k_codes<FORM, CPL, UNITS, MP>, grid, block, lds, stream, b.row_ptr[0], b.values[0], b.idx[0], b.qparams[0], b.x[0], b.y[0], g))
+#define EGT_C(TPI, MP)                                                                                                       \
+  (FORM != CODES_MIXED && count > 1 ? launch(k_codes_batch<FORM == CODES_MIXED ? CODES_14 : FORM, CPL, UNITS, TPI, MP>, grid, block, lds, stream, b, g) \
+             : launch(k_codes<FORM, CPL, UNITS, TPI, MP>, grid, block, lds, stream, b.row_ptr[0], b.values[0], b.idx[0], b.qparams[0], b.x[0], b.y[0], g))
+#define EGT_T(MP) (tpi == 1 ? EGT_C(1, MP) : tpi == 2 ? EGT_C(2, MP) : EGT_C(4, MP))
   if constexpr (!((FORM == CODES_24 || FORM == CODES_24P) && CPL == 64))
-    if (g.phases > 1) return EGT_C(true);
-  return EGT_C(false);
+    if (g.phases > 1) return EGT_T(true);
+  return EGT_T(false);
+#undef EGT_T
 #undef EGT_C
 }
 

@@ -59,6 +59,13 @@ hipError_t launch_int4_m1_batch(const uint8_t *const *qs, const uint16_t *const 
   bool pre;
   dense_geometry(rows, cols, group, g, pre);
   int tpi = 4, wpp = g.phases == 1 ? 4 : (g.phases <= 8 ? 2 : 1);   // measured; K = 11008 (6 phases): 7.65 us with 2, 8.24 with 1
+  // few tiles: one or two to a wave, as in egt_mfma_m1.hip (4096 x 1024 2.8 -> 2.6 us, 2048 x 2048 2.9 -> 2.7, 1024 x 4096 3.2 -> 3.0, 1024 x 11008
+  // 4.9 -> 3.9; 4096 x 2048: 2.95 with four, 3.2 with one; 2048 x 4096: 3.3, 3.45)
+  const int64_t tiles = (int64_t)g.ntiles * count;
+  if (g.phases == 1 ? tiles <= 2048 : tiles <= 1024) {
+    tpi = g.phases <= 4 ? 1 : 2;
+    if (g.phases <= 4) wpp = 4;
+  }
   tune_pair("EGT_DENSE_TUNE", tpi, wpp);
   if (wpp < 1) wpp = 1;
   if (wpp * g.phases > 16) wpp = 16 / g.phases;

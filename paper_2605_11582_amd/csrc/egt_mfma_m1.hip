@@ -99,6 +99,24 @@ bool sparse_m1_supported(const egt_2bitcsr &w) {
   return true;
 }
 
+// Few tiles: one or two to a wave.  With four, a matrix of a few megabytes leaves compute units idle and the launch lasts
+// as long as one wave's four tiles; with fewer than that for a large one every four rows or fewer stage an x.  us per launch with
+// the tiles per wave before, and now (weights in the last-level cache): 1024 x 1024 3.05, 2.6; 4096 x 1024 3.2, 2.7; 1024 x 4096 3.0,
+// 2.7; 2048 x 4096 3.1, 2.8 (3072 x 4096: 3.1 with four, 3.2 with one or two); 9000 x 2048 3.9, 3.6 (40000 x 2048: 7.1 with
+// four, 7.7 with two); 512 x 8192 3.6, 3.2; 1024 x 11008 4.4, 3.7; 1024 x 16384 4.8, 4.0 (2048 x 16384: 5.0, 5.5); FP16
+// values 512 x 4096 3.2, 2.7; 6000 x 4096 6.2, 5.5 (8000 x 4096: 6.5 with four, 6.7 with two).
+static void m1_few_tiles(const M1Geom &g, bool f16, int count, int &tpi, int &wpp) {
+  const int64_t tiles = (int64_t)g.ntiles * count;
+  if (g.phases == 1) {
+    const bool mr = g.mr_shift >= 0;
+    if (tiles <= (mr ? 2304 : f16 ? 1024 : 1536)) tpi = 1;
+    else if (tiles <= (mr ? 10240 : f16 ? 6144 : 2304)) tpi = 2;
+  } else if (tiles <= 1024) {
+    tpi = 1;
+    wpp = g.phases <= 4 ? 4 : 16 / g.phases;
+  }
+}
+
 hipError_t launch_sparse_m1_batch(const egt_2bitcsr *ws, const uint16_t *const *xs, uint16_t *const *ys,
                                   int count, hipStream_t stream) {
   const egt_2bitcsr &w = ws[0];
@@ -116,6 +134,7 @@ hipError_t launch_sparse_m1_batch(const egt_2bitcsr *ws, const uint16_t *const *
   // measured optima: 4 tiles per wave and 4 waves per phase for one phase, 2 waves per phase
   // for several - except three phases (K = 11008: 6.97 against 7.30 us with 2 and 4)
   int tpi = g.phases == 3 ? 2 : 4, wpp = (g.phases == 1 || g.phases == 3) ? 4 : 2;
+  if (!g32) m1_few_tiles(g, w.val_kind == EGT_VAL_FP16, count, tpi, wpp);
   tune_pair("EGT_M1_TUNE", tpi, wpp);
   if (wpp < 1) wpp = 1;
   if (wpp * g.phases > 16) wpp = 16 / g.phases;
@@ -209,8 +228,8 @@ hipError_t launch_sparse_m1_paired(const egt_2bitcsr &w, const uint16_t *x, uint
   M1Geom g;
   m1_geometry(c, g);
   g.nib_mask = 0x000F000Fu; g.nib_magic = 0x64006400u; g.nib_magic2 = 0x54005400u;
-  const int tpi = g.phases == 3 ? 2 : 4;
-  int wpp = (g.phases == 1 || g.phases == 3) ? 4 : 2;
+  int tpi = g.phases == 3 ? 2 : 4, wpp = (g.phases == 1 || g.phases == 3) ? 4 : 2;
+  m1_few_tiles(g, false, 1, tpi, wpp);
   if (wpp * g.phases > 16) wpp = 16 / g.phases;
   LaunchShape ls;
   if (!m1_block_shape(g, false, wpp, tpi, 1, 4, ls)) return hipErrorInvalidConfiguration;
@@ -221,18 +240,20 @@ hipError_t launch_sparse_m1_paired(const egt_2bitcsr &w, const uint16_t *x, uint
     g.hi_blocks = nb;
     const int per_hi = ls.nwaves * tpi, per_lo = ls.nwaves * (tpi - 1);
     const int even = 256 * ((g.ntiles + 256 * per_hi - 1) / (256 * per_hi));
-    if (even <= 1024 && even * per_lo < g.ntiles) {
+    if (tpi > 1 && even <= 1024 && even * per_lo < g.ntiles) {
       nb = even;
       g.hi_blocks = (g.ntiles - nb * per_lo + ls.nwaves - 1) / ls.nwaves;
     }
-    return ls.xp <= 1 ? launch(k_sparse_m1_one<4, 1, 1, true>, dim3(nb), block, ls.lds, stream, EGT_ARGS)
-                      : launch(k_sparse_m1_one<4, 2, 1, true>, dim3(nb), block, ls.lds, stream, EGT_ARGS);
+#define EGT_P1(TPI) (ls.xp <= 1 ? launch(k_sparse_m1_one<TPI, 1, 1, true>, dim3(nb), block, ls.lds, stream, EGT_ARGS) \
+                                : launch(k_sparse_m1_one<TPI, 2, 1, true>, dim3(nb), block, ls.lds, stream, EGT_ARGS))
+    return tpi == 1 ? EGT_P1(1) : tpi == 2 ? EGT_P1(2) : EGT_P1(4);
+#undef EGT_P1
   }
   const dim3 grid(ls.nblocks);
 #define EGT_P(TPI) (ls.xp <= 1 ? launch(k_sparse_m1<EGT_VAL_INT4, TPI, 1, 1, false, true>, grid, block, ls.lds, stream, EGT_ARGS) \
                     : ls.xp == 2 ? launch(k_sparse_m1<EGT_VAL_INT4, TPI, 2, 1, false, true>, grid, block, ls.lds, stream, EGT_ARGS) \
                                  : launch(k_sparse_m1<EGT_VAL_INT4, TPI, 4, 1, false, true>, grid, block, ls.lds, stream, EGT_ARGS))
-  return tpi == 2 ? EGT_P(2) : EGT_P(4);
+  return tpi == 1 ? EGT_P(1) : tpi == 2 ? EGT_P(2) : EGT_P(4);
 #undef EGT_P
 #undef EGT_ARGS
 }
@@ -268,6 +289,8 @@ hipError_t launch_sparse_m1_tokens(const egt_2bitcsr &w, const uint16_t *X, int6
   // four tokens take about 200 registers: two waves per SIMD, workgroups of at most 8 waves;
   // FP16 values (64 B per lane and tile): two tiles per wave
   int tpi = (f16 && g.phases < 3) ? 2 : 4, wpp = g.phases == 1 ? 4 : 2;
+  // (few rows, as m1_few_tiles: 1024 x 4096 at two tokens 3.8 -> 3.4 us, at four 4.9 -> 4.3; 4096 x 4096: 4.0 with four tiles, 4.1 with two)
+  if (!f16 && g.phases == 1 && w.rows <= 1536) tpi = 2;
   tune_pair("EGT_M1T_TUNE", tpi, wpp);
   if (f16 && mt == 4) tpi = 2;                        // the only four-token form with FP16 values
   if (wpp < 1) wpp = 1;

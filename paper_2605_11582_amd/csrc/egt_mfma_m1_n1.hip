@@ -63,6 +63,9 @@ hipError_t launch_sparse_m1_n1_batch(const egt_2bitcsr *ws, const uint16_t *cons
   n1_geometry(w, lin, g, ni);
   int tpi = g.phases == 1 ? 2 : 4, wpp = 4;
   if (lin) tpi = ni == 4 ? 2 : 4;
+  // few tiles: one to a wave, as in egt_mfma_m1.hip (4096 x 2048 3.2 -> 2.8 us, 512 x 4096 3.1 -> 2.9, 1024 x 11008 5.8 -> 3.8; 4096 x 4096,
+  // 2048 tiles: 3.35 with two, 3.45 with one)
+  if (!lin && (int64_t)g.ntiles * count <= 1024) tpi = 1;
   tune_pair("EGT_M1N1_TUNE", tpi, wpp);
   if (wpp < 1) wpp = 1;
   if (wpp * g.phases > 16) wpp = 16 / g.phases;

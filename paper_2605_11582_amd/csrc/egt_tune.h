@@ -11,7 +11,7 @@
 //   EGT_STACK_TUNE=waves,tpi_mode  EGT_STREAM_TUNE=force,blocks_per_cu  EGT_STREAM_WAVES=waves  EGT_STREAM_ITEM=kilobytes
 //   EGT_SM_KS=slices,row_blocks    (multi-matrix launches; K split at small M)
 //   EGT_ROWS_TUNE=waves,waves_per_cu  row-walking M = 1 kernel of FP16 values
-//   EGT_CODES_TUNE=waves  products of exact codes    EGT_NO_CODES   (set = slot by slot)
+//   EGT_CODES_TUNE=waves,tiles  products of exact codes    EGT_NO_CODES   (set = slot by slot)   EGT_CODES_ALL   (set = wherever they apply)
 //   EGT_SM_NOHOLD   (set = no small-M products with X in registers)
 //   EGT_NO_M1T, EGT_M1N1_NOLIN, EGT_M1_NOONE, EGT_M1_NOEVEN, EGT_SM_NOXS   (set = that path is not used)
 //   EGT_SM_XS   (set = the small-M form with X held in LDS wherever it applies, not only where it is the faster one)

@@ -150,16 +150,15 @@ def test_requests_of_the_row_walking_kernel_match_the_wait_count(tmp_path):
 
 
 def test_requests_of_the_exact_codes_match_the_wait_count(tmp_path):
-    # k_codes<FORM, ...>: x, then a wave's tiles (rows of different lengths five requests each, dense rows two, the others three)
+    # k_codes<FORM, CPL, UNITS, TPI, MP>: x, then a wave's tiles (rows of different lengths five requests each, dense rows two, the others three)
     text = open(os.path.join(CSRC, "egt_mfma_codes.hip")).read()
-    tpi = int(re.search(r"CODES_TPI = (\d+);", text).group(1))
     dense, mixed, other = (int(v) for v in re.search(r"LOADS = DENSE \? (\d+) : MIXED \? (\d+) : (\d+);", text).groups())
     seen = 0
     for name, body in _assembly("egt_mfma_codes.hip", tmp_path):
-        m = re.search(r"k_codes(?:_batch)?ILi(\d)E", name)
+        m = re.search(r"k_codes(?:_batch)?ILi(\d)ELi\d+ELi\d+ELi(\d)E", name)
         if not m:
             continue
-        loads = tpi * {2: mixed, 3: dense}.get(int(m.group(1)), other)
+        loads = int(m.group(2)) * {2: mixed, 3: dense}.get(int(m.group(1)), other)
         registers, to_lds = _prologue(body, loads)
         assert len(registers) == loads and to_lds == 1, (name, registers, to_lds)
         assert _lane_loops(body) == 0 and not re.search(r"\bscratch_|\bflat_", body), name

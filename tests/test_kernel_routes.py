@@ -170,3 +170,26 @@ def test_dense_rows_of_exact_codes(launches, w, codes):
 def test_a_batch_of_exact_codes_is_one_launch(launches, w):
     (call,) = launches([{"call": "gemv_batch", "w": w, "count": 4}])
     assert len(call) == 1 and "k_codes_batch" in call[0][0] and call[0][2] == 4, call
+
+
+# (rows, cols, n_keep, group, value kind), tiles of a wave: the second number (dense: the first) of the kernel's template arguments after the
+# value kind; on both sides of each line
+@pytest.mark.parametrize("w,kernel,tiles", [
+    ((1536, 4096, 2, 128, 0), "k_sparse_m1_oneILi%dE", 1), ((1537, 4096, 2, 128, 0), "k_sparse_m1_oneILi%dE", 2), ((2305, 4096, 2, 128, 0), "k_sparse_m1_oneILi%dE", 4),
+    ((1536, 4096, 2, 128, 2), "k_sparse_m1_oneILi%dE", 1), ((2304, 4096, 2, 128, 2), "k_sparse_m1_oneILi%dE", 2), ((2305, 4096, 2, 128, 2), "k_sparse_m1_oneILi%dE", 4),
+    ((9216, 1024, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 1), ((9217, 1024, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 2), ((20482, 2048, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 4),
+    ((1024, 16384, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 1), ((1025, 16384, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 4), ((1024, 11008, 2, 128, 2), "k_sparse_m1ILi0ELi%dE", 1),
+    ((1025, 11008, 2, 128, 2), "k_sparse_m1ILi0ELi%dE", 2), ((3, 32768, 2, 128, 0), "k_sparse_m1ILi0ELi%dE", 1),
+    ((1024, 4096, 2, 0, 1), "k_sparse_m1ILi1ELi%dE", 1), ((6144, 4096, 2, 0, 1), "k_sparse_m1ILi1ELi%dE", 2), ((6145, 4096, 2, 0, 1), "k_sparse_m1ILi1ELi%dE", 4),
+    ((1024, 8192, 1, 128, 0), "k_sparse_m1_n1ILi0ELi%dE", 1), ((1025, 8192, 1, 128, 0), "k_sparse_m1_n1ILi0ELi%dE", 2),
+    ((2048, 1920, 2, 128, 0), "k_codesILi0ELi64ELi32ELi%dE", 1), ((4098, 1920, 2, 128, 0), "k_codesILi0ELi64ELi32ELi%dE", 2), ((5121, 3072, 2, 128, 0), "k_codesILi0ELi64ELi32ELi%dE", 4)])
+def test_tiles_of_a_wave(launches, w, kernel, tiles):
+    (call,) = launches([{"call": "gemv", "w": (*w, 0)}])
+    assert len(call) == 1 and kernel % tiles in call[0][0], call
+
+
+@pytest.mark.parametrize("w,kernel,tiles", [((2048, 2048, 128), "k_int4_m1ILi%dE", 1), ((2049, 2048, 128), "k_int4_m1ILi%dE", 4), ((1024, 8192, 128), "k_int4_m1ILi%dE", 1), ((1025, 8192, 128), "k_int4_m1ILi%dE", 4),
+                                            ((1024, 11008, 128), "k_int4_m1ILi%dE", 2), ((5120, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 2), ((5121, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 4)])
+def test_tiles_of_a_wave_of_dense_rows(launches, w, kernel, tiles):
+    (call,) = launches([{"call": "int4", "w": w}])
+    assert len(call) == 1 and kernel % tiles in call[0][0], call
