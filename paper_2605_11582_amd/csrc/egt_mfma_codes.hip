@@ -264,7 +264,7 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
 #pragma unroll
           for (int d = 0; d < NB; ++d) {
             if (d % 2 == 0) {
-              iw = spread_idx((t[k].iw[0] >> (8 * d)) & 0xFFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u);
+              iw = d ? spread_idx<1>(t[k].iw[0], 0x0F0F0F0Fu, 0x33333333u) : spread_idx<0>(t[k].iw[0], 0x0F0F0F0Fu, 0x33333333u);
               iw |= iw << 2;
             }
             u4 a;                                     // slot 4 d + q in both halves

@@ -88,13 +88,30 @@ __device__ __forceinline__ float quad_xor2(float v) {
 }
 
 
-// 16-bit index word (8 fields of 2 bits) -> 32 bits with field j at bits [4j, 4j+1]: the
+// Half H of a dword of index words (8 fields of 2 bits a word) -> 32 bits with field j at bits [4j, 4j+1]: the
 // index operand of an instruction whose compressed values are {value, 0} pairs (1:4).
-// The masks 0x00FF00FF, 0x0F0F0F0F, 0x33333333 are passed in so that they live in registers.
-__device__ __forceinline__ uint32_t spread_idx(uint32_t w, uint32_t m8, uint32_t m4, uint32_t m2) {
-  uint32_t t = (w | (w << 8)) & m8;
+// The masks 0x0F0F0F0F and 0x33333333 are passed in so that they live in registers.
+template <int H>
+__device__ __forceinline__ uint32_t spread_idx(uint32_t w, uint32_t m4, uint32_t m2) {
+  uint32_t t = __builtin_amdgcn_perm(w, w, H ? 0x0c030c02u : 0x0c010c00u);      // the bytes of the word apart
   t = (t | (t << 4)) & m4;
   return (t | (t << 2)) & m2;
+}
+// 1:4: half H of a dword of codes -> its four slots as {s (q - z), 0}; off: {1024 + z, 64 + z}, s0: the scale in the low half (what
+// the high half holds does not matter).  The multiplication by {s, 0} takes one half of a pair of slots for both of its halves (an
+// operand selection of the packed instruction): the split costs one operation more than the scaling of the pair, not two.
+template <int H>
+__device__ __forceinline__ u4 dequant4_14(uint32_t d, uint32_t off, uint32_t s0, uint32_t mask, uint32_t magic) {
+  const h2 s = {__builtin_bit_cast(h2, s0)[0], (_Float16)0.f};
+  u4 r;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const uint32_t t = __builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)(2 * H + p) * 0x00010001u);
+    const h2 v = __builtin_bit_cast(h2, pk_sub_f16(and_or(t, mask, magic), off));
+    r[2 * p] = __builtin_bit_cast(uint32_t, h2{v[0], v[0]} * s);
+    r[2 * p + 1] = __builtin_bit_cast(uint32_t, h2{v[1], v[1]} * s);
+  }
+  return r;
 }
 
 // Explicit waits around the loads that write LDS directly: they count as vector-memory

@@ -61,7 +61,7 @@ struct SmallMKsGeom {
   uint32_t val_bytes, idx_bytes, qp_bytes, x_bytes;   // extents of the arrays
   int64_t ldx, ldy;
   uint32_t nib_mask, nib_magic;                        // 0x00F0000F, FP16 {1024.0, 64.0}
-  uint32_t m8, m4, m2;                                 // masks of spread_idx
+  uint32_t m4, m2;                                     // masks of spread_idx
   // K split over workgroups (blockIdx.y = slice s of nslices: nsteps = slice_q * nslices + slice_r, the first
   // slice_r slices have slice_q + 1 K-steps, the others slice_q), and where the FP32 partial sums of
   // slice s, token m, row r go: ws[(s * M + m) * ws_ld + r]
@@ -360,23 +360,16 @@ __device__ __forceinline__ void smallm_ks_body(const uint32_t *__restrict__ row_
       }
     }
     if (N1) {
-      iwv[0] = spread_idx(t.iw[0] & 0xFFFFu, g.m8, g.m4, g.m2);
-      iwv[1] = spread_idx(t.iw[0] >> 16, g.m8, g.m4, g.m2);
-      iwv[NM / 2 - 2] = spread_idx(t.iw[1] & 0xFFFFu, g.m8, g.m4, g.m2);
-      iwv[NM / 2 - 1] = spread_idx(t.iw[1] >> 16, g.m8, g.m4, g.m2);
+      iwv[0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
+      iwv[1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
+      iwv[NM / 2 - 2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
+      iwv[NM / 2 - 1] = spread_idx<1>(t.iw[1], g.m4, g.m2);
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         if constexpr (INT4) {
-          // slots 4 m .. 4 m + 3 = bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1; the two
-          // slots of a byte are dequantised as a pair, then split into {w, 0} registers
-          const uint32_t d = t.nib[0][(m >> 1) & 3];
-#pragma unroll
-          for (int p = 0; p < 2; ++p) {
-            const uint32_t t2 = __builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)(2 * (m & 1) + p) * 0x00010001u);
-            const uint32_t pair = pk_mul_f16(pk_sub_f16(and_or(t2, g.nib_mask, magic), off[m * QW / 8]), s2[m * QW / 8]);
-            av[m][2 * p] = pair & 0xFFFFu;
-            av[m][2 * p + 1] = pair >> 16;
-          }
+          // slots 4 m .. 4 m + 3 = bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
+          const uint32_t d = t.nib[0][(m >> 1) & 3], of = off[m * QW / 8], sc = s2[m * QW / 8];
+          av[m] = m & 1 ? dequant4_14<1>(d, of, sc, g.nib_mask, magic) : dequant4_14<0>(d, of, sc, g.nib_mask, magic);
         } else {
           const uint32_t v0 = live ? t.nib[(m >> 1) & 3][2 * (m & 1)] : 0u;
           const uint32_t v1 = live ? t.nib[(m >> 1) & 3][2 * (m & 1) + 1] : 0u;
@@ -742,7 +735,7 @@ static void smallm_geometry(const egt_2bitcsr &w, int64_t ldx, uint16_t *Y, int6
   g.qp_bytes = (uint32_t)((uint64_t)w.rows * g.groups_per_row * 4);
   g.x_bytes = (uint32_t)(((uint64_t)(M - 1) * ldx + w.cols) * 2);
   g.nib_mask = 0x00F0000Fu; g.nib_magic = 0x54006400u;
-  g.m8 = 0x00FF00FFu; g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
+  g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
   g.nslices = 1; g.ws_ld = 0; g.ws = nullptr;
 }
 // Fills in the launch: workgroups, waves, and what the kernel would have to divide for.
@@ -1159,20 +1152,14 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
       if constexpr (N1) {
         // every slot becomes the pair {value, 0} with its offset in the even index field; instruction m takes
         // slots 4 m .. 4 m + 3 of the chunk: bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
-        iwv[0] = spread_idx(t.iw[0] & 0xFFFFu, g.m8, g.m4, g.m2);
-        iwv[1] = spread_idx(t.iw[0] >> 16, g.m8, g.m4, g.m2);
-        iwv[2] = spread_idx(t.iw[1] & 0xFFFFu, g.m8, g.m4, g.m2);
-        iwv[3] = spread_idx(t.iw[1] >> 16, g.m8, g.m4, g.m2);
+        iwv[0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
+        iwv[1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
+        iwv[2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
+        iwv[3] = spread_idx<1>(t.iw[1], g.m4, g.m2);
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           const uint32_t d = t.nib[0][m >> 1];
-#pragma unroll
-          for (int p = 0; p < 2; ++p) {
-            const uint32_t t2 = __builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)(2 * (m & 1) + p) * 0x00010001u);
-            const uint32_t pair = pk_mul_f16(pk_sub_f16(and_or(t2, g.nib_mask, magic), off), s2);
-            av[m][2 * p] = pair & 0xFFFFu;
-            av[m][2 * p + 1] = pair >> 16;
-          }
+          av[m] = m & 1 ? dequant4_14<1>(d, off, s2, g.nib_mask, magic) : dequant4_14<0>(d, off, s2, g.nib_mask, magic);
         }
       } else {
         iwv[0] = t.iw[0];

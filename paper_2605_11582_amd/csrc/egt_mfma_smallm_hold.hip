@@ -41,7 +41,7 @@ struct SmallMHoldGeom {
   int vec_store;
   uint32_t val_bytes, idx_bytes, qp_bytes, x_bytes;
   int64_t ldx, ldy;
-  uint32_t nib_mask, nib_magic, m8, m4, m2;
+  uint32_t nib_mask, nib_magic, m4, m2;
   int nw;              // waves: streams * nsteps
   int streams, stream_shift, step_inv;      // wave = stream * nsteps + step; ceil(65536 / nsteps)
   int sets, sets_more; // sets of a workgroup of tiles_q and of one of tiles_q + 1 row tiles
@@ -209,22 +209,16 @@ __device__ __forceinline__ void smallm_hold_body(const SmallMBatch &b, const Sma
         for (int grp = 0; grp < NG; ++grp) acc[grp] = f4{0.f, 0.f, 0.f, 0.f};
         uint32_t sp[4];
         if constexpr (N1) {
-          sp[0] = spread_idx(iw0 & 0xFFFFu, g.m8, g.m4, g.m2); sp[1] = spread_idx(iw0 >> 16, g.m8, g.m4, g.m2);
-          sp[2] = spread_idx(iw1 & 0xFFFFu, g.m8, g.m4, g.m2); sp[3] = spread_idx(iw1 >> 16, g.m8, g.m4, g.m2);
+          sp[0] = spread_idx<0>(iw0, g.m4, g.m2); sp[1] = spread_idx<1>(iw0, g.m4, g.m2);
+          sp[2] = spread_idx<0>(iw1, g.m4, g.m2); sp[3] = spread_idx<1>(iw1, g.m4, g.m2);
         }
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           u4 av;
           int iword;
           if constexpr (N1) {
-            const uint32_t d = nib[m >> 1];
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-              const uint32_t t2 = __builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)(2 * (m & 1) + p) * 0x00010001u);
-              const uint32_t pair = pk_mul_f16(pk_sub_f16(and_or(t2, g.nib_mask, magic), off[m * QW / 8]), s2[m * QW / 8]);
-              av[2 * p] = pair & 0xFFFFu;
-              av[2 * p + 1] = pair >> 16;
-            }
+            const uint32_t d = nib[m >> 1], of = off[m * QW / 8], sc = s2[m * QW / 8];
+            av = m & 1 ? dequant4_14<1>(d, of, sc, g.nib_mask, magic) : dequant4_14<0>(d, of, sc, g.nib_mask, magic);
             iword = (int)sp[m >> 1];
           } else {
             av = dequant8(nib[m], off[m * QW / 4], s2[m * QW / 4], g.nib_mask, magic);
@@ -317,7 +311,7 @@ static bool hold_plan(const egt_2bitcsr &w, int64_t ldx, int64_t ldy, int M, int
   g.val_bytes = (uint32_t)(16 * chunks); g.idx_bytes = (uint32_t)(8 * chunks); g.qp_bytes = (uint32_t)qb; g.x_bytes = (uint32_t)xb;
   g.ldx = ldx; g.ldy = ldy;
   g.nib_mask = 0x00F0000Fu; g.nib_magic = 0x54006400u;
-  g.m8 = 0x00FF00FFu; g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
+  g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
   g.mtiles = (w.rows + 15) / 16;
   const int ntiles = g.mtiles * count;
   g.blocks = std::min(256, ntiles);

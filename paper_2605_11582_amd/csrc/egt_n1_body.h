@@ -17,7 +17,7 @@ struct M1N1Geom {
   int groups_per_row;
   uint32_t last_chunk;
   int part_offset;
-  uint32_t m8, m4, m2; // masks of spread_idx, passed in so that they live in registers
+  uint32_t m4, m2;     // masks of spread_idx, passed in so that they live in registers
   uint32_t nib_mask;   // 0x00F0000F
   uint32_t nib_magic;  // 0x54006400: FP16 {1024.0, 64.0}
   int wpp, wpp_inv;    // waves per phase in a workgroup, ceil(65536 / wpp)
@@ -172,19 +172,14 @@ __device__ __forceinline__ void k_sparse_m1_n1_body(const uint32_t *__restrict__
 #pragma unroll
   for (int t = 0; t < TPI; ++t) {
     f4 acc = {0.f, 0.f, 0.f, 0.f};
-    uint32_t s2[QW], off[QW];
+    uint32_t off[QW];
 #pragma unroll
-    for (int k = 0; k < QW; ++k) {
-      s2[k] = off[k] = 0;
-      if (KIND == EGT_VAL_INT4) {
-        s2[k] = __builtin_amdgcn_perm(qp[t][k], qp[t][k], 0x01000100u);                            // {s, s}
-        off[k] = pk_add_f16(__builtin_amdgcn_perm(qp[t][k], qp[t][k], 0x03020302u), g.nib_magic);  // {1024+z, 64+z}
-      }
-    }
+    for (int k = 0; k < QW; ++k)
+      off[k] = KIND == EGT_VAL_INT4 ? pk_add_f16(__builtin_amdgcn_perm(qp[t][k], qp[t][k], 0x03020302u), g.nib_magic) : 0u;  // {1024+z, 64+z}
     if constexpr (LIN) {
 #pragma unroll
       for (int k = 0; k < NI; ++k) {
-        const int iword = (int)spread_idx(iwl[t][k], g.m8, g.m4, g.m2);
+        const int iword = (int)spread_idx<0>(iwl[t][k], g.m4, g.m2);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const uint32_t v0 = nib[t][k][2 * e], v1 = nib[t][k][2 * e + 1];
@@ -198,22 +193,15 @@ __device__ __forceinline__ void k_sparse_m1_n1_body(const uint32_t *__restrict__
       s[t] = acc[0] + row_shl<1>(acc[1]) + row_shl<2>(acc[2]) + row_shl<3>(acc[3]);
       continue;
     }
-    const uint32_t sp[4] = {spread_idx(iw[t][0] & 0xFFFFu, g.m8, g.m4, g.m2), spread_idx(iw[t][0] >> 16, g.m8, g.m4, g.m2),
-                            spread_idx(iw[t][1] & 0xFFFFu, g.m8, g.m4, g.m2), spread_idx(iw[t][1] >> 16, g.m8, g.m4, g.m2)};
+    const uint32_t sp[4] = {spread_idx<0>(iw[t][0], g.m4, g.m2), spread_idx<1>(iw[t][0], g.m4, g.m2),
+                            spread_idx<0>(iw[t][1], g.m4, g.m2), spread_idx<1>(iw[t][1], g.m4, g.m2)};
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
       u4 a;
       if (KIND == EGT_VAL_INT4) {
         // slots 4 m .. 4 m + 3 = bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
-        const uint32_t d = nib[t][0][m >> 1];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          // the two slots of a byte are dequantised as a pair, then split into {w, 0} registers
-          const uint32_t t2 = __builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)(2 * (m & 1) + p) * 0x00010001u);
-          const uint32_t pair = pk_mul_f16(pk_sub_f16(and_or(t2, g.nib_mask, magic), off[m * QW / 8]), s2[m * QW / 8]);
-          a[2 * p] = pair & 0xFFFFu;
-          a[2 * p + 1] = pair >> 16;
-        }
+        const uint32_t d = nib[t][0][m >> 1], of = off[m * QW / 8], q = qp[t][m * QW / 8];
+        a = m & 1 ? dequant4_14<1>(d, of, q, g.nib_mask, magic) : dequant4_14<0>(d, of, q, g.nib_mask, magic);
       } else {
         // FP16 values: slots 4 m .. 4 m + 3 are two dwords of the lane's 64 B
         const uint32_t v0 = nib[t][m >> 1][2 * (m & 1)], v1 = nib[t][m >> 1][2 * (m & 1) + 1];
@@ -284,7 +272,7 @@ inline void n1_geometry(const egt_2bitcsr &w, bool lin, M1N1Geom &g, int &ni) {
     g.groups_per_row = w.cols / w.group_size;
   }
   g.last_chunk = (uint32_t)w.rows * (uint32_t)g.nchunks - 1u;
-  g.m8 = 0x00FF00FFu; g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
+  g.m4 = 0x0F0F0F0Fu; g.m2 = 0x33333333u;
   g.nib_mask = 0x00F0000Fu; g.nib_magic = 0x54006400u;
 }
 

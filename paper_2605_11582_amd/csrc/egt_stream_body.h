@@ -263,7 +263,7 @@ __device__ __forceinline__ void stream_item_s14(const StreamMatrix &m, uint8_t *
     }
   }
   const uint32_t magic = in_vgpr(nib_magic);
-  const uint32_t m8 = in_vgpr(0x00FF00FFu), m4 = in_vgpr(0x0F0F0F0Fu), m2 = in_vgpr(0x33333333u);
+  const uint32_t m4 = in_vgpr(0x0F0F0F0Fu), m2 = in_vgpr(0x33333333u);
   float *my_part = part + 4 * phase + (lane >> 4);                       // + 4 * phases * tile
   const bool writer = (lane == 0) | (lane == 20) | (lane == 40) | (lane == 60);
 
@@ -273,23 +273,14 @@ __device__ __forceinline__ void stream_item_s14(const StreamMatrix &m, uint8_t *
       if (j < n) {                                                        // uniform; the requests stay outside
         f4 acc = {0.f, 0.f, 0.f, 0.f};
         const uint32_t q = qp[d.v];
-        const uint32_t s2 = __builtin_amdgcn_perm(q, q, 0x01000100u);                           // {s, s}
         const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(q, q, 0x03020302u), nib_magic);   // {1024+z, 64+z}
-        const uint32_t sp[4] = {spread_idx(iw[d.v][0] & 0xFFFFu, m8, m4, m2), spread_idx(iw[d.v][0] >> 16, m8, m4, m2),
-                                spread_idx(iw[d.v][1] & 0xFFFFu, m8, m4, m2), spread_idx(iw[d.v][1] >> 16, m8, m4, m2)};
+        const uint32_t sp[4] = {spread_idx<0>(iw[d.v][0], m4, m2), spread_idx<1>(iw[d.v][0], m4, m2),
+                                spread_idx<0>(iw[d.v][1], m4, m2), spread_idx<1>(iw[d.v][1], m4, m2)};
 #pragma unroll
         for (int mm = 0; mm < 8; ++mm) {
-          // slots 4 mm .. 4 mm + 3 = bytes 2 (mm & 1), 2 (mm & 1) + 1 of dword mm >> 1: the two slots of a byte
-          // are dequantised as a pair, then split into {w, 0} registers
+          // slots 4 mm .. 4 mm + 3 = bytes 2 (mm & 1), 2 (mm & 1) + 1 of dword mm >> 1
           const uint32_t dw = nib[d.v][mm >> 1];
-          u4 a;
-#pragma unroll
-          for (int p = 0; p < 2; ++p) {
-            const uint32_t t2 = __builtin_amdgcn_perm(dw, dw, 0x0c000c00u + (uint32_t)(2 * (mm & 1) + p) * 0x00010001u);
-            const uint32_t pair = pk_mul_f16(pk_sub_f16(and_or(t2, nib_mask, magic), off), s2);
-            a[2 * p] = pair & 0xFFFFu;
-            a[2 * p + 1] = pair >> 16;
-          }
+          const u4 a = mm & 1 ? dequant4_14<1>(dw, off, q, nib_mask, magic) : dequant4_14<0>(dw, off, q, nib_mask, magic);
           const int iword = (int)sp[mm >> 1];
           if (mm & 1)
             acc = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h16, bx[mm]), acc, iword, 0, 1);
