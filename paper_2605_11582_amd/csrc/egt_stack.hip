@@ -156,14 +156,14 @@ namespace {
 bool plan_stream(const egt_gemv_item *items, const std::vector<ItemShape> &shapes, const std::vector<StackEntry> &block_entries,
                  int count, int nwaves, bool whatever_the_size, std::vector<StreamMatrix> &mats, std::vector<uint32_t> &first,
                  std::vector<StreamItem> &work, egt_stack_part &plan) {
-  std::vector<uint64_t> row_bytes_of;
+  std::vector<uint64_t> row_cost_of;
   std::vector<int> rpt_of;
   int force = -1, bpc = 0, item_kb = 4096;
   tune_pair("EGT_STREAM_TUNE", force, bpc);             // developer build: 1 = whatever the size; workgroups per compute unit
   { int unused = 0; tune_pair("EGT_STREAM_ITEM", item_kb, unused); }
   if (force == 0 || nwaves == 0) return false;
   item_kb = item_kb < 16 ? 16 : item_kb > 4096 ? 4096 : item_kb;
-  uint64_t total = 0;
+  uint64_t total = 0, cost = 0;
   int forms = 0;
   size_t x_bytes = 0, part_floats = 0;
   int xp = 0;
@@ -224,8 +224,11 @@ bool plan_stream(const egt_gemv_item *items, const std::vector<ItemShape> &shape
     if (cap < wpp * rpt) return false;
     m.item_rows = cap;
     rpt_of.push_back(rpt);
-    row_bytes_of.push_back(row_bytes);
+    // what a row costs: its bytes; at 1:4, where vector instructions bind, its tiles, the last of which may be partly filled
+    const uint64_t row_cost = e.form == FORM_S14 && m.mr_shift < 0 ? row_bytes * 64 * (uint64_t)m.phases / (uint64_t)m.nchunks : row_bytes;
+    row_cost_of.push_back(row_cost);
     total += (uint64_t)m.rows * row_bytes;
+    cost += (uint64_t)m.rows * row_cost;
     const size_t xb = 16 * (size_t)lds_pieces + 16 * (size_t)((lds_pieces + (1 << pad_shift) - 1) >> pad_shift);
     x_bytes = xb > x_bytes ? xb : x_bytes;
     const size_t pf = 4 * (size_t)m.phases * (size_t)(m.item_rows / rpt);
@@ -239,25 +242,26 @@ bool plan_stream(const egt_gemv_item *items, const std::vector<ItemShape> &shape
   if (xp > 8 || total == 0) return false;
   const size_t lds = x_bytes + sizeof(float) * part_floats;
   if (lds > 64 * 1024) return false;
-  // spans of equal byte count, one per workgroup, in table order: workgroup b streams the
-  // bytes [b, b + 1) * total / blocks of the concatenated matrices (cut at row boundaries)
+  // spans of equal cost, one per workgroup, in table order: workgroup b streams what lies in [b, b + 1) * cost / blocks of
+  // the concatenated matrices (cut at row boundaries).  (1:4: equal byte counts left the workgroups of rows that end in a
+  // partly filled tile to finish last, 77 matrices 118 us, now 112.)
   // Two to eight workgroups per compute unit, two of them resident at a time: spans of about
-  // 1.4 MB (x is staged once per item, so a span should hold many rows; shorter spans finish
-  // more evenly: the 3 GB stack takes 546 us with 512 spans, 530 with 1024, 520 with 2048).
+  // 0.9 MB (x is staged once per item, so a span should hold many rows; shorter spans finish
+  // more evenly: 1.9 GB of 2:4 and dense matrices take 318 us with 1280 spans, 314 with 1536, 308 with 2048).
   // below 72 MB one span per compute unit
   // (1:4: two at least - its workgroups have 8 waves, and one per compute unit would leave half the waves out)
-  if (bpc < 1) { bpc = (int)((total + (179ull << 20)) / (358ull << 20)); bpc = (total < (72ull << 20) && forms != 2) ? 1 : bpc < 2 ? 2 : bpc; }
+  if (bpc < 1) { bpc = (int)((total + (110ull << 20)) / (220ull << 20)); bpc = (total < (72ull << 20) && forms != 2) ? 1 : bpc < 2 ? 2 : bpc; }
   bpc = bpc < 1 ? 1 : bpc > 8 ? 8 : bpc;
   int blocks = DEVICE_CUS * bpc;
   first.assign(1, 0u);
-  uint64_t done = 0;                                   // bytes of the rows handed out so far
+  uint64_t done = 0;                                   // cost of the rows handed out so far
   for (int k = 0; k < count; ++k) {
     const StreamMatrix &m = mats[k];
-    const uint64_t rb = row_bytes_of[k];
+    const uint64_t rb = row_cost_of[k];
     int r = 0;
     while (r < m.rows) {
       const int b = (int)first.size() - 1;             // workgroup being filled
-      const uint64_t budget_end = (total * (uint64_t)(b + 1) + (uint64_t)blocks - 1) / (uint64_t)blocks;
+      const uint64_t budget_end = (cost * (uint64_t)(b + 1) + (uint64_t)blocks - 1) / (uint64_t)blocks;
       uint64_t room_rows = budget_end > done ? (budget_end - done + rb - 1) / rb : 0;
       if (room_rows == 0 && b + 1 < blocks) { first.push_back((uint32_t)work.size()); continue; }
       int n = m.rows - r;

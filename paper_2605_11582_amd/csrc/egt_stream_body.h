@@ -5,7 +5,7 @@
 // waits, computes, and leaves.  That is the right shape for a matrix of a few megabytes -
 // the whole matrix is on its way within a microsecond - but as a stream of short-lived
 // workgroups it leaves the memory system idle whenever a workgroup starts up or drains.
-// Here the planner cuts the concatenation of all matrices into spans of equal byte count, one
+// Here the planner cuts the concatenation of all matrices into spans of equal byte count (1:4: of equal tiles), one
 // per workgroup (eight per compute unit, two of them resident at a time: 24 waves, each with
 // its own requests in flight; spans this short also even out the finish), so a workgroup
 // streams one contiguous stretch of the table; a span is a short
@@ -164,7 +164,7 @@ __device__ __forceinline__ void stream_item_s24(const StreamMatrix &m, uint8_t *
   }
   const uint32_t magic = in_vgpr(nib_magic);
   float *my_part = part + 4 * phase + (lane >> 4);                       // + 4 * phases * row
-  const bool writer = (lane == 0) | (lane == 20) | (lane == 40) | (lane == 60);
+  const bool writer = (lane & 15) == 4 * (lane >> 4);           // (lanes 0, 20, 40, 60: one comparison; named one by one they became a tree of branches in every tile)
 
   for (int j0 = 0; j0 < n; j0 += DEPTH) {
     static_for<0, DEPTH>([&](auto d) {
@@ -223,6 +223,7 @@ __device__ __forceinline__ void stream_item_s14(const StreamMatrix &m, uint8_t *
   const __amdgpu_buffer_rsrc_t r_qp = stream_rsrc(m.qparams, m.qp_bytes);
   // lane part of the chunk number: the tile's 64 chunks in lane order, or chunk c_ld of the row
   const uint32_t l_chunk = multirow ? (uint32_t)cit : (uint32_t)c_ld;
+  const uint32_t tile_chunks = multirow ? 64u : (uint32_t)m.nchunks;      // from one tile's first chunk (its row's) to the next's
   const uint32_t l_qp = 4u * ((uint32_t)rsub * (uint32_t)m.groups_per_row + (uint32_t)(c_ld >> m.gshift));
   u4 nib[DEPTH];
   u2 iw[DEPTH];
@@ -230,7 +231,7 @@ __device__ __forceinline__ void stream_item_s14(const StreamMatrix &m, uint8_t *
   auto request = [&](int slot, int j) {
     const bool on = j < n;                                                // uniform
     const uint32_t tile = (uint32_t)((row0 >> rpt_shift) + wslot + (on ? j : 0) * wpp);
-    const uint32_t cu = multirow ? 64u * tile : tile * (uint32_t)m.nchunks;                 // first chunk of the tile / of its row
+    const uint32_t cu = tile * tile_chunks;
     // (a tile that reaches past the last row is cut off by the buffer resources: zeros)
     nib[slot] = __builtin_amdgcn_raw_buffer_load_b128(r_val, on ? 16u * l_chunk : STREAM_OFF_RANGE, 16u * cu, STREAM_NT);
     iw[slot] = __builtin_amdgcn_raw_buffer_load_b64(r_idx, on ? 8u * l_chunk : STREAM_OFF_RANGE, 8u * cu, STREAM_NT);
@@ -265,7 +266,7 @@ __device__ __forceinline__ void stream_item_s14(const StreamMatrix &m, uint8_t *
   const uint32_t magic = in_vgpr(nib_magic);
   const uint32_t m4 = in_vgpr(0x0F0F0F0Fu), m2 = in_vgpr(0x33333333u);
   float *my_part = part + 4 * phase + (lane >> 4);                       // + 4 * phases * tile
-  const bool writer = (lane == 0) | (lane == 20) | (lane == 40) | (lane == 60);
+  const bool writer = (lane & 15) == 4 * (lane >> 4);           // (lanes 0, 20, 40, 60: one comparison; named one by one they became a tree of branches in every tile)
 
   for (int j0 = 0; j0 < n; j0 += DEPTH) {
     static_for<0, DEPTH>([&](auto d) {
@@ -354,7 +355,7 @@ __device__ __forceinline__ void stream_item_dense(const StreamMatrix &m, uint8_t
   const float xq = xsum[0];
   const uint32_t magic = in_vgpr(nib_magic);
   float *my_part = part + 4 * phase + (lane >> 4);
-  const bool writer = (lane == 0) | (lane == 20) | (lane == 40) | (lane == 60);
+  const bool writer = (lane & 15) == 4 * (lane >> 4);           // (lanes 0, 20, 40, 60: one comparison; named one by one they became a tree of branches in every tile)
 
   for (int j0 = 0; j0 < n; j0 += DEPTH) {
     static_for<0, DEPTH>([&](auto d) {
