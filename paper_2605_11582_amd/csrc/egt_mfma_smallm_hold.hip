@@ -13,7 +13,10 @@
 // sums of one set of tiles are added up and stored while the next set is multiplied.
 //
 // What bounds it: the start (a launch, X and the first tiles from memory, 3 to 4 us) for a few
-// tiles per workgroup, the memory beyond (65536 x 4096 at 5 tokens: 24.7 us, 4.5 TB/s).
+// tiles per workgroup, instructions and the memory beyond (65536 x 4096 at 5 tokens: 22.0 us, 5.1 TB/s).
+// A wave adds up a whole tile of a set, four rows of a token a lane; an output per lane took four times the
+// reads, compares and selects: 65536 x 4096 at 5 tokens 23.7, 22.0; 11008 x 4096 at 16 7.06, 6.70; 20000 x 1024
+// at 8 5.5, 5.1; 11008 x 2048 at 32 7.1, 6.6 (with one address per lane for all tiles; 1:4 alike or up to 8 % less).
 // Before and now, in microseconds: 4096 x 4096 at 5 tokens 5.0, 3.9; 22016 x 4096 at 16 tokens 14.2,
 // 11.8; 65536 x 4096 39.5, 26.4; 20000 x 1024 at 8 tokens 8.6, 5.2; two 1:4 matrices of 11008 x
 // 4096 under one X 13.7, 11.8.
@@ -127,31 +130,33 @@ __device__ __forceinline__ void smallm_hold_body(const SmallMBatch &b, const Sma
 
   const bool chunk_on = 4 * step + lc < g.nchunks;
   const uint32_t c_lane = (uint32_t)li * (uint32_t)g.nchunks + (uint32_t)(4 * step + lc);
-  const uint32_t q_lane = 4u * ((uint32_t)li * (uint32_t)g.groups_per_row +
-                                (QW > 1 ? (uint32_t)QW * (uint32_t)(4 * step + lc) : (uint32_t)((4 * step + lc) >> g.gshift)));
+  const uint32_t q_lane = (uint32_t)li * (uint32_t)g.groups_per_row +
+                          (QW > 1 ? (uint32_t)QW * (uint32_t)(4 * step + lc) : (uint32_t)((4 * step + lc) >> g.gshift));
+  const uint32_t at_val = chunk_on ? 16u * c_lane : OUT, at_idx = chunk_on ? 8u * c_lane : OUT, at_qp = chunk_on ? 4u * q_lane : OUT;
+  // A tile's buffers begin at its first row and end with the matrix, so that rows past the last one lie past the
+  // buffer: one address per lane for all tiles.  (With a test per lane and request the compiler made two requests
+  // under opposite masks of each.)
   auto load = [&](Tile &t, int k) {
     const bool have = k < mytiles;                    // uniform
     int v = have ? (int)blockIdx.x + k * g.blocks : 0;
     if constexpr (JOINT) asm volatile("" : "+s"(v));  // (the member's resources are worked out per request: kept, they would spill)
     const unsigned m = (unsigned)member(v);
-    const __amdgpu_buffer_rsrc_t r_val = make_rsrc(JOINT ? pick4(b.values, m) : b.values[0], g.val_bytes);
-    const __amdgpu_buffer_rsrc_t r_idx = make_rsrc(JOINT ? pick4(b.idx, m) : b.idx[0], g.idx_bytes);
-    const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(JOINT ? pick4(b.qparams, m) : b.qparams[0], g.qp_bytes);
-    const bool on = chunk_on && have && li < g.rows - 16 * v;
-    const uint32_t cu = have ? (uint32_t)(16 * v) * (uint32_t)g.nchunks : 0u;
-    t.iw = __builtin_amdgcn_raw_buffer_load_b64(r_idx, on ? 8u * c_lane : OUT, 8u * cu, 0);
-    t.nib = __builtin_amdgcn_raw_buffer_load_b128(r_val, on ? 16u * c_lane : OUT, 16u * cu, 0);
-    const uint32_t qu = have ? 4u * (uint32_t)(16 * v) * (uint32_t)g.groups_per_row : 0u;
+    const uint32_t cu = (uint32_t)(16 * v) * (uint32_t)g.nchunks, qu = 4u * (uint32_t)(16 * v) * (uint32_t)g.groups_per_row;
+    const __amdgpu_buffer_rsrc_t r_val = make_rsrc((JOINT ? pick4(b.values, m) : b.values[0]) + 16u * cu, have ? g.val_bytes - 16u * cu : 0u);
+    const __amdgpu_buffer_rsrc_t r_idx = make_rsrc((JOINT ? pick4(b.idx, m) : b.idx[0]) + 8u * cu, have ? g.idx_bytes - 8u * cu : 0u);
+    const __amdgpu_buffer_rsrc_t r_qp = make_rsrc((JOINT ? pick4(b.qparams, m) : b.qparams[0]) + qu, have ? g.qp_bytes - qu : 0u);
+    t.iw = __builtin_amdgcn_raw_buffer_load_b64(r_idx, at_idx, 0, 0);
+    t.nib = __builtin_amdgcn_raw_buffer_load_b128(r_val, at_val, 0, 0);
     if constexpr (QW == 4) {
-      const u4 q = __builtin_amdgcn_raw_buffer_load_b128(r_qp, on ? q_lane : OUT, qu, 0);
+      const u4 q = __builtin_amdgcn_raw_buffer_load_b128(r_qp, at_qp, 0, 0);
 #pragma unroll
       for (int j = 0; j < QW; ++j) t.qp[j] = q[j];
     } else if constexpr (QW == 2) {
-      const u2 q = __builtin_amdgcn_raw_buffer_load_b64(r_qp, on ? q_lane : OUT, qu, 0);
+      const u2 q = __builtin_amdgcn_raw_buffer_load_b64(r_qp, at_qp, 0, 0);
 #pragma unroll
       for (int j = 0; j < QW; ++j) t.qp[j] = q[j];
     } else {
-      t.qp[0] = __builtin_amdgcn_raw_buffer_load_b32(r_qp, on ? q_lane : OUT, qu, 0);
+      t.qp[0] = __builtin_amdgcn_raw_buffer_load_b32(r_qp, at_qp, 0, 0);
     }
   };
   Tile ring[RING];
@@ -237,42 +242,50 @@ __device__ __forceinline__ void smallm_hold_body(const SmallMBatch &b, const Sma
           *(f4 *)(mine + (slot0 + u * NG + grp) * g.slot_stride + 16 * lane) = acc[grp];
       }
     }
-    {
+    if (64 * wave < 16 * RING * S) {                  // uniform
       int k;
       const int r = flag_row(set, k);
       if ((int)threadIdx.x < 16 * RING * S) flags[(set & 1) * 16 * RING * S + (int)threadIdx.x] = (r < g.rows && rp == (uint32_t)r * S_row) ? 1u : 0u;
       if constexpr (!LAST) rp = load_rp(set + 1);
     }
     lds_barrier();
-    // ---- outputs of the set: float 4 l + v of a tile's kilobyte is D[row 4 (l >> 4) + v][token l & 15]
-    for (int e = (int)threadIdx.x; e < RING * S * NG * 256; e += 64 * nw) {
-      const int tg = __builtin_amdgcn_readfirstlane(e >> 8), ts = tg / NG, grp = tg % NG;    // tile of the set, token group
+    // ---- outputs of the set: a wave takes a tile's kilobyte, four rows of a token a lane: float 4 l + v of it is
+    // D[row 4 (l >> 4) + v][token l & 15].  The waves take turns from set to set.
+    int first = wave - (set * RING * S * NG) % nw;
+    first += first < 0 ? nw : 0;
+    for (int tg = first; tg < RING * S * NG; tg += nw) {
+      const int ts = tg / NG, grp = tg % NG;          // tile of the set, token group
       const int t = set * RING * S + ts;
-      if (t >= mytiles) break;                        // (uniform; later e are later tiles)
+      if (t >= mytiles) break;                        // (later tg are later tiles)
       const int u = ONE ? ts : ts >> g.stream_shift, str = ONE ? 0 : ts & (S - 1);
-      const uint8_t *src = xs + str * g.nsteps * g.wave_stride + (slot0 + u * NG + grp) * g.slot_stride + 4 * (e & 255);
-      // (eight requested before the first is added; in ascending order of the K-steps)
-      float sum = 0.f;
-      for (int st0 = 0; st0 < g.nsteps; st0 += 8) {
-        float part[8];
+      const uint8_t *src = xs + str * g.nsteps * g.wave_stride + (slot0 + u * NG + grp) * g.slot_stride + 16 * lane;
+      const u4 ok = *(const u4 *)(flags + (set & 1) * 16 * RING * S + 16 * ts + 4 * (lane >> 4));
+      // (several requested before the first is added, fewer where B, still needed, leaves few registers; in ascending order of the K-steps)
+      constexpr int PARTS = LAST ? 8 : N1 ? 2 : NG > 1 ? 4 : 8;
+      f4 sum = f4{0.f, 0.f, 0.f, 0.f};
+      int st = 0;
+      for (; st + PARTS <= g.nsteps; st += PARTS) {
+        f4 part[PARTS];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) part[q] = *(const float *)(src + min(st0 + q, g.nsteps - 1) * g.wave_stride);
+        for (int q = 0; q < PARTS; ++q) part[q] = *(const f4 *)(src + (st + q) * g.wave_stride);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sum += st0 + q < g.nsteps ? part[q] : 0.f;
+        for (int q = 0; q < PARTS; ++q) sum += part[q];
       }
+      for (; st < g.nsteps; ++st) sum += *(const f4 *)(src + st * g.wave_stride);
       int v = (int)blockIdx.x + t * g.blocks;
       const int k = member(v);
-      const int rr = e & 3, sl = (e >> 2) & 63;
-      const int row0 = 16 * v + 4 * (sl >> 4), row = row0 + rr, tok = 16 * grp + (sl & 15);
-      uint32_t hv = 0x7E00u;
-      if (flags[(set & 1) * 16 * RING * S + 16 * ts + 4 * (sl >> 4) + rr]) hv = __half_as_ushort(__float2half(sum));
-      const uint32_t h1 = quad_bcast<1>(hv), h2 = quad_bcast<2>(hv), h3 = quad_bcast<3>(hv);
+      const int row0 = 16 * v + 4 * (lane >> 4), tok = 16 * grp + (lane & 15);
+      uint32_t hv[4];
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) hv[rr] = ok[rr] ? __half_as_ushort(__float2half(sum[rr])) : 0x7E00u;
       if (tok < g.M) {
-        __half *dst = (JOINT ? pick4(b.Y, (unsigned)k) : b.Y[0]) + (int64_t)tok * g.ldy + row;
+        __half *dst = (JOINT ? pick4(b.Y, (unsigned)k) : b.Y[0]) + (int64_t)tok * g.ldy + row0;
         if (g.vec_store && row0 + 3 < g.rows) {
-          if (rr == 0) *(u2 *)dst = u2{hv | (h1 << 16), h2 | (h3 << 16)};
-        } else if (row < g.rows) {
-          *dst = __ushort_as_half((uint16_t)hv);
+          *(u2 *)dst = u2{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16)};
+        } else {
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+            if (row0 + rr < g.rows) dst[rr] = __ushort_as_half((uint16_t)hv[rr]);
         }
       }
     }
