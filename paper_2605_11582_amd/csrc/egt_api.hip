@@ -292,7 +292,7 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
   out.M = M;
   out.n_keep = n_keep;
   out.grid_x = (int32_t)nwg;
-  egt::smallm_stack_shape(M, n_keep, out.block_threads, out.lds_bytes);
+  egt::smallm_stack_shape(M, n_keep, out.grid_x, out.block_threads, out.lds_bytes);
   out.table_bytes = gemm_table_bytes(count, out.grid_x);
   if (table) {
     if ((uint64_t)table_bytes < out.table_bytes) return EGT_ERR_SHAPE;
@@ -322,7 +322,7 @@ egt_status egt_gemm_stack_run(const void *table_dev, const egt_gemm_plan *plan, 
       (plan->n_keep == 1 && plan->M > 32))
     return EGT_ERR_SHAPE;
   int threads, lds;
-  egt::smallm_stack_shape(plan->M, plan->n_keep, threads, lds);
+  egt::smallm_stack_shape(plan->M, plan->n_keep, plan->grid_x, threads, lds);
   if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || plan->block_threads != threads || plan->lds_bytes != lds ||
       plan->table_bytes != gemm_table_bytes(plan->count, plan->grid_x))
     return EGT_ERR_SHAPE;

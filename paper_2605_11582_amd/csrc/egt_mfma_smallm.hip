@@ -959,7 +959,14 @@ static_assert(sizeof(SmallMStackEntry) <= EGT_STACK_ENTRY_BYTES, "descriptor lar
 // More than 16 tokens: NG token groups of 16.  The token rows of all groups are staged per
 // round, the operands of a K-step are dequantised once and serve every group (NG sums per
 // wave), and a round is two K-steps, so that the regions still fit: up to 32 tokens two
-// groups and 8 waves (two workgroups per compute unit), beyond four groups and 16 waves.
+// groups and 8 waves (two workgroups per compute unit), beyond four groups and 16 row tiles.
+// There (and for 1:4 beyond 16 tokens) one workgroup fills the LDS of a compute unit, and what binds is the
+// reads of B from it, 8 KB a K-step, token group and row tile (1:4 16 KB) beside 1.7 KB of weights.  So 8 waves
+// with twice the registers own two tiles each (T), and an operand read from LDS serves both.  us with 16 waves and one
+// tile each, with 8 and two: 16 layers of a 7B stack at 64 tokens 576, 544; eleven 1:4 layers at 32 249, 226; four 1:4 layers of
+// 1024 x 3072 at 17 20.1, 17.2.  Not at fewer tokens, where two workgroups share a compute unit and operands are
+// not what binds (two tiles a wave there: 16 tokens 341, 353; 1:4 166, 167;
+// 32 tokens 423, 431).
 #ifndef EGT_RS_WAVES
 #define EGT_RS_WAVES 8
 #endif
@@ -974,8 +981,9 @@ constexpr int rs_step_bytes(bool n1) { return n1 ? 16 * KS_TOKEN_N1 : 8 * KS_PAI
 constexpr int rs_lds_bytes(int ng, int q, bool n1 = false) { return RS_BUFS * ng * q * rs_step_bytes(n1); }
 
 // N1: 1:4 sparsity (chunks of 128 columns, eight instructions a K-step, a request of X per token).
-template <int NG, int Q, int W, bool N1 = false>
-__global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__restrict__ table, int count) {
+// T: row tiles of a wave.
+template <int NG, int Q, int W, bool N1, int T>
+__device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ table, int count) {
   constexpr int RS_WAVES = W, RS_Q = Q, RS_STEP = rs_step_bytes(N1), RS_REGION = NG * Q * RS_STEP;
   constexpr int XREQ = N1 ? 16 : 8;                   // requests of X per K-step and token group
   constexpr int NM = N1 ? 8 : 4;                      // matrix instructions per K-step
@@ -999,16 +1007,16 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, kb = lane >> 4;            // operand form: row i of the tile, chunk kb of the step
-  // this wave's row tile (a wave past the last tile has none, but still stages its share of X
+  // this wave's row tiles (a wave past the last tile has none, but still stages its share of X
   // and meets the barriers)
-  const int tile = wg * RS_WAVES + wave;
-  const bool has_tile = tile < g.ntiles;
+  const int tile0 = T * (wg * RS_WAVES + wave);
+  const int ntiles = min(max(g.ntiles - tile0, 0), T);                      // uniform
   const int nsteps = g.nsteps, nrounds = (nsteps + RS_Q - 1) / RS_Q;
   const uint32_t magic = in_vgpr(g.nib_magic);
   const uint32_t S_row = (uint32_t)g.nchunks * 32u;
   // row pointers first, checked at the end: a row whose pointer is not r * S yields NaN
-  const int frow = 16 * tile + lane;
-  const bool fchecked = has_tile && lane < 16 && frow < g.rows;
+  const int frow = 16 * tile0 + lane;
+  const bool fchecked = lane < 16 * ntiles && frow < g.rows;
   const uint32_t frp = fchecked ? row_ptr[frow] : 0u;
 
   const __amdgpu_buffer_rsrc_t r_val = make_rsrc((const uint8_t *)(g_u8)e->values, g.val_bytes);
@@ -1028,8 +1036,9 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
   // (rows 4 to 7 of a request keep their chunks in the other order of halves - lane (r, c) fetches chunk c ^ (r & 4):
   //  the lanes that a lane permutation reads for rows r and r + 4 then lie in different LDS banks)
   const int r8 = lane >> 3, c8 = (lane & 7) ^ ((lane >> 3) & 4);
-  auto load_half = [&](RoundRegs &a, int round, int p) {   // the requests (0, p) and (1, p): 2 * LPT of them
-    const bool on = has_tile && RS_Q * round + 2 * p < nsteps;                // uniform
+  auto load_half = [&](RoundRegs &a, int round, int p, int t) {   // the requests (0, p) and (1, p) of tile t: 2 * LPT of them
+    const int tile = tile0 + t;
+    const bool on = t < ntiles && RS_Q * round + 2 * p < nsteps;              // uniform
     const int c0 = 4 * RS_Q * round + 8 * p;                                  // first chunk of the request
     const uint32_t lcc = (uint32_t)min((int)in_vgpr((uint32_t)c8), g.nchunks - 1 - c0);       // chunk inside the request (clamped)
 #pragma unroll
@@ -1109,25 +1118,31 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
     return u8v{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   };
 
-  f4 acc[NG];
+  f4 acc[T][NG];
 #pragma unroll
-  for (int grp = 0; grp < NG; ++grp) acc[grp] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int grp = 0; grp < NG; ++grp) acc[t][grp] = f4{0.f, 0.f, 0.f, 0.f};
   // The A tiles are requested two rounds ahead (two sets of fetch registers), X one round
   // ahead.  Requests in a round, in this order: X(j + 1), then A(j + 2) - so that at the top
-  // of round j the requests still allowed to be pending are exactly the RS_Q * LPT of A(j + 1).
+  // of round j the requests still allowed to be pending are exactly the T * RS_Q * LPT of A(j + 1).
   // The barrier is issued with its own wait counts: a fence would wait for every pending
   // request, the LDS-bound ones of X among them, and give the depth away.
-  RoundRegs raw0, raw1;
+  RoundRegs raw0[T], raw1[T];
+  auto load_pair = [&](RoundRegs (&a)[T], int round, int p) {
 #pragma unroll
-  for (int p = 0; p < RS_Q / 2; ++p) load_half(raw0, 0, p);
+    for (int t = 0; t < T; ++t) load_half(a[t], round, p, t);
+  };
+#pragma unroll
+  for (int p = 0; p < RS_Q / 2; ++p) load_pair(raw0, 0, p);
   dma_x(0, 0);
   if (nrounds > 1) {
 #pragma unroll
-    for (int p = 0; p < RS_Q / 2; ++p) load_half(raw1, 1, p);
+    for (int p = 0; p < RS_Q / 2; ++p) load_pair(raw1, 1, p);
   }
   int buf = 0;                                        // region of round j: j % 2
-  auto round = [&](RoundRegs &cur, int j) {
-    if (j + 1 < nrounds) wait_vmem<RS_Q * LPT>(); else wait_vmem<0>();   // A(j) and this wave's share of X(j) have arrived
+  auto round = [&](RoundRegs (&cur)[T], int j) {
+    if (j + 1 < nrounds) wait_vmem<T * RS_Q * LPT>(); else wait_vmem<0>();   // A(j) and this wave's share of X(j) have arrived
     zero_tail(j, buf);
     // X(j) of every wave has landed; nobody reads the region of round j - 1 any more
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -1136,36 +1151,41 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
     for (int q = 0; q < RS_Q; ++q) {
       // (a step past K, a wave without a tile: requested out of range, zeros with scale 0)
       const int step = RS_Q * j + q;
-      Tile t;
-      to_operand(cur, q, t);
+      Tile tiles[T];
+#pragma unroll
+      for (int k = 0; k < T; ++k) to_operand(cur[k], q, tiles[k]);
       // (both K-steps of a pair of requests consumed: their fetch registers are free again)
       if ((q & 1) && j + 2 < nrounds) {
         wait_lds();
-        load_half(cur, j + 2, q >> 1);
+        load_pair(cur, j + 2, q >> 1);
       }
       const bool live = 4 * step + kb < g.nchunks;    // false: a chunk past the end of K
-      const uint32_t s2 = live ? __builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x01000100u) : 0u;
-      const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x03020302u), g.nib_magic);
       // the operands of the step's instructions serve every token group
-      u4 av[NM];
-      uint32_t iwv[NM / 2];
-      if constexpr (N1) {
-        // every slot becomes the pair {value, 0} with its offset in the even index field; instruction m takes
-        // slots 4 m .. 4 m + 3 of the chunk: bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
-        iwv[0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
-        iwv[1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
-        iwv[2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
-        iwv[3] = spread_idx<1>(t.iw[1], g.m4, g.m2);
+      u4 av[T][NM];
+      uint32_t iwv[T][NM / 2];
 #pragma unroll
-        for (int m = 0; m < NM; ++m) {
-          const uint32_t d = t.nib[0][m >> 1];
-          av[m] = m & 1 ? dequant4_14<1>(d, off, s2, g.nib_mask, magic) : dequant4_14<0>(d, off, s2, g.nib_mask, magic);
+      for (int k = 0; k < T; ++k) {
+        const Tile &t = tiles[k];
+        const uint32_t s2 = live ? __builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x01000100u) : 0u;
+        const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x03020302u), g.nib_magic);
+        if constexpr (N1) {
+          // every slot becomes the pair {value, 0} with its offset in the even index field; instruction m takes
+          // slots 4 m .. 4 m + 3 of the chunk: bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
+          iwv[k][0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
+          iwv[k][1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
+          iwv[k][2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
+          iwv[k][3] = spread_idx<1>(t.iw[1], g.m4, g.m2);
+#pragma unroll
+          for (int m = 0; m < NM; ++m) {
+            const uint32_t d = t.nib[0][m >> 1];
+            av[k][m] = m & 1 ? dequant4_14<1>(d, off, s2, g.nib_mask, magic) : dequant4_14<0>(d, off, s2, g.nib_mask, magic);
+          }
+        } else {
+          iwv[k][0] = t.iw[0];
+          iwv[k][1] = t.iw[1];
+#pragma unroll
+          for (int m = 0; m < NM; ++m) av[k][m] = dequant8(t.nib[0][m], off, s2, g.nib_mask, magic);
         }
-      } else {
-        iwv[0] = t.iw[0];
-        iwv[1] = t.iw[1];
-#pragma unroll
-        for (int m = 0; m < NM; ++m) av[m] = dequant8(t.nib[0][m], off, s2, g.nib_mask, magic);
       }
 #pragma unroll
       for (int grp = 0; grp < NG; ++grp) {
@@ -1174,11 +1194,15 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           const u8v bx = read_b(bregion, m);          // (read per instruction: 8 registers of B at a time)
-          const int iword = (int)iwv[m >> 1];
-          if (m & 1)
-            acc[grp] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[m]), __builtin_bit_cast(h16, bx), acc[grp], iword, 0, 1);
-          else
-            acc[grp] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[m]), __builtin_bit_cast(h16, bx), acc[grp], iword, 0, 0);
+#pragma unroll
+          for (int k = 0; k < T; ++k) {
+            const int iword = (int)iwv[k][m >> 1];
+            f4 &sum = acc[k][grp];
+            if (m & 1)
+              sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[k][m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 1);
+            else
+              sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[k][m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 0);
+          }
         }
       }
     }
@@ -1190,25 +1214,38 @@ __global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__rest
   }
   // register v of lane l = D[row 4 (l >> 4) + v][token l & 15]: four consecutive rows of one token
   const uint64_t good = __builtin_amdgcn_ballot_w64(fchecked && frp == (uint32_t)frow * S_row);
-  if (!has_tile) return;
-  const int row0 = 16 * tile + 4 * (lane >> 4);
 #pragma unroll
-  for (int grp = 0; grp < NG; ++grp) {
-    const int tok = 16 * grp + (lane & 15);
-    if (tok >= g.M) continue;
-    uint32_t hv[4];
+  for (int t = 0; t < T; ++t) {
+    if (t >= ntiles) return;
+    const int row0 = 16 * (tile0 + t) + 4 * (lane >> 4);
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      hv[v] = ((good >> (4 * (lane >> 4) + v)) & 1) ? (uint32_t)__half_as_ushort(__float2half(acc[grp][v])) : 0x7E00u;
-    __half *dst = Y + (int64_t)tok * g.ldy + row0;
-    if (g.vec_store && row0 + 3 < g.rows) {
-      *(u2 *)dst = u2{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16)};
-    } else {
+    for (int grp = 0; grp < NG; ++grp) {
+      const int tok = 16 * grp + (lane & 15);
+      if (tok >= g.M) continue;
+      uint32_t hv[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (row0 + v < g.rows) dst[v] = __ushort_as_half((uint16_t)hv[v]);
+        hv[v] = ((good >> (16 * t + 4 * (lane >> 4) + v)) & 1) ? (uint32_t)__half_as_ushort(__float2half(acc[t][grp][v])) : 0x7E00u;
+      __half *dst = Y + (int64_t)tok * g.ldy + row0;
+      if (g.vec_store && row0 + 3 < g.rows) {
+        *(u2 *)dst = u2{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16)};
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (row0 + v < g.rows) dst[v] = __ushort_as_half((uint16_t)hv[v]);
+      }
     }
   }
+}
+
+template <int NG, int Q, int W, bool N1 = false>
+__global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__restrict__ table, int count) {
+  smallm_rows_body<NG, Q, W, N1, 1>(table, count);
+}
+// two row tiles a wave
+template <int NG, int Q, int W, bool N1 = false>
+__global__ __launch_bounds__(64 * W, 2) void k_smallm_rows_two(const uint8_t *__restrict__ table, int count) {
+  smallm_rows_body<NG, Q, W, N1, 2>(table, count);
 }
 
 // Shapes the stack takes: INT4 with one {scale, zero} pair per chunk, 2:4 (up to 64 tokens) or 1:4 (up to 32: the
@@ -1219,17 +1256,21 @@ bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
   return sparse_smallm_supported(w, w.cols, M);
 }
 
-static int stack_waves(int M, bool n1) { return M <= (n1 ? 16 : 32) ? RS_WAVES : 16; }
+// Waves of a workgroup that owns sixteen row tiles: sixteen, or eight with two tiles each (see k_smallm_rows).
+// Tables of fewer than 128 workgroups leave half of the compute units idle in either form and keep the first.
+static bool stack_two_tiles(int grid_x) { return grid_x >= 128; }
+static bool stack_sixteen(int M, bool n1) { return M > (n1 ? 16 : 32); }
 
-// workgroups of a matrix: one per row tile and wave
+// workgroups of a matrix
 int smallm_stack_blocks(int M, int n_keep, int rows) {
-  const int ntiles = (rows + 15) / 16, w = stack_waves(M, n_keep == 1);
-  return (ntiles + w - 1) / w;
+  const int ntiles = (rows + 15) / 16, per = stack_sixteen(M, n_keep == 1) ? 16 : RS_WAVES;
+  return (ntiles + per - 1) / per;
 }
 
-void smallm_stack_shape(int M, int n_keep, int &block_threads, int &lds_bytes) {
+// Launch shape of a table of grid_x workgroups.
+void smallm_stack_shape(int M, int n_keep, int grid_x, int &block_threads, int &lds_bytes) {
   const bool n1 = n_keep == 1;
-  block_threads = 64 * stack_waves(M, n1);
+  block_threads = 64 * (stack_sixteen(M, n1) ? (stack_two_tiles(grid_x) ? 8 : 16) : RS_WAVES);
   if (n1) lds_bytes = rs_lds_bytes(M <= 16 ? 1 : 2, 2, true);
   else lds_bytes = M <= 16 ? rs_lds_bytes(1, RS_Q) : M <= 32 ? rs_lds_bytes(2, 2) : rs_lds_bytes(4, 2);
 }
@@ -1248,16 +1289,16 @@ void smallm_stack_entry(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, in
 
 hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, hipStream_t stream) {
   int threads, lds;
-  smallm_stack_shape(M, n_keep, threads, lds);
+  smallm_stack_shape(M, n_keep, grid_x, threads, lds);
   const dim3 grid(grid_x), block(threads);
   const uint8_t *t = (const uint8_t *)table_dev;
-  if (n_keep == 1) {
-    if (M <= 16) return launch(k_smallm_rows<1, 2, RS_WAVES, true>, grid, block, (size_t)lds, stream, t, count);
-    return launch(k_smallm_rows<2, 2, 16, true>, grid, block, (size_t)lds, stream, t, count);
-  }
-  if (M <= 16) return launch(k_smallm_rows<1, RS_Q, RS_WAVES>, grid, block, (size_t)lds, stream, t, count);
-  if (M <= 32) return launch(k_smallm_rows<2, 2, RS_WAVES>, grid, block, (size_t)lds, stream, t, count);
-  return launch(k_smallm_rows<4, 2, 16>, grid, block, (size_t)lds, stream, t, count);
+#define EGT_RS(...) launch(k_smallm_rows<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
+#define EGT_RS2(...) launch(k_smallm_rows_two<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
+  const bool two = stack_two_tiles(grid_x);
+  if (n_keep == 1) return M <= 16 ? EGT_RS(1, 2, RS_WAVES, true) : two ? EGT_RS2(2, 2, 8, true) : EGT_RS(2, 2, 16, true);
+  return M <= 16 ? EGT_RS(1, RS_Q, RS_WAVES) : M <= 32 ? EGT_RS(2, 2, RS_WAVES) : two ? EGT_RS2(4, 2, 8) : EGT_RS(4, 2, 16);
+#undef EGT_RS2
+#undef EGT_RS
 }
 
 // `count` (2..4) identically shaped members in one launch (the caller has checked the shapes

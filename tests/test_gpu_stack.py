@@ -543,6 +543,44 @@ def test_gemm_stack_equals_the_oracle_and_the_separate_products(M, n):
         assert np.array_equal(Y2[k].cpu().numpy().view(np.uint16), first[k].view(np.uint16)), ("other table differs", k)
 
 
+@pytest.mark.parametrize("M,n", [(33, 2), (50, 2), (64, 2), (17, 1), (32, 1)])
+def test_gemm_stack_of_many_workgroups_has_the_bits_of_small_tables(M, n):
+    # from 128 workgroups on a wave takes two row tiles: last workgroups with an odd tile, a ragged tile and waves without
+    # one, row lengths that end inside a K-step and inside a round, matrices with rows of the same length (whose
+    # workgroups are dealt to the XCDs) and an empty one; the sums are those of a table of each matrix alone
+    torch = G.torch_mod()
+    print(f"case gemm stack many workgroups M={M} n={n}", flush=True)
+    c = 128 // n
+    shapes = [(16384, 5 * c), (16 * 1001 + 5, 8 * c), (0, 8 * c), (40, 5 * c), (16 * 17, 17 * c), (15, 33 * c), (2000, 8 * c)]
+    ps, Xd = [], []
+    for k, (rows, cols) in enumerate(shapes):
+        w = synth.weights(rows, cols, 8950 + k)
+        ps.append(B.pack_2bitcsr(w, B.prune_n4(w, n), n, c, B.VAL_INT4))
+        Xd.append(G.to_dev(synth.activation_rows(M, cols, 8950 + k).view(np.uint16)).view(torch.float16))
+    ps[6].row_ptr[1203] += 8                          # NaN for every token, in either form
+    pds = [p.to("cuda:0") for p in ps]
+    ybufs = [torch.full((128 + M * p.rows,), G.CANARY, dtype=torch.int16, device="cuda:0") for p in ps]
+    Yd = [yb[64:64 + M * p.rows].view(torch.float16).view(M, p.rows) for yb, p in zip(ybufs, ps)]
+    call = B.prepared_gemm_stack(list(zip(pds, Xd, Yd)))
+    assert call.plan.grid_x >= 128 and call.plan.block_threads == 512
+    call()
+    torch.cuda.synchronize()
+    for k, p in enumerate(ps):
+        host = ybufs[k].cpu().numpy().view(np.uint16)
+        assert np.all(host[:64] == G.CANARY) and np.all(host[64 + M * p.rows:] == G.CANARY), ("write outside Y", k)
+        if p.rows == 0:
+            continue
+        alone = torch.zeros((M, p.rows), dtype=torch.float16, device="cuda:0")
+        one = B.prepared_gemm_stack([(pds[k], Xd[k], alone)])
+        assert one.plan.grid_x <= 64 and one.plan.block_threads == 1024
+        one()
+        torch.cuda.synchronize()
+        Y, want = host[64:64 + M * p.rows].reshape(M, p.rows), alone.cpu().numpy().view(np.uint16)
+        nan = np.zeros(p.rows, dtype=bool)
+        nan[[1203] if k == 6 else []] = True
+        assert np.array_equal(Y[:, ~nan], want[:, ~nan]) and np.all(np.isnan(Y.view(np.float16)) == nan), ("member", k)
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_gemm_stack_seeded_sweep_of_shapes(seed):
     # seeded tables: row counts around the tile and workgroup sizes, row lengths that end anywhere inside a K-step or
