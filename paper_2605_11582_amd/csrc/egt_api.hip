@@ -304,11 +304,31 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return items[a].sparse->cols > items[b].sparse->cols; });
     std::memset(table, 0, (size_t)out.table_bytes);
     uint32_t *list = (uint32_t *)((uint8_t *)table + (size_t)count * EGT_STACK_ENTRY_BYTES);
-    for (int k = 0; k < count; ++k) {
-      const egt_gemm_item &it = items[order[(size_t)k]];
-      egt::smallm_stack_entry(*it.sparse, it.X, it.Y, M, (uint8_t *)table + (size_t)k * EGT_STACK_ENTRY_BYTES);
-      const int blocks = egt::smallm_stack_blocks(M, n_keep, it.sparse->rows);
-      for (int x = 0; x < blocks; ++x) *list++ = ((uint32_t)k << 16) | (uint32_t)x;   // matrix, place in the matrix
+    for (int k0 = 0, k1 = 0; k0 < count; k0 = k1) {
+      // A run of matrices with equally long rows, its workgroups in the order of the matrices.  Workgroups are dealt to the
+      // XCDs in turn, and each XCD has an L2 of its own: where the run has several matrices, each XCD takes a contiguous
+      // eighth of it, so that the token rows of a matrix are fetched by one or two of them and not by all eight (us:
+      // sixteen layers of 4096 x 11008 at 64 tokens 549 -> 536, 32 tokens 426 -> 419, 16 tokens 351 -> 349; four
+      // layers of 1024 x 3072 at 64 tokens 30.2 -> 29.0, at 6 12.9 -> 12.4).
+      uint64_t n = 0, at = 0, first = 0;              // workgroups of the run; the next one's place in it, and that place modulo 8
+      int members = 0;
+      for (; k1 < count && items[order[(size_t)k1]].sparse->cols == items[order[(size_t)k0]].sparse->cols; ++k1) {
+        const int blocks = egt::smallm_stack_blocks(M, n_keep, items[order[(size_t)k1]].sparse->rows);
+        n += (uint64_t)blocks;
+        members += blocks != 0;
+      }
+      const uint64_t step = members > 1 ? 8 : 1;
+      for (int k = k0; k < k1; ++k) {
+        const egt_gemm_item &it = items[order[(size_t)k]];
+        egt::smallm_stack_entry(*it.sparse, it.X, it.Y, M, (uint8_t *)table + (size_t)k * EGT_STACK_ENTRY_BYTES);
+        const int blocks = egt::smallm_stack_blocks(M, n_keep, it.sparse->rows);
+        for (int x = 0; x < blocks; ++x) {
+          list[at] = ((uint32_t)k << 16) | (uint32_t)x;                        // matrix, place in the matrix
+          at += step;
+          if (at >= n) at = ++first;
+        }
+      }
+      list += n;
     }
   }
   *plan = out;

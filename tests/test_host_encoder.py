@@ -613,6 +613,29 @@ def test_stack_plan_checks_items_and_reports_the_launch_shape():
     assert L.egt_gemv_stack_run(16, ctypes.byref(empty), None) == 0       # all matrices empty: nothing to launch
 
 
+@pytest.mark.parametrize("M,n,rows", [(16, 2, [4096, 4096, 0, 11008]), (2, 2, [1, 17]), (64, 2, [300] * 3 + [5000]), (32, 1, [16, 0, 40, 130]), (5, 1, [129] * 9)])
+def test_gemm_stack_list_gives_each_xcd_a_contiguous_part_of_every_run(M, n, rows):
+    # two runs (rows of 2048 and of 1024 columns), the first with a single matrix: in its own order; the second: every
+    # workgroup once, and the places with the same remainder modulo 8 hold consecutive ones
+    L = B.lib()
+    views = [B.View(700, 2048, n, 128, 0, 16, 16, 16, 16)] + [B.View(r, 1024, n, 128, 0, 16, 16, 16, 16) for r in rows]
+    items = (B.GemmItem * len(views))()
+    for k, v in enumerate(views):
+        items[k].sparse, items[k].X, items[k].Y = ctypes.pointer(v), 16, 16
+    plan = B.GemmPlan()
+    assert L.egt_gemm_stack_plan(items, len(views), M, None, 0, ctypes.byref(plan)) == 0
+    table = np.full(plan.table_bytes, 0xA5, dtype=np.uint8)
+    assert L.egt_gemm_stack_plan(items, len(views), M, table.ctypes.data, table.nbytes, ctypes.byref(plan)) == 0
+    wgs = table[len(views) * B.STACK_ENTRY_BYTES:].view(np.uint32)
+    assert not np.any(wgs[plan.grid_x:])
+    tiles = 16 if M > (16 if n == 1 else 32) else 8
+    blocks = [-(-v.rows // (16 * tiles)) for v in views]
+    every = np.concatenate([(k << 16) + np.arange(b) for k, b in enumerate(blocks)])
+    assert np.array_equal(wgs[:blocks[0]], every[:blocks[0]])
+    run = wgs[blocks[0]:plan.grid_x]
+    assert np.array_equal(np.concatenate([run[s::8] for s in range(8)]), every[blocks[0]:])
+
+
 def test_gemm_stack_plan_checks_items_and_reports_the_launch_shape():
     L = B.lib()
     views = [B.View(4096, 4096, 2, 128, 0, 16, 16, 16, 16), B.View(4096, 11008, 2, 128, 0, 16, 16, 16, 16),
