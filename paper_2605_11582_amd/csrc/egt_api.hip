@@ -343,11 +343,12 @@ egt_status egt_gemm_stack_run(const void *table_dev, const egt_gemm_plan *plan, 
     return EGT_ERR_SHAPE;
   int threads, lds;
   egt::smallm_stack_shape(plan->M, plan->n_keep, plan->grid_x, threads, lds);
-  if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || plan->block_threads != threads || plan->lds_bytes != lds ||
+  if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || plan->lds_bytes != lds ||
+      !egt::smallm_stack_threads_ok(plan->M, plan->n_keep, plan->grid_x, plan->block_threads) ||
       plan->table_bytes != gemm_table_bytes(plan->count, plan->grid_x))
     return EGT_ERR_SHAPE;
   if (plan->grid_x == 0) return EGT_OK;               // every matrix is empty
-  return done(egt::launch_smallm_stack(table_dev, plan->count, plan->M, plan->n_keep, plan->grid_x, (hipStream_t)stream));
+  return done(egt::launch_smallm_stack(table_dev, plan->count, plan->M, plan->n_keep, plan->grid_x, plan->block_threads, (hipStream_t)stream));
 }
 
 egt_status egt_int4_gemv_batch(const uint8_t *const *q, const uint16_t *const *qparams, int rows,

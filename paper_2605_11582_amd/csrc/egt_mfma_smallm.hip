@@ -1287,14 +1287,22 @@ void smallm_stack_entry(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, in
   std::memcpy(entry, &e, sizeof(e));
 }
 
-hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, hipStream_t stream) {
+// The kernel follows the plan's threads: a plan with sixteen waves, as every such table once had, is good at any size
+// (the table is the same in either form).
+bool smallm_stack_threads_ok(int M, int n_keep, int grid_x, int block_threads) {
   int threads, lds;
   smallm_stack_shape(M, n_keep, grid_x, threads, lds);
-  const dim3 grid(grid_x), block(threads);
+  return block_threads == threads || (stack_sixteen(M, n_keep == 1) && block_threads == 1024);
+}
+
+hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, int block_threads, hipStream_t stream) {
+  int threads, lds;
+  smallm_stack_shape(M, n_keep, grid_x, threads, lds);
+  const dim3 grid(grid_x), block(block_threads);
   const uint8_t *t = (const uint8_t *)table_dev;
 #define EGT_RS(...) launch(k_smallm_rows<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
 #define EGT_RS2(...) launch(k_smallm_rows_two<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
-  const bool two = stack_two_tiles(grid_x);
+  const bool two = block_threads == 512;
   if (n_keep == 1) return M <= 16 ? EGT_RS(1, 2, RS_WAVES, true) : two ? EGT_RS2(2, 2, 8, true) : EGT_RS(2, 2, 16, true);
   return M <= 16 ? EGT_RS(1, RS_Q, RS_WAVES) : M <= 32 ? EGT_RS(2, 2, RS_WAVES) : two ? EGT_RS2(4, 2, 8) : EGT_RS(4, 2, 16);
 #undef EGT_RS2

@@ -579,6 +579,17 @@ def test_gemm_stack_of_many_workgroups_has_the_bits_of_small_tables(M, n):
         nan = np.zeros(p.rows, dtype=bool)
         nan[[1203] if k == 6 else []] = True
         assert np.array_equal(Y[:, ~nan], want[:, ~nan]) and np.all(np.isnan(Y.view(np.float16)) == nan), ("member", k)
+    # a plan kept from a library that gave such tables sixteen waves: the same table, the same bits
+    first = [yb.clone() for yb in ybufs]
+    for y in Yd:
+        y.zero_()
+    call.plan.block_threads = 1024
+    call()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(first, ybufs))
+    call.plan.block_threads = 768
+    with pytest.raises(B.EgtError):
+        call()
 
 
 @pytest.mark.parametrize("seed", range(8))
