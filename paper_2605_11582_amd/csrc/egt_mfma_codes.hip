@@ -122,12 +122,17 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = (int)(blockDim.x >> 6);
   const int ps = (wave * g.wpp_inv) >> 16, slot = wave - ps * g.wpp;       // phase, row set
   const int i = lane % UNITS, kb = lane / UNITS;
-  const __amdgpu_buffer_rsrc_t r_val = make_rsrc(P.values, g.val_bytes), r_idx = make_rsrc(P.idx, g.idx_bytes);
-  const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(P.qparams, g.qp_bytes), r_x = make_rsrc(P.x, 16u * (uint32_t)g.npieces);
-
   // ---- this wave's rows: TPI row groups; this workgroup's from wg_row0 on
   const int rpw = MP ? TPI : TPI * g.rpt;
   const int wg_row0 = (int)blockIdx.x * g.wpp * rpw, row0 = wg_row0 + slot * rpw;
+  // The wave's buffers begin at its first row and end with the matrix (for a wave past the last row they are empty), and a
+  // request's place in them lies in its lane offset as a whole: a row past the last one lies past the buffer.  (A uniform
+  // offset is only added where it is below the buffer's size: the range check subtracts it from the size.)  Buffers begin on
+  // four bytes; rows of index words at 1:4 in groups of 32 on two, the rest goes into the lane offset.
+  const uint32_t row_base = (uint32_t)min(row0, g.rows), i_row = MIXED ? 0u : row_base * g.idx_row, i_rest = IB == 1 ? i_row & 3u : 0u;
+  const uint32_t v_base = MIXED ? 0u : row_base * g.val_row, i_base = i_row - i_rest, q_base = 4u * row_base * (uint32_t)g.groups_per_row;
+  const __amdgpu_buffer_rsrc_t r_val = make_rsrc(P.values + v_base, g.val_bytes - v_base), r_idx = make_rsrc(P.idx + i_base, g.idx_bytes - i_base);
+  const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(P.qparams + q_base, g.qp_bytes - q_base), r_x = make_rsrc(P.x, 16u * (uint32_t)g.npieces);
   uint32_t rp = 0, rp_end = 0;                        // rows differ: lane j holds the row pointers of row row0 + j and the next
   if constexpr (MIXED) {
     if (row0 + lane < g.rows) {
@@ -168,14 +173,12 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
     if (slot_by_slot(rn, rp) || row0 + lane >= g.rows) rn = 0;
   }
 
-  // (rows past the last one lie past the ends of the buffers: zeros, no traffic)
   auto load = [&](Tile (&t)[TPI], int p) {
     const bool on = lane_on & (cl < g.nchunks - (MP ? 64 * p : 0));
-    const uint32_t v_lane = on ? (uint32_t)rs * g.val_row + (uint32_t)(VB * cl) : OUT, i_lane = on ? (uint32_t)rs * g.idx_row + (uint32_t)(IB * cl) : OUT;
+    const uint32_t v_lane = on ? (uint32_t)rs * g.val_row + (uint32_t)(VB * cl) + (uint32_t)(64 * VB * p) : OUT;
+    const uint32_t i_lane = on ? (uint32_t)rs * g.idx_row + (uint32_t)(IB * cl) + (uint32_t)(64 * IB * p) + i_rest : OUT;
     const uint32_t grp = (uint32_t)((ui + (MP ? UNITS * p : 0)) >> g.gshift);
     const uint32_t q_lane = on ? 4u * ((uint32_t)rs * (uint32_t)g.groups_per_row + grp) : OUT;
-    const uint32_t v0 = (uint32_t)row0 * g.val_row + (uint32_t)(64 * VB * p), i0 = (uint32_t)row0 * g.idx_row + (uint32_t)(64 * IB * p);
-    const uint32_t q0 = 4u * (uint32_t)row0 * (uint32_t)g.groups_per_row;
 #pragma unroll
     for (int k = 0; k < TPI; ++k) {
       const uint32_t r = (uint32_t)(k * g.rpt);       // from row0 on
@@ -201,10 +204,10 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
         t[k].iw[0] = IB == 8 ? j[0][0] : j[0][0] | (j[1][0] << (4 * IB));
         t[k].iw[IB == 8] = IB == 8 ? j[1][0] : t[k].iw[0];
       } else {
-        codes_fetch<VB>(t[k].v, r_val, v_lane, v0 + r * g.val_row);
-        if constexpr (!DENSE) codes_fetch<IB>(t[k].iw, r_idx, i_lane, i0 + r * g.idx_row);
+        codes_fetch<VB>(t[k].v, r_val, v_lane + r * g.val_row, 0u);
+        if constexpr (!DENSE) codes_fetch<IB>(t[k].iw, r_idx, i_lane + r * g.idx_row, 0u);
       }
-      t[k].qp = __builtin_amdgcn_raw_buffer_load_b32(r_qp, q_lane, q0 + 4u * r * (uint32_t)g.groups_per_row, 0);
+      t[k].qp = __builtin_amdgcn_raw_buffer_load_b32(r_qp, q_lane + 4u * r * (uint32_t)g.groups_per_row, 0u, 0);
     }
   };
 

@@ -185,3 +185,19 @@ def test_requests_of_the_exact_codes_match_the_wait_count(tmp_path):
         assert _lane_loops(body) == 0 and not re.search(r"\bscratch_|\bflat_", body), name
         seen += 1
     assert seen >= 40
+
+
+def test_rows_past_the_last_one_are_requested_past_the_buffer_by_the_lane_offset(tmp_path):
+    # k_codes: a wave's buffers begin at its first row, and the whole place of a request lies in its lane offset, which the range
+    # check compares with the buffer's size.  A uniform offset beyond the size (the check subtracts it) is never there: only
+    # the codes and index words of rows of different lengths have one, four requests a tile, from checked row pointers.
+    seen = 0
+    for name, body in _assembly("egt_mfma_codes.hip", tmp_path):
+        m = re.search(r"k_codes(?:_batch)?ILi(\d)ELi\d+ELi\d+ELi(\d)E", name)
+        if not m:
+            continue
+        requests = [ln for ln in body.split("\n") if re.search(r"\bbuffer_load", ln)]
+        uniform = [ln for ln in requests if not re.search(r", 0 offen\b", ln)]
+        assert requests and len(uniform) == (4 * int(m.group(2)) if m.group(1) == "2" else 0), (name, uniform)
+        seen += 1
+    assert seen >= 40
