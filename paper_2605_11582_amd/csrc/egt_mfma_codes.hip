@@ -462,7 +462,9 @@ void codes_shape(CodesGeom &g, int unit, bool dense, int count, int &tpi, dim3 &
   const int rows_wg = g.wpp * tpi * g.rpt, sets = (nrg + tpi - 1) / tpi;
   g.red_stride = rows_wg | 1;
   g.split = 0;
-  while (g.split < 4 && (rows_wg << (g.split + 1)) <= 64 * g.wpp * g.phases) ++g.split;
+  // (the threads of a row fix the order of its additions, so they follow from the row alone, as if every wave had its four tiles:
+  // a member of a batch has the bits of its own call)
+  while (g.split < 4 && ((CODES_TPI * g.rpt) << (g.split + 1)) <= 64 * g.phases) ++g.split;
   lds = x_bytes + (size_t)g.phases * (size_t)g.upr * (size_t)g.red_stride * sizeof(float);
   grid = dim3((unsigned)((sets + g.wpp - 1) / g.wpp));
   block = dim3(64u * (unsigned)(g.wpp * g.phases));

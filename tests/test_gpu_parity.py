@@ -202,6 +202,38 @@ def test_batches_of_exact_codes_equal_separate_calls(rows, cols, g, n, kind, cou
         assert np.array_equal(y.cpu().numpy().view(np.uint16), G.run_sparse_gemv(p, x).view(np.uint16))
 
 
+# Rows of a few units (a tile holds several rows, more than one thread adds up a row); one member and four lie on different
+# sides of a line of the tiles of a wave.  Two units of a row cancel and are 2^13 times the others, so the order of the additions shows.
+@pytest.mark.parametrize("rows,cols,g,form", [(8000, 768, 128, 2), (6000, 1152, 128, "paired"), (8000, 384, 128, 1), (8000, 1280, 256, 2), (8000, 640, 64, "dense"), (8000, 640, 128, "dense")])
+def test_large_batches_of_exact_codes_equal_separate_calls(rows, cols, g, form):
+    torch = G.torch_mod()
+    unit, half = min(g, 128), cols // min(g, 128) // 2 * min(g, 128)
+    w = synth.weights(rows, cols, 9700 + cols)
+    w[:, half:half + unit] = w[:, :unit]
+    if g > unit:
+        w[:, unit:g] = w[:, :g - unit]                       # (the repeated units under the same scale)
+        w[:, half:half + g] = w[:, :g]
+    xs = [synth.activations(cols, 9700 + k) for k in range(4)]
+    for x in xs:
+        x[:unit] *= np.float16(8192)
+        x[half:half + unit] = -x[:unit]
+    xd = [G.to_dev(x.view(np.uint16)).view(torch.float16) for x in xs]
+    ys = [torch.full((rows,), 9.0, dtype=torch.float16, device="cuda") for _ in range(4)]
+    if form == "dense":
+        q, qp = B.quant_int4(w, g)
+        qd, qpd = G.to_dev(q), G.to_dev(qp)
+        B.int4_gemv_batch([qd] * 4, [qpd] * 4, rows, cols, g, xd, ys)
+        one = lambda x: G.run_int4_gemv(q, qp, g, x)
+    else:
+        n, kind = (2, 2) if form == "paired" else (form, 0)
+        p = B.pack_2bitcsr(w, B.prune_n4(w, n), n, g, kind)
+        B.sparse_gemv_batch([p.to("cuda")] * 4, xd, ys)
+        one = lambda x: G.run_sparse_gemv(p, x)
+    torch.cuda.synchronize()
+    for x, y in zip(xs, ys):
+        assert np.array_equal(y.cpu().numpy().view(np.uint16), one(x).view(np.uint16))
+
+
 @pytest.mark.parametrize("rows,cols,n,g,M", [(70, 4096, 2, 64, 1), (70, 4096, 1, 32, 1), (300, 1024, 2, 128, 6)])
 def test_row_group_sizes_run_on_the_ordinary_kernels(rows, cols, n, g, M):
     # rows quantised with group sizes of their own are stored at the finest granularity
