@@ -21,7 +21,7 @@
 //  - Rows of different lengths: the chunk of a row that keeps one of four spans the same columns
 //    as that of a row that keeps two, so both use the same B operand; a tile is one row.  A chunk is requested in halves, the
 //    second out of range for a row that keeps one (a branch around the requests would be waited behind).  Rows that
-//    keep three or four are followed slot by slot, by the waves of their row set in turn.
+//    keep three or four are left to the vector units, dealt to all waves of their workgroup (codes_wide_rows).
 //  - One shot, as the row-per-wave kernels: a wave requests its four tiles (of one phase) at once, the phases of a row
 //    are different waves, whose sums meet in LDS; small workgroups, so that one set of rows waits for no other.  (A walk over
 //    more tiles with two sets of registers, and a loop over row sets under one staged x, were slower on all but the longest rows:
@@ -32,7 +32,6 @@
 // dense 5003 x 2880 groups of 64 5.6, 4.8; 2:4 20000 x 2816 14.5, 7.5; 2000 x 3072 5.8, 3.5; 50000 x 512 14.4, 4.3; 1:4 4096 x 3072 5.3,
 // 3.7; dense 60000 x 384 11.6, 4.6; 512 x 14400 8.5, 4.4.  What bounds it: the launch for a few megabytes, then vector issue (about 85
 // instructions for 4096 columns of a row, 470 a wave) and memory (20000 x 2816: 42 MB at 5.7 TB/s).
-#include "egt_generic_body.h"
 #include "egt_mfma_common.h"
 #include "egt_tune.h"
 
@@ -57,6 +56,8 @@ struct CodesGeom {
   int groups_per_row;
   int npieces;         // 16-byte pieces of x
   int units;           // units of x in LDS
+  int blocks;          // CODES_MIXED: blocks of 64 spans of 32 columns of a row
+  int span_shift;      // and log2 of the lanes a row has in a block
   uint32_t val_row, idx_row;                          // bytes of a row (uniform rows)
   uint32_t slots_row;                                 // slots of a row; CODES_MIXED: of a row that keeps one of four
   uint32_t total_slots;                               // CODES_MIXED
@@ -108,6 +109,114 @@ __device__ __forceinline__ uint32_t codes_pair(uint32_t d, int p, uint32_t off, 
   return pk_sub_f16(and_or(__builtin_amdgcn_perm(d, d, 0x0c000c00u + (uint32_t)p * 0x00010001u), mask, magic), off);
 }
 
+// 32 columns of a row that keeps N of four: its N words of codes and of indices, its parameter pair and its activations (half2
+// registers): s sum (q - z) x, of the kept columns alone.
+struct CodesSpan {
+  uint32_t v[4], iw[3], qp;
+};
+template <int N>
+__device__ __forceinline__ float codes_span_dot(const CodesSpan &in, const u4 (&x)[4], uint32_t nib_mask, uint32_t nib_magic, uint32_t magic) {
+  const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(in.qp, in.qp, 0x03020302u), nib_magic);
+  float sum = 0.f;
+#pragma unroll
+  for (int p = 0; p < 4 * N; ++p) {
+    const h2 v = __builtin_bit_cast(h2, codes_pair(in.v[p / 4], p % 4, off, nib_mask, magic));
+#pragma unroll
+    for (int k = 2 * p; k < 2 * p + 2; ++k) {          // slot k, of 4-group k / N
+      const uint32_t x01 = x[k / N / 2][2 * (k / N % 2)], x23 = x[k / N / 2][2 * (k / N % 2) + 1];
+      _Float16 xk;
+      if constexpr (N == 4) {
+        xk = __builtin_bit_cast(h2, k & 2 ? x23 : x01)[k & 1];                                   // (all four: the offsets of a 4-group ascend)
+      } else {
+        const uint32_t o = (in.iw[k / 8 < 3 ? k / 8 : 0] >> (2 * (k % 8))) & 3u;
+        xk = __builtin_bit_cast(h2, __builtin_amdgcn_perm(x23, x01, 0x0100u + 0x0202u * o))[0];
+      }
+      sum = fmaf((float)v[k & 1], (float)xk, sum);
+    }
+  }
+  return __half2float(__ushort_as_half((uint16_t)(in.qp & 0xFFFFu))) * sum;
+}
+
+// Rows of a workgroup that the matrix cores do not take (the bits of `wide`), on the vector units, a span of 32 columns a lane (one
+// quantisation group, one unit of x).  A row is cut into blocks of 64 spans; PACKED: rows of 32 spans and fewer, of which a block
+// holds two or four.  Blocks are dealt to the waves, which request two before they use the first.  `kept`, lane j: row j's first
+// slot and in the low bits what it keeps.  Every sixteen lanes leave a sum.
+// Measured, us, 11008 x 4096 with a half, a quarter and a tenth of rows that keep three or four: 11.4, 9.4 and 7.6, slot by slot 18.3, 14.4
+// and 13.9; where these rows were followed slot by slot beside the others, a wave a row, 28.2, 18.3 and 18.0.
+template <int UNIT, bool PACKED>
+__device__ __forceinline__ void codes_wide_rows(const uint8_t *xs, float *part, uint64_t wide, uint32_t kept, __amdgpu_buffer_rsrc_t r_val,
+                                                __amdgpu_buffer_rsrc_t r_idx, __amdgpu_buffer_rsrc_t r_qp, const CodesGeom &g, int wave, int nw, int lane, uint32_t magic) {
+  constexpr uint32_t OUT = 0x7FFFFFF0u;
+  constexpr int QM = UNIT / 8 > 16 ? 15 : UNIT / 8 - 1;
+  const int spans = g.npieces / 4, rows_of_block = PACKED ? 64 >> g.span_shift : 1, group = PACKED ? lane >> g.span_shift : 0;
+  const int lane_of_row = PACKED ? lane & ((1 << g.span_shift) - 1) : lane;
+  uint64_t left = wide;                               // the block in turn: of the row of the lowest bit, or of the lowest bits
+  int block = 0;
+  auto advance = [&](int by) {
+    for (block += by; block >= g.blocks && left != 0; block -= g.blocks)
+      for (int k = 0; k < rows_of_block; ++k) left &= left - 1;
+  };
+  advance(wave);
+  while (left != 0) {
+    CodesSpan in[2];
+    int in_n[2], in_row[2], in_block[2];
+    bool any[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t from = 0;                              // of this lane's row: uniform unless PACKED
+      int row = 0;
+      if constexpr (PACKED) {
+        uint64_t rest = left;
+        for (int k = 0; k < rows_of_block && rest != 0; ++k, rest &= rest - 1) {
+          const int r = __builtin_ctzll(rest);
+          const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)kept, r);
+          from = group == k ? f : from;
+          row = group == k ? r : row;
+        }
+      } else if (left != 0) {
+        row = __builtin_ctzll(left);
+        from = (uint32_t)__builtin_amdgcn_readlane((int)kept, row);
+      }
+      const int n = (int)(from & 7u), span = 64 * block + lane_of_row;
+      const uint32_t word = (from >> 3) + (uint32_t)(n * span);
+      const bool on = span < spans;
+      in_n[u] = n;
+      in_row[u] = row;
+      in_block[u] = block;
+      any[u] = left != 0;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        in[u].v[d] = __builtin_amdgcn_raw_buffer_load_b32(r_val, on && d < n ? 4 * (word + d) : OUT, 0u, 0);
+        if (d < 3) in[u].iw[d] = __builtin_amdgcn_raw_buffer_load_b16(r_idx, on && d < n && n < 4 ? 2 * (word + d) : OUT, 0u, 0);
+      }
+      in[u].qp = __builtin_amdgcn_raw_buffer_load_b32(r_qp, on && n != 0 ? 4 * (uint32_t)(row * g.groups_per_row + (32 * span / UNIT >> g.gshift)) : OUT, 0u, 0);
+      advance(nw);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (!any[u]) break;
+      const int span = 64 * in_block[u] + lane_of_row;
+      const bool on = span < spans && in_n[u] != 0;
+      float sum = 0.f;
+      if (on) {
+        const uint32_t at = (uint32_t)(64 * span) ^ (uint32_t)(16 * ((32 * span / UNIT) & QM));  // (the swizzle of its unit)
+        u4 x[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) x[d] = *(const u4 *)(xs + (at ^ (uint32_t)(16 * d)));
+        if (in_n[u] == 1) sum = codes_span_dot<1>(in[u], x, g.nib_mask, g.nib_magic, magic);
+        if (in_n[u] == 2) sum = codes_span_dot<2>(in[u], x, g.nib_mask, g.nib_magic, magic);
+        if (in_n[u] == 3) sum = codes_span_dot<3>(in[u], x, g.nib_mask, g.nib_magic, magic);
+        if (in_n[u] == 4) sum = codes_span_dot<4>(in[u], x, g.nib_mask, g.nib_magic, magic);
+      }
+      sum += row_shl<8>(sum);
+      sum += row_shl<4>(sum);
+      sum += row_shl<2>(sum);
+      sum += row_shl<1>(sum);
+      if ((lane & 15) == 0 && on) part[4 * (in_row[u] * g.blocks + in_block[u]) + (lane_of_row >> 4)] = sum;
+    }
+  }
+}
+
 // FORM: CODES_*.  CPL: columns of a chunk.  UNITS: of a tile.  MP: a row takes several tiles.
 template <int FORM, int CPL, int UNITS, int TPI, bool MP>
 __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &g) {
@@ -129,15 +238,16 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   // request's place in them lies in its lane offset as a whole: a row past the last one lies past the buffer.  (A uniform
   // offset is only added where it is below the buffer's size: the range check subtracts it from the size.)  Buffers begin on
   // four bytes; rows of index words at 1:4 in groups of 32 on two, the rest goes into the lane offset.
-  const uint32_t row_base = (uint32_t)min(row0, g.rows), i_row = MIXED ? 0u : row_base * g.idx_row, i_rest = IB == 1 ? i_row & 3u : 0u;
+  const uint32_t row_base = (uint32_t)min(MIXED ? wg_row0 : row0, g.rows), i_row = MIXED ? 0u : row_base * g.idx_row, i_rest = IB == 1 ? i_row & 3u : 0u;
   const uint32_t v_base = MIXED ? 0u : row_base * g.val_row, i_base = i_row - i_rest, q_base = 4u * row_base * (uint32_t)g.groups_per_row;
   const __amdgpu_buffer_rsrc_t r_val = make_rsrc(P.values + v_base, g.val_bytes - v_base), r_idx = make_rsrc(P.idx + i_base, g.idx_bytes - i_base);
   const __amdgpu_buffer_rsrc_t r_qp = make_rsrc(P.qparams + q_base, g.qp_bytes - q_base), r_x = make_rsrc(P.x, 16u * (uint32_t)g.npieces);
-  uint32_t rp = 0, rp_end = 0;                        // rows differ: lane j holds the row pointers of row row0 + j and the next
+  uint32_t rp = 0, rp_end = 0;                        // rows differ: lane j holds the row pointers of row wg_row0 + j and the next
+  const int own = MIXED ? slot * TPI : 0;             // (of which this wave's begin here; a workgroup has at most 64 rows)
   if constexpr (MIXED) {
-    if (row0 + lane < g.rows) {
-      rp = P.row_ptr[row0 + lane];
-      rp_end = P.row_ptr[row0 + lane + 1];
+    if (wg_row0 + lane < g.rows) {
+      rp = P.row_ptr[wg_row0 + lane];
+      rp_end = P.row_ptr[wg_row0 + lane + 1];
     }
   }
 
@@ -166,12 +276,16 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   };
   // rows that keep three or four, and rows whose requests would not be aligned
   auto slot_by_slot = [&](int n, uint32_t start) { return n > 2 || (n != 0 && (start & ALIGN) != 0); };
-  // Lane j: what row row0 + j keeps where the matrix cores take it, 1 or 2, else 0.
-  int rn = 0;
+  // Lane j: where row wg_row0 + j begins (whole words of eight slots), and in the low bits what it keeps; which rows the matrix cores
+  // do not take.
+  uint32_t kept = 0;
+  uint64_t wide = 0;
   if constexpr (MIXED) {
-    rn = lane_n(rp, rp_end);
-    if (slot_by_slot(rn, rp) || row0 + lane >= g.rows) rn = 0;
+    const int n = wg_row0 + lane < g.rows ? lane_n(rp, rp_end) : 0;
+    kept = n ? rp | (uint32_t)n : 0u;
+    wide = __ballot(lane < g.wpp * rpw && slot_by_slot(n, rp));
   }
+  auto row_n = [&](int row) { return __builtin_amdgcn_readlane((int)kept, row) & 7; };
 
   auto load = [&](Tile (&t)[TPI], int p) {
     const bool on = lane_on & (cl < g.nchunks - (MP ? 64 * p : 0));
@@ -181,10 +295,10 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
     const uint32_t q_lane = on ? 4u * ((uint32_t)rs * (uint32_t)g.groups_per_row + grp) : OUT;
 #pragma unroll
     for (int k = 0; k < TPI; ++k) {
-      const uint32_t r = (uint32_t)(k * g.rpt);       // from row0 on
+      const uint32_t r = (uint32_t)(MIXED ? own + k : k * g.rpt);       // from the buffers' first row on
       if constexpr (MIXED) {
-        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)rp, k);
-        const int n = __builtin_amdgcn_readlane(rn, k);
+        const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)kept, own + k) & ~7u;
+        const int n = (wide >> (own + k)) & 1 ? 0 : row_n(own + k);
         // the halves of a chunk at 2:4, of which a chunk at 1:4 is the first (a branch would be waited behind)
         constexpr int VH = VB / 2, IH = IB / 2;
         const uint32_t s_v = n ? (start >> 1) + (uint32_t)(64 * VH * n) * (uint32_t)p : 0u, s_i = s_v >> 1;
@@ -300,7 +414,7 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
         if constexpr (FORM == CODES_14) {
           one_of_four();
         } else if constexpr (MIXED) {
-          if (__builtin_amdgcn_readlane(rn, k) == 1) one_of_four();              // (the same for all lanes; a row of neither kind is zeros)
+          if (row_n(own + k) == 1) one_of_four();           // (the same for all lanes; a row of neither kind is zeros)
           else two_of_four();
         } else {
           two_of_four();
@@ -324,9 +438,9 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   load(t, ps);
   wait_vmem<TPI * LOADS>();
   // (2^split threads add up a row; the first of them stores it, and asks for its row pointers now)
-  const int out_k = (int)threadIdx.x >> g.split, part = (int)threadIdx.x & ((1 << g.split) - 1), out_row = wg_row0 + out_k;
+  const int out_k = (int)threadIdx.x >> g.split, out_part = (int)threadIdx.x & ((1 << g.split) - 1), out_row = wg_row0 + out_k;
   const bool in_wg = out_k < g.wpp * rpw;
-  bool out_on = in_wg && part == 0 && out_row < g.rows;
+  bool out_on = in_wg && out_part == 0 && out_row < g.rows;
   uint32_t out_rp = 0, out_end = 0;
   if (!DENSE && out_on) {
     out_rp = P.row_ptr[out_row];
@@ -340,7 +454,7 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   read_b(ps);
   consume(t);
 
-  // [phase][unit of a row][row of the workgroup]
+  // [phase][unit of a row][row of the workgroup]; rows differ: then four sums for each [row of the workgroup][block]
   float *red = (float *)(xs + (size_t)kib * 1024);
   if (kb == ((i >> 2) & (L - 1)) && lane_on) {
 #pragma unroll
@@ -350,7 +464,7 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   float v = 0.f;
   if (in_wg) {
 #pragma unroll 4
-    for (int k = part; k < g.phases * g.upr; k += 1 << g.split) v += red[k * g.red_stride + out_k];
+    for (int k = out_part; k < g.phases * g.upr; k += 1 << g.split) v += red[k * g.red_stride + out_k];
   }
   if (g.split > 3) v += row_shl<8>(v);
   if (g.split > 2) v += row_shl<4>(v);
@@ -366,22 +480,20 @@ __device__ __forceinline__ void codes_body(const CodesPtrs &P, const CodesGeom &
   if (out_on) P.y[out_row] = ok ? __float2half(v) : __ushort_as_half((uint16_t)0x7E00);
 
   if constexpr (MIXED) {
-    // the other rows of this row set, dealt to its waves
-    const int n = lane_n(rp, rp_end);
-    uint64_t wide = __ballot(lane < TPI && row0 + lane < g.rows && slot_by_slot(n, rp));
-    for (int turn = 0; wide; wide &= wide - 1, turn = turn + 1 == g.phases ? 0 : turn + 1) {
-      if (turn != ps) continue;
-      const int k = __builtin_ctzll(wide), nk = __builtin_amdgcn_readlane(n, k);
-      const uint32_t start = (uint32_t)__builtin_amdgcn_readlane((int)rp, k);
-      const uint32_t g4 = (uint32_t)(L * CPL / 4) << g.gshift, inv_g4 = (uint32_t)((0x100000000ull + g4 - 1) / g4);
-      const uint32_t *qrow = (const uint32_t *)P.qparams + (size_t)(row0 + k) * (size_t)g.groups_per_row;
-      float sum = row_dot_any<EGT_VAL_INT4>(nk, P.values, (const uint16_t *)P.idx, qrow, start, ((uint32_t)nk * g.slots_row) >> 3, g4, inv_g4, lane,
-                                            [&](uint32_t c, uint32_t) {
-                                              const uint32_t Q = c / (L * CPL);
-                                              return __half2float(*(const __half *)(xs + QB * Q + 16 * (((c >> 3) % QP) ^ (Q & QM)) + 2 * (c & 7u)));
-                                            });
-      for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-      if (lane == 0) P.y[row0 + k] = __float2half(sum);
+    // The other rows of the workgroup.  (Rows of several tiles have more than 1024 columns, rows of one in groups of 32 as many at most.)
+    if (wide == 0) return;
+    float *part = red + g.phases * g.upr * g.red_stride;
+    const bool packed = !MP && (CPL == 16 || g.span_shift < 6);
+    if (packed) {
+      if constexpr (!MP) codes_wide_rows<L * CPL, true>(xs, part, wide, kept, r_val, r_idx, r_qp, g, wave, nw, lane, magic);
+    } else {
+      if constexpr (MP || CPL > 16) codes_wide_rows<L * CPL, false>(xs, part, wide, kept, r_val, r_idx, r_qp, g, wave, nw, lane, magic);
+    }
+    lds_barrier();
+    if (threadIdx.x < 64 && ((wide >> lane) & 1)) {
+      float v = 0.f;
+      for (int k = 0; k < (g.npieces / 4 + 15) / 16; ++k) v += part[4 * lane * g.blocks + k];
+      P.y[wg_row0 + lane] = __float2half(v);
     }
   }
 }
@@ -425,6 +537,8 @@ bool codes_geometry(int form, int rows, int cols, int n_keep, int group, uint32_
   g.rpt = g.phases > 1 || mixed ? 1 : std::min(per_tile / g.upr, 16);
   g.groups_per_row = cols / group;
   g.npieces = cols / 8;
+  g.blocks = (cols + 2047) / 2048;
+  g.span_shift = cols <= 512 ? 4 : cols <= 1024 ? 5 : 6;
   g.units = g.phases > 1 ? per_tile * g.phases : units;
   const int n = n_keep ? n_keep : 1;
   g.val_row = dense ? (uint32_t)cols / 2 : mixed ? 0u : (uint32_t)(n * (cols / 8));
@@ -444,14 +558,14 @@ bool codes_geometry(int form, int rows, int cols, int n_keep, int group, uint32_
 }
 
 // The waves of a workgroup are the phases of `wpp` row sets.
-void codes_shape(CodesGeom &g, int unit, bool dense, int count, int &tpi, dim3 &grid, dim3 &block, size_t &lds) {
+void codes_shape(CodesGeom &g, int unit, int form, int count, int &tpi, dim3 &grid, dim3 &block, size_t &lds) {
   const size_t x_bytes = ((size_t)g.units * (size_t)(2 * unit) + 1023) & ~(size_t)1023;
   const int nrg = (g.rows + g.rpt - 1) / g.rpt;       // row groups
   // Few tiles: one or two to a wave, since the launch then lasts as long as a wave's instructions (us with 1, 2, 4 tiles a wave:
   // 300 x 768 2.6, 2.8, 3.3; 4000 x 1920 3.1, 3.2, 3.7; 5000 x 3072 4.1, 4.0, 4.4; 11008 x 3072 6.1, 5.6, 5.4; dense 5003 x 2880,
   // 10006 tiles, 5.3, 4.7, 4.9).
   const int64_t tiles = (int64_t)nrg * g.phases * count;
-  tpi = tiles <= 2048 ? 1 : tiles <= (dense ? 10240 : 5120) ? 2 : 4;
+  tpi = tiles <= 2048 ? 1 : tiles <= (form == CODES_DENSE ? 10240 : 5120) ? 2 : 4;
   int waves = 4;                                      // (2, 6 and 8 waves: 1.1 to 1.5 times the time on 20000 x 2816 and 11008 x 4096)
   tune_pair("EGT_CODES_TUNE", waves, tpi);
   if (tpi != 1 && tpi != 2) tpi = 4;
@@ -466,6 +580,7 @@ void codes_shape(CodesGeom &g, int unit, bool dense, int count, int &tpi, dim3 &
   // a member of a batch has the bits of its own call)
   while (g.split < 4 && ((CODES_TPI * g.rpt) << (g.split + 1)) <= 64 * g.phases) ++g.split;
   lds = x_bytes + (size_t)g.phases * (size_t)g.upr * (size_t)g.red_stride * sizeof(float);
+  if (form == CODES_MIXED) lds += (size_t)rows_wg * (size_t)(4 * g.blocks) * sizeof(float);   // (rows on the vector units)
   grid = dim3((unsigned)((sets + g.wpp - 1) / g.wpp));
   block = dim3(64u * (unsigned)(g.wpp * g.phases));
 }
@@ -484,11 +599,16 @@ int codes_form(const egt_2bitcsr &w) {
 //    with groups of 64 win throughout (0.57 to 0.88), and groups of 128 and more.
 //  - Dense rows of few columns: staging x costs what it saves (300 x 384 1.17, 1000 x 896 1.11, 2000 x 896 1.09; 4000 x 896 0.97,
 //    300 x 1600 0.98).
+//  - Rows of different lengths: a row that keeps three or four costs up to a third more than one of both other kinds together
+//    and less than slot by slot (its time over slot by slot with half of the rows at three and four: 11008 x 4096 0.67, 20000 x 1024
+//    0.95), on rows shorter than 768 columns more (20000 x 640 1.13, x 512 1.13, 3000 x 512 1.14).  What the rows keep is known here as an
+//    average only: short rows half of which keep one, the others two, are at 1.5 (0.80 to 0.88), and up to 1.55 few keep three or four.
 static bool codes_pay(int form, const CodesGeom &g, int unit) {
   const bool dense = form == CODES_DENSE;
   const int64_t cols = 8 * (int64_t)g.npieces;
   if (tune_flag("EGT_CODES_ALL")) return true;
   if (dense && cols < 1536 && g.rows * cols < 3500000) return false;
+  if (form == CODES_MIXED && cols < 768 && 20 * (uint64_t)g.total_slots > 31 * (uint64_t)g.rows * g.slots_row) return false;
   if (unit == 128 || (dense && unit == 64)) return true;
   const bool one = form == CODES_14 || form == CODES_MIXED;
   return g.phases <= (one ? 2 : 4) || (int64_t)g.phases * ((g.rows + CODES_TPI - 1) / CODES_TPI) <= (one ? 4096 : 8192);
@@ -513,7 +633,7 @@ static hipError_t go(const GemvBatch &b, CodesGeom &g, int count, hipStream_t st
   dim3 grid, block;
   size_t lds;
   int tpi;
-  codes_shape(g, CPL * (64 / UNITS), FORM == CODES_DENSE, count, tpi, grid, block, lds);
+  codes_shape(g, CPL * (64 / UNITS), FORM, count, tpi, grid, block, lds);
   grid.y = (unsigned)count;
 #define EGT_C(TPI, MP)                                                                                                       \
   (FORM != CODES_MIXED && count > 1 ? launch(k_codes_batch<FORM == CODES_MIXED ? CODES_14 : FORM, CPL, UNITS, TPI, MP>, grid, block, lds, stream, b, g) \

@@ -190,6 +190,19 @@ def test_exact_codes_at_the_edges_of_their_tiles(rows, cols, g, form):
     assert np.all(np.abs(run(x).astype(np.float64) - y_ref) <= 2.0**-11 * np.abs(y_ref) + cols * 2.0**-24 * a_ref + 2.0**-25)
 
 
+# Rows that keep three or four among others: a lane a span of 32 columns, 64 spans a block; a block exactly, one span more, three blocks,
+# the most; two and four rows a block; rows that end inside a workgroup, one and four rows a wave.
+@pytest.mark.parametrize("rows,cols,g,form", [(67, 2048, 128, "34"), (21, 2080, 32, "1234"), (67, 4128, 32, "34"), (37, 4096, 128, "13"), (5, 24576, 128, "34"), (5125, 1152, 64, "1234"), (2605, 4224, 128, "234"), (1, 96, 32, "4"),
+                                              (67, 512, 128, "1234"), (7, 544, 32, "34"), (5125, 1024, 128, "234"), (5125, 480, 32, "134"), (67, 1056, 32, "1234")])
+def test_rows_that_keep_three_or_four_among_others(rows, cols, g, form):
+    w = synth.weights(rows, cols, 9650 + rows + cols)
+    run, ref, _ = _slot_by_slot_case(rows, cols, g, form, w)
+    x = synth.activations(cols, 9650 + cols)
+    y_ref, a_ref = ref(x)
+    # (as above)
+    assert np.all(np.abs(run(x).astype(np.float64) - y_ref) <= 2.0**-11 * np.abs(y_ref) + cols * 2.0**-24 * a_ref + 2.0**-25)
+
+
 @pytest.mark.parametrize("rows,cols,g,n,kind,count", [(70, 1920, 128, 2, 0, 3), (19, 2112, 64, 1, 0, 4), (33, 4128, 32, 2, 2, 2), (131, 96, 32, 2, 0, 4)])
 def test_batches_of_exact_codes_equal_separate_calls(rows, cols, g, n, kind, count):
     torch = G.torch_mod()

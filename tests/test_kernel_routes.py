@@ -159,6 +159,13 @@ def test_rows_of_exact_codes(launches, w, codes):
     assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
 
 
+# (rows that differ, and the slots of the matrix)
+@pytest.mark.parametrize("rows,cols,slots,codes", [(300, 736, 300 * 184 * 31 // 20, True), (300, 736, 300 * 184 * 31 // 20 + 8, False), (300, 768, 300 * 192 * 4, True), (20000, 2048, 20000 * 512 * 3, True)])
+def test_short_rows_that_differ_of_exact_codes(launches, rows, cols, slots, codes):
+    (call,) = launches([{"call": "gemv", "w": (rows, cols, 0, 32, 0, slots)}])
+    assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
+
+
 @pytest.mark.parametrize("w,codes", [((5003, 2880, 64), True), ((70, 1536, 128), True), ((2278, 1504, 32), False), ((2400, 1504, 32), True), ((300, 384, 128), False), ((300, 2944, 128), False),
                                      ((300, 24512, 64), True), ((300, 24640, 64), False), ((24000, 4064, 32), True), ((6552, 4128, 32), True), ((6553, 4128, 32), False), ((300, 2880, 36), False)])
 def test_dense_rows_of_exact_codes(launches, w, codes):
