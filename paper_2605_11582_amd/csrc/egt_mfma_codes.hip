@@ -532,6 +532,7 @@ bool codes_geometry(int form, int rows, int cols, int n_keep, int group, uint32_
   g.phases = (units + per_tile - 1) / per_tile;
   if (g.phases > CODES_WAVES) return false;
   if (g.phases > 1 && (form == CODES_24 || form == CODES_24P) && cpl == 64) return false;   // (4096 columns and more: egt_mfma_m1.hip)
+  if (g.phases > 1 && dense && unit == 128) return false;                                   // (2048 columns and more: egt_mfma_dense.hip)
   g.upr = g.phases > 1 ? per_tile : units;
   g.upr_inv = (65536 + g.upr - 1) / g.upr;
   g.rpt = g.phases > 1 || mixed ? 1 : std::min(per_tile / g.upr, 16);
@@ -639,9 +640,13 @@ static hipError_t go(const GemvBatch &b, CodesGeom &g, int count, hipStream_t st
   (FORM != CODES_MIXED && count > 1 ? launch(k_codes_batch<FORM == CODES_MIXED ? CODES_14 : FORM, CPL, UNITS, TPI, MP>, grid, block, lds, stream, b, g) \
              : launch(k_codes<FORM, CPL, UNITS, TPI, MP>, grid, block, lds, stream, b.row_ptr[0], b.values[0], b.idx[0], b.qparams[0], b.x[0], b.y[0], g))
 #define EGT_T(MP) (tpi == 1 ? EGT_C(1, MP) : tpi == 2 ? EGT_C(2, MP) : EGT_C(4, MP))
-  if constexpr (!((FORM == CODES_24 || FORM == CODES_24P) && CPL == 64))
+  // (not of several tiles: sparse rows of whole 128s from 4096 columns on, dense rows of whole 128s from 2048 columns on, which are the
+  // row-per-wave kernels'; dense rows of one tile in groups of 32 are 3400 tiles at least, see codes_pay)
+  constexpr bool dense = FORM == CODES_DENSE, several = dense ? UNITS == 32 : !((FORM == CODES_24 || FORM == CODES_24P) && CPL == 64);
+  if constexpr (several)
     if (g.phases > 1) return EGT_T(true);
-  return EGT_T(false);
+  if constexpr (dense && CPL == 16) return tpi <= 2 ? EGT_C(2, false) : EGT_C(4, false);
+  else return EGT_T(false);
 #undef EGT_T
 #undef EGT_C
 }
