@@ -176,8 +176,11 @@ def test_infinite_activations_of_dense_rows_off_the_tiles():
 # 32: other units), with rows that end inside a wave and inside a workgroup.
 CODES_EDGES = [(r, c, g, f) for g, cols in ((128, (128, 1920, 2048, 2176, 3968)), (64, (64, 1984, 2112)), (32, (32, 992, 1056, 4064))) for c in cols
                for r, f in ((67, "dense"), (1, 2), (67, 2), (5, "paired"), (18, 1), (63, "12"))]
-CODES_EDGES += [(5, 4224, 128, 1), (18, 7936, 256, "12"), (63, 4096, 128, "12"), (3, 24576, 128, "1234"), (3, 24576, 64, "dense"), (5, 16384, 32, "12"), (7, 16352, 32, "paired"),
-                (5, 16320, 32, 1), (3300, 1056, 32, "dense"), (70, 5184, 64, "1234"), (19, 2592, 32, "1234")]
+CODES_EDGES += [(5, 4224, 128, 1), (18, 7936, 256, "12"), (63, 4096, 128, "12"), (3, 24576, 128, "1234"), (3, 24512, 64, "dense"), (5, 16384, 32, "12"), (7, 16352, 32, "paired"),
+                (5, 16320, 32, 1), (3320, 1056, 32, "dense"), (70, 5184, 64, "1234"), (19, 2592, 32, "1234"),
+                # (dense rows below 1536 columns are slot by slot in small matrices, rows of 2048 columns and dense ones of whole
+                # 128s beyond it the row-per-wave kernels')
+                (109400, 32, 32, "dense"), (3533, 992, 32, "dense"), (10243, 544, 32, "dense")]
 
 
 @pytest.mark.parametrize("rows,cols,g,form", CODES_EDGES)
@@ -188,6 +191,72 @@ def test_exact_codes_at_the_edges_of_their_tiles(rows, cols, g, form):
     y_ref, a_ref = ref(x)
     # half a unit in the last place of the result, and a rounding to FP32 for every addition of the row
     assert np.all(np.abs(run(x).astype(np.float64) - y_ref) <= 2.0**-11 * np.abs(y_ref) + cols * 2.0**-24 * a_ref + 2.0**-25)
+
+
+# A wave of the M = 1 kernels takes one, two or four tiles, more the more tiles a matrix has, and the bits of a row do not depend on it.
+# So: the rows of a small matrix (one tile a wave; against the oracle), again and again, so many that the last wave of two and of
+# four tiles and the last workgroup are ragged.
+MANY_TILES = [
+    # exact codes: rows of one tile, several rows a tile, rows of several tiles; groups of 128, 64 and 32
+    *[(r, c, g, f) for f in (2, "paired", 1) for r, c, g in ((2053, 2176, 128), (5125, 2176, 128), (10247, 1920, 128), (2053, 1088, 64), (5125, 1088, 64), (1027, 2112, 64), (2563, 2112, 64),
+                                                             (2053, 544, 32), (10247, 480, 32), (1027, 1056, 32), (2563, 1056, 32))],
+    (1027, 4224, 128, 1), (2563, 4224, 128, 1),
+    *[(r, c, g, "12") for r, c, g in ((2053, 896, 128), (5125, 896, 128), (1027, 4224, 128), (2563, 4224, 128), (2053, 832, 64), (5125, 832, 64), (1027, 2112, 64), (2563, 2112, 64),
+                                      (2053, 800, 32), (5125, 800, 32), (1027, 1056, 32), (2563, 1056, 32))],
+    (2053, 896, 128, "1234"), (5125, 896, 128, "1234"), (2563, 2112, 64, "1234"),
+    (2053, 1664, 128, "dense"), (10243, 1536, 128, "dense"), (2053, 1856, 64, "dense"), (10243, 1600, 64, "dense"), (1027, 2624, 64, "dense"), (5123, 2624, 64, "dense"),
+    (2053, 1568, 32, "dense"), (5123, 1568, 32, "dense"),
+    # the row-per-wave kernels
+    *[(r, c, 128, f) for f in (2, "paired") for r, c in ((9219, 1024), (40965, 1024), (1539, 4096), (2307, 4096), (1027, 8192), (1025, 11008))], (1025, 16384, 128, 2),
+    *[(r, c, 0, "fp16") for r, c in ((1027, 4096), (6147, 4096), (1027, 8192))],
+    *[(r, c, 128, 1) for r, c in ((4099, 2048), (1027, 8192), (1027, 11008))],
+    *[(r, c, 128, "dense") for r, c in ((8197, 512), (4099, 1024), (1027, 4096), (1027, 11008))],
+]
+
+
+@pytest.mark.parametrize("rows,cols,g,form", MANY_TILES)
+def test_the_bits_of_a_row_do_not_depend_on_the_tiles_of_a_wave(rows, cols, g, form):
+    base = 61
+    w = synth.weights(base, cols, 9800 + cols)
+    x = synth.activations(cols, 9800 + cols)
+    again = lambda a, per: np.resize(np.asarray(a).reshape(base, per), (rows, per))
+    if form == "dense":
+        q, qp = B.quant_int4(w, g)
+        y_ref, a_ref = O.int4_gemv(q, qp, g, x)
+        small, many = G.run_int4_gemv(q, qp, g, x), G.run_int4_gemv(again(q, cols // 2), again(qp, 2 * (cols // g)).reshape(rows, cols // g, 2), g, x)
+    else:
+        if isinstance(form, str) and form.isdigit():
+            nk = np.resize([int(k) for k in form], base).astype(np.int32)
+            mask = np.choose((nk - 1)[:, None], [B.prune_n4(w, n) for n in (1, 2, 3, 4)]).astype(np.uint8)
+            p = B.pack_2bitcsr_rows(w, mask, nk, g, 0)
+            y_ref, a_ref = O.gemv_rows(G.oracle_view(p), x)
+            start, n_all = np.asarray(p.row_ptr, dtype=np.int64), np.resize(nk, rows)
+            ptr = np.concatenate([[0], np.cumsum(n_all * (cols // 4))])
+            part = lambda a, slots: np.concatenate([a[start[r] // slots:start[r + 1] // slots] for r in np.resize(np.arange(base), rows)])
+            big = B.Packed(rows, cols, 0, g, 0, ptr.astype(np.uint32), part(np.asarray(p.values), 2), part(np.asarray(p.idx), 8), again(p.qparams, 2 * (cols // g)).reshape(rows, cols // g, 2), int(ptr[-1]))
+        else:
+            n, kind = {"paired": (2, 2), "fp16": (2, 1)}.get(form, (form, 0))
+            p = B.pack_2bitcsr(w, B.prune_n4(w, n), n, g, kind)
+            y_ref, a_ref = O.gemv(G.oracle_view(p), x)
+            slots = n * cols // 4
+            big = B.Packed(rows, cols, n, g, kind, (np.arange(rows + 1) * slots).astype(np.uint32), again(p.values, 2 * slots if kind == 1 else slots // 2).reshape(-1),
+                           again(p.idx, slots // 8).reshape(-1), None if kind == 1 else again(p.qparams, 2 * (cols // g)).reshape(rows, cols // g, 2))
+        small, many = G.run_sparse_gemv(p, x), G.run_sparse_gemv(big, x)
+    G.assert_close(small, y_ref, a_ref, "61 rows")
+    assert np.array_equal(many.view(np.uint16), np.resize(small.view(np.uint16), rows))
+
+
+@pytest.mark.parametrize("M", [2, 4])
+def test_the_bits_of_a_row_of_few_tokens_do_not_depend_on_the_tiles_of_a_wave(M):
+    rows, base, cols, slots = 1539, 61, 4096, 2048
+    p, o = _small_case(base, cols, 2, 128, 0, seed=9900)
+    X = synth.activation_rows(M, cols, 9900)
+    Y_ref, A_ref = O.gemm_smallm(o, X)
+    again = lambda a, per: np.resize(np.asarray(a).reshape(base, per), (rows, per)).reshape(-1)
+    big = B.Packed(rows, cols, 2, 128, 0, (np.arange(rows + 1) * slots).astype(np.uint32), again(p.values, slots // 2), again(p.idx, slots // 8), again(p.qparams, 64).reshape(rows, 32, 2))
+    small = G.run_sparse_gemm(p, X)
+    G.assert_close(small, Y_ref, A_ref, "61 rows")
+    assert np.array_equal(G.run_sparse_gemm(big, X).view(np.uint16), small.view(np.uint16)[:, np.arange(rows) % base])
 
 
 # Rows that keep three or four among others: a lane a span of 32 columns, 64 spans a block; a block exactly, one span more, three blocks,
@@ -1017,7 +1086,9 @@ def test_fused_projections_equal_the_separate_products(M):
 
 
 @pytest.mark.parametrize("rows,cols,g,count", [(50, 4096, 128, 3), (21, 11008, 128, 2), (30, 320, 64, 2),
-                                               (40, 4096, 64, 4), (40, 4096, 256, 2)])
+                                               (40, 4096, 64, 4), (40, 4096, 256, 2),
+                                               # exact codes: one tile of each unit, several tiles
+                                               (67, 1664, 128, 3), (67, 1856, 64, 2), (19, 2624, 64, 4), (67, 1568, 32, 4), (3533, 992, 32, 2)])
 def test_int4_gemv_batch_equals_separate_calls(rows, cols, g, count):
     torch = G.torch_mod()
     qs, qps, xs = [], [], []

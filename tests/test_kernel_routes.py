@@ -46,7 +46,7 @@ for c in json.loads({calls!r}):
     elif k == "int4": st = L.egt_int4_gemv(P, P, *c["w"], P, P, None)
     else:
         count = c["count"]
-        views = (B.View * count)(*[view(*c["w"]) for _ in range(count)])
+        if k != "int4_batch": views = (B.View * count)(*[view(*c["w"]) for _ in range(count)])
         xs = (C.c_void_p * count)(*[P + (0 if c.get("shared") else 4096 * j) for j in range(count)])
         ys = (C.c_void_p * count)(*[P + (j << 24) for j in range(count)])
         if k == "gemv_batch": st = L.egt_sparse_gemv_batch(views, xs, ys, count, None)
@@ -173,6 +173,12 @@ def test_dense_rows_of_exact_codes(launches, w, codes):
     assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
 
 
+@pytest.mark.parametrize("w", [(300, 1664, 128), (300, 1856, 64), (300, 2624, 64), (4000, 992, 32), (300, 1568, 32)])
+def test_a_batch_of_dense_exact_codes_is_one_launch(launches, w):
+    (call,) = launches([{"call": "int4_batch", "w": w, "count": 4}])
+    assert len(call) == 1 and "k_codes_batchILi3E" in call[0][0] and call[0][2] == 4, call
+
+
 @pytest.mark.parametrize("w", [(300, 1920, 2, 128, 0), (300, 2112, 1, 64, 0), (300, 4128, 2, 32, 2)])
 def test_a_batch_of_exact_codes_is_one_launch(launches, w):
     (call,) = launches([{"call": "gemv_batch", "w": w, "count": 4}])
@@ -200,3 +206,20 @@ def test_tiles_of_a_wave(launches, w, kernel, tiles):
 def test_tiles_of_a_wave_of_dense_rows(launches, w, kernel, tiles):
     (call,) = launches([{"call": "int4", "w": w}])
     assert len(call) == 1 and kernel % tiles in call[0][0], call
+
+
+def test_matrices_of_many_tiles_reach_other_kernels_than_their_first_rows(launches):
+    # (the GPU test of the same cases compares the two)
+    from test_gpu_parity import MANY_TILES
+
+    def call(rows, cols, g, form):
+        if form == "dense":
+            return {"call": "int4", "w": (rows, cols, g)}
+        if isinstance(form, str) and form.isdigit():
+            return {"call": "gemv", "w": (rows, cols, 0, g, 0, sum(int(form[r % len(form)]) for r in range(rows)) * (cols // 4))}
+        n, kind = {"paired": (2, 2), "fp16": (2, 1)}.get(form, (form, 0))
+        return {"call": "gemv", "w": (rows, cols, n, g, kind, 0)}
+    many = _names(launches([call(*c) for c in MANY_TILES]))
+    few = _names(launches([call(61, *c[1:]) for c in MANY_TILES]))
+    for c, a, b in zip(MANY_TILES, many, few):
+        assert len(a) == len(b) == 1 and a != b and a[0].split("IL")[0][-8:] == b[0].split("IL")[0][-8:], (c, a, b)
