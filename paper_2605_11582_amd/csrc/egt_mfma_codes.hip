@@ -594,10 +594,13 @@ int codes_form(const egt_2bitcsr &w) {
 
 // Where the slot-by-slot kernels are not the faster ones (their time over this kernel's, weights in the last-level cache).
 //  - Groups of 64 and 32 make a tile 2048 and 1024 columns: a workgroup that stages a long row of x for four rows.  Two phases
-//    at 1:4 and where rows differ, four otherwise, always win (24000 x 2592 groups of 32: dense 0.78, paired 0.77; 30000 x 2624
-//    groups of 64: 1:4 0.89, rows differ 0.85); more phases while their waves are resident at a time (1000 x 12352, groups of 64:
-//    0.55, 4000 x 4160: 0.9), not beyond (4000 x 8224, groups of 32: 1.1 to 1.7; 24000 x 8224 1.4 to 2.5).  Dense rows
-//    with groups of 64 win throughout (0.57 to 0.88), and groups of 128 and more.
+//    at 1:4 and where rows differ, four otherwise, always win (30000 x 2592 groups of 32: dense 0.80, paired 0.81; 30000 x 2624
+//    groups of 64: 1:4 0.90, rows differ 0.83), but for 1:4 in groups of 32 with many rows (1696 columns: 16000 rows 0.94, 30000 1.03,
+//    60000 1.13).  More phases while their waves are resident at a time (1:4 groups of 32: 5000 x 2592 0.78, 8000 0.93, 16000 1.05; 2:4 5000
+//    x 5152 0.79, 8000 1.02); of long rows fewer: 1:4 and rows that
+//    differ from five phases on up to 2048 rows (2000 and 3200 rows: 1:4 4128 columns 0.87, 1.13; 8256, groups of 64, 0.77, 1.27; rows that
+//    differ 0.66, 1.20), 2:4 from nine phases on the same (8224 columns 0.78, 1.10; 12320 0.74, 1.14), dense 1024 (1000 and 2000 rows: 8224 columns
+//    0.74, 1.14; 12320 0.69, 1.04).  Dense rows with groups of 64 win throughout (0.37 to 0.97), and groups of 128 and more.
 //  - Dense rows of few columns: staging x costs what it saves (300 x 384 1.17, 1000 x 896 1.11, 2000 x 896 1.09; 4000 x 896 0.97,
 //    300 x 1600 0.98).
 //  - Rows of different lengths: a row that keeps three or four costs up to a third more than one of both other kinds together
@@ -612,6 +615,8 @@ static bool codes_pay(int form, const CodesGeom &g, int unit) {
   if (form == CODES_MIXED && cols < 768 && 20 * (uint64_t)g.total_slots > 31 * (uint64_t)g.rows * g.slots_row) return false;
   if (unit == 128 || (dense && unit == 64)) return true;
   const bool one = form == CODES_14 || form == CODES_MIXED;
+  if (form == CODES_14 && unit == 32 && g.phases == 2 && g.rows > 20000) return false;
+  if (g.phases >= (one ? 5 : 9) && g.rows > (dense ? 1024 : 2048)) return false;
   return g.phases <= (one ? 2 : 4) || (int64_t)g.phases * ((g.rows + CODES_TPI - 1) / CODES_TPI) <= (one ? 4096 : 8192);
 }
 

@@ -151,6 +151,9 @@ def test_a_batch_of_short_fp16_rows_is_one_launch(launches, cols):
     ((300, 4224, 1, 128, 0), True), ((300, 4096, 1, 128, 0), False),
     ((30000, 4096, 0, 64, 0), True), ((5460, 4160, 1, 64, 0), True), ((5461, 4160, 1, 64, 0), False), ((5461, 4160, 1, 32, 0), False),    # waves of a row, waves of a launch
     ((5460, 4160, 0, 64, 0), True), ((5461, 4160, 0, 64, 0), False), ((30000, 4096, 2, 32, 2), True), ((6552, 4128, 2, 32, 2), True), ((6553, 4128, 2, 32, 2), False),
+    ((20000, 1696, 1, 32, 0), True), ((20001, 1696, 1, 32, 0), False), ((30000, 1696, 0, 32, 0), True), ((60000, 2112, 1, 64, 0), True),    # long rows, many rows
+    ((2048, 4128, 1, 32, 0), True), ((2049, 4128, 1, 32, 0), False), ((2048, 8256, 0, 64, 0), True), ((2049, 8832, 0, 64, 0), False),
+    ((2048, 8224, 2, 32, 0), True), ((2049, 8224, 2, 32, 0), False), ((2049, 8224, 2, 32, 2), False), ((5000, 5152, 2, 32, 2), True),
     ((300, 16384, 0, 32, 0), True), ((300, 16416, 0, 32, 0), False),
     ((300, 2816, 0, 0, 1), False),                                                                          # FP16 values
 ])
@@ -167,7 +170,8 @@ def test_short_rows_that_differ_of_exact_codes(launches, rows, cols, slots, code
 
 
 @pytest.mark.parametrize("w,codes", [((5003, 2880, 64), True), ((70, 1536, 128), True), ((2278, 1504, 32), False), ((2400, 1504, 32), True), ((300, 384, 128), False), ((300, 2944, 128), False),
-                                     ((300, 24512, 64), True), ((300, 24640, 64), False), ((24000, 4064, 32), True), ((6552, 4128, 32), True), ((6553, 4128, 32), False), ((300, 2880, 36), False)])
+                                     ((300, 24512, 64), True), ((300, 24640, 64), False), ((24000, 4064, 32), True), ((6552, 4128, 32), True), ((6553, 4128, 32), False), ((300, 2880, 36), False),
+                                     ((1024, 8224, 32), True), ((1025, 8224, 32), False)])
 def test_dense_rows_of_exact_codes(launches, w, codes):
     (call,) = launches([{"call": "int4", "w": w}])
     assert len(call) == 1 and ("k_codes" in call[0][0]) == codes, call
