@@ -62,7 +62,9 @@ hipError_t launch_int4_m1_batch(const uint8_t *const *qs, const uint16_t *const 
   // few tiles: one or two to a wave, as in egt_mfma_m1.hip (4096 x 1024 2.8 -> 2.6 us, 2048 x 2048 2.9 -> 2.7, 1024 x 4096 3.2 -> 3.0, 1024 x 11008
   // 4.9 -> 3.9; 4096 x 2048: 2.95 with four, 3.2 with one; 2048 x 4096: 3.3, 3.45)
   const int64_t tiles = (int64_t)g.ntiles * count;
-  if (g.phases == 1 ? tiles <= 2048 : tiles <= 1024) {
+  // (of more than eight phases one wave each: 400 x 20224 4.8 with four, 4.3 with two; 512 4.9, 4.4; 640 4.7, 5.2;
+  // 768 4.7, 5.3; 1024 4.9, 6.0; 1024 x 28672 6.2, 7.1)
+  if (tiles <= (g.phases == 1 ? 2048 : g.phases > 8 ? 512 : 1024)) {
     tpi = g.phases <= 4 ? 1 : 2;
     if (g.phases <= 4) wpp = 4;
   }

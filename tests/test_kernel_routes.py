@@ -206,7 +206,7 @@ def test_tiles_of_a_wave(launches, w, kernel, tiles):
 
 
 @pytest.mark.parametrize("w,kernel,tiles", [((2048, 2048, 128), "k_int4_m1ILi%dE", 1), ((2049, 2048, 128), "k_int4_m1ILi%dE", 4), ((1024, 8192, 128), "k_int4_m1ILi%dE", 1), ((1025, 8192, 128), "k_int4_m1ILi%dE", 4),
-                                            ((1024, 11008, 128), "k_int4_m1ILi%dE", 2), ((5120, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 2), ((5121, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 4)])
+                                            ((1024, 11008, 128), "k_int4_m1ILi%dE", 2), ((512, 20224, 256), "k_int4_m1ILi%dE", 2), ((513, 20224, 256), "k_int4_m1ILi%dE", 4), ((1024, 16384, 128), "k_int4_m1ILi%dE", 2), ((5120, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 2), ((5121, 2880, 64), "k_codesILi3ELi32ELi32ELi%dE", 4)])
 def test_tiles_of_a_wave_of_dense_rows(launches, w, kernel, tiles):
     (call,) = launches([{"call": "int4", "w": w}])
     assert len(call) == 1 and kernel % tiles in call[0][0], call
