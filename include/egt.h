@@ -90,8 +90,8 @@ typedef enum {
  * `word & 0x00F000F0` the pair (2, 3), and the same two masks on `word >> 8` the pairs
  * (4, 5) and (6, 7): the pairs a matrix-core operand register wants, without a byte
  * permute.  Everything else (index words, parameters, sizes, row pointers) is as for
- * EGT_VAL_INT4.  The M = 1 kernels for 2:4 with groups of 128 columns and more are tuned
- * for it; every other call takes it through the slot-by-slot kernels. */
+ * EGT_VAL_INT4.  At M = 1 and 2:4 with groups of 32 << j columns it runs on the matrix
+ * cores as EGT_VAL_INT4 does; every other call takes it through the slot-by-slot kernels. */
 typedef enum { EGT_VAL_INT4 = 0, EGT_VAL_FP16 = 1, EGT_VAL_INT4_PAIRED = 2 } egt_val_kind;
 
 /* A view of one matrix in 2bit-CSR.  The struct itself lives in host memory.
@@ -201,9 +201,9 @@ egt_status egt_int4_gemv(const uint8_t *q, const uint16_t *qparams, int rows, in
 /* DEVICE.  SparseGemv (Sec. 3.3 "Computational Acceleration"): y = W.x for W in
  * 2bit-CSR with INT4 or FP16 values.  x: cols FP16, y: rows FP16.  A row whose
  * row_ptr entry is not r*S yields NaN in y[r] (the kernel checks it).  Rows of
- * different lengths (n_keep = 0) are followed through row_ptr by a slot-by-slot kernel;
- * a row whose pointers do not describe a whole row of 1..4 entries per 4-group that
- * starts on an index word and ends inside total_slots yields NaN and is never read. */
+ * different lengths (n_keep = 0) are followed through row_ptr; a row whose pointers do not
+ * describe a whole row of 1..4 entries per 4-group that starts on an index word and ends
+ * inside total_slots yields NaN and is never read. */
 egt_status egt_sparse_gemv(const egt_2bitcsr *w, const uint16_t *x, uint16_t *y, void *stream);
 
 /* DEVICE.  Small-M form for tree-based parallel verification (Sec. 3.4): the M
@@ -253,9 +253,9 @@ egt_status egt_sparse_gemm_smallm_static(const egt_2bitcsr *w, const uint16_t *X
  * launch: the q/k/v or gate/up projections of a decoder layer.  Sec. 3.3 starts from
  * one kernel per linear layer; fusing the launches removes the fixed cost a short
  * kernel cannot amortise.  w: array of `count` views; x, y: arrays of `count` device
- * pointers (host arrays of device pointers).  Where no batched kernel takes the shape (the
- * paired nibble order, shapes of the slot-by-slot kernels) the members run as one launch
- * each.  Results equal those of `count` separate
+ * pointers (host arrays of device pointers).  Where no batched kernel takes the shape (rows
+ * of different lengths; the paired nibble order with 1024 or 2048 columns or whole 64s from
+ * 4096 on; shapes of the slot-by-slot kernels) the members run as one launch each.  Results equal those of `count` separate
  * egt_sparse_gemv / egt_int4_gemv calls bit for bit. */
 egt_status egt_sparse_gemv_batch(const egt_2bitcsr *w, const uint16_t *const *x, uint16_t *const *y,
                                  int count, void *stream);

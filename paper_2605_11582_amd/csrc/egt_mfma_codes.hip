@@ -28,10 +28,10 @@
 //    requests out of range at the end of a walk are not free.)
 //  - x goes from global memory straight into LDS, its pieces swizzled as in egt_rows.hip.
 //
-// Measured, us per launch slot by slot and now (weights in the last-level cache): half of 11008 x 4096's rows at 1:4 11.6, 6.5;
-// dense 5003 x 2880 groups of 64 5.6, 4.8; 2:4 20000 x 2816 14.5, 7.5; 2000 x 3072 5.8, 3.5; 50000 x 512 14.4, 4.3; 1:4 4096 x 3072 5.3,
-// 3.7; dense 60000 x 384 11.6, 4.6; 512 x 14400 8.5, 4.4.  What bounds it: the launch for a few megabytes, then vector issue (about 85
-// instructions for 4096 columns of a row, 470 a wave) and memory (20000 x 2816: 42 MB at 5.7 TB/s).
+// Measured, us per launch slot by slot and now (weights in the last-level cache): half of 11008 x 4096's rows at 1:4 11.6, 6.1;
+// dense 5003 x 2880 groups of 64 5.6, 4.3; 2:4 20000 x 2816 14.5, 7.0; 2000 x 3072 5.8, 2.8; 50000 x 512 14.4, 3.9; 1:4 4096 x 3072 5.3,
+// 3.2; dense 60000 x 384 11.6, 4.2; 512 x 14400 8.5, 4.4.  What bounds it: the launch for a few megabytes, then vector issue (a wave
+// of four tiles 460 instructions at 2:4, 590 where rows differ, of two dense ones 240) and memory (20000 x 2816: 42 MB at 6.0 TB/s).
 #include "egt_mfma_common.h"
 #include "egt_tune.h"
 
@@ -562,9 +562,11 @@ bool codes_geometry(int form, int rows, int cols, int n_keep, int group, uint32_
 void codes_shape(CodesGeom &g, int unit, int form, int count, int &tpi, dim3 &grid, dim3 &block, size_t &lds) {
   const size_t x_bytes = ((size_t)g.units * (size_t)(2 * unit) + 1023) & ~(size_t)1023;
   const int nrg = (g.rows + g.rpt - 1) / g.rpt;       // row groups
-  // Few tiles: one or two to a wave, since the launch then lasts as long as a wave's instructions (us with 1, 2, 4 tiles a wave:
-  // 300 x 768 2.6, 2.8, 3.3; 4000 x 1920 3.1, 3.2, 3.7; 5000 x 3072 4.1, 4.0, 4.4; 11008 x 3072 6.1, 5.6, 5.4; dense 5003 x 2880,
-  // 10006 tiles, 5.3, 4.7, 4.9).
+  // Few tiles: one or two to a wave, since the launch then lasts as long as a wave's instructions.  Us with 1, 2, 4 tiles a wave,
+  // on either side of the lines: 2:4 2000 x 3072 2.9, 2.8, 3.2; 3000 3.1, 3.1, 3.3; 5000 3.8, 3.6, 4.0; 6000 4.05, 3.7, 4.1; 7000 4.4, 4.1, 4.1;
+  // 11000 5.5, 5.1, 5.0 (1:4 and the paired order alike); rows that differ 5000 x 4096 4.4, 4.3, 5.0, 7000 5.3, 4.9, 5.1, 11000 6.9, 6.3, 6.1;
+  // dense 1050 x 2880, two tiles a row, 2.9, 2.9, 3.1, 4000 4.3, 3.9, 3.8, 5000 4.8, 4.2, 4.4, 5200 5.0, 4.5, 4.4, 8000 6.3, 5.4, 5.1; dense 10000 x
+  // 1664 4.3, 3.75, 4.0, 12000 4.8, 4.05, 4.1.  (Sparse rows of 5120 to 6500 tiles would gain up to a tenth with two.)
   const int64_t tiles = (int64_t)nrg * g.phases * count;
   tpi = tiles <= 2048 ? 1 : tiles <= (form == CODES_DENSE ? 10240 : 5120) ? 2 : 4;
   int waves = 4;                                      // (2, 6 and 8 waves: 1.1 to 1.5 times the time on 20000 x 2816 and 11008 x 4096)

@@ -247,7 +247,10 @@ bool plan_stream(const egt_gemv_item *items, const std::vector<ItemShape> &shape
   // partly filled tile to finish last, 77 matrices 118 us, now 112.)
   // Two to eight workgroups per compute unit, two of them resident at a time: spans of about
   // 0.9 MB (x is staged once per item, so a span should hold many rows; shorter spans finish
-  // more evenly: 1.9 GB of 2:4 and dense matrices take 318 us with 1280 spans, 314 with 1536, 308 with 2048).
+  // more evenly): one more per compute unit for every 220 MiB.  Us with one, two, three, five and eight per compute unit, * what
+  // the rule takes at that size: 2:4 and dense matrices 0.19 GB 38, *35, 36, 36, 40; 0.57 GB 101, *102, 99, 94, 92; 0.76 GB 139, 137, *130,
+  // 129, 123; 1.14 GB 202, 202, 199, *188, 188; 1.9 GB 340, 333, 317, 317, *307; 2.7 GB 468, 463, 438, 437, *432; 1:4 0.35 GB 86, *80, 78, 79, 81;
+  // 0.62 GB 147, 131, *130, 128, 133; 1.24 GB 283, 257, 244, *248, 250; dense 0.65 GB 114, 114, *110, 106, 103; 1.08 GB 187, 184, 178, *179, 171.
   // below 72 MB one span per compute unit
   // (1:4: two at least - its workgroups have 8 waves, and one per compute unit would leave half the waves out)
   if (bpc < 1) { bpc = (int)((total + (110ull << 20)) / (220ull << 20)); bpc = (total < (72ull << 20) && forms != 2) ? 1 : bpc < 2 ? 2 : bpc; }
