@@ -268,7 +268,7 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
                                egt_gemm_plan *plan) {
   if (!items || !plan) return EGT_ERR_NULL;
   if (count < 1 || count > 65535 || M < 2 || M > 64) return EGT_ERR_SHAPE;
-  uint64_t nwg = 0;
+  uint64_t limit = 0, nwg = 0;
   for (int k = 0; k < count; ++k) {
     const egt_2bitcsr *w = items[k].sparse;
     if (!w) return EGT_ERR_NULL;
@@ -282,17 +282,22 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
     if (w->n_keep != items[0].sparse->n_keep) return EGT_ERR_UNSUPPORTED;   // one storage form per table (one kernel)
     const int blocks = egt::smallm_stack_blocks(M, w->n_keep, w->rows);
     if (blocks > 0xFFFF) return EGT_ERR_UNSUPPORTED;                         // (the list names a workgroup's place in 16 bits)
-    nwg += (uint64_t)blocks;
+    limit += (uint64_t)blocks;
   }
-  if (nwg > (1u << 24)) return EGT_ERR_UNSUPPORTED;
+  if (limit > (1u << 24)) return EGT_ERR_UNSUPPORTED;
   const int n_keep = items[0].sparse->n_keep;
+  int threads, lds, tiles;
+  egt::smallm_stack_shape(M, n_keep, items, count, threads, lds, tiles);
+  auto blocks_of = [&](int r) { return ((r + 15) / 16 + tiles - 1) / tiles; };
+  for (int k = 0; k < count; ++k) nwg += (uint64_t)blocks_of(items[k].sparse->rows);   // (no more of them than counted above)
   egt_gemm_plan out;
   std::memset(&out, 0, sizeof(out));
   out.count = count;
   out.M = M;
   out.n_keep = n_keep;
   out.grid_x = (int32_t)nwg;
-  egt::smallm_stack_shape(M, n_keep, out.grid_x, out.block_threads, out.lds_bytes);
+  out.block_threads = threads;
+  out.lds_bytes = lds;
   out.table_bytes = gemm_table_bytes(count, out.grid_x);
   if (table) {
     if ((uint64_t)table_bytes < out.table_bytes) return EGT_ERR_SHAPE;
@@ -313,7 +318,7 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
       uint64_t n = 0, at = 0, first = 0;              // workgroups of the run; the next one's place in it, and that place modulo 8
       int members = 0;
       for (; k1 < count && items[order[(size_t)k1]].sparse->cols == items[order[(size_t)k0]].sparse->cols; ++k1) {
-        const int blocks = egt::smallm_stack_blocks(M, n_keep, items[order[(size_t)k1]].sparse->rows);
+        const int blocks = blocks_of(items[order[(size_t)k1]].sparse->rows);
         n += (uint64_t)blocks;
         members += blocks != 0;
       }
@@ -321,7 +326,7 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
       for (int k = k0; k < k1; ++k) {
         const egt_gemm_item &it = items[order[(size_t)k]];
         egt::smallm_stack_entry(*it.sparse, it.X, it.Y, M, (uint8_t *)table + (size_t)k * EGT_STACK_ENTRY_BYTES);
-        const int blocks = egt::smallm_stack_blocks(M, n_keep, it.sparse->rows);
+        const int blocks = blocks_of(it.sparse->rows);
         for (int x = 0; x < blocks; ++x) {
           list[at] = ((uint32_t)k << 16) | (uint32_t)x;                        // matrix, place in the matrix
           at += step;
@@ -341,14 +346,11 @@ egt_status egt_gemm_stack_run(const void *table_dev, const egt_gemm_plan *plan, 
   if (plan->count < 1 || plan->count > 65535 || plan->M < 2 || plan->M > 64 || (plan->n_keep != 1 && plan->n_keep != 2) ||
       (plan->n_keep == 1 && plan->M > 32))
     return EGT_ERR_SHAPE;
-  int threads, lds;
-  egt::smallm_stack_shape(plan->M, plan->n_keep, plan->grid_x, threads, lds);
-  if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || plan->lds_bytes != lds ||
-      !egt::smallm_stack_threads_ok(plan->M, plan->n_keep, plan->grid_x, plan->block_threads) ||
+  if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || !egt::smallm_stack_form_ok(plan->M, plan->n_keep, plan->block_threads, plan->lds_bytes) ||
       plan->table_bytes != gemm_table_bytes(plan->count, plan->grid_x))
     return EGT_ERR_SHAPE;
   if (plan->grid_x == 0) return EGT_OK;               // every matrix is empty
-  return done(egt::launch_smallm_stack(table_dev, plan->count, plan->M, plan->n_keep, plan->grid_x, plan->block_threads, (hipStream_t)stream));
+  return done(egt::launch_smallm_stack(table_dev, plan->count, plan->M, plan->n_keep, plan->grid_x, plan->block_threads, plan->lds_bytes, (hipStream_t)stream));
 }
 
 egt_status egt_int4_gemv_batch(const uint8_t *const *q, const uint16_t *const *qparams, int rows,

@@ -1248,6 +1248,10 @@ __global__ __launch_bounds__(64 * W, 2) void k_smallm_rows_two(const uint8_t *__
   smallm_rows_body<NG, Q, W, N1, 2>(table, count);
 }
 
+}  // namespace egt
+#include "egt_stack_tiles_body.h"
+namespace egt {
+
 // Shapes the stack takes: INT4 with one {scale, zero} pair per chunk, 2:4 (up to 64 tokens) or 1:4 (up to 32: the
 // token rows of a K-step are twice as long).
 bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
@@ -1256,23 +1260,54 @@ bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
   return sparse_smallm_supported(w, w.cols, M);
 }
 
-// Waves of a workgroup that owns sixteen row tiles: sixteen, or eight with two tiles each (see k_smallm_rows).
-// Tables of fewer than 128 workgroups leave half of the compute units idle in either form and keep the first.
-static bool stack_two_tiles(int grid_x) { return grid_x >= 128; }
+// Launch forms of a table, told apart by the plan's threads and LDS bytes:
+//  - k_stack_tiles with a row tile a wave or two;
+//  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, and at any size plans that were kept from
+//    before there was k_stack_tiles.
+struct StackForm {
+  int threads, tiles, lds;                            // of a workgroup
+};
 static bool stack_sixteen(int M, bool n1) { return M > (n1 ? 16 : 32); }
+static int stack_lds_rows(int M, bool n1) {
+  if (n1) return rs_lds_bytes(M <= 16 ? 1 : 2, 2, true);
+  return M <= 16 ? rs_lds_bytes(1, RS_Q) : M <= 32 ? rs_lds_bytes(2, 2) : rs_lds_bytes(4, 2);
+}
+// Two row tiles a wave: four token groups (at 1:4 two) always, since one workgroup then fills the LDS of a compute unit
+// anyway; two groups (1:4: one) in tables of 400 MB and more.  Those are fetched from HBM whatever ran before, in 128-byte pieces
+// of a row with two tiles and 64-byte ones with one; smaller tables would miss the second workgroup of a compute unit.  us with
+// one tile, two, three tables in turn: 24 tokens, layers of 4096 x 11008: two of them (164 MB) 57.8, 74.3; four 106.3,
+// 107.7; six (490 MB) 155.1, 150.0; ten of 6144 x 20480 (2.1 GB) 584.8, 552.6; 1:4 at 16 tokens, two of 4096 x 11008 35.4,
+// 43.9, eight (330 MB) 123.2, 120.2, ten of 6144 x 20480 358.2, 333.1; at 5 tokens twelve of 2048 x 8192 (160 MB) 59.7, 65.9.
+// 2:4 up to 16 tokens always one: sixteen layers of a 7B stack at 16 tokens 297, 304.
+static bool stack_two_tiles(int M, bool n1, uint64_t bytes) { return stack_sixteen(M, n1) || ((n1 || M > 16) && bytes >= 400000000ull); }
+static StackForm stack_form_tiles(int M, bool n1, bool two) {
+  if (stack_sixteen(M, n1)) return {512, 16, st_lds_bytes(n1 ? 2 : 4, 2, 32, false, n1)};
+  const int ng = M <= 16 ? 1 : 2;
+  if (ng == 1 && !n1) return {512, 8, st_lds_bytes(1, 1, 128, false, false)};
+  return two ? StackForm{512, 16, st_lds_bytes(ng, 2, 128, false, n1)} : StackForm{512, 8, st_lds_bytes(ng, 1, 32, true, n1)};
+}
+static StackForm stack_form_rows(int M, bool n1) {
+  return stack_sixteen(M, n1) ? StackForm{1024, 16, stack_lds_rows(M, n1)} : StackForm{64 * RS_WAVES, RS_WAVES, stack_lds_rows(M, n1)};
+}
 
-// workgroups of a matrix
+// Workgroups of a matrix in the forms that every table once had: what a plan may not exceed.
 int smallm_stack_blocks(int M, int n_keep, int rows) {
-  const int ntiles = (rows + 15) / 16, per = stack_sixteen(M, n_keep == 1) ? 16 : RS_WAVES;
+  const int ntiles = (rows + 15) / 16, per = stack_form_rows(M, n_keep == 1).tiles;
   return (ntiles + per - 1) / per;
 }
 
-// Launch shape of a table of grid_x workgroups.
-void smallm_stack_shape(int M, int n_keep, int grid_x, int &block_threads, int &lds_bytes) {
+// Launch shape of a table: threads, LDS bytes and row tiles of a workgroup.
+void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles) {
   const bool n1 = n_keep == 1;
-  block_threads = 64 * (stack_sixteen(M, n1) ? (stack_two_tiles(grid_x) ? 8 : 16) : RS_WAVES);
-  if (n1) lds_bytes = rs_lds_bytes(M <= 16 ? 1 : 2, 2, true);
-  else lds_bytes = M <= 16 ? rs_lds_bytes(1, RS_Q) : M <= 32 ? rs_lds_bytes(2, 2) : rs_lds_bytes(4, 2);
+  uint64_t bytes = 0, blocks = 0;
+  for (int k = 0; k < count; ++k) {
+    const egt_2bitcsr &w = *items[k].sparse;
+    bytes += (uint64_t)w.rows * (uint64_t)(w.n_keep * (w.cols / 16) * 3 + 4 * (w.cols / w.group_size));
+  }
+  StackForm f = stack_form_tiles(M, n1, stack_two_tiles(M, n1, bytes));
+  for (int k = 0; k < count; ++k) blocks += (uint64_t)(((items[k].sparse->rows + 15) / 16 + f.tiles - 1) / f.tiles);
+  if (blocks <= (n1 || M > 32 ? 127 : 64)) f = stack_form_rows(M, n1);
+  block_threads = f.threads; lds_bytes = f.lds; tiles = f.tiles;
 }
 
 // Descriptor of one item into 160 bytes of the table.
@@ -1287,19 +1322,27 @@ void smallm_stack_entry(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, in
   std::memcpy(entry, &e, sizeof(e));
 }
 
-// The kernel follows the plan's threads: a plan with sixteen waves, as every such table once had, is good at any size
-// (the table is the same in either form).
-bool smallm_stack_threads_ok(int M, int n_keep, int grid_x, int block_threads) {
-  int threads, lds;
-  smallm_stack_shape(M, n_keep, grid_x, threads, lds);
-  return block_threads == threads || (stack_sixteen(M, n_keep == 1) && block_threads == 1024);
+// The kernel follows the plan's threads and LDS bytes.  A plan with sixteen waves, as every table of sixteen tiles a workgroup once
+// had, is good at any size (the table is the same in every form with sixteen tiles).
+bool smallm_stack_form_ok(int M, int n_keep, int block_threads, int lds_bytes) {
+  const bool n1 = n_keep == 1;
+  const bool known = lds_bytes == stack_lds_rows(M, n1) || lds_bytes == stack_form_tiles(M, n1, false).lds || lds_bytes == stack_form_tiles(M, n1, true).lds;
+  return known && (block_threads == 512 || (block_threads == 1024 && stack_sixteen(M, n1)));
 }
 
-hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, int block_threads, hipStream_t stream) {
-  int threads, lds;
-  smallm_stack_shape(M, n_keep, grid_x, threads, lds);
+hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, int block_threads, int lds_bytes, hipStream_t stream) {
+  const bool n1 = n_keep == 1;
   const dim3 grid(grid_x), block(block_threads);
   const uint8_t *t = (const uint8_t *)table_dev;
+#define EGT_ST(...) launch(k_stack_tiles<__VA_ARGS__>, grid, block, (size_t)lds_bytes, stream, t, count)
+  if (block_threads == 512 && lds_bytes == stack_form_tiles(M, n1, false).lds) {
+    if (n1) return M <= 16 ? EGT_ST(1, 1, 32, true, true) : EGT_ST(2, 2, 32, false, true);
+    return M <= 16 ? EGT_ST(1, 1, 128, false, false) : M <= 32 ? EGT_ST(2, 1, 32, true, false) : EGT_ST(4, 2, 32, false, false);
+  }
+  if (block_threads == 512 && lds_bytes == stack_form_tiles(M, n1, true).lds)
+    return n1 ? EGT_ST(1, 2, 128, false, true) : EGT_ST(2, 2, 128, false, false);
+#undef EGT_ST
+  const int lds = stack_lds_rows(M, n1);
 #define EGT_RS(...) launch(k_smallm_rows<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
 #define EGT_RS2(...) launch(k_smallm_rows_two<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
   const bool two = block_threads == 512;

@@ -592,6 +592,90 @@ def test_gemm_stack_of_many_workgroups_has_the_bits_of_small_tables(M, n):
         call()
 
 
+# LDS bytes of a plan that runs on k_smallm_rows, and its threads where a workgroup owns sixteen row tiles
+ROWS_FORM = {2: [(16, 67584, 512), (32, 67584, 512), (64, 135168, 1024)], 1: [(16, 66560, 512), (32, 133120, 1024)]}
+
+
+def _on_smallm_rows(plan):
+    plan.lds_bytes, plan.block_threads = next((lds, threads) for top, lds, threads in ROWS_FORM[plan.n_keep] if plan.M <= top)
+
+
+@pytest.mark.parametrize("M,n", [(2, 2), (5, 2), (16, 2), (17, 2), (32, 2), (33, 2), (64, 2), (3, 1), (16, 1), (17, 1), (32, 1)])
+def test_gemm_stack_windows_of_parameters(M, n):
+    # k_stack_tiles fetches the parameters of a row 32, 64 or 128 bytes at a time: rows whose pairs fill such windows and rows
+    # whose last one is short, an odd number of chunks, groups of half a window and of many, ragged last tiles, a row of one
+    # chunk; against the oracle, and the bits of the kernel that takes small tables
+    torch = G.torch_mod()
+    print(f"case gemm stack windows M={M} n={n}", flush=True)
+    if n == 2:
+        shapes = [(33000, 256, 64), (21, 4160, 64), (130, 4096, 128), (50, 4224, 128), (33, 2112, 64), (17, 512, 512), (40, 64, 64),
+                  (1, 128, 128), (16, 2048, 64), (47, 8192, 8192)]
+    else:
+        shapes = [(33000, 256, 128), (21, 4224, 128), (130, 8192, 256), (50, 4096, 128), (33, 4352, 128), (17, 1024, 1024), (40, 128, 128)]
+    ps, os_, Xs = [], [], []
+    for k, (rows, cols, g) in enumerate(shapes):
+        w = synth.weights(rows, cols, 9400 + k)
+        mask = O.prune_n4_magnitude(w, n)
+        ps.append(B.pack_2bitcsr(w, mask, n, g, B.VAL_INT4))
+        os_.append(O.pack_2bitcsr(w, mask, n, g, B.VAL_INT4) if rows <= 200 else None)
+        Xs.append(synth.activation_rows(M, cols, 9400 + k))
+    ps[2].row_ptr[77] += 8
+    pds = [p.to("cuda:0") for p in ps]
+    Xd = [G.to_dev(X.view(np.uint16)).view(torch.float16) for X in Xs]
+    ybufs = [torch.full((128 + M * p.rows,), G.CANARY, dtype=torch.int16, device="cuda:0") for p in ps]
+    Yd = [yb[64:64 + M * p.rows].view(torch.float16).view(M, p.rows) for yb, p in zip(ybufs, ps)]
+    call = B.prepared_gemm_stack(list(zip(pds, Xd, Yd)))
+    assert call.plan.block_threads == 512 and call.plan.lds_bytes not in [lds for _, lds, _ in ROWS_FORM[n]]
+    call()
+    torch.cuda.synchronize()
+    for k, p in enumerate(ps):
+        host = ybufs[k].cpu().numpy().view(np.uint16)
+        assert np.all(host[:64] == G.CANARY) and np.all(host[64 + M * p.rows:] == G.CANARY), ("write outside Y", k)
+        if os_[k] is None:
+            continue
+        Y = host[64:64 + M * p.rows].view(np.float16).reshape(M, p.rows)
+        Y_ref, A_ref = O.gemm_smallm(os_[k], Xs[k])
+        good = np.ones(p.rows, dtype=bool)
+        good[[77] if k == 2 else []] = False
+        assert np.all(np.isnan(Y[:, ~good]))
+        G.assert_close(Y[:, good], Y_ref[:, good], A_ref[:, good], f"windows member {k}")
+    first = [yb.clone() for yb in ybufs]
+    for y in Yd:
+        y.zero_()
+    _on_smallm_rows(call.plan)                        # (as a plan that was kept from before; the table is the same)
+    call()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(first, ybufs))
+
+
+@pytest.mark.parametrize("M,n", [(17, 2), (32, 2), (5, 1), (16, 1)])
+def test_gemm_stack_large_tables_take_two_tiles_a_wave(M, n):
+    # tables of 400 MB and more (one matrix many times over, each with a Y of its own): the bits of a table of one
+    torch = G.torch_mod()
+    print(f"case gemm stack large M={M} n={n}", flush=True)
+    rows, cols = 11000 + 5, 4096 + 128
+    w = synth.weights(rows, cols, 9500)
+    p = B.pack_2bitcsr(w, B.prune_n4(w, n), n, 128, B.VAL_INT4).to("cuda:0")
+    X = G.to_dev(synth.activation_rows(M, cols, 9500).view(np.uint16)).view(torch.float16)
+    count = -(-400_000_000 // (p.nbytes() - 4 * (rows + 1)))
+    alone = torch.zeros((M, rows), dtype=torch.float16, device="cuda:0")
+    one = B.prepared_gemm_stack([(p, X, alone)])
+    one()
+    Y = torch.zeros((count, M, rows), dtype=torch.float16, device="cuda:0")
+    call = B.prepared_gemm_stack([(p, X, y) for y in Y])
+    fewer = B.prepared_gemm_stack([(p, X, y) for y in Y[1:]])
+    assert call.plan.grid_x == count * -(-rows // 256) and fewer.plan.grid_x == (count - 1) * -(-rows // 128)
+    call()
+    torch.cuda.synchronize()
+    assert all(torch.equal(y.view(torch.int16), alone.view(torch.int16)) for y in Y) and float(alone.abs().max()) > 0
+    again = torch.zeros_like(alone)
+    kept = B.prepared_gemm_stack([(p, X, again)])
+    _on_smallm_rows(kept.plan)
+    kept()
+    torch.cuda.synchronize()
+    assert torch.equal(again.view(torch.int16), alone.view(torch.int16))
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_gemm_stack_seeded_sweep_of_shapes(seed):
     # seeded tables: row counts around the tile and workgroup sizes, row lengths that end anywhere inside a K-step or
