@@ -211,12 +211,17 @@ __device__ __forceinline__ void stack_tiles_body(const uint8_t *__restrict__ tab
   load(raw0, 0);
   dma_x(0, 0);
   load(raw1, 1);
-  auto round = [&](RoundRegs (&cur)[T], int j, int buf) {
-    wait_vmem<T * LPT>();                             // the weights of the round and this wave's share of X(j) have arrived
+  // (The last round of an odd number requests nothing and waits for everything: the compiler drops or moves requests whose
+  //  registers are not read on the way there, so none may be counted on.)
+  auto round = [&](RoundRegs (&cur)[T], int j, int buf, auto last_round) {
+    constexpr bool LAST = decltype(last_round)::v != 0;
+    // the weights of the round and this wave's share of X(j) have arrived
+    if constexpr (LAST) wait_vmem<0>();
+    else wait_vmem<T * LPT>();
     zero_tail(j, buf);
     // X(j) of every wave has landed; nobody reads the region of round j - 1 any more
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    dma_x(j + 1, buf ^ 1);
+    if constexpr (!LAST) dma_x(j + 1, buf ^ 1);
     Operands ops[Q][T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -225,11 +230,11 @@ __device__ __forceinline__ void stack_tiles_body(const uint8_t *__restrict__ tab
       for (int q = 0; q < Q; ++q) ops[q][t].qp = get_q(Q * j + q, t);
     }
     const int next = Q * (j + 1);
-    if ((next & window_mask) == 0 && next < nsteps) { // uniform: the next round begins a window
+    if (!LAST && (next & window_mask) == 0 && next < nsteps) { // uniform: the next round begins a window
       wait_lds();                                     // this one has been read
       load_q(next / (window_mask + 1));
     }
-    load(cur, j + 2);                                 // (the fetch registers are free again)
+    if constexpr (!LAST) load(cur, j + 2);            // (the fetch registers are free again)
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       // (a step past K, a wave without a tile: requested out of range, zeros with scale 0)
@@ -283,10 +288,10 @@ __device__ __forceinline__ void stack_tiles_body(const uint8_t *__restrict__ tab
   };
   int j = 0;
   for (; j + 2 <= nrounds; j += 2) {
-    round(raw0, j, 0);
-    round(raw1, j + 1, 1);
+    round(raw0, j, 0, IC<0>());
+    round(raw1, j + 1, 1, IC<0>());
   }
-  if (j < nrounds) round(raw0, j, 0);
+  if (j < nrounds) round(raw0, j, 0, IC<1>());
   wait_vmem<0>();                                     // (no request for LDS outlives the workgroup)
   // register v of lane l = D[row 4 (l >> 4) + v][token l & 15]: four consecutive rows of one token
   const uint64_t good = __builtin_amdgcn_ballot_w64(fchecked && frp == (uint32_t)frow * S_row);
