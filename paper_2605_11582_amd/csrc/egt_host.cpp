@@ -4,6 +4,7 @@
 #include "egt.h"
 
 #include "egt_host_simd.h"
+#include "egt_host_simd512.h"
 
 #include <algorithm>
 #include <atomic>
@@ -329,11 +330,20 @@ egt_status egt_prune_n4(const uint16_t *w, int64_t ldw, int rows, int cols, int 
   if (!w || !mask) return EGT_ERR_NULL;
   if (rows < 0 || cols < 0 || cols % 4 != 0 || n_keep < 1 || n_keep > 4 || ldw < cols || ldm < cols)
     return EGT_ERR_SHAPE;
+#ifdef EGT_HOST_SIMD512
+  const bool wide = egt_simd512::available() && cols % 64 == 0;
+#endif
   parallel_rows(rows, cols, [=](int r0, int r1) {
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       uint8_t *mr = mask + (int64_t)r * ldm;
 #ifdef EGT_HOST_SIMD
+#ifdef EGT_HOST_SIMD512
+      if (wide) {
+        egt_simd::with_n(n_keep, [&](auto c) { egt_simd512::prune_row<decltype(c)::n>(wr, cols, mr); });
+        continue;
+      }
+#endif
       if (egt_simd::available()) { egt_simd::prune_row(wr, cols, n_keep, mr); continue; }
 #endif
       for (int c = 0; c < cols; c += 4) {
@@ -448,6 +458,10 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
                              : check_shape(rows, cols, n_keep, group, val_kind);
   if (st != EGT_OK) return st;
   auto n_of = [=](int r) { return row_n_keep ? (int)row_n_keep[r] : n_keep; };
+#ifdef EGT_HOST_SIMD512
+  // (whole registers only: a matrix with a ragged end takes the 256-bit loops for all of it)
+  const bool wide = egt_simd512::available() && cols % 64 == 0 && (!is_int4(val_kind) || group % 32 == 0);
+#endif
   if (ldw < cols || ldm < cols) return EGT_ERR_SHAPE;
   if (!out->row_ptr || !out->values || !out->idx) return EGT_ERR_NULL;
   if (is_int4(val_kind) && !out->qparams) return EGT_ERR_NULL;
@@ -469,6 +483,9 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
       const uint8_t *mr = mask + (int64_t)r * ldm;
       const int n_row = n_of(r);
 #ifdef EGT_HOST_SIMD
+#ifdef EGT_HOST_SIMD512
+      if (wide && egt_simd512::row_valid(wr, mr, cols, n_row)) continue;
+#endif
       if (egt_simd::available() && egt_simd::row_valid(wr, mr, cols, n_row)) continue;
 #endif
       for (int c = 0; c < cols; c += 4) {
@@ -522,6 +539,10 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
 #ifdef EGT_HOST_SIMD
           if (simd) {
             float lo, hi;
+#ifdef EGT_HOST_SIMD512
+            if (wide) egt_simd512::extrema(wr + g0 * group, mr + g0 * group, gr, lo, hi);
+            else
+#endif
             egt_simd::extrema(wr + g0 * group, mr + g0 * group, gr, lo, hi);
             p = make_qparam_simd(lo, hi);
           } else
@@ -549,6 +570,12 @@ egt_status pack_rows(const uint16_t *w, int64_t ldw, const uint8_t *mask, int64_
         // (a row starts on a whole index word and a whole byte of values)
         egt_simd::with_n(n_row, [&](auto c) {
           constexpr int n = decltype(c)::n;
+#ifdef EGT_HOST_SIMD512
+          if (wide && val_kind == EGT_VAL_FP16) egt_simd512::pack_row_fp16<n>(wr, mr, cols, (uint8_t *)(vals16 + t), (uint8_t *)(idx + (t >> 3)));
+          else if (wide) egt_simd512::pack_row_int4<n>(wr, mr, cols, group, qr, val_kind == EGT_VAL_INT4_PAIRED, vals8 + (t >> 1),
+                                                       (uint8_t *)(idx + (t >> 3)));
+          else
+#endif
           if (val_kind == EGT_VAL_FP16) egt_simd::pack_row_fp16<n>(wr, mr, cols, (uint8_t *)(vals16 + t), (uint8_t *)(idx + (t >> 3)));
           else egt_simd::pack_row_int4<n>(wr, mr, cols, group, qr, val_kind == EGT_VAL_INT4_PAIRED, vals8 + (t >> 1),
                                           (uint8_t *)(idx + (t >> 3)));
@@ -720,18 +747,30 @@ egt_status egt_quant_int4(const uint16_t *w, int64_t ldw, int rows, int cols, in
 #ifdef EGT_HOST_SIMD
     const bool simd = egt_simd::available() && group % 8 == 0;
 #endif
+#ifdef EGT_HOST_SIMD512
+    const bool wide = simd && egt_simd512::available() && group % 64 == 0;
+#endif
     for (int r = r0; r < r1; ++r) {
       const uint16_t *wr = w + (int64_t)r * ldw;
       for (int g = 0; g < G; ++g) {
 #ifdef EGT_HOST_SIMD
         if (simd) {
           float lo, hi;
+#ifdef EGT_HOST_SIMD512
+          if (wide) egt_simd512::extrema(wr + g * group, nullptr, group, lo, hi);
+          else
+#endif
           egt_simd::extrema(wr + g * group, nullptr, group, lo, hi);
           const QParam p = make_qparam_simd(lo, hi);
           uint16_t *o = qparams + ((int64_t)r * G + g) * 2;
           o[0] = p.s_bits;
           o[1] = zero_bits(p.z);
-          egt_simd::quant_group(wr + g * group, group, (float)p.s, p.z, q + (int64_t)r * (cols / 2) + g * group / 2);
+          uint8_t *to = q + (int64_t)r * (cols / 2) + g * group / 2;
+#ifdef EGT_HOST_SIMD512
+          if (wide) egt_simd512::quant_group(wr + g * group, group, (float)p.s, p.z, to);
+          else
+#endif
+          egt_simd::quant_group(wr + g * group, group, (float)p.s, p.z, to);
           continue;
         }
 #endif
