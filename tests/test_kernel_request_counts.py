@@ -223,3 +223,34 @@ def test_rows_past_the_last_one_are_requested_past_the_buffer_by_the_lane_offset
         assert requests and len(uniform) == (4 * int(m.group(2)) if m.group(1) == "2" else 0), (name, uniform)
         seen += 1
     assert seen >= 40
+
+
+def test_requests_of_the_product_for_many_tokens_match_its_wait_counts(smallm_asm):
+    # k_smallm_wide*<NG, NIT>: phases 0 and 1 are asked for ahead, a phase of the loop asks for its next but one after its first
+    # unit of x, the odd last phase asks for no tiles and counts none (3 NIT requests a phase, 8 a unit of x)
+    seen = 0
+    for name, body in smallm_asm:
+        m = re.search(r"k_smallm_wide(?:_batch|_ks_joint)?ILi(\d)ELi(\d)E", name)
+        if not m:
+            continue
+        ng, na = int(m.group(1)), 3 * int(m.group(2))
+        events = []
+        lines = body.split("\n")
+        for k, ln in enumerate(lines):
+            w = re.match(r"\s*s_waitcnt vmcnt\((\d+)\)\s*$", ln)
+            if w and "ASMSTART" in lines[k - 1]:
+                events.append(int(w.group(1)))
+            elif re.search(r"\bbuffer_load", ln):
+                events.append("x" if " lds" in ln else "a")
+        assert events.count("a") == 4 * na, (name, events.count("a"))
+        assert events.count("x") == 8 * (2 + 3 * ng) and _lane_loops(body) == 0, name
+        assert not re.search(r"\bscratch_|\bflat_", body), name
+        waits = [e for e in events if isinstance(e, int)]
+        allowed = {8, 8 + na, 8 + 2 * na, 0}
+        assert set(waits) == allowed and waits.count(0) == 1 and waits.count(8 + 2 * na) >= 1, (name, waits)
+        # the odd last phase: units whose wait counts x alone, and no tiles between them
+        first = " ".join(str(e) for e in events).replace("x " * 8, "X ").replace("a " * na, "A ")
+        assert first.startswith("X A X A "), (name, first[:60])
+        assert ("8 X " * ng).strip() in first, (name, first)
+        seen += 1
+    assert seen == 24

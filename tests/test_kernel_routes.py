@@ -227,3 +227,14 @@ def test_matrices_of_many_tiles_reach_other_kernels_than_their_first_rows(launch
     few = _names(launches([call(61, *c[1:]) for c in MANY_TILES]))
     for c, a, b in zip(MANY_TILES, many, few):
         assert len(a) == len(b) == 1 and a != b and a[0].split("IL")[0][-8:] == b[0].split("IL")[0][-8:], (c, a, b)
+
+
+# kind: 0 INT4, 1 FP16
+@pytest.mark.parametrize("w,M,count,shared,wide", [
+    ((1000, 4096, 2, 128, 0), 33, 1, True, "k_smallm_wide"), ((1000, 4096, 2, 128, 0), 64, 1, True, "k_smallm_wide"),
+    ((4234, 1792, 2, 64, 0), 50, 3, True, "ks_joint"), ((4234, 1792, 2, 64, 0), 50, 3, False, "k_smallm_wide_batch"),
+    ((1000, 4096, 2, 128, 0), 32, 1, True, None), ((1000, 4096, 2, 32, 0), 64, 1, True, None), ((1000, 4096, 2, 0, 1), 64, 1, True, None),
+    ((1000, 4096, 1, 128, 0), 64, 1, True, None)])
+def test_more_than_two_token_groups_take_one_pass(launches, w, M, count, shared, wide):
+    (call,) = launches([{"call": "gemm_batch" if count > 1 else "gemm", "w": w, "M": M, "count": count, "shared": shared}])
+    assert len(call) == 1 and ("k_smallm_wide" in call[0][0]) == (wide is not None) and (wide or "") in call[0][0], call
