@@ -31,7 +31,8 @@
 // for A: with NT = 2 token groups the second group of a phase is requested before the
 // A tiles of the next phase and nothing needed soon queues behind the long latency of
 // A.  More than 16 NT tokens are handled in passes over the same rows (the weights of
-// the later passes come from the caches).  In the last phase nothing is requested any
+// the later passes come from the caches).  (2:4 INT4 beyond 32 tokens:
+// one pass, egt_smallm_wide_body.h.)  In the last phase nothing is requested any
 // more and the row tiles are consumed as they arrive.  Then the waves leave their sums
 // in LDS, one barrier later 4-lane groups add them up over the waves in wave order (a
 // fixed order: the result does not depend on timing) and store four consecutive rows of

@@ -13,7 +13,7 @@
 //  - The compiler waited for all requests at the top of every other round: a request under a condition, and a round of
 //    the loop under one, make its count of what is pending the smallest of all paths.  Here rounds past the last one are requested
 //    too (out of range: no traffic), and a loop turn is two rounds, the odd last round behind it.
-// us before, now (bits the same): 2:4 341 -> 294 at 16 tokens, 318 -> 266 at 4, 527 -> 502 at 64, 416 -> 370 at 32
+// us before, now (bits the same): 2:4 341 -> 294 at 16 tokens, 318 -> 266 at 4, 527 -> 502 at 64, 410 -> 362 at 32
 // (two tiles a wave); 1:4 (eleven layers) 170 -> 150 at 16, 158 -> 144 at 5, 217 -> 208 at 32.
 // What bounds it now: HBM and the L2 (the weights and token rows alone take 260 us at 16 tokens, 178 without weights).
 #ifndef EGT_STACK_TILES_BODY_H
