@@ -374,7 +374,8 @@ typedef struct {
   int32_t block_threads; /* threads per workgroup                                            */
   int32_t lds_bytes;     /* dynamic LDS per workgroup                                        */
   int32_t n_keep;        /* storage form of every matrix of the table: 2 (2:4) or 1 (1:4)    */
-  uint64_t table_bytes;  /* the descriptors and 4 bytes per workgroup, a multiple of 16      */
+  uint64_t table_bytes;  /* the descriptors and 4 bytes per workgroup, rounded up to 16; 16 more
+                            where a workgroup owns twice as many rows as in smaller tables   */
 } egt_gemm_plan;
 
 /* HOST.  As egt_gemv_stack_plan: checks `count` (1..65535) items for M tokens each, writes

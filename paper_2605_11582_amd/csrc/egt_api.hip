@@ -259,9 +259,10 @@ egt_status egt_sparse_gemm_smallm_batch(const egt_2bitcsr *w, const uint16_t *co
   return done(egt::launch_sparse_gemm_batch(w, X, ldx, Y, ldy, M, count, (hipStream_t)stream));
 }
 
-// descriptors, then one 32-bit word per workgroup, rounded up to 16 bytes
-static uint64_t gemm_table_bytes(int count, int grid_x) {
-  return (uint64_t)count * EGT_STACK_ENTRY_BYTES + (((uint64_t)grid_x * 4 + 15) & ~(uint64_t)15);
+// descriptors, then one 32-bit word per workgroup, rounded up to 16 bytes; 16 bytes more mark a table of sixteen row tiles a
+// workgroup where the kernel of another one with as many tokens takes eight (nothing reads them)
+static uint64_t gemm_table_bytes(int count, int grid_x, bool marked) {
+  return (uint64_t)count * EGT_STACK_ENTRY_BYTES + (((uint64_t)grid_x * 4 + 15) & ~(uint64_t)15) + (marked ? 16 : 0);
 }
 
 egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, void *table, size_t table_bytes,
@@ -287,7 +288,8 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
   if (limit > (1u << 24)) return EGT_ERR_UNSUPPORTED;
   const int n_keep = items[0].sparse->n_keep;
   int threads, lds, tiles;
-  egt::smallm_stack_shape(M, n_keep, items, count, threads, lds, tiles);
+  bool marked;
+  egt::smallm_stack_shape(M, n_keep, items, count, threads, lds, tiles, marked);
   auto blocks_of = [&](int r) { return ((r + 15) / 16 + tiles - 1) / tiles; };
   for (int k = 0; k < count; ++k) nwg += (uint64_t)blocks_of(items[k].sparse->rows);   // (no more of them than counted above)
   egt_gemm_plan out;
@@ -298,7 +300,7 @@ egt_status egt_gemm_stack_plan(const egt_gemm_item *items, int count, int M, voi
   out.grid_x = (int32_t)nwg;
   out.block_threads = threads;
   out.lds_bytes = lds;
-  out.table_bytes = gemm_table_bytes(count, out.grid_x);
+  out.table_bytes = gemm_table_bytes(count, out.grid_x, marked);
   if (table) {
     if ((uint64_t)table_bytes < out.table_bytes) return EGT_ERR_SHAPE;
     // Descriptors in the order of falling row length (a stable sort): a workgroup walks all of K, so the matrices
@@ -346,9 +348,10 @@ egt_status egt_gemm_stack_run(const void *table_dev, const egt_gemm_plan *plan, 
   if (plan->count < 1 || plan->count > 65535 || plan->M < 2 || plan->M > 64 || (plan->n_keep != 1 && plan->n_keep != 2) ||
       (plan->n_keep == 1 && plan->M > 32))
     return EGT_ERR_SHAPE;
-  if (plan->grid_x < 0 || plan->grid_x > (1 << 24) || !egt::smallm_stack_form_ok(plan->M, plan->n_keep, plan->block_threads, plan->lds_bytes) ||
-      plan->table_bytes != gemm_table_bytes(plan->count, plan->grid_x))
-    return EGT_ERR_SHAPE;
+  if (plan->grid_x < 0 || plan->grid_x > (1 << 24)) return EGT_ERR_SHAPE;
+  const bool marked = plan->table_bytes == gemm_table_bytes(plan->count, plan->grid_x, true);
+  if (!marked && plan->table_bytes != gemm_table_bytes(plan->count, plan->grid_x, false)) return EGT_ERR_SHAPE;
+  if (!egt::smallm_stack_form_ok(plan->M, plan->n_keep, plan->grid_x, plan->block_threads, plan->lds_bytes, marked)) return EGT_ERR_SHAPE;
   if (plan->grid_x == 0) return EGT_OK;               // every matrix is empty
   return done(egt::launch_smallm_stack(table_dev, plan->count, plan->M, plan->n_keep, plan->grid_x, plan->block_threads, plan->lds_bytes, (hipStream_t)stream));
 }

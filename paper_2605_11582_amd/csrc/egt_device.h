@@ -66,9 +66,10 @@ hipError_t launch_sparse_smallm_hold(const egt_2bitcsr *ws, const uint16_t *X, i
 // any number of 2:4 (or of 1:4) INT4 small-M products in one launch (egt_gemm_stack_plan / egt_gemm_stack_run)
 bool smallm_stack_item_ok(const egt_2bitcsr &w, int M);
 int smallm_stack_blocks(int M, int n_keep, int rows);
-void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles);
+void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles,
+                        bool &marked);
 void smallm_stack_entry(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, int M, void *entry);
-bool smallm_stack_form_ok(int M, int n_keep, int block_threads, int lds_bytes);
+bool smallm_stack_form_ok(int M, int n_keep, int grid_x, int block_threads, int lds_bytes, bool marked);
 hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, int block_threads, int lds_bytes, hipStream_t stream);
 // (dispatch: identically shaped members; falls back to one launch per member where no batched kernel applies)
 hipError_t launch_sparse_gemm_batch(const egt_2bitcsr *ws, const uint16_t *const *Xs, int64_t ldx, uint16_t *const *Ys,

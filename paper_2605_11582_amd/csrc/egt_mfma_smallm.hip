@@ -1279,12 +1279,13 @@ bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
   return sparse_smallm_supported(w, w.cols, M);
 }
 
-// Launch forms of a table, told apart by the plan's threads and LDS bytes:
+// Launch forms of a table, told apart by the plan's workgroups, threads and LDS bytes:
 //  - k_stack_tiles with a row tile a wave or two;
 //  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, and at any size plans that were kept from
 //    before there was k_stack_tiles.
 struct StackForm {
   int threads, tiles, lds;                            // of a workgroup
+  bool of(int t, int l) const { return t == threads && l == lds; }
 };
 static bool stack_sixteen(int M, bool n1) { return M > (n1 ? 16 : 32); }
 static int stack_lds_rows(int M, bool n1) {
@@ -1309,14 +1310,18 @@ static StackForm stack_form_rows(int M, bool n1) {
   return stack_sixteen(M, n1) ? StackForm{1024, 16, stack_lds_rows(M, n1)} : StackForm{64 * RS_WAVES, RS_WAVES, stack_lds_rows(M, n1)};
 }
 
+// The most workgroups of a table that k_smallm_rows takes.
+static int stack_few(int M, bool n1) { return n1 || M > 32 ? 127 : 64; }
+
 // Workgroups of a matrix in the forms that every table once had: what a plan may not exceed.
 int smallm_stack_blocks(int M, int n_keep, int rows) {
   const int ntiles = (rows + 15) / 16, per = stack_form_rows(M, n_keep == 1).tiles;
   return (ntiles + per - 1) / per;
 }
 
-// Launch shape of a table: threads, LDS bytes and row tiles of a workgroup.
-void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles) {
+// Launch shape of a table: threads, LDS bytes and row tiles of a workgroup, and whether it carries the mark of sixteen row tiles
+// where one form has eight and another sixteen.
+void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles, bool &marked) {
   const bool n1 = n_keep == 1;
   uint64_t bytes = 0, blocks = 0;
   for (int k = 0; k < count; ++k) {
@@ -1325,8 +1330,9 @@ void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count
   }
   StackForm f = stack_form_tiles(M, n1, stack_two_tiles(M, n1, bytes));
   for (int k = 0; k < count; ++k) blocks += (uint64_t)(((items[k].sparse->rows + 15) / 16 + f.tiles - 1) / f.tiles);
-  if (blocks <= (n1 || M > 32 ? 127 : 64)) f = stack_form_rows(M, n1);
+  if (blocks <= (uint64_t)stack_few(M, n1)) f = stack_form_rows(M, n1);
   block_threads = f.threads; lds_bytes = f.lds; tiles = f.tiles;
+  marked = !stack_sixteen(M, n1) && f.tiles == 16;
 }
 
 // Descriptor of one item into 160 bytes of the table.
@@ -1341,12 +1347,18 @@ void smallm_stack_entry(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, in
   std::memcpy(entry, &e, sizeof(e));
 }
 
-// The kernel follows the plan's threads and LDS bytes.  A plan with sixteen waves, as every table of sixteen tiles a workgroup once
-// had, is good at any size (the table is the same in every form with sixteen tiles).
-bool smallm_stack_form_ok(int M, int n_keep, int block_threads, int lds_bytes) {
-  const bool n1 = n_keep == 1;
-  const bool known = lds_bytes == stack_lds_rows(M, n1) || lds_bytes == stack_form_tiles(M, n1, false).lds || lds_bytes == stack_form_tiles(M, n1, true).lds;
-  return known && (block_threads == 512 || (block_threads == 1024 && stack_sixteen(M, n1)));
+// Whether a plan's threads and LDS bytes are those of a form that its table can have.  A kernel that takes eight row tiles a
+// workgroup would leave half of the rows of a table of sixteen: where both are possible, the size of the table tells them
+// apart (`marked`).  Beside the forms that smallm_stack_shape gives, a plan may be one that its caller kept: k_smallm_rows at
+// any size, and with sixteen tiles a workgroup either number of waves from 128 workgroups on (the table is the same).
+bool smallm_stack_form_ok(int M, int n_keep, int grid_x, int block_threads, int lds_bytes, bool marked) {
+  const bool n1 = n_keep == 1, sixteen = stack_sixteen(M, n1), few = grid_x <= stack_few(M, n1);
+  const StackForm rows = stack_form_rows(M, n1), one = stack_form_tiles(M, n1, false), two = stack_form_tiles(M, n1, true);
+  if (marked) return !few && two.tiles != one.tiles && two.of(block_threads, lds_bytes);
+  if (rows.of(block_threads, lds_bytes)) return true;
+  if (few) return false;
+  return one.of(block_threads, lds_bytes) ||
+         (sixteen && ((block_threads == 1024 && lds_bytes == one.lds) || (block_threads == 512 && lds_bytes == rows.lds)));
 }
 
 hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_keep, int grid_x, int block_threads, int lds_bytes, hipStream_t stream) {

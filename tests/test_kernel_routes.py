@@ -58,8 +58,8 @@ for c in json.loads({calls!r}):
 
 
 @pytest.fixture(scope="module")
-def launches(tmp_path_factory):
-    """launches(calls): per call the list of (kernel, grid x, grid y, threads) it launches."""
+def child(tmp_path_factory):
+    """child(script, calls): the lines that the script prints with these calls and the stand-in for the launch."""
     cc = shutil.which("gcc")
     if not cc:
         pytest.skip("no host compiler")
@@ -68,14 +68,41 @@ def launches(tmp_path_factory):
     (d / "launch.c").write_text(STAND_IN)
     subprocess.run([cc, "-shared", "-fPIC", "-O1", str(d / "launch.c"), "-o", lib], check=True)
 
-    def run(calls):
+    def run(script, calls):
         env = dict(os.environ)
         env["LD_PRELOAD"] = " ".join(v for v in (lib, env.get("LD_PRELOAD", "")) if v)
-        out = subprocess.run([sys.executable, "-c", CHILD.replace("{root!r}", repr(ROOT)).replace("{calls!r}", repr(json.dumps(calls)))],
+        out = subprocess.run([sys.executable, "-c", script.replace("{root!r}", repr(ROOT)).replace("{calls!r}", repr(json.dumps(calls)))],
                              capture_output=True, text=True, env=env, timeout=120)
         assert out.returncode == 0, out.stderr[-2000:]
+        return out.stdout.splitlines()
+    return run
+
+
+@pytest.fixture(scope="module")
+def runs_of_plans(child):
+    """runs_of_plans(tables): per table, for its plan as made and for each changed form of it: ([(kernel, grid x, threads, LDS
+    bytes)], status, and the plan's grid, threads, LDS bytes and table bytes as made)."""
+    def run(tables):
+        res, lines = [], iter(child(PLANS, tables))
+        for table in tables:
+            res.append([])
+            for _ in range(1 + len(table[5])):
+                assert next(lines) == "call"
+                seen = []
+                while not (line := next(lines)).startswith("plan "):
+                    name, gx, _, threads, lds = line.split()[1:]
+                    seen.append((name, int(gx), int(threads), int(lds)))
+                res[-1].append((seen, *(int(v) for v in line.split()[1:])))
+        return res
+    return run
+
+
+@pytest.fixture(scope="module")
+def launches(child):
+    """launches(calls): per call the list of (kernel, grid x, grid y, threads) it launches."""
+    def run(calls):
         res = []
-        for line in out.stdout.splitlines():
+        for line in child(CHILD, calls):
             if line == "call":
                 res.append([])
             elif line.startswith("launch "):
@@ -238,3 +265,64 @@ def test_matrices_of_many_tiles_reach_other_kernels_than_their_first_rows(launch
 def test_more_than_two_token_groups_take_one_pass(launches, w, M, count, shared, wide):
     (call,) = launches([{"call": "gemm_batch" if count > 1 else "gemm", "w": w, "M": M, "count": count, "shared": shared}])
     assert len(call) == 1 and ("k_smallm_wide" in call[0][0]) == (wide is not None) and (wide or "") in call[0][0], call
+
+
+PLANS = r"""
+import ctypes as C, json, sys
+sys.path.insert(0, {root!r})
+from paper_2605_11582_amd import binding as B
+L = B._declare(C.CDLL(B.LIB_PATH))                          # (without PyTorch)
+P = 1 << 20
+for M, n, rows, cols, count, changes in json.loads({calls!r}):
+    views = [B.View(rows, cols, n, 128, 0, P, P, P, P) for _ in range(count)]
+    items = (B.GemmItem * count)()
+    for k, v in enumerate(views):
+        items[k].sparse, items[k].X, items[k].Y = C.pointer(v), P, P
+    plan = B.GemmPlan()
+    assert L.egt_gemm_stack_plan(items, count, M, None, 0, C.byref(plan)) == 0
+    for change in [{}] + changes:
+        p = B.GemmPlan.from_buffer_copy(plan)
+        for field, value in change.items(): setattr(p, field, value)
+        print("call", flush=True)
+        print("plan", L.egt_gemm_stack_run(P, C.byref(p), None), plan.grid_x, plan.block_threads, plan.lds_bytes, plan.table_bytes, flush=True)
+"""
+
+ROWS_LDS = {(16, 2): 67584, (32, 2): 67584, (64, 2): 135168, (16, 1): 66560, (32, 1): 133120}            # k_smallm_rows, by most tokens and form
+TILES_LDS = {(16, 2): (66560,), (32, 2): (79872, 116736), (64, 2): (159744,), (16, 1): (78848, 115712), (32, 1): (157696,)}   # k_stack_tiles: a row tile a wave, two
+
+
+@pytest.mark.parametrize("top,n", list(TILES_LDS))
+def test_a_plan_runs_only_in_the_form_its_table_was_laid_out_for(runs_of_plans, top, n):
+    # tables of few workgroups, of more, and of 400 MB and more; every plan runs in its own form, and with the threads or LDS bytes
+    # of another form it is refused where it always was: half of a matrix would stay unwritten where a workgroup of the
+    # table owns sixteen row tiles and the kernel takes eight
+    lds = (ROWS_LDS[top, n],) + TILES_LDS[top, n]
+    sixteen = top == (64 if n == 2 else 32)
+    changes = [{"lds_bytes": v, "block_threads": t} for v in lds for t in (256, 512, 1024)]
+    tables = [(top, n, 1024, 4096, 1), (top, n, 1024, 4096, 40), (top, n, 8192, 8192, 30)]
+    # (kernel, LDS bytes of the launch) of each table
+    forms = ["k_smallm_rows", "k_stack_tiles", "k_stack_tiles"]
+    own = [lds[0], lds[1], lds[-1]]
+    for table, form, at, res in zip(tables, forms, own, runs_of_plans([(*t, changes) for t in tables])):
+        (launched, status, grid, threads, lds_bytes, table_bytes), rest = res[0], res[1:]
+        assert status == 0 and len(launched) == 1 and form in launched[0][0] and lds_bytes == at, (table, res[0])
+        assert launched[0][1:] == (grid, threads, lds_bytes), (table, res[0])
+        assert threads == (1024 if form == "k_smallm_rows" and sixteen else 512)
+        two = len(TILES_LDS[top, n]) == 2 and at == lds[-1]
+        for change, (again, st, *_) in zip(changes, rest):
+            pair = (change["block_threads"], change["lds_bytes"])
+            ok = pair == (threads, lds_bytes)
+            if not two:
+                # k_smallm_rows takes every table of its tiles a workgroup; with sixteen of them the number of its waves is free in
+                # a large table (plans that a caller kept)
+                ok = ok or pair == ((1024 if sixteen else 512), lds[0]) or (sixteen and grid >= 128 and pair in [(512, lds[0]), (1024, lds[1])])
+            assert (st == 0) == ok and len(again) == (1 if ok else 0) and st in (0, 2), (table, change, st)
+
+
+def test_a_plan_without_the_mark_of_two_tiles_a_wave_is_refused(runs_of_plans):
+    # (30 descriptors of 160 bytes, 32 workgroups a matrix; the mark alone in a table without it is refused too)
+    plain = 30 * 160 + 4 * 30 * 32
+    two, one = runs_of_plans([(24, 2, 8192, 8192, 30, [{"table_bytes": plain}, {"table_bytes": plain + 32}, {"lds_bytes": 79872}, {"lds_bytes": 67584}]),
+                              (24, 2, 4096, 1024, 30, [{"table_bytes": plain + 16}, {"table_bytes": plain + 16, "lds_bytes": 67584}])])
+    assert [r[1] for r in two] == [0, 2, 2, 2, 2] and two[0][2:] == (30 * 32, 512, 116736, plain + 16), two
+    assert [r[1] for r in one] == [0, 2, 2] and one[0][2:] == (30 * 32, 512, 79872, plain), one
