@@ -986,13 +986,10 @@ static_assert(sizeof(SmallMStackEntry) <= EGT_STACK_ENTRY_BYTES, "descriptor lar
 // 1024 x 3072 at 17 20.1, 17.2.  Not at fewer tokens, where two workgroups share a compute unit and operands are
 // not what binds (two tiles a wave there: 16 tokens 341, 353; 1:4 166, 167;
 // 32 tokens 423, 431).
-#ifndef EGT_RS_WAVES
-#define EGT_RS_WAVES 8
-#endif
 #ifndef EGT_RS_Q
 #define EGT_RS_Q 4
 #endif
-constexpr int RS_WAVES = EGT_RS_WAVES, RS_Q = EGT_RS_Q, RS_BUFS = 2;
+constexpr int RS_WAVES = 8, RS_Q = EGT_RS_Q, RS_BUFS = 2;
 // LDS bytes of the token rows of one K-step and token group: 2:4 eight pairs of tokens (256 columns), 1:4 sixteen
 // tokens of 512 columns
 constexpr int rs_step_bytes(bool n1) { return n1 ? 16 * KS_TOKEN_N1 : 8 * KS_PAIR; }
@@ -1313,7 +1310,8 @@ static StackForm stack_form_rows(int M, bool n1) {
 // The most workgroups of a table that k_smallm_rows takes.
 static int stack_few(int M, bool n1) { return n1 || M > 32 ? 127 : 64; }
 
-// Workgroups of a matrix in the forms that every table once had: what a plan may not exceed.
+// Workgroups of a matrix in the forms that every table once had: what a plan may not exceed.  (No form has fewer tiles a workgroup.)
+static_assert(RS_WAVES == ST_WAVES, "k_stack_tiles with a row tile a wave has the workgroups that a plan's limits count");
 int smallm_stack_blocks(int M, int n_keep, int rows) {
   const int ntiles = (rows + 15) / 16, per = stack_form_rows(M, n_keep == 1).tiles;
   return (ntiles + per - 1) / per;
