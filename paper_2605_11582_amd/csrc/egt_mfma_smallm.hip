@@ -978,14 +978,7 @@ static_assert(sizeof(SmallMStackEntry) <= EGT_STACK_ENTRY_BYTES, "descriptor lar
 // More than 16 tokens: NG token groups of 16.  The token rows of all groups are staged per
 // round, the operands of a K-step are dequantised once and serve every group (NG sums per
 // wave), and a round is two K-steps, so that the regions still fit: up to 32 tokens two
-// groups and 8 waves (two workgroups per compute unit), beyond four groups and 16 row tiles.
-// There (and for 1:4 beyond 16 tokens) one workgroup fills the LDS of a compute unit, and what binds is the
-// reads of B from it, 8 KB a K-step, token group and row tile (1:4 16 KB) beside 1.7 KB of weights.  So 8 waves
-// with twice the registers own two tiles each (T), and an operand read from LDS serves both.  us with 16 waves and one
-// tile each, with 8 and two: 16 layers of a 7B stack at 64 tokens 576, 544; eleven 1:4 layers at 32 249, 226; four 1:4 layers of
-// 1024 x 3072 at 17 20.1, 17.2.  Not at fewer tokens, where two workgroups share a compute unit and operands are
-// not what binds (two tiles a wave there: 16 tokens 341, 353; 1:4 166, 167;
-// 32 tokens 423, 431).
+// groups and 8 waves (two workgroups per compute unit), beyond (and for 1:4 beyond 16 tokens) four groups (two) and 16 waves.
 #ifndef EGT_RS_Q
 #define EGT_RS_Q 4
 #endif
@@ -997,9 +990,8 @@ constexpr int rs_step_bytes(bool n1) { return n1 ? 16 * KS_TOKEN_N1 : 8 * KS_PAI
 constexpr int rs_lds_bytes(int ng, int q, bool n1 = false) { return RS_BUFS * ng * q * rs_step_bytes(n1); }
 
 // N1: 1:4 sparsity (chunks of 128 columns, eight instructions a K-step, a request of X per token).
-// T: row tiles of a wave.
-template <int NG, int Q, int W, bool N1, int T>
-__device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ table, int count) {
+template <int NG, int Q, int W, bool N1 = false>
+__global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__restrict__ table, int count) {
   constexpr int RS_WAVES = W, RS_Q = Q, RS_STEP = rs_step_bytes(N1), RS_REGION = NG * Q * RS_STEP;
   constexpr int XREQ = N1 ? 16 : 8;                   // requests of X per K-step and token group
   constexpr int NM = N1 ? 8 : 4;                      // matrix instructions per K-step
@@ -1023,16 +1015,16 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 15, kb = lane >> 4;            // operand form: row i of the tile, chunk kb of the step
-  // this wave's row tiles (a wave past the last tile has none, but still stages its share of X
+  // this wave's row tile (a wave past the last one has none, but still stages its share of X
   // and meets the barriers)
-  const int tile0 = T * (wg * RS_WAVES + wave);
-  const int ntiles = min(max(g.ntiles - tile0, 0), T);                      // uniform
+  const int tile = wg * RS_WAVES + wave;
+  const bool mine = tile < g.ntiles;                  // uniform
   const int nsteps = g.nsteps, nrounds = (nsteps + RS_Q - 1) / RS_Q;
   const uint32_t magic = in_vgpr(g.nib_magic);
   const uint32_t S_row = (uint32_t)g.nchunks * 32u;
   // row pointers first, checked at the end: a row whose pointer is not r * S yields NaN
-  const int frow = 16 * tile0 + lane;
-  const bool fchecked = lane < 16 * ntiles && frow < g.rows;
+  const int frow = 16 * tile + lane;
+  const bool fchecked = lane < 16 && mine && frow < g.rows;
   const uint32_t frp = fchecked ? row_ptr[frow] : 0u;
 
   const __amdgpu_buffer_rsrc_t r_val = make_rsrc((const uint8_t *)(g_u8)e->values, g.val_bytes);
@@ -1052,9 +1044,8 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
   // (rows 4 to 7 of a request keep their chunks in the other order of halves - lane (r, c) fetches chunk c ^ (r & 4):
   //  the lanes that a lane permutation reads for rows r and r + 4 then lie in different LDS banks)
   const int r8 = lane >> 3, c8 = (lane & 7) ^ ((lane >> 3) & 4);
-  auto load_half = [&](RoundRegs &a, int round, int p, int t) {   // the requests (0, p) and (1, p) of tile t: 2 * LPT of them
-    const int tile = tile0 + t;
-    const bool on = t < ntiles && RS_Q * round + 2 * p < nsteps;              // uniform
+  auto load_half = [&](RoundRegs &a, int round, int p) {      // the requests (0, p) and (1, p): 2 * LPT of them
+    const bool on = mine && RS_Q * round + 2 * p < nsteps;                    // uniform
     const int c0 = 4 * RS_Q * round + 8 * p;                                  // first chunk of the request
     const uint32_t lcc = (uint32_t)min((int)in_vgpr((uint32_t)c8), g.nchunks - 1 - c0);       // chunk inside the request (clamped)
 #pragma unroll
@@ -1134,31 +1125,25 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
     return u8v{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   };
 
-  f4 acc[T][NG];
+  f4 acc[NG];
 #pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int grp = 0; grp < NG; ++grp) acc[t][grp] = f4{0.f, 0.f, 0.f, 0.f};
-  // The A tiles are requested two rounds ahead (two sets of fetch registers), X one round
+  for (int grp = 0; grp < NG; ++grp) acc[grp] = f4{0.f, 0.f, 0.f, 0.f};
+  // The A tile is requested two rounds ahead (two sets of fetch registers), X one round
   // ahead.  Requests in a round, in this order: X(j + 1), then A(j + 2) - so that at the top
-  // of round j the requests still allowed to be pending are exactly the T * RS_Q * LPT of A(j + 1).
+  // of round j the requests still allowed to be pending are exactly the RS_Q * LPT of A(j + 1).
   // The barrier is issued with its own wait counts: a fence would wait for every pending
   // request, the LDS-bound ones of X among them, and give the depth away.
-  RoundRegs raw0[T], raw1[T];
-  auto load_pair = [&](RoundRegs (&a)[T], int round, int p) {
+  RoundRegs raw0, raw1;
 #pragma unroll
-    for (int t = 0; t < T; ++t) load_half(a[t], round, p, t);
-  };
-#pragma unroll
-  for (int p = 0; p < RS_Q / 2; ++p) load_pair(raw0, 0, p);
+  for (int p = 0; p < RS_Q / 2; ++p) load_half(raw0, 0, p);
   dma_x(0, 0);
   if (nrounds > 1) {
 #pragma unroll
-    for (int p = 0; p < RS_Q / 2; ++p) load_pair(raw1, 1, p);
+    for (int p = 0; p < RS_Q / 2; ++p) load_half(raw1, 1, p);
   }
   int buf = 0;                                        // region of round j: j % 2
-  auto round = [&](RoundRegs (&cur)[T], int j) {
-    if (j + 1 < nrounds) wait_vmem<T * RS_Q * LPT>(); else wait_vmem<0>();   // A(j) and this wave's share of X(j) have arrived
+  auto round = [&](RoundRegs &cur, int j) {
+    if (j + 1 < nrounds) wait_vmem<RS_Q * LPT>(); else wait_vmem<0>();       // A(j) and this wave's share of X(j) have arrived
     zero_tail(j, buf);
     // X(j) of every wave has landed; nobody reads the region of round j - 1 any more
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -1167,41 +1152,36 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
     for (int q = 0; q < RS_Q; ++q) {
       // (a step past K, a wave without a tile: requested out of range, zeros with scale 0)
       const int step = RS_Q * j + q;
-      Tile tiles[T];
-#pragma unroll
-      for (int k = 0; k < T; ++k) to_operand(cur[k], q, tiles[k]);
+      Tile t;
+      to_operand(cur, q, t);
       // (both K-steps of a pair of requests consumed: their fetch registers are free again)
       if ((q & 1) && j + 2 < nrounds) {
         wait_lds();
-        load_pair(cur, j + 2, q >> 1);
+        load_half(cur, j + 2, q >> 1);
       }
       const bool live = 4 * step + kb < g.nchunks;    // false: a chunk past the end of K
       // the operands of the step's instructions serve every token group
-      u4 av[T][NM];
-      uint32_t iwv[T][NM / 2];
+      u4 av[NM];
+      uint32_t iwv[NM / 2];
+      const uint32_t s2 = live ? __builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x01000100u) : 0u;
+      const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x03020302u), g.nib_magic);
+      if constexpr (N1) {
+        // every slot becomes the pair {value, 0} with its offset in the even index field; instruction m takes
+        // slots 4 m .. 4 m + 3 of the chunk: bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
+        iwv[0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
+        iwv[1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
+        iwv[2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
+        iwv[3] = spread_idx<1>(t.iw[1], g.m4, g.m2);
 #pragma unroll
-      for (int k = 0; k < T; ++k) {
-        const Tile &t = tiles[k];
-        const uint32_t s2 = live ? __builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x01000100u) : 0u;
-        const uint32_t off = pk_add_f16(__builtin_amdgcn_perm(t.qp[0], t.qp[0], 0x03020302u), g.nib_magic);
-        if constexpr (N1) {
-          // every slot becomes the pair {value, 0} with its offset in the even index field; instruction m takes
-          // slots 4 m .. 4 m + 3 of the chunk: bytes 2 (m & 1), 2 (m & 1) + 1 of dword m >> 1
-          iwv[k][0] = spread_idx<0>(t.iw[0], g.m4, g.m2);
-          iwv[k][1] = spread_idx<1>(t.iw[0], g.m4, g.m2);
-          iwv[k][2] = spread_idx<0>(t.iw[1], g.m4, g.m2);
-          iwv[k][3] = spread_idx<1>(t.iw[1], g.m4, g.m2);
-#pragma unroll
-          for (int m = 0; m < NM; ++m) {
-            const uint32_t d = t.nib[0][m >> 1];
-            av[k][m] = m & 1 ? dequant4_14<1>(d, off, s2, g.nib_mask, magic) : dequant4_14<0>(d, off, s2, g.nib_mask, magic);
-          }
-        } else {
-          iwv[k][0] = t.iw[0];
-          iwv[k][1] = t.iw[1];
-#pragma unroll
-          for (int m = 0; m < NM; ++m) av[k][m] = dequant8(t.nib[0][m], off, s2, g.nib_mask, magic);
+        for (int m = 0; m < NM; ++m) {
+          const uint32_t d = t.nib[0][m >> 1];
+          av[m] = m & 1 ? dequant4_14<1>(d, off, s2, g.nib_mask, magic) : dequant4_14<0>(d, off, s2, g.nib_mask, magic);
         }
+      } else {
+        iwv[0] = t.iw[0];
+        iwv[1] = t.iw[1];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) av[m] = dequant8(t.nib[0][m], off, s2, g.nib_mask, magic);
       }
 #pragma unroll
       for (int grp = 0; grp < NG; ++grp) {
@@ -1210,15 +1190,12 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           const u8v bx = read_b(bregion, m);          // (read per instruction: 8 registers of B at a time)
-#pragma unroll
-          for (int k = 0; k < T; ++k) {
-            const int iword = (int)iwv[k][m >> 1];
-            f4 &sum = acc[k][grp];
-            if (m & 1)
-              sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[k][m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 1);
-            else
-              sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[k][m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 0);
-          }
+          const int iword = (int)iwv[m >> 1];
+          f4 &sum = acc[grp];
+          if (m & 1)
+            sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 1);
+          else
+            sum = __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, av[m]), __builtin_bit_cast(h16, bx), sum, iword, 0, 0);
         }
       }
     }
@@ -1230,38 +1207,25 @@ __device__ __forceinline__ void smallm_rows_body(const uint8_t *__restrict__ tab
   }
   // register v of lane l = D[row 4 (l >> 4) + v][token l & 15]: four consecutive rows of one token
   const uint64_t good = __builtin_amdgcn_ballot_w64(fchecked && frp == (uint32_t)frow * S_row);
+  if (!mine) return;
+  const int row0 = 16 * tile + 4 * (lane >> 4);
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    if (t >= ntiles) return;
-    const int row0 = 16 * (tile0 + t) + 4 * (lane >> 4);
+  for (int grp = 0; grp < NG; ++grp) {
+    const int tok = 16 * grp + (lane & 15);
+    if (tok >= g.M) continue;
+    uint32_t hv[4];
 #pragma unroll
-    for (int grp = 0; grp < NG; ++grp) {
-      const int tok = 16 * grp + (lane & 15);
-      if (tok >= g.M) continue;
-      uint32_t hv[4];
+    for (int v = 0; v < 4; ++v)
+      hv[v] = ((good >> (4 * (lane >> 4) + v)) & 1) ? (uint32_t)__half_as_ushort(__float2half(acc[grp][v])) : 0x7E00u;
+    __half *dst = Y + (int64_t)tok * g.ldy + row0;
+    if (g.vec_store && row0 + 3 < g.rows) {
+      *(u2 *)dst = u2{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16)};
+    } else {
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        hv[v] = ((good >> (16 * t + 4 * (lane >> 4) + v)) & 1) ? (uint32_t)__half_as_ushort(__float2half(acc[t][grp][v])) : 0x7E00u;
-      __half *dst = Y + (int64_t)tok * g.ldy + row0;
-      if (g.vec_store && row0 + 3 < g.rows) {
-        *(u2 *)dst = u2{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16)};
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (row0 + v < g.rows) dst[v] = __ushort_as_half((uint16_t)hv[v]);
-      }
+        if (row0 + v < g.rows) dst[v] = __ushort_as_half((uint16_t)hv[v]);
     }
   }
-}
-
-template <int NG, int Q, int W, bool N1 = false>
-__global__ __launch_bounds__(64 * W, 4) void k_smallm_rows(const uint8_t *__restrict__ table, int count) {
-  smallm_rows_body<NG, Q, W, N1, 1>(table, count);
-}
-// two row tiles a wave
-template <int NG, int Q, int W, bool N1 = false>
-__global__ __launch_bounds__(64 * W, 2) void k_smallm_rows_two(const uint8_t *__restrict__ table, int count) {
-  smallm_rows_body<NG, Q, W, N1, 2>(table, count);
 }
 
 }  // namespace egt
@@ -1278,8 +1242,7 @@ bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
 
 // Launch forms of a table, told apart by the plan's workgroups, threads and LDS bytes:
 //  - k_stack_tiles with a row tile a wave or two;
-//  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, and at any size plans that were kept from
-//    before there was k_stack_tiles.
+//  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, and at any size plans that a caller kept.
 struct StackForm {
   int threads, tiles, lds;                            // of a workgroup
   bool of(int t, int l) const { return t == threads && l == lds; }
@@ -1290,7 +1253,7 @@ static int stack_lds_rows(int M, bool n1) {
   return M <= 16 ? rs_lds_bytes(1, RS_Q) : M <= 32 ? rs_lds_bytes(2, 2) : rs_lds_bytes(4, 2);
 }
 // Two row tiles a wave: four token groups (at 1:4 two) always, since one workgroup then fills the LDS of a compute unit
-// anyway; two groups (1:4: one) in tables of 400 MB and more.  Those are fetched from HBM whatever ran before, in 128-byte pieces
+// anyway and an operand read from it serves both tiles; two groups (1:4: one) in tables of 400 MB and more.  Those are fetched from HBM whatever ran before, in 128-byte pieces
 // of a row with two tiles and 64-byte ones with one; smaller tables would miss the second workgroup of a compute unit.  us with
 // one tile, two, three tables in turn: 24 tokens, layers of 4096 x 11008: two of them (164 MB) 57.8, 74.3; four 106.3,
 // 107.7; six (490 MB) 155.1, 150.0; ten of 6144 x 20480 (2.1 GB) 584.8, 552.6; 1:4 at 16 tokens, two of 4096 x 11008 35.4,
@@ -1363,21 +1326,18 @@ hipError_t launch_smallm_stack(const void *table_dev, int count, int M, int n_ke
   const bool n1 = n_keep == 1;
   const dim3 grid(grid_x), block(block_threads);
   const uint8_t *t = (const uint8_t *)table_dev;
-#define EGT_ST(...) launch(k_stack_tiles<__VA_ARGS__>, grid, block, (size_t)lds_bytes, stream, t, count)
-  if (block_threads == 512 && lds_bytes == stack_form_tiles(M, n1, false).lds) {
-    if (n1) return M <= 16 ? EGT_ST(1, 1, 32, true, true) : EGT_ST(2, 2, 32, false, true);
-    return M <= 16 ? EGT_ST(1, 1, 128, false, false) : M <= 32 ? EGT_ST(2, 1, 32, true, false) : EGT_ST(4, 2, 32, false, false);
-  }
-  if (block_threads == 512 && lds_bytes == stack_form_tiles(M, n1, true).lds)
-    return n1 ? EGT_ST(1, 2, 128, false, true) : EGT_ST(2, 2, 128, false, false);
+  const StackForm one = stack_form_tiles(M, n1, false), two = stack_form_tiles(M, n1, true);
+  // (sixteen tiles a workgroup: the waves name the kernel, whichever of its LDS sizes a kept plan holds)
+  if (stack_sixteen(M, n1) ? block_threads == one.threads : lds_bytes == one.lds || lds_bytes == two.lds) {
+#define EGT_ST(F, ...) launch(k_stack_tiles<__VA_ARGS__>, grid, block, (size_t)F.lds, stream, t, count)
+    if (lds_bytes == two.lds && two.lds != one.lds) return n1 ? EGT_ST(two, 1, 2, 128, false, true) : EGT_ST(two, 2, 2, 128, false, false);
+    if (n1) return M <= 16 ? EGT_ST(one, 1, 1, 32, true, true) : EGT_ST(one, 2, 2, 32, false, true);
+    return M <= 16 ? EGT_ST(one, 1, 1, 128, false, false) : M <= 32 ? EGT_ST(one, 2, 1, 32, true, false) : EGT_ST(one, 4, 2, 32, false, false);
 #undef EGT_ST
-  const int lds = stack_lds_rows(M, n1);
-#define EGT_RS(...) launch(k_smallm_rows<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
-#define EGT_RS2(...) launch(k_smallm_rows_two<__VA_ARGS__>, grid, block, (size_t)lds, stream, t, count)
-  const bool two = block_threads == 512;
-  if (n_keep == 1) return M <= 16 ? EGT_RS(1, 2, RS_WAVES, true) : two ? EGT_RS2(2, 2, 8, true) : EGT_RS(2, 2, 16, true);
-  return M <= 16 ? EGT_RS(1, RS_Q, RS_WAVES) : M <= 32 ? EGT_RS(2, 2, RS_WAVES) : two ? EGT_RS2(4, 2, 8) : EGT_RS(4, 2, 16);
-#undef EGT_RS2
+  }
+#define EGT_RS(...) launch(k_smallm_rows<__VA_ARGS__>, grid, block, (size_t)stack_lds_rows(M, n1), stream, t, count)
+  if (n1) return M <= 16 ? EGT_RS(1, 2, RS_WAVES, true) : EGT_RS(2, 2, 16, true);
+  return M <= 16 ? EGT_RS(1, RS_Q, RS_WAVES) : M <= 32 ? EGT_RS(2, 2, RS_WAVES) : EGT_RS(4, 2, 16);
 #undef EGT_RS
 }
 

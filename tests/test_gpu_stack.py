@@ -587,6 +587,13 @@ def test_gemm_stack_of_many_workgroups_has_the_bits_of_small_tables(M, n):
     call()
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(first, ybufs))
+    # and one of as many threads that names the LDS bytes of sixteen waves: k_stack_tiles with its own
+    for y in Yd:
+        y.zero_()
+    call.plan.block_threads, call.plan.lds_bytes = 512, 135168 if n == 2 else 133120
+    call()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(first, ybufs))
     call.plan.block_threads = 768
     with pytest.raises(B.EgtError):
         call()

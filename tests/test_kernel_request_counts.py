@@ -106,27 +106,6 @@ def test_requests_of_the_row_split_stack_kernel_match_its_wait_counts(smallm_asm
     assert seen == 5
 
 
-def test_requests_of_the_two_tile_stack_kernel_match_its_wait_counts(smallm_asm):
-    # k_smallm_rows_two<NG, Q, W>: as above, the tiles' requests twice
-    text = open(os.path.join(CSRC, "egt_mfma_smallm.hip")).read()
-    loads = int(re.search(r"static constexpr int LOADS = KIND == EGT_VAL_INT4 \? (\d+) : 1 \+ VW;", text).group(1))
-    seen = 0
-    for name, body in smallm_asm:
-        m = re.search(r"k_smallm_rows_twoILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", name)
-        if not m:
-            continue
-        ng, q, w, n1 = (int(v) for v in m.groups())
-        per_round, x_per_round = 2 * q * loads, ng * q * (16 if n1 else 8) // w
-        requests = [ln for ln in body.split("\n") if re.search(r"\bbuffer_load_dword", ln)]
-        to_lds = [ln for ln in requests if " lds" in ln]
-        assert len(requests) - len(to_lds) == 4 * per_round and len(to_lds) == 3 * x_per_round, (name, len(requests), len(to_lds))
-        waits = [int(v) for v in re.findall(r"vmcnt\((\d+)\)", body)]
-        assert waits.count(per_round) >= 2 and max(waits) <= 2 * per_round + x_per_round + 1, (name, sorted(set(waits)))
-        assert len(re.findall(r"\bs_barrier\b", body)) == 2 and not re.search(r"\bscratch_|\bflat_", body), name
-        seen += 1
-    assert seen == 2
-
-
 def test_waits_of_the_stack_kernel_count_only_requests_that_are_there(smallm_asm):
     # k_stack_tiles<NG, T, QW, NARROW, N1>: a round of the loop lets the 4 T requests of the next round's weights stay pending;
     # the odd last round, on whose way the compiler may leave requests out, waits for all of them

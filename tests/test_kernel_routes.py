@@ -317,6 +317,10 @@ def test_a_plan_runs_only_in_the_form_its_table_was_laid_out_for(runs_of_plans, 
                 # a large table (plans that a caller kept)
                 ok = ok or pair == ((1024 if sixteen else 512), lds[0]) or (sixteen and grid >= 128 and pair in [(512, lds[0]), (1024, lds[1])])
             assert (st == 0) == ok and len(again) == (1 if ok else 0) and st in (0, 2), (table, change, st)
+            if ok:                                           # sixteen tiles: the waves name the kernel; it gets its own LDS
+                kernel = ("k_smallm_rows" if pair[0] == 1024 else "k_stack_tiles") if sixteen else ("k_smallm_rows" if pair[1] == lds[0] else "k_stack_tiles")
+                assert kernel in again[0][0] and again[0][2] == pair[0], (table, change, again)
+                assert again[0][3] == ({"k_smallm_rows": lds[0], "k_stack_tiles": lds[1]}[kernel] if sixteen else pair[1]), (table, change, again)
 
 
 def test_a_plan_without_the_mark_of_two_tiles_a_wave_is_refused(runs_of_plans):
