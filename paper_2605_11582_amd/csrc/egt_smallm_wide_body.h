@@ -269,7 +269,8 @@ template <int NG, int NIT>
 static hipError_t go_wide(const egt_2bitcsr &w, const uint16_t *X, uint16_t *Y, const SmallMKsLaunch &g, int nblocks, hipStream_t stream,
                           const SmallMBatch *batch, int count) {
   const size_t lds = (size_t)g.nw * 2 * WIDE_REGION + 64 * 4;
-  if (batch && g.mtiles) return launch(k_smallm_wide_ks_joint<NG, NIT>, dim3(nblocks), dim3(64 * g.nw), lds, stream, *batch, g);
+  if constexpr (NIT > 2)                              // (members as one matrix: three tiles a workgroup and more)
+    if (batch && g.mtiles) return launch(k_smallm_wide_ks_joint<NG, NIT>, dim3(nblocks), dim3(64 * g.nw), lds, stream, *batch, g);
   if (batch) return launch(k_smallm_wide_batch<NG, NIT>, dim3(nblocks, count), dim3(64 * g.nw), lds, stream, *batch, g);
   return launch(k_smallm_wide<NG, NIT>, dim3(nblocks), dim3(64 * g.nw), lds, stream, w.row_ptr, (const uint8_t *)w.values,
                 (const uint8_t *)w.idx, (const uint8_t *)w.qparams, (const __half *)X, (__half *)Y, g);

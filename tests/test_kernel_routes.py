@@ -256,6 +256,21 @@ def test_matrices_of_many_tiles_reach_other_kernels_than_their_first_rows(launch
         assert len(a) == len(b) == 1 and a != b and a[0].split("IL")[0][-8:] == b[0].split("IL")[0][-8:], (c, a, b)
 
 
+def test_members_as_one_matrix_have_three_tiles_a_workgroup_and_more_beyond_32_tokens(launches):
+    # (the only forms of k_smallm_wide_ks_joint: the smallest sizes that run as one matrix, and sizes around the next rounds)
+    calls = [{"call": "gemm_batch", "w": (16 * t - 3, 2048, 2, 128, 0), "M": M, "count": c, "shared": True}
+             for M in (33, 64) for c in (2, 3, 4) for t in (*range(120, 400, 9), 512, 513, 640, 768, 769, 1024, 1025, 1300)]
+    joint = 0
+    for call, c in zip(launches(calls), calls):
+        assert len(call) == 1 and "k_smallm_wide" in call[0][0], (c, call)
+        if "ks_joint" in call[0][0]:
+            tiles = -(-((c["w"][0] + 15) // 16 * c["count"]) // call[0][1])
+            rounds = -(-tiles // 4)
+            assert tiles >= 3 and f"ks_jointILi{3 if c['M'] <= 48 else 4}ELi{-(-tiles // rounds)}E" in call[0][0], (c, call)
+            joint += 1
+    assert joint > 40
+
+
 # kind: 0 INT4, 1 FP16
 @pytest.mark.parametrize("w,M,count,shared,wide", [
     ((1000, 4096, 2, 128, 0), 33, 1, True, "k_smallm_wide"), ((1000, 4096, 2, 128, 0), 64, 1, True, "k_smallm_wide"),
