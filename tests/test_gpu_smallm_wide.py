@@ -1,5 +1,6 @@
 """The product for 33 to 64 tokens (k_smallm_wide) at the edges of its tiles, K-steps and token groups, against the oracle;
-batches under one X and under tokens of their own give the bits of the single product."""
+the bits are those of the kernel for up to 32 tokens, and batches under one X and under tokens of their own give the bits of
+the single product."""
 import numpy as np
 import pytest
 
@@ -30,6 +31,22 @@ def test_products_for_many_tokens(rows, cols, g, M):
     for pad in (0, 6, 7):        # 8-byte stores of four rows, the 2-byte fallback, odd strides
         Y = G.run_sparse_gemm(p, X, ldx_pad=pad - pad % 2, ldy_pad=pad)
         G.assert_close(Y, Y_ref, A_ref, f"smallm wide {rows}x{cols} M={M} pad={pad}")
+
+
+# rows of more than 2048 columns: 32 tokens go to k_sparse_smallm_ks there (test_kernel_routes), which splits K over as many waves
+MORE_THAN_2048 = [(1, 2112, 64, 33), (50, 4160, 64, 64), (31, 11008, 128, 47), (4100, 2304, 128, 48), (8203, 2176, 64, 57),
+                  (12300, 2112, 64, 49), (16400, 2560, 512, 64)]
+
+
+@pytest.mark.parametrize("rows,cols,g,M", MORE_THAN_2048)
+def test_the_bits_are_those_of_the_kernel_for_fewer_tokens(rows, cols, g, M):
+    print(f"case smallm wide bits {rows}x{cols} g={g} M={M}", flush=True)
+    w = synth.weights(rows, cols, 7500 + cols)
+    p = B.pack_2bitcsr(w, B.prune_n4(w, 2), 2, g, B.VAL_INT4)
+    X = synth.activation_rows(M, cols, 7501)
+    Y = G.run_sparse_gemm(p, X).view(np.uint16)
+    for k in (0, M - 32):                             # the first 32 tokens and the last: every token, other token groups
+        assert np.array_equal(Y[k:k + 32], G.run_sparse_gemm(p, X[k:k + 32]).view(np.uint16)), k
 
 
 @pytest.mark.parametrize("rows,cols,M,count", [(4234, 1792, 50, 3), (2064, 4096, 33, 4), (300, 640, 64, 2), (4500, 2112, 40, 2)])

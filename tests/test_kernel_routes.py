@@ -256,6 +256,14 @@ def test_matrices_of_many_tiles_reach_other_kernels_than_their_first_rows(launch
         assert len(a) == len(b) == 1 and a != b and a[0].split("IL")[0][-8:] == b[0].split("IL")[0][-8:], (c, a, b)
 
 
+def test_rows_of_more_than_2048_columns_take_two_kernels_up_to_32_tokens_and_beyond(launches):
+    # (those whose bits the GPU tests compare)
+    from test_gpu_smallm_wide import MORE_THAN_2048
+    for rows, cols, g, M in MORE_THAN_2048:
+        few, many = _names(launches([{"call": "gemm", "w": (rows, cols, 2, g, 0), "M": m, "count": 1} for m in (32, M)]))
+        assert len(few) == len(many) == 1 and "k_sparse_smallm_ks" in few[0] and "k_smallm_wide" in many[0], (rows, cols, few, many)
+
+
 def test_members_as_one_matrix_have_three_tiles_a_workgroup_and_more_beyond_32_tokens(launches):
     # (the only forms of k_smallm_wide_ks_joint: the smallest sizes that run as one matrix, and sizes around the next rounds)
     calls = [{"call": "gemm_batch", "w": (16 * t - 3, 2048, 2, 128, 0), "M": M, "count": c, "shared": True}
