@@ -223,11 +223,12 @@ egt_status egt_sparse_gemm_smallm(const egt_2bitcsr *w, const uint16_t *X, int64
  * only.  The workspace is dead after the call's kernels have run; calls that share one
  * must not overlap.
  * egt_sparse_gemm_smallm_ws_bytes (HOST): the bytes this matrix and M need; 0 where the
- * split form is not the faster one (it is for 2:4 INT4 with groups of 64 columns and more
- * and either M > 32 with K >= 8192 or at least 8192 rows - there the slice of X of a
- * workgroup stays in LDS - or M > 16, K >= 8192 and at most 4096 rows: the down projection
- * under verification), in which case egt_sparse_gemm_smallm_ws ignores the workspace and is
- * the one-launch call.
+ * split form is not taken, in which case egt_sparse_gemm_smallm_ws ignores the workspace and
+ * is the one-launch call.  It is taken for 2:4 INT4 with groups of 64 columns and more and
+ * either M > 32 with K >= 8192 or at least 8192 rows - there the slice of X of a workgroup
+ * stays in LDS - or M > 16, K >= 8192 and at most 4096 rows: the down projection under
+ * verification.  That is not everywhere the faster call: at M > 32 with at least 8192 rows
+ * and K < 8192 egt_sparse_gemm_smallm is (11008 x 4096, M = 64: 16.5 us, split 19.2).
  * EGT_ERR_SHAPE when workspace_bytes is smaller than required. */
 egt_status egt_sparse_gemm_smallm_ws_bytes(const egt_2bitcsr *w, int64_t ldx, int M, size_t *bytes);
 egt_status egt_sparse_gemm_smallm_ws(const egt_2bitcsr *w, const uint16_t *X, int64_t ldx,

@@ -10,9 +10,9 @@
 //    to it; any other is at least 2^-13 away from one (see egt_host_simd.h).
 //
 // One core of a Zen 5 on rows in its L2, ns for 64 columns of 2:4, AVX2 -> here: pruning 5.6 -> 2.5, validation 3.3 -> 1.3,
-// extrema 3.1 -> 1.7, codes and offsets 11.6 -> 6.0, dense codes 8.1 -> 3.8.  With 16 threads memory takes its share: 4096 x
-// 4096, groups of 128, pruning and packing 1000 -> 810 us (pruning 228 -> 145), dense quantisation 529 -> 420; 2048 x 4096
-// pruning and packing 546 -> 418.
+// extrema 3.1 -> 1.7, codes and offsets 11.6 -> 6.0, dense codes 8.1 -> 3.8.  With 16 threads, us of whole calls, medians of 60
+// in turn: 4096 x 4096, groups of 128, pruning and packing 886 -> 786 (quartiles 3 percent apart; pruning 222 -> 156), dense quantisation
+// 500 -> 382; 2048 x 4096 pruning and packing 483 -> 408; 256 x 4096 220 -> 211.
 #ifndef EGT_HOST_SIMD512_H
 #define EGT_HOST_SIMD512_H
 

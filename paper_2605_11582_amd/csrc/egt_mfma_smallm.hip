@@ -762,8 +762,8 @@ static void smallm_launch_geometry(SmallMKsLaunch &g, int nblocks, int nw, int n
 // order.  That price is only recovered where a workgroup still gets by with one round of
 // row tiles (a second round would fetch its X slice again), and measured it is: 2:4 INT4,
 // one {scale, zero} pair per chunk, more than 16 tokens, K >= 8192 and at most 256 row
-// tiles - four slices, a quarter of the row tiles per workgroup column (4096 x 11008:
-// 21.9 against 24.9 us at M = 64, 14.3 against 14.9 at M = 32; with more rows, e.g.
+// tiles - four slices, a quarter of the row tiles per workgroup column (4096 x 11008
+// at M = 32: 14.3 against 14.9 us; with more rows, e.g.
 // 11008 x 4096, every split measured was slower than the one-launch kernel).
 // Returns the number of slices (1: no split) and the row blocks.
 static int smallm_slices(const egt_2bitcsr &w, int M, int &row_blocks) {
@@ -873,6 +873,9 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
   //    36 -> 136 us; 4234 x 1792, 50 tokens, three members: 31.3 -> 17.6);
   //  - with two token groups a pass from the third tile of a workgroup on (1102 x 6336, 25 tokens, four members, two
   //    tiles: 15.8 -> 18.1 us; 2948 x 7104, 31 tokens, three members, three tiles: 25.5 -> 18.7).
+  // The figures at more than 32 tokens are those of two passes over the rows; in one pass (k_smallm_wide, 2:4) the same rule takes
+  // the faster form (apart / as one: 4234 x 1792, 50 tokens, three members 21.6 / 13.2, two of 11008 x 4096 at 64 31.1 / 32.2,
+  // at 33 27.5 / 28.7, four of 13211 x 512 at 56 17.8 / 39.2, two of 4500 x 2112 at 40 16.7 / 12.9).
   // (FP16 values: a product of more than 256 tiles has fewer waves, another order of additions.)
   bool joint = batch != nullptr && int4;
   for (int k = 1; batch && k < count; ++k) joint = joint && batch->X[k] == batch->X[0];
@@ -892,8 +895,9 @@ static hipError_t smallm_one_launch(const egt_2bitcsr &w, const uint16_t *X, int
   const int nw = g.nsteps < nwmax ? g.nsteps : nwmax;
   smallm_launch_geometry(g, nblocks, nw);
   if (joint) g.mtiles = mtiles;
-  // More than 32 tokens at 2:4: one pass over the rows for all token groups instead of one for two (every shape that was
-  // measured gained, 4 to 55 percent; egt_smallm_wide_body.h).  Up to 32 one pass does there too, and X by token groups then
+  // More than 32 tokens at 2:4: one pass over the rows for all token groups instead of one for two (300 sizes of 512 to 28672
+  // rows and 512 to 16384 columns, from memory: the median takes 0.77 of the time, the best half of it; 1 to 3 percent more at
+  // 49 to 56 tokens on 3000 to 4096 rows of 3584 to 4096 columns, which from the caches gain 2 to 8; egt_smallm_wide_body.h).  Up to 32 one pass does there too, and X by token groups then
   // only waits more often (17 tokens: 4096 x 4096 7.4 -> 9.1 us, 4096 x 11008 13.3 -> 15.8).
   if (int4 && !n1 && qw == 1 && M > 32) {
     // (a workgroup's rounds of tiles are of one length: 2 + 2, not 3 + 1)
@@ -944,9 +948,9 @@ hipError_t launch_sparse_smallm(const egt_2bitcsr &w, const uint16_t *X, int64_t
 // compute unit, K split over its waves.  Such a workgroup runs its loads, products and the
 // sum across waves one after the other, and nothing else is resident to fill the gaps.  A
 // table offers many matrices at once, so the stack uses smaller workgroups, few per matrix,
-// and the compute units work on several matrices at the same time (16 layers of a 7B stack,
-// 1.3 GB: 347 us at 16 tokens against 951 us of single products replayed from a graph, 594
-// against 2008 us at 64 tokens).  The host writes the descriptors in the order of falling row
+// and the compute units work on several matrices at the same time (32 layers of a 7B stack,
+// 2.6 GB: 599 us at 16 tokens against 1734 us of 224 single products, 989
+// against 3281 us at 64 tokens).  The host writes the descriptors in the order of falling row
 // length, so that the launch ends on short workgroups.
 struct SmallMStackEntry {
   uint64_t row_ptr, values, idx, qparams, X, Y;      // device addresses
@@ -1258,7 +1262,8 @@ static int stack_lds_rows(int M, bool n1) {
 // one tile, two, three tables in turn: 24 tokens, layers of 4096 x 11008: two of them (164 MB) 57.8, 74.3; four 106.3,
 // 107.7; six (490 MB) 155.1, 150.0; ten of 6144 x 20480 (2.1 GB) 584.8, 552.6; 1:4 at 16 tokens, two of 4096 x 11008 35.4,
 // 43.9, eight (330 MB) 123.2, 120.2, ten of 6144 x 20480 358.2, 333.1; at 5 tokens twelve of 2048 x 8192 (160 MB) 59.7, 65.9.
-// 2:4 up to 16 tokens always one: sixteen layers of a 7B stack at 16 tokens 297, 304.
+// 2:4 up to 16 tokens always one: at 16 tokens sixteen layers of a 7B stack 297, 304, 32 of 4096 x 11008 132, 135, 160 of 11008 x
+// 4096 (2.9 GB) 640, 660, 300 of 2048 x 2048 121, 146, four of 4096 x 11008 29.8, 48.7; at 4 tokens ten of 6144 x 20480 100, 105.
 static bool stack_two_tiles(int M, bool n1, uint64_t bytes) { return stack_sixteen(M, n1) || ((n1 || M > 16) && bytes >= 400000000ull); }
 static StackForm stack_form_tiles(int M, bool n1, bool two) {
   if (stack_sixteen(M, n1)) return {512, 16, st_lds_bytes(n1 ? 2 : 4, 2, 32, false, n1)};
@@ -1270,7 +1275,10 @@ static StackForm stack_form_rows(int M, bool n1) {
   return stack_sixteen(M, n1) ? StackForm{1024, 16, stack_lds_rows(M, n1)} : StackForm{64 * RS_WAVES, RS_WAVES, stack_lds_rows(M, n1)};
 }
 
-// The most workgroups of a table that k_smallm_rows takes.
+// The most workgroups of a table that k_smallm_rows takes.  The line keeps the plans of such tables, threads and LDS bytes, what
+// they were before there was k_stack_tiles.  It is not where the times cross: us of k_smallm_rows / k_stack_tiles, tables of 16, 64 and
+// 256 workgroups of 4096 columns: 2:4 16 tokens 17.4 / 13.3, 17.6 / 13.8, 20.9 / 16.3, 32 20.2 / 18.0, 21.0 / 18.5, 24.4 / 21.0, 64
+// 38.1 / 35.0, 39.6 / 36.3, 49.7 / 46.1; 1:4 16 tokens 13.1 / 12.4, 13.4 / 12.8, 15.1 / 14.4, 32 28.2 / 23.5, 29.4 / 24.1, 32.9 / 28.2.
 static int stack_few(int M, bool n1) { return n1 || M > 32 ? 127 : 64; }
 
 // Workgroups of a matrix in the forms that every table once had: what a plan may not exceed.  (No form has fewer tiles a workgroup.)

@@ -234,10 +234,14 @@ __global__ __launch_bounds__(512) void k_smallm_xs(const uint32_t *__restrict__ 
 bool sparse_smallm_xs_plan(const egt_2bitcsr &w, int64_t ldx, int M, bool force, SmallMXsGeom &g, int &ng, int &sps_cap, int &nw,
                            size_t &lds) {
   if (w.val_kind != EGT_VAL_INT4 || w.n_keep != 2 || M < 17 || M > 64 || w.rows < 1) return false;
-  // Where it is the faster form (measured against the one-launch kernel and the split with
-  // X re-fetched per workgroup): more than 32 tokens on long rows or on many rows.  The
-  // partial sums cost a write-back at the end of the kernel, a second launch and their read;
-  // that is recovered only where X, not W, dominates the one-launch kernel.
+  // More than 32 tokens on long rows or on many rows.  The partial sums cost a write-back at the end of the kernel, a
+  // second launch and their read; that is recovered only where X, not W, dominates the one-launch kernel.  The line was drawn
+  // against a one-launch kernel that walked its rows twice, and stays because callers hold workspaces of these sizes.
+  // Against k_smallm_wide, us from memory, one launch / split, 33 and 64 tokens: this form is the faster one on few long rows
+  // (2000 x 8192 14.4 / 12.6 and 16.9 / 13.1, 4096 x 11008 18.3 / 17.7 and 22.4 / 18.1, 4096 x 16384 24.9 / 20.0 and 31.3 / 20.8,
+  // 8192 x 16384 31.7 / 29.7 and 39.3 / 34.3), not on many rows of fewer than 8192 columns (8192 x 2048 7.9 / 11.9 and 8.9 / 12.9,
+  // 11008 x 4096 14.4 / 17.0 and 16.5 / 19.2, 16384 x 6144 22.5 / 26.9 and 25.5 / 29.1), and either may be from about 8192 rows
+  // on beyond (8192 x 11008 23.4 / 26.0 and 28.0 / 28.0, 16384 x 8192 26.8 / 30.7 and 31.3 / 36.0, 28672 x 8192 48.0 / 45.7 and 56.0 / 56.9).
   if (!force && !(M > 32 && (w.cols >= 8192 || w.rows >= 8192))) return false;
   if (w.cols % 256 != 0 || w.cols < 256 || ldx % 8 != 0) return false;
   const int gm = w.group_size / 64;

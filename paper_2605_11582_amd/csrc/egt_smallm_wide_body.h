@@ -5,7 +5,7 @@
 // That kernel takes two token groups a pass: at more than 32 tokens it walks its rows twice, and the operands are
 // fetched (from the caches), exchanged between lanes and dequantised twice.  Here a K-step of the row tiles is
 // dequantised once, stays in registers (16 a tile) and serves all token groups.  What bounds it then is X: every
-// workgroup pulls all of X through the L2 (11008 x 4096, 64 tokens: 134 MB beside 27 MB of weights).  So X comes in units
+// workgroup pulls all of X through the L2 (11008 x 4096, 64 tokens: 134 MB beside 18 MB of weights).  So X comes in units
 // of one token group of one K-step, into two regions of a wave's own: the unit after the next is requested as soon as a
 // region has been read, across K-steps, and there is always one on its way.  The number of token groups is the
 // compiler's: counted in the kernel, its branches cost 0.5 to 1 us a product.
@@ -15,9 +15,9 @@
 // count what is newer than the unit that is needed.  The odd last phase (LAST) asks for no tiles and counts none: the
 // compiler leaves out requests whose registers nothing reads any more.
 //
-// Matrices from memory, us, before -> now, 64 tokens: 11008 x 4096 21.4 -> 17.7, 13824 x 5120 28.3 -> 22.8, 4096 x 4096
-// 13.6 -> 12.6, 4096 x 11008 28.1 -> 24.8, 4096 x 512 9.1 -> 5.9, two of 11008 x 4096 39.3 -> 32.4; 48 tokens: 4096 x 4096
-// 12.0 -> 11.2, three of 8192 x 2048 29.3 -> 19.6; 33 tokens: 4096 x 4096 11.1 -> 10.6, 5120 x 5120 (40) 20.0 -> 13.8.
+// Matrices from memory, us, before -> now, 64 tokens: 11008 x 4096 20.1 -> 16.4, 13824 x 5120 27.0 -> 21.6, 4096 x 4096
+// 11.7 -> 11.4, 4096 x 11008 25.0 -> 22.5, 4096 x 512 7.7 -> 5.9, two of 11008 x 4096 37.9 -> 30.8; 48 tokens: 4096 x 4096
+// 10.7 -> 10.2, three of 8192 x 2048 28.1 -> 18.4; 33 tokens: 4096 x 4096 9.9 -> 9.9, 5120 x 5120 18.7 -> 12.5.
 #ifndef EGT_SMALLM_WIDE_BODY_H
 #define EGT_SMALLM_WIDE_BODY_H
 

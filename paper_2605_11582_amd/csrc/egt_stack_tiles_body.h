@@ -7,14 +7,14 @@
 // requests of the weights out of range, that is everything but the memory, 206):
 //  - Lane permutations took 80 of the 206 us (fourteen and seven selects a K-step).  Here a wave writes what it
 //    fetched to 2 KB of LDS and reads it back in operand form: six writes and four reads for two K-steps.
-//  - Parameters are a 26th of the bytes and took 40 of the 341 us: 16 bytes a row and round, of lines that were gone from
+//  - Parameters are a 13th of the bytes and took 40 of the 341 us: 16 bytes a row and round, of lines that were gone from
 //    the caches before the next round.  Here a window of QW bytes of each row is fetched into LDS at once, whole lines
 //    with QW = 128.
 //  - The compiler waited for all requests at the top of every other round: a request under a condition, and a round of
 //    the loop under one, make its count of what is pending the smallest of all paths.  Here rounds past the last one are requested
 //    too (out of range: no traffic), and a loop turn is two rounds, the odd last round behind it.
-// us before, now (bits the same): 2:4 341 -> 294 at 16 tokens, 318 -> 266 at 4, 527 -> 502 at 64, 410 -> 362 at 32
-// (two tiles a wave); 1:4 (eleven layers) 170 -> 150 at 16, 158 -> 144 at 5, 217 -> 208 at 32.
+// us before, now (bits the same; another clock than the 341 above, both sides of it in turn): 2:4 344 -> 303 at 16 tokens, 322 ->
+// 274 at 4, 531 -> 511 at 64, 419 -> 365 at 32 (two tiles a wave); 1:4 (eleven layers) 174 -> 158 at 16, 165 -> 151 at 4, 225 -> 215 at 32.
 // What bounds it now: HBM and the L2 (the weights and token rows alone take 260 us at 16 tokens, 178 without weights).
 #ifndef EGT_STACK_TILES_BODY_H
 #define EGT_STACK_TILES_BODY_H
