@@ -1257,14 +1257,20 @@ static int stack_lds_rows(int M, bool n1) {
   return M <= 16 ? rs_lds_bytes(1, RS_Q) : M <= 32 ? rs_lds_bytes(2, 2) : rs_lds_bytes(4, 2);
 }
 // Two row tiles a wave: four token groups (at 1:4 two) always, since one workgroup then fills the LDS of a compute unit
-// anyway and an operand read from it serves both tiles; two groups (1:4: one) in tables of 400 MB and more.  Those are fetched from HBM whatever ran before, in 128-byte pieces
-// of a row with two tiles and 64-byte ones with one; smaller tables would miss the second workgroup of a compute unit.  us with
+// anyway and an operand read from it serves both tiles; two groups (1:4: one) in tables of 400 MB and more with rows of at least 4096
+// columns.  Such tables are fetched from HBM whatever ran before, in 128-byte pieces
+// of a row with two tiles and 64-byte ones with one; smaller tables would miss the second workgroup of a compute unit, and shorter
+// rows leave a workgroup too few rounds to make up for its start.  us with
 // one tile, two, three tables in turn: 24 tokens, layers of 4096 x 11008: two of them (164 MB) 57.8, 74.3; four 106.3,
 // 107.7; six (490 MB) 155.1, 150.0; ten of 6144 x 20480 (2.1 GB) 584.8, 552.6; 1:4 at 16 tokens, two of 4096 x 11008 35.4,
 // 43.9, eight (330 MB) 123.2, 120.2, ten of 6144 x 20480 358.2, 333.1; at 5 tokens twelve of 2048 x 8192 (160 MB) 59.7, 65.9.
+// 500 MB of 2048 rows each, one tile / two / k_smallm_rows: 24 tokens, 1024 columns 167, 204, 157, 2048 154, 167, 167, 3072 155, 155, 162, 4096
+// 151, 145, 168; 1:4 at 16 tokens, 1024 185, 224, 186, 2048 165, 202, 158, 3072 159, 183, 169, 4096 161, 164, 177, 5120 162, 156, 175.
 // 2:4 up to 16 tokens always one: at 16 tokens sixteen layers of a 7B stack 297, 304, 32 of 4096 x 11008 132, 135, 160 of 11008 x
 // 4096 (2.9 GB) 640, 660, 300 of 2048 x 2048 121, 146, four of 4096 x 11008 29.8, 48.7; at 4 tokens ten of 6144 x 20480 100, 105.
-static bool stack_two_tiles(int M, bool n1, uint64_t bytes) { return stack_sixteen(M, n1) || ((n1 || M > 16) && bytes >= 400000000ull); }
+static bool stack_two_tiles(int M, bool n1, uint64_t bytes, int shortest) {
+  return stack_sixteen(M, n1) || ((n1 || M > 16) && bytes >= 400000000ull && shortest >= 4096);
+}
 static StackForm stack_form_tiles(int M, bool n1, bool two) {
   if (stack_sixteen(M, n1)) return {512, 16, st_lds_bytes(n1 ? 2 : 4, 2, 32, false, n1)};
   const int ng = M <= 16 ? 1 : 2;
@@ -1293,11 +1299,13 @@ int smallm_stack_blocks(int M, int n_keep, int rows) {
 void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles, bool &marked) {
   const bool n1 = n_keep == 1;
   uint64_t bytes = 0, blocks = 0;
+  int shortest = 1 << 30;                             // columns of a row
   for (int k = 0; k < count; ++k) {
     const egt_2bitcsr &w = *items[k].sparse;
+    if (w.rows > 0) shortest = std::min(shortest, w.cols);
     bytes += (uint64_t)w.rows * (uint64_t)(w.n_keep * (w.cols / 16) * 3 + 4 * (w.cols / w.group_size));
   }
-  StackForm f = stack_form_tiles(M, n1, stack_two_tiles(M, n1, bytes));
+  StackForm f = stack_form_tiles(M, n1, stack_two_tiles(M, n1, bytes, shortest));
   for (int k = 0; k < count; ++k) blocks += (uint64_t)(((items[k].sparse->rows + 15) / 16 + f.tiles - 1) / f.tiles);
   if (blocks <= (uint64_t)stack_few(M, n1)) f = stack_form_rows(M, n1);
   block_threads = f.threads; lds_bytes = f.lds; tiles = f.tiles;

@@ -297,7 +297,8 @@ from paper_2605_11582_amd import binding as B
 L = B._declare(C.CDLL(B.LIB_PATH))                          # (without PyTorch)
 P = 1 << 20
 for M, n, rows, cols, count, changes in json.loads({calls!r}):
-    views = [B.View(rows, cols, n, 128, 0, P, P, P, P) for _ in range(count)]
+    each = cols if isinstance(cols, list) else [cols]       # row lengths in turn
+    views = [B.View(rows, each[k % len(each)], n, 128, 0, P, P, P, P) for k in range(count)]
     items = (B.GemmItem * count)()
     for k, v in enumerate(views):
         items[k].sparse, items[k].X, items[k].Y = C.pointer(v), P, P
@@ -344,6 +345,19 @@ def test_a_plan_runs_only_in_the_form_its_table_was_laid_out_for(runs_of_plans, 
                 kernel = ("k_smallm_rows" if pair[0] == 1024 else "k_stack_tiles") if sixteen else ("k_smallm_rows" if pair[1] == lds[0] else "k_stack_tiles")
                 assert kernel in again[0][0] and again[0][2] == pair[0], (table, change, again)
                 assert again[0][3] == ({"k_smallm_rows": lds[0], "k_stack_tiles": lds[1]}[kernel] if sixteen else pair[1]), (table, change, again)
+
+
+@pytest.mark.parametrize("M,n", [(17, 2), (32, 2), (4, 1), (16, 1)])
+def test_two_tiles_a_wave_take_long_rows(runs_of_plans, M, n):
+    # tables of 400 MB and more: with rows of fewer than 4096 columns a workgroup is over before two tiles a wave pay for the second
+    # workgroup of a compute unit, whatever the other rows
+    one, two = TILES_LDS[32 if n == 2 else 16, n]
+    tables = [(M, n, 2048, cols, 400, []) for cols in (2560, 3968, 4096, 11008, [11008, 4096], [11008, 3968], [3968, 11008])]
+    for (*_, cols, count, _), (res,) in zip(tables, runs_of_plans(tables)):
+        launched, status, grid, threads, lds, _ = res
+        tiles = 16 if min(cols if isinstance(cols, list) else [cols]) >= 4096 else 8
+        assert status == 0 and len(launched) == 1 and lds == (two if tiles == 16 else one) and threads == 512, (cols, res)
+        assert "k_stack_tiles" in launched[0][0] and grid == count * 2048 // (16 * tiles), (cols, res)
 
 
 def test_a_plan_without_the_mark_of_two_tiles_a_wave_is_refused(runs_of_plans):
