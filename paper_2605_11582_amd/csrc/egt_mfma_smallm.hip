@@ -1246,7 +1246,8 @@ bool smallm_stack_item_ok(const egt_2bitcsr &w, int M) {
 
 // Launch forms of a table, told apart by the plan's workgroups, threads and LDS bytes:
 //  - k_stack_tiles with a row tile a wave or two;
-//  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, and at any size plans that a caller kept.
+//  - k_smallm_rows: tables of few workgroups, whose plans are what they always were, large tables of short rows, and at any size plans that a
+//    caller kept.
 struct StackForm {
   int threads, tiles, lds;                            // of a workgroup
   bool of(int t, int l) const { return t == threads && l == lds; }
@@ -1281,7 +1282,19 @@ static StackForm stack_form_rows(int M, bool n1) {
   return stack_sixteen(M, n1) ? StackForm{1024, 16, stack_lds_rows(M, n1)} : StackForm{64 * RS_WAVES, RS_WAVES, stack_lds_rows(M, n1)};
 }
 
-// The most workgroups of a table that k_smallm_rows takes.  The line keeps the plans of such tables, threads and LDS bytes, what
+// Rows of three or four K-steps, two rounds of k_stack_tiles, in tables that are fetched from HBM: a workgroup is little but its start, and
+// k_smallm_rows, which asks for nothing past the last round, is the faster one.  us of k_smallm_rows / k_stack_tiles with a tile a wave, matrices
+// of 2048 rows, tables of 150, 250, 300 and 400 MB: 2:4, 1024 columns, 24 tokens 43.6 / 43.9, 74.5 / 76.5, 94.1 / 100.4, 124.1 / 135.9; 4 tokens
+// 34.2 / 33.4, 55.6 / 55.1, 74.3 / 74.1, 101.0 / 104.2; 768 columns, 16 tokens 43.2 / 42.9, 76.4 / 76.7, 94.6 / 97.3, 127.4 / 133.1; 1:4,
+// 2048 columns, 16 tokens 46.2 / 46.6, 75.2 / 77.9, 93.5 / 97.6, 126.9 / 134.9.
+// 2:4 at up to 16 tokens that kernel takes four K-steps a round, shorter rows waste most of it (512 columns 20 to 27 percent more); other
+// rows of one or two K-steps differ by 3 percent either way; five are 6 to 10 percent faster in k_stack_tiles.
+static bool stack_short_rows(int M, bool n1, uint64_t bytes, int longest) {
+  const int steps = (longest + (n1 ? 511 : 255)) / (n1 ? 512 : 256);
+  return !stack_sixteen(M, n1) && bytes >= 250000000ull && (steps == 3 || steps == 4);
+}
+
+// The most workgroups of a table that k_smallm_rows takes at any row length.  The line keeps the plans of such tables, threads and LDS bytes, what
 // they were before there was k_stack_tiles.  It is not where the times cross: us of k_smallm_rows / k_stack_tiles, tables of 16, 64 and
 // 256 workgroups of 4096 columns: 2:4 16 tokens 17.4 / 13.3, 17.6 / 13.8, 20.9 / 16.3, 32 20.2 / 18.0, 21.0 / 18.5, 24.4 / 21.0, 64
 // 38.1 / 35.0, 39.6 / 36.3, 49.7 / 46.1; 1:4 16 tokens 13.1 / 12.4, 13.4 / 12.8, 15.1 / 14.4, 32 28.2 / 23.5, 29.4 / 24.1, 32.9 / 28.2.
@@ -1299,15 +1312,15 @@ int smallm_stack_blocks(int M, int n_keep, int rows) {
 void smallm_stack_shape(int M, int n_keep, const egt_gemm_item *items, int count, int &block_threads, int &lds_bytes, int &tiles, bool &marked) {
   const bool n1 = n_keep == 1;
   uint64_t bytes = 0, blocks = 0;
-  int shortest = 1 << 30;                             // columns of a row
+  int shortest = 1 << 30, longest = 0;                // columns of a row
   for (int k = 0; k < count; ++k) {
     const egt_2bitcsr &w = *items[k].sparse;
-    if (w.rows > 0) shortest = std::min(shortest, w.cols);
+    if (w.rows > 0) { shortest = std::min(shortest, w.cols); longest = std::max(longest, w.cols); }
     bytes += (uint64_t)w.rows * (uint64_t)(w.n_keep * (w.cols / 16) * 3 + 4 * (w.cols / w.group_size));
   }
   StackForm f = stack_form_tiles(M, n1, stack_two_tiles(M, n1, bytes, shortest));
   for (int k = 0; k < count; ++k) blocks += (uint64_t)(((items[k].sparse->rows + 15) / 16 + f.tiles - 1) / f.tiles);
-  if (blocks <= (uint64_t)stack_few(M, n1)) f = stack_form_rows(M, n1);
+  if (blocks <= (uint64_t)stack_few(M, n1) || stack_short_rows(M, n1, bytes, longest)) f = stack_form_rows(M, n1);
   block_threads = f.threads; lds_bytes = f.lds; tiles = f.tiles;
   marked = !stack_sixteen(M, n1) && f.tiles == 16;
 }

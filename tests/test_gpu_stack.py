@@ -683,6 +683,33 @@ def test_gemm_stack_large_tables_take_two_tiles_a_wave(M, n):
     assert torch.equal(again.view(torch.int16), alone.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,n", [(5, 2), (16, 2), (17, 2), (32, 2), (16, 1)])
+def test_gemm_stack_large_tables_of_short_rows(M, n):
+    # rows of three and four K-steps in tables of 250 MB and more (two matrices many times over): the bits of k_stack_tiles
+    torch = G.torch_mod()
+    print(f"case gemm stack short rows M={M} n={n}", flush=True)
+    shapes = [(4099, 2048 // n), (4099, 768 if n == 2 else 1408)]
+    ps, Xs = [], []
+    for k, (rows, cols) in enumerate(shapes):
+        w = synth.weights(rows, cols, 9600 + k)
+        ps.append(B.pack_2bitcsr(w, B.prune_n4(w, n), n, 128, B.VAL_INT4).to("cuda:0"))
+        Xs.append(G.to_dev(synth.activation_rows(M, cols, 9600 + k).view(np.uint16)).view(torch.float16))
+    count = 2 * -(-250_000_000 // sum(p.nbytes() - 4 * (p.rows + 1) for p in ps))
+    Y = torch.full((count, M, 4099), float("nan"), dtype=torch.float16, device="cuda")
+    call = B.prepared_gemm_stack([(ps[k % 2], Xs[k % 2], Y[k]) for k in range(count)])
+    assert call.plan.grid_x == count * -(-4099 // 128) and (call.plan.lds_bytes, call.plan.block_threads) == next(
+        (lds, threads) for top, lds, threads in ROWS_FORM[n] if M <= top)
+    call()
+    torch.cuda.synchronize()
+    first = Y.view(torch.int16).clone()
+    assert not torch.isnan(Y).any() and all(torch.equal(first[k], first[k % 2]) for k in range(count))
+    Y.fill_(float("nan"))
+    call.plan.lds_bytes = (66560 if M <= 16 else 79872) if n == 2 else 78848
+    call()
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int16), first)
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_gemm_stack_seeded_sweep_of_shapes(seed):
     # seeded tables: row counts around the tile and workgroup sizes, row lengths that end anywhere inside a K-step or

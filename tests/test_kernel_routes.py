@@ -360,6 +360,22 @@ def test_two_tiles_a_wave_take_long_rows(runs_of_plans, M, n):
         assert "k_stack_tiles" in launched[0][0] and grid == count * 2048 // (16 * tiles), (cols, res)
 
 
+@pytest.mark.parametrize("M,n", [(4, 2), (16, 2), (17, 2), (32, 2), (4, 1), (16, 1)])
+def test_large_tables_of_short_rows_keep_their_kernel(runs_of_plans, M, n):
+    # rows of three and four K-steps in tables of 250 MB and more: k_smallm_rows, as before there was k_stack_tiles
+    top, step = (32 if M > 16 else 16), 512 // n
+    nbytes = lambda cols: 2048 * (n * (cols // 16) * 3 + 4 * (cols // 128))
+    few, many = (lambda cols: 249_999_999 // nbytes(cols)), (lambda cols: -(-250_000_000 // nbytes(cols)))
+    tables = [(M, n, 2048, c, many(c), []) for c in (2 * step, 3 * step, 3 * step - 128, 4 * step, 4 * step - 128, 4 * step + 128)]
+    tables += [(M, n, 2048, c, few(c), []) for c in (3 * step, 4 * step)]
+    tables += [(M, n, 2048, [step, 4 * step], 2 * many(step), []), (M, n, 2048, [4 * step, 4 * step + 128], 2 * many(4 * step), [])]
+    want = [False, True, True, True, True, False, False, False, True, False]
+    for (*_, cols, count, _), rows, (res,) in zip(tables, want, runs_of_plans(tables)):
+        launched, status, grid, threads, lds, _ = res
+        assert status == 0 and len(launched) == 1 and ("k_smallm_rows" in launched[0][0]) == rows, (cols, res)
+        assert (lds == ROWS_LDS[top, n]) == rows and threads == 512 and grid == count * 16, (cols, res)
+
+
 def test_a_plan_without_the_mark_of_two_tiles_a_wave_is_refused(runs_of_plans):
     # (30 descriptors of 160 bytes, 32 workgroups a matrix; the mark alone in a table without it is refused too)
     plain = 30 * 160 + 4 * 30 * 32
